@@ -2,14 +2,18 @@
 // (Sec. 2.3: "Neighbour walk" culled to the true neighbours, and the
 // one-dimensional "Neighbour list").
 //
-// One wave per group of sibling leaves (k_walk.hip), taking the group's
-// leaves in turn. Lanes are (sink slot s, slice j) over the leaf's particles
-// (near_tile.h: S = min(c, 64) sinks, J = 64 / S slices). The candidate
-// cells of the leaf (cells of the group's near list, ascending labels, whose
-// candidate mask has the leaf) are staged through LDS 64 particles at a
-// time; slice j of sink s tests tile entries j, j + J, .... A pair is a
-// neighbour iff b != a and |r_a - r_b|^2 < (2 h_a)^2 in FP64 on the tree's
-// copy of the inputs (the same predicate for every precision mode).
+// One wave (a workgroup of its own) per leaf. Lanes are (sink slot s, slice
+// j) over the leaf's particles (near_tile.h: S = min(c, 64) sinks, J = 64 / S
+// slices; c: the sinks still to do). The candidate cells of the leaf (cells
+// of its group's near list, ascending labels, whose candidate mask has the
+// leaf) are staged through LDS 64 particles at a time; slice j of sink s
+// tests tile entries j, j + J, .... A pair is a neighbour iff b != a and
+// |r_a - r_b|^2 < (2 h_a)^2 in FP64 on the tree's copy of the inputs (the
+// same predicate for every precision mode).
+// A leaf's work varies tenfold, so wider units of work leave the chip waiting
+// for the longest: one wave per group of 8 leaves took 690 us for 37,000
+// particles (512 groups), per leaf 202; at 4M 2313 and 2021 us, at 16M 9.75
+// and 9.38 ms (rcb_neighbours_count).
 // Staging keeps only the sources inside the leaf's sphere (centre g_A,
 // radius h_node(A) padded by 2^-32, Sec. 2.3.1): a neighbour b of a sink a
 // has |r_b - g_A| <= |r_b - r_a| + |r_a - g_A| < 2 h_a + |r_a - g_A|
@@ -20,13 +24,16 @@
 // The count call writes each particle's count into the caller's offsets
 // array (scanned in place afterwards) and its first kNbCap ids into a slab
 // row indexed by caller id (by tree position for very large N, see
-// tree_rows), the next ones into chunks of a shared pool. The fill call
-// streams the slab in caller order,
+// tree_rows), the next ones into a chain of chunks of a shared pool. The fill
+// call streams the slab in caller order,
 // sorts each list ascending (a 64-input sorting network held by 8 lanes) and
-// stores it into the CSR. Lowest-level cells holding a particle with more
-// neighbours than the slab takes (queued by the count call) are searched
-// again, one wave each, writing only those particles' lists at their
-// offsets; each such list is then sorted by one workgroup.
+// stores it into the CSR; longer lists follow wave by wave. Lowest-level
+// cells holding a particle for which the pool had no chunk left (queued by
+// the count call) are searched again, one wave each, writing only those
+// particles' lists at their offsets; each such list is then sorted by one
+// workgroup.
+#include <algorithm>
+
 #include "near_tile.h"
 #include "rcb_internal.h"
 
@@ -35,13 +42,9 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr int kWaves = kBlock / kWave;
-// The search takes one wave per workgroup: the work of a group of cells
-// varies tenfold, and a wider workgroup would hold its LDS until its slowest
-// wave ends.
-constexpr int kSearchWaves = 1;
 constexpr int kNbCap = 64;        // slab slots per particle (~50 neighbours expected)
 constexpr int kNbChunk = 64;      // slots of an overflow chunk
-constexpr int kNbChunks = 3;      // chunks a list may take: lists of up to 256 ids
+constexpr int kNbWaveMax = 256;   // lists of up to 256 ids are sorted by one wave in registers
 constexpr int kLongLds = 4096;    // lists searched again: sorted in LDS up to this length
 constexpr int kRingMask = 2 * kWave - 1;
 constexpr int kRingBytes = 2 * kWave * 32;   // the ring of SrcN, in bytes
@@ -63,15 +66,17 @@ struct NeighArgs {
     const int64_t *offsets;   // fill mode: list starts (caller order)
     int32_t *ids;             // fill mode: final lists; slab mode: kNbCap slots per caller index
     int32_t *pool;            // slab mode: overflow chunks of kNbChunk slots
-    int32_t *longc;           // slab mode: the kNbChunks chunks of each entry of longq
-    int64_t pool_cap;         // chunks in pool
-    int32_t *head;            // per caller index: its chunk, or -1 for a list searched again
-    int32_t *ctl;             // [0] lists searched again, [1] leaves queued, [2] chunks taken,
-                              // [3] lists in chunks (slab mode); [0] lists written (fill mode)
+    int32_t *next;            // slab mode: the chunk after each chunk of a list
+    int64_t sub_cap;          // chunks of each sub-pool
+    int32_t sub_mask;         // sub-pools - 1 (a power of two of them)
+    int32_t *head;            // per caller index: its first chunk, or -1 for a list searched again
+    int32_t *ctl;             // [0] lists searched again, [1] leaves queued, [2] kept lists of more than
+                              // kNbWaveMax ids (slab mode); [kSubCtl (1 + i)] chunks taken from sub-pool
+                              // i; fill mode: [0] lists appended to longq
     int32_t *queue;           // leaves (index from 0) holding a list searched again: appended in
                               // slab mode, searched again (wave i: queue[i]) otherwise
-    int32_t *longq;           // caller indices: lists in chunks (slab mode), lists written (fill)
-    int64_t nq;               // fill mode: entries of queue
+    int32_t *longq;           // fill mode: the caller indices of the lists written here
+    int64_t first;            // slab mode: this launch's first leaf (one per workgroup)
     bool tree_rows;           // slab mode: rows by tree position (else by caller index)
 };
 
@@ -86,206 +91,202 @@ struct alignas(16) SrcN {
 // row is padded with sources that can never be neighbours (pb = -1 at
 // infinite distance). cnt / chunk: per sink slot of the pass, the
 // neighbours found so far (slots are handed out by LDS atomics, so a list is
-// stored in no particular order; the fill call sorts it) and its chunk.
+// stored in no particular order; the fill call sorts it) and its last two
+// chunks, by parity (the slots that one row hands to a sink are at most 64
+// consecutive ones and touch at most two chunks).
 struct NeighShared {
     EntryChunk ec;
     SrcN tile[2 * kWave];
     int32_t cnt[kWave];
-    int32_t chunk[kWave][kNbChunks];
+    int32_t chunk[kWave][2];
 };
 
-// SLAB: ids go to slab row (caller index) while it has room, then to a chunk
-// of the pool taken by the sink's 65th neighbour; lists longer than both, or
-// whose chunk could not be had, are only counted, and their leaf is queued.
+// Chunk counters: one per sub-pool, 64 bytes apart, and neighbouring groups
+// take different sub-pools. With one counter every list past its row (nearly
+// all of them at 105 neighbours) waited for the same address: 500,000 such
+// lists cost 5.0 of the search's 5.7 ms, about 10 ns each.
+constexpr int kSubMax = 64;
+constexpr int kSubCtl = 16;
+constexpr int kCtlWords = kSubCtl * (1 + kSubMax);
+
+// SLAB: ids go to slab row (caller index) while it has room, then to a chain
+// of chunks, each taken by the hit of its first slot; lists whose chunk could
+// not be had are only counted from there on, and their leaf is queued.
 // Otherwise only the sinks queued that way are searched, their ids going to
 // offsets[pid] + slot.
 template <bool SLAB>
-__global__ __launch_bounds__(kSearchWaves * kWave) void k_neigh(NeighArgs a) {
-    __shared__ NeighShared sh_all[kSearchWaves];
-    NeighShared &sh = sh_all[threadIdx.x / kWave];
+__global__ __launch_bounds__(kWave) void k_neigh(NeighArgs a) {
+    __shared__ NeighShared sh;
     const int lane = lane_id();
     const int G = 1 << a.gk;
-    int64_t gi;
-    int li0, li1;   // the group's leaves to search
+    int64_t l;   // the wave's leaf, from 0
     if constexpr (SLAB) {
-        gi = xcd_wave_index();
-        if (gi >= a.ngroup) return;
-        li0 = 0;
-        li1 = G;
+        l = a.first + xcd_wave_index();
     } else {
-        const int64_t q = wave_index();
-        if (q >= a.nq) return;
-        const int32_t l = a.queue[q];
-        gi = l >> a.gk;
-        li0 = l & (G - 1);
-        li1 = li0 + 1;
+        l = __builtin_amdgcn_readfirstlane(a.queue[wave_index()]);
     }
-    const int64_t GL = (a.nleaf >> a.gk) + gi;
-    if (a.ncount[GL] == 0) return;
+    const int64_t gi = l >> a.gk, A = a.nleaf + l;
+    const int li = (int)(l & (G - 1));
+    const int32_t sA = a.nfirst[A], c = a.ncount[A];
+    if (c == 0) return;
     const int64_t n0 = a.gnear_beg[gi], n1 = a.gnear_end[gi];
-    for (int li = li0; li < li1; ++li) {
-        const int64_t A = a.nleaf + gi * G + li;
-        const int32_t sA = a.nfirst[A], c = a.ncount[A];
-        if (c == 0) continue;
-        bool leaf_over = false;   // slab mode: a list of this leaf is searched again
-        const LeafLanes L = leaf_lanes(c);
-        const double4 gA = a.rec[2 * A];
-        const double rA = a.hnode[A] * kReachPad;
-        const double rA2 = rA * rA;
-        for (int g0 = 0; g0 < c; g0 += L.S) {
-            const int si = g0 + L.sslot;
-            bool has_sink = L.sslot < L.S && si < c;
-            const int32_t pa = sA + (has_sink ? si : 0);
-            const int32_t oa = a.pid[pa];
-            int64_t obase = (int64_t)(a.tree_rows ? pa : oa) * kNbCap;
-            if constexpr (!SLAB) {   // the lists the count call could not keep
-                const int64_t o0 = has_sink ? a.offsets[oa] : 0;
-                has_sink = has_sink && a.offsets[oa + 1] - o0 > kNbCap && a.head[oa] < 0;
-                obase = o0;
-                if (ballot(has_sink) == 0ull) continue;
-            }
-            const double xa = a.px[pa], ya = a.py[pa], za = a.pz[pa];
-            const double two_h = 2.0 * a.ph[pa];
-            const double lim = has_sink ? two_h * two_h : -1.0;
-            if (L.slice == 0) {
-                sh.cnt[L.sslot] = 0;
-#pragma unroll
-                for (int q = 0; q < kNbChunks; ++q) sh.chunk[L.sslot][q] = -1;
-            }
-            tile_sync();
-            int head = 0;   // ring position of the first waiting source
-            int32_t *const row = a.ids + obase;
-            // hit h with slot r (0 for lanes without a hit): into the slab row, or
-            // (rare) one of the sink's chunks, each taken by the hit of its first slot
-            auto put = [&](bool h, uint32_t r, int32_t id) {
-                const bool low = !SLAB || r < (uint32_t)kNbCap;
-                if (h & low) row[r] = id;
-                if constexpr (SLAB) {
-                    // lanes with r >= kNbCap, as the comparison's own lane mask
-                    if (__builtin_amdgcn_uicmp(r, (uint32_t)kNbCap, kIcmpUge) != 0ull) {
-                        const uint32_t q = (r - kNbCap) / kNbChunk, o = (r - kNbCap) % kNbChunk;
-                        const bool kept = !low && q < (uint32_t)kNbChunks;
-                        if (kept && o == 0) {
-                            const int32_t ch = atomicAdd(a.ctl + 2, 1);
-                            sh.chunk[L.sslot][q] = ch < a.pool_cap ? ch : -2;
-                        }
-                        tile_sync();
-                        if (kept) {
-                            const int32_t ch = sh.chunk[L.sslot][q];
-                            if (ch >= 0) a.pool[(int64_t)ch * kNbChunk + o] = id;
-                        }
-                        tile_sync();
-                    }
-                }
-            };
-            auto test = [&](const SrcN &src) {
-                return (src.pb != pa) & (dist2(xa, ya, za, src.x, src.y, src.z) < lim);
-            };
-            // the ring as byte offsets: (offset & kRingBytes - 1) wraps it
-            auto at = [&](int b) -> const SrcN & {
-                return *reinterpret_cast<const SrcN *>(reinterpret_cast<const char *>(sh.tile) +
-                                                       (b & (kRingBytes - 1)));
-            };
-            // rows [0, np) of the waiting sources: slice j of a sink tests j, j + J,
-            // ...; two rows per step, so that their LDS traffic overlaps
-            auto rows = [&](int np) {
-                const int b0 = (head + L.slice) * (int)sizeof(SrcN), bJ = L.J * (int)sizeof(SrcN);
-                int u0 = 0;
-                for (; u0 + L.J < np; u0 += 2 * L.J) {
-                    const int b = b0 + u0 * (int)sizeof(SrcN);
-                    const SrcN s0 = at(b), s1 = at(b + bJ);
-                    const bool h0 = test(s0), h1 = test(s1);
-                    uint32_t r0 = 0, r1 = 0;
-                    if (h0) r0 = atomicAdd((uint32_t *)&sh.cnt[L.sslot], 1u);
-                    if (h1) r1 = atomicAdd((uint32_t *)&sh.cnt[L.sslot], 1u);
-                    put(h0, r0, s0.id);
-                    put(h1, r1, s1.id);
-                }
-                if (u0 < np) {
-                    const SrcN s0 = at(b0 + u0 * (int)sizeof(SrcN));
-                    const bool h0 = test(s0);
-                    uint32_t r0 = 0;
-                    if (h0) r0 = atomicAdd((uint32_t *)&sh.cnt[L.sslot], 1u);
-                    put(h0, r0, s0.id);
-                }
-                head = (head + np) & kRingMask;
-            };
-            int fill = 0;   // kept sources waiting in the ring from head
-            for (int64_t e0 = n0; e0 < n1; e0 += kWave) {
-                const int tot =
-                    load_entry_chunk(a.gnear, a.nfirst, a.ncount, e0, n1, 1u << (8 + li), sh.ec);
-                for (int t = 0; t < tot; t += kWave) {
-                    const int q = t + lane;
-                    double sx = 0.0, sy = 0.0, sz = 0.0;
-                    int32_t spb = -1, sid = -1;
-                    if (q < tot) {
-                        const int k = entry_of(sh.ec, q);
-                        const int32_t pb = sh.ec.fB[k] + (q - sh.ec.pos[k]);
-                        sx = a.px[pb];
-                        sy = a.py[pb];
-                        sz = a.pz[pb];
-                        spb = pb;
-                        sid = a.pid[pb];
-                    }
-                    const bool keep = q < tot && dist2(gA.x, gA.y, gA.z, sx, sy, sz) < rA2;
-                    const uint64_t kb = ballot(keep);
-                    if (keep) {   // appended in order after the waiting ones
-                        SrcN &dst = sh.tile[(head + fill + rank_below(kb)) & kRingMask];
-                        dst.x = sx;
-                        dst.y = sy;
-                        dst.z = sz;
-                        dst.pb = spb;
-                        dst.id = sid;
-                    }
-                    // every gather has landed: otherwise the waits for them (which on
-                    // this chip also wait for all earlier stores) are left to the rows
-                    __builtin_amdgcn_s_waitcnt(kVmcnt0);
-                    const int avail = fill + __popcll(kb);
-                    tile_sync();
-                    if (avail >= kWave) {   // whole rows only; the rest waits
-                        const int np = avail - avail % L.J;
-                        rows(np);
-                        fill = avail - np;
-                        tile_sync();
-                    } else {
-                        fill = avail;
-                    }
-                }
-            }
-            {   // pads the last partial row
-                SrcN &dst = sh.tile[(head + fill + lane) & kRingMask];
-                dst.x = dst.y = dst.z = __builtin_inf();
-                dst.pb = -1;
-                dst.id = -1;
-            }
-            tile_sync();
-            rows(fill);
-            tile_sync();
-            if (SLAB && has_sink && L.slice == 0) {
-                const int cnt = sh.cnt[L.sslot];
-                a.counts[oa] = cnt;
-                if (cnt > kNbCap) {
-                    const int need = (cnt - kNbCap + kNbChunk - 1) / kNbChunk;
-                    bool ok = need <= kNbChunks;
-                    for (int q = 0; ok && q < need; ++q) ok = sh.chunk[L.sslot][q] >= 0;
-                    if (ok) {   // at most one entry per chunk taken, so longq has room
-                        const int32_t e = atomicAdd(a.ctl + 3, 1);
-                        a.longq[e] = oa;
-#pragma unroll
-                        for (int q = 0; q < kNbChunks; ++q) a.longc[kNbChunks * e + q] = sh.chunk[L.sslot][q];
-                        a.head[oa] = e;
-                    } else {
-                        a.head[oa] = -1;
-                        atomicAdd(a.ctl, 1);
-                        leaf_over = true;
-                    }
-                }
-            }
-            if (!SLAB && has_sink && L.slice == 0) a.longq[atomicAdd(a.ctl, 1)] = oa;
-            tile_sync();   // cnt / chunk are reset by the next pass
+    bool leaf_over = false;   // slab mode: a list of this leaf is searched again
+    const double4 gA = a.rec[2 * A];
+    const double rA = a.hnode[A] * kReachPad;
+    const double rA2 = rA * rA;
+    for (int g0 = 0; g0 < c; g0 += kWave) {
+        const LeafLanes L = leaf_lanes(c - g0);   // the last pass of a big leaf spreads its rest
+        const int si = g0 + L.sslot;
+        bool has_sink = L.sslot < L.S && si < c;
+        const int32_t pa = sA + (has_sink ? si : 0);
+        const int32_t oa = a.pid[pa];
+        int64_t obase = (int64_t)(a.tree_rows ? pa : oa) * kNbCap;
+        if constexpr (!SLAB) {   // the lists the count call could not keep
+            const int64_t o0 = has_sink ? a.offsets[oa] : 0;
+            has_sink = has_sink && a.offsets[oa + 1] - o0 > kNbCap && a.head[oa] < 0;
+            obase = o0;
+            if (ballot(has_sink) == 0ull) continue;
         }
-        if (SLAB && ballot(leaf_over) != 0ull && lane == 0) a.queue[atomicAdd(a.ctl + 1, 1)] = (int32_t)(A - a.nleaf);
+        const double xa = a.px[pa], ya = a.py[pa], za = a.pz[pa];
+        const double two_h = 2.0 * a.ph[pa];
+        const double lim = has_sink ? two_h * two_h : -1.0;
+        if (L.slice == 0) sh.cnt[L.sslot] = 0;
+        tile_sync();
+        int head = 0;   // ring position of the first waiting source
+        int32_t *const row = a.ids + obase;
+        // hit h with slot r (0 for lanes without a hit): into the slab row, or
+        // (rare) one of the sink's chunks, each taken by the hit of its first slot
+        auto put = [&](bool h, uint32_t r, int32_t id) {
+            const bool low = !SLAB || r < (uint32_t)kNbCap;
+            if (h & low) row[r] = id;
+            if constexpr (SLAB) {
+                // lanes with r >= kNbCap, as the comparison's own lane mask
+                if (__builtin_amdgcn_uicmp(r, (uint32_t)kNbCap, kIcmpUge) != 0ull) {
+                    const uint32_t q = (r - kNbCap) / kNbChunk, o = (r - kNbCap) % kNbChunk;
+                    if (!low && o == 0) {
+                        const int32_t prev = q ? sh.chunk[L.sslot][(q - 1) & 1] : 0;
+                        int32_t ch = -1;
+                        if (prev >= 0) {
+                            const int32_t sub = (int32_t)gi & a.sub_mask;
+                            const int32_t i = atomicAdd(a.ctl + kSubCtl * (1 + sub), 1);
+                            if (i < a.sub_cap) {
+                                ch = (int32_t)(sub * a.sub_cap) + i;
+                                if (q) a.next[prev] = ch;
+                                else a.head[oa] = ch;
+                            }
+                        }
+                        sh.chunk[L.sslot][q & 1] = ch;
+                    }
+                    tile_sync();
+                    if (!low) {
+                        const int32_t ch = sh.chunk[L.sslot][q & 1];
+                        if (ch >= 0) a.pool[(int64_t)ch * kNbChunk + o] = id;
+                    }
+                    tile_sync();
+                }
+            }
+        };
+        auto test = [&](const SrcN &src) {
+            return (src.pb != pa) & (dist2(xa, ya, za, src.x, src.y, src.z) < lim);
+        };
+        // the ring as byte offsets: (offset & kRingBytes - 1) wraps it
+        auto at = [&](int b) -> const SrcN & {
+            return *reinterpret_cast<const SrcN *>(reinterpret_cast<const char *>(sh.tile) +
+                                                   (b & (kRingBytes - 1)));
+        };
+        // rows [0, np) of the waiting sources: slice j of a sink tests j, j + J,
+        // ...; two rows per step, so that their LDS traffic overlaps
+        auto rows = [&](int np) {
+            const int b0 = (head + L.slice) * (int)sizeof(SrcN), bJ = L.J * (int)sizeof(SrcN);
+            int u0 = 0;
+            for (; u0 + L.J < np; u0 += 2 * L.J) {
+                const int b = b0 + u0 * (int)sizeof(SrcN);
+                const SrcN s0 = at(b), s1 = at(b + bJ);
+                const bool h0 = test(s0), h1 = test(s1);
+                uint32_t r0 = 0, r1 = 0;
+                if (h0) r0 = atomicAdd((uint32_t *)&sh.cnt[L.sslot], 1u);
+                if (h1) r1 = atomicAdd((uint32_t *)&sh.cnt[L.sslot], 1u);
+                put(h0, r0, s0.id);
+                put(h1, r1, s1.id);
+            }
+            if (u0 < np) {
+                const SrcN s0 = at(b0 + u0 * (int)sizeof(SrcN));
+                const bool h0 = test(s0);
+                uint32_t r0 = 0;
+                if (h0) r0 = atomicAdd((uint32_t *)&sh.cnt[L.sslot], 1u);
+                put(h0, r0, s0.id);
+            }
+            head = (head + np) & kRingMask;
+        };
+        int fill = 0;   // kept sources waiting in the ring from head
+        for (int64_t e0 = n0; e0 < n1; e0 += kWave) {
+            const int tot =
+                load_entry_chunk(a.gnear, a.nfirst, a.ncount, e0, n1, 1u << (8 + li), sh.ec);
+            for (int t = 0; t < tot; t += kWave) {
+                const int q = t + lane;
+                double sx = 0.0, sy = 0.0, sz = 0.0;
+                int32_t spb = -1, sid = -1;
+                if (q < tot) {
+                    const int k = entry_of(sh.ec, q);
+                    const int32_t pb = sh.ec.fB[k] + (q - sh.ec.pos[k]);
+                    sx = a.px[pb];
+                    sy = a.py[pb];
+                    sz = a.pz[pb];
+                    spb = pb;
+                    sid = a.pid[pb];
+                }
+                const bool keep = q < tot && dist2(gA.x, gA.y, gA.z, sx, sy, sz) < rA2;
+                const uint64_t kb = ballot(keep);
+                if (keep) {   // appended in order after the waiting ones
+                    SrcN &dst = sh.tile[(head + fill + rank_below(kb)) & kRingMask];
+                    dst.x = sx;
+                    dst.y = sy;
+                    dst.z = sz;
+                    dst.pb = spb;
+                    dst.id = sid;
+                }
+                // every gather has landed: otherwise the waits for them (which on
+                // this chip also wait for all earlier stores) are left to the rows
+                __builtin_amdgcn_s_waitcnt(kVmcnt0);
+                const int avail = fill + __popcll(kb);
+                tile_sync();
+                if (avail >= kWave) {   // whole rows only; the rest waits
+                    const int np = avail - avail % L.J;
+                    rows(np);
+                    fill = avail - np;
+                    tile_sync();
+                } else {
+                    fill = avail;
+                }
+            }
+        }
+        {   // pads the last partial row
+            SrcN &dst = sh.tile[(head + fill + lane) & kRingMask];
+            dst.x = dst.y = dst.z = __builtin_inf();
+            dst.pb = -1;
+            dst.id = -1;
+        }
+        tile_sync();
+        rows(fill);
+        tile_sync();
+        if (SLAB && has_sink && L.slice == 0) {
+            const int cnt = sh.cnt[L.sslot];
+            a.counts[oa] = cnt;
+            if (cnt > kNbCap) {
+                const int last = (cnt - kNbCap - 1) / kNbChunk;   // its last chunk
+                if (sh.chunk[L.sslot][last & 1] >= 0) {
+                    if (cnt > kNbWaveMax) atomicAdd(a.ctl + 2, 1);
+                } else {
+                    a.head[oa] = -1;
+                    atomicAdd(a.ctl, 1);
+                    leaf_over = true;
+                }
+            }
+        }
+        if (!SLAB && has_sink && L.slice == 0) a.longq[atomicAdd(a.ctl, 1)] = oa;
+        tile_sync();   // cnt / chunk are reset by the next pass
     }
+    if (SLAB && ballot(leaf_over) != 0ull && lane == 0) a.queue[atomicAdd(a.ctl + 1, 1)] = (int32_t)l;
 }
 
 // caller index -> tree position (slab rows by tree position)
@@ -367,83 +368,6 @@ __device__ __forceinline__ void net64_merge(uint32_t (&v)[8], int j0) {
     if constexpr (K >= 64) net64_stride<K / 64>(v, j0);
 }
 
-// slab rows -> the caller's CSR, in caller order: 8 lanes per particle, each
-// loading 8 consecutive slots of the row (keys past the count are 2^32 - 1,
-// i.e. last); the lists are sorted ascending, staged in LDS and stored one
-// particle at a time, each list by consecutive lanes. Lists longer than the
-// row are the long-list kernels'.
-__global__ __launch_bounds__(kBlock) void k_nb_compact(int64_t n, const int32_t *__restrict__ inv,
-                                                       const int64_t *__restrict__ offsets,
-                                                       const int32_t *__restrict__ slab,
-                                                       int32_t *__restrict__ ids) {
-    __shared__ uint32_t stage[kWaves][8 * kNbCap];
-    uint32_t *st = stage[threadIdx.x / kWave];
-    const int lane = lane_id();
-    const int64_t a = (blockIdx.x * (int64_t)kBlock + threadIdx.x) / 8;
-    const int j0 = lane % 8, p = lane / 8;
-    int64_t o = 0, c = 0;
-    if (a < n) {
-        o = offsets[a];
-        c = offsets[a + 1] - o;
-        if (c > kNbCap) c = 0;
-    }
-    uint32_t v[8];
-    if (8 * j0 < c) {
-        const int64_t r = inv ? (int64_t)inv[a] : a;   // the particle's slab row
-        const int4 *src = reinterpret_cast<const int4 *>(slab + r * kNbCap + 8 * j0);
-        const int4 x = src[0], y = src[1];
-        v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
-        v[4] = y.x; v[5] = y.y; v[6] = y.z; v[7] = y.w;
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (8 * j0 + u >= c) v[u] = 0xffffffffu;
-    } else {
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = 0xffffffffu;
-    }
-    if (ballot(c > 1) != 0ull) {   // wave-uniform: every lane takes part in the exchanges
-        net64_merge<2>(v, j0);
-        net64_merge<4>(v, j0);
-        net64_merge<8>(v, j0);
-        net64_merge<16>(v, j0);
-        net64_merge<32>(v, j0);
-        net64_merge<64>(v, j0);
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) st[p * kNbCap + 8 * j0 + u] = v[u];
-    tile_sync();
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {   // particle q of the wave: its list by lanes 0 .. c - 1
-        const int64_t oq = ((int64_t)__builtin_amdgcn_readlane((int)(o >> 32), 8 * q) << 32) |
-                           (uint32_t)__builtin_amdgcn_readlane((int)o, 8 * q);
-        const int cq = __builtin_amdgcn_readlane((int)c, 8 * q);
-        if (lane < cq) ids[oq + lane] = (int32_t)st[q * kNbCap + lane];
-    }
-}
-
-// Network of the same kind over P = 2^logP keys in LDS (P <= kLongLds),
-// comparators split over the nt threads of the caller (tid < nt); sync() is
-// called after each stage.
-template <typename Sync>
-__device__ __forceinline__ void lds_network(uint32_t *key, int logP, int tid, int nt, Sync sync) {
-    const int P = 1 << logP;
-    for (int lk = 1; lk <= logP; ++lk) {
-        for (int ld = lk - 1; ld >= 0; --ld) {
-            const int d = 1 << ld;
-            for (int t = tid; t < P / 2; t += nt) {
-                const int i = ((t >> ld) << (ld + 1)) | (t & (d - 1));   // bit d of i is clear
-                const int j = ld == lk - 1 ? (i ^ ((1 << lk) - 1)) : (i + d);
-                const uint32_t x = key[i], y = key[j];
-                if (y < x) {
-                    key[i] = y;
-                    key[j] = x;
-                }
-            }
-            sync();
-        }
-    }
-}
-
 // The same all-ascending network over 64 U keys held U per lane (key i in
 // register i % U of lane i / U): strides below U are exchanges between
 // registers, the others between lanes (shuffles).
@@ -479,53 +403,141 @@ __device__ __forceinline__ void net_lanes(uint32_t (&v)[U], int lane) {
     }
 }
 
-// Lists of kNbCap < c <= kNbCap + kNbChunks kNbChunk ids kept by the count
-// call (row plus chunks): one wave per list, 4 keys per lane (16-byte loads:
-// lanes 0-15 read the row, every further 16 lanes one chunk), sorted in
-// registers.
-__global__ __launch_bounds__(kBlock) void k_nb_compact_long(int32_t nlong, const int32_t *__restrict__ inv,
-                                                            const int32_t *__restrict__ longq,
-                                                            const int64_t *__restrict__ offsets,
-                                                            const int32_t *__restrict__ slab,
-                                                            const int32_t *__restrict__ longc,
-                                                            const int32_t *__restrict__ pool,
-                                                            int32_t *__restrict__ ids) {
-    static_assert(kNbCap + kNbChunks * kNbChunk == 4 * kWave, "row + chunks = 4 keys per lane");
-    const int64_t w = wave_index();
-    if (w >= nlong) return;
+// slab rows -> the caller's CSR, in caller order: 8 lanes per particle, each
+// loading 8 consecutive slots of the row (keys past the count are 2^32 - 1,
+// i.e. last); the lists are sorted ascending, staged in LDS and stored one
+// particle at a time, each list by consecutive lanes. Then the wave takes its
+// particles' lists longer than the row, one after the other: up to kNbWaveMax
+// ids as 4 keys per lane (16-byte loads: lanes 0-15 read the row, every
+// further 16 lanes one chunk), sorted in registers; longer ones are copied
+// and queued for k_nb_sort_long. Lists searched again (head -1) are skipped.
+__global__ __launch_bounds__(kBlock) void k_nb_compact(int64_t n, const int32_t *__restrict__ inv,
+                                                       const int64_t *__restrict__ offsets,
+                                                       const int32_t *__restrict__ slab,
+                                                       const int32_t *__restrict__ head,
+                                                       const int32_t *__restrict__ next,
+                                                       const int32_t *__restrict__ pool,
+                                                       int32_t *__restrict__ ids, int32_t *__restrict__ nlong,
+                                                       int32_t *__restrict__ longq) {
+    __shared__ uint32_t stage[kWaves][8 * kNbCap];
+    uint32_t *st = stage[threadIdx.x / kWave];
     const int lane = lane_id();
-    const int32_t a = longq[w];
-    const int64_t o = offsets[a];
-    const int c = (int)(offsets[a + 1] - o);
-    const int i0 = 4 * lane;
-    uint32_t v[4] = {0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu};
-    if (i0 < c) {
-        const int32_t *src = i0 < kNbCap
-                                 ? slab + (int64_t)(inv ? inv[a] : a) * kNbCap + i0
-                                 : pool + (int64_t)longc[kNbChunks * w + (i0 - kNbCap) / kNbChunk] * kNbChunk +
-                                       (i0 - kNbCap) % kNbChunk;
-        const int4 q = *reinterpret_cast<const int4 *>(src);
-        v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (i0 + u >= c) v[u] = 0xffffffffu;
+    const int64_t a = (blockIdx.x * (int64_t)kBlock + threadIdx.x) / 8;
+    const int j0 = lane % 8, p = lane / 8;
+    int64_t o = 0, call = 0;
+    if (a < n) {
+        o = offsets[a];
+        call = offsets[a + 1] - o;
     }
-    net_lanes<4>(v, lane);
+    const int c = call > kNbCap ? 0 : (int)call;
+    uint32_t v[8];
+    if (8 * j0 < c) {
+        const int64_t r = inv ? (int64_t)inv[a] : a;   // the particle's slab row
+        const int4 *src = reinterpret_cast<const int4 *>(slab + r * kNbCap + 8 * j0);
+        const int4 x = src[0], y = src[1];
+        v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
+        v[4] = y.x; v[5] = y.y; v[6] = y.z; v[7] = y.w;
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-        if (i0 + u < c) ids[o + i0 + u] = (int32_t)v[u];
+        for (int u = 0; u < 8; ++u)
+            if (8 * j0 + u >= c) v[u] = 0xffffffffu;
+    } else {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = 0xffffffffu;
+    }
+    if (ballot(c > 1) != 0ull) {   // wave-uniform: every lane takes part in the exchanges
+        net64_merge<2>(v, j0);
+        net64_merge<4>(v, j0);
+        net64_merge<8>(v, j0);
+        net64_merge<16>(v, j0);
+        net64_merge<32>(v, j0);
+        net64_merge<64>(v, j0);
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) st[p * kNbCap + 8 * j0 + u] = v[u];
+    tile_sync();
+    const auto list_start = [&](int l) {   // o of lane l (uniform)
+        return ((int64_t)__builtin_amdgcn_readlane((int)(o >> 32), l) << 32) |
+               (uint32_t)__builtin_amdgcn_readlane((int)o, l);
+    };
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {   // particle q of the wave: its list by lanes 0 .. c - 1
+        const int64_t oq = list_start(8 * q);
+        const int cq = __builtin_amdgcn_readlane(c, 8 * q);
+        if (lane < cq) ids[oq + lane] = (int32_t)st[q * kNbCap + lane];
+    }
+    uint64_t lm = ballot(j0 == 0 && call > kNbCap);
+    if (lm == 0) return;
+    const int64_t a0 = a - p;
+    while (lm) {
+        const int l = __ffsll((long long)lm) - 1;
+        lm &= lm - 1;
+        const int64_t al = a0 + l / 8, ol = list_start(l);
+        const int cl = __builtin_amdgcn_readlane((int)call, l);   // < n <= 2^31 - 1
+        int32_t ch = head[al];
+        if (ch < 0) continue;
+        const int32_t *const row = slab + (inv ? (int64_t)inv[al] : al) * kNbCap;
+        if (cl <= kNbWaveMax) {
+            const int32_t c1 = cl > kNbCap + kNbChunk ? next[ch] : 0;
+            const int32_t c2 = cl > kNbCap + 2 * kNbChunk ? next[c1] : 0;
+            const int i0 = 4 * lane;
+            uint32_t w[4] = {0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu};
+            if (i0 < cl) {
+                const int32_t cq = i0 < kNbCap + kNbChunk ? ch : (i0 < kNbCap + 2 * kNbChunk ? c1 : c2);
+                const int32_t *src =
+                    i0 < kNbCap ? row + i0 : pool + (int64_t)cq * kNbChunk + (i0 - kNbCap) % kNbChunk;
+                const int4 x = *reinterpret_cast<const int4 *>(src);
+                w[0] = x.x; w[1] = x.y; w[2] = x.z; w[3] = x.w;
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (i0 + u >= cl) w[u] = 0xffffffffu;
+            }
+            net_lanes<4>(w, lane);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (i0 + u < cl) ids[ol + i0 + u] = (int32_t)w[u];
+        } else {
+            ids[ol + lane] = row[lane];
+            for (int i = kNbCap;; i += kNbChunk) {
+                if (i + lane < cl) ids[ol + i + lane] = pool[(int64_t)ch * kNbChunk + lane];
+                if (i + kNbChunk >= cl) break;
+                ch = next[ch];
+            }
+            if (lane == 0) longq[atomicAdd(nlong, 1)] = (int32_t)al;
+        }
+    }
 }
 
-// One workgroup per list searched again by the fill call: the same network
+// Network of the same kind over P = 2^logP keys in LDS (P <= kLongLds),
+// comparators split over the nt threads of the caller (tid < nt); sync() is
+// called after each stage.
+template <typename Sync>
+__device__ __forceinline__ void lds_network(uint32_t *key, int logP, int tid, int nt, Sync sync) {
+    const int P = 1 << logP;
+    for (int lk = 1; lk <= logP; ++lk) {
+        for (int ld = lk - 1; ld >= 0; --ld) {
+            const int d = 1 << ld;
+            for (int t = tid; t < P / 2; t += nt) {
+                const int i = ((t >> ld) << (ld + 1)) | (t & (d - 1));   // bit d of i is clear
+                const int j = ld == lk - 1 ? (i ^ ((1 << lk) - 1)) : (i + d);
+                const uint32_t x = key[i], y = key[j];
+                if (y < x) {
+                    key[i] = y;
+                    key[j] = x;
+                }
+            }
+            sync();
+        }
+    }
+}
+
+// One workgroup per list of more than kNbWaveMax ids or searched again by the
+// fill call: the same network
 // over the list's length rounded up to a power of two P, in LDS (padded with
 // 2^32 - 1) when P <= kLongLds, else in place in the CSR with the comparators
 // that reach past the end left out (with every comparator ascending, keys of
 // 2^32 - 1 past the end would never move).
-__global__ __launch_bounds__(kBlock) void k_nb_sort_long(const int32_t *__restrict__ longq,
-                                                         const int64_t *__restrict__ offsets,
-                                                         int32_t *__restrict__ ids) {
-    __shared__ uint32_t sm[kLongLds];
-    const int32_t a = longq[blockIdx.x];
+__device__ __forceinline__ void sort_long_list(uint32_t *sm, int32_t a, const int64_t *__restrict__ offsets,
+                                               int32_t *__restrict__ ids) {
     const int64_t o = offsets[a], L = offsets[a + 1] - o;
     int logP = 0;
     while (((int64_t)1 << logP) < L) ++logP;
@@ -558,6 +570,16 @@ __global__ __launch_bounds__(kBlock) void k_nb_sort_long(const int32_t *__restri
     }
 }
 
+__global__ __launch_bounds__(kBlock) void k_nb_sort_long(int64_t nsort, const int32_t *__restrict__ longq,
+                                                         const int64_t *__restrict__ offsets,
+                                                         int32_t *__restrict__ ids) {
+    __shared__ uint32_t sm[kLongLds];
+    for (int64_t i = blockIdx.x; i < nsort; i += gridDim.x) {
+        sort_long_list(sm, longq[i], offsets, ids);
+        __syncthreads();
+    }
+}
+
 // Slab rows go by caller index, so that the fill call streams them in the
 // CSR's order; past 4 GiB of slab (16.7M particles) by tree position instead,
 // where a wave's rows are contiguous: the search's scattered stores into a
@@ -580,29 +602,36 @@ rcb_status neighbours_count(rcb_tree *t, int64_t *offsets, int64_t *total, hipSt
     rcb_status st = ensure_walk(t, s);
     if (st != RCB_OK) return st;
     if (!t->nb_slab) {
-        // one 64-slot chunk for every 8th particle: lists past 64 ids are 3% (Plummer)
-        // to 8% (clumps) at ~50 neighbours on average; the rest is searched again by
-        // the fill call
-        t->nb_pool_cap = t->n / 8 + 1;
+        // overflow chunks: one for every 8th particle (lists past 64 ids are 3%
+        // (Plummer) to 8% (clumps) at ~50 neighbours on average), and the number
+        // that the walk's estimate of each cell's neighbour count asks for (at
+        // most 4 per particle; at 105 neighbours, one for nearly each)
+        t->nb_subs = 1;
+        while (t->nb_subs < kSubMax && t->nb_subs * 8 < t->ngroup) t->nb_subs *= 2;
+        const int64_t base = t->n / 8 + 1;
+        const int64_t more = std::min<int64_t>({t->nb_est, 4 * t->n, ((int64_t)1 << 30) - base});   // (int32 chunk ids)
         t->nb_slab = (int32_t *)dalloc(t, sizeof(int32_t) * t->n * kNbCap, s, t->list_allocs);
-        t->nb_pool = (int32_t *)dalloc(t, sizeof(int32_t) * t->nb_pool_cap * kNbChunk, s, t->list_allocs);
+        for (int64_t want : {base + more, base}) {   // the smaller pool if the larger cannot be had
+            t->nb_sub_cap = (want + t->nb_subs - 1) / t->nb_subs + 8;
+            t->nb_pool = (int32_t *)dalloc(t, sizeof(int32_t) * t->nb_sub_cap * t->nb_subs * kNbChunk, s, t->list_allocs);
+            if (t->nb_pool || more == 0) break;
+        }
+        t->nb_next = (int32_t *)dalloc(t, sizeof(int32_t) * t->nb_sub_cap * t->nb_subs, s, t->list_allocs);
         t->nb_head = (int32_t *)dalloc(t, sizeof(int32_t) * t->n, s, t->list_allocs);
-        t->nb_longq = (int32_t *)dalloc(t, sizeof(int32_t) * t->nb_pool_cap, s, t->list_allocs);
-        t->nb_longc = (int32_t *)dalloc(t, sizeof(int32_t) * kNbChunks * t->nb_pool_cap, s, t->list_allocs);
         t->nb_queue = (int32_t *)dalloc(t, sizeof(int32_t) * t->nleaf, s, t->list_allocs);
-        t->nb_ctl = (int32_t *)dalloc(t, sizeof(int32_t) * 4, s, t->list_allocs);
-        if (!t->nb_slab || !t->nb_pool || !t->nb_head || !t->nb_longq || !t->nb_longc || !t->nb_queue ||
-            !t->nb_ctl)
+        t->nb_ctl = (int32_t *)dalloc(t, sizeof(int32_t) * kCtlWords, s, t->list_allocs);
+        if (!t->nb_slab || !t->nb_pool || !t->nb_next || !t->nb_head || !t->nb_queue || !t->nb_ctl)
             return RCB_ENOMEM;
     }
-    RCB_ZERO(t->nb_ctl, sizeof(int32_t) * 4, s);
+    RCB_ZERO(t->nb_ctl, sizeof(int32_t) * kCtlWords, s);
     NeighArgs a{t->nleaf, t->gk, t->ngroup, t->wrec, t->nhnode, t->nfirst, t->ncount, t->gnear_beg,
                 t->gnear_end, t->gnear, t->px, t->py, t->pz, t->ph, t->pid, offsets, nullptr, t->nb_slab,
-                t->nb_pool, t->nb_longc, t->nb_pool_cap, t->nb_head, t->nb_ctl, t->nb_queue, t->nb_longq, 0,
-                tree_rows(t)};
-    const unsigned grid = (unsigned)((t->ngroup + kSearchWaves - 1) / kSearchWaves);
-    k_neigh<true><<<grid, kSearchWaves * kWave, 0, s>>>(a);
-    RCB_LAUNCH_CHECK("k_neigh<slab>");
+                t->nb_pool, t->nb_next, t->nb_sub_cap, t->nb_subs - 1, t->nb_head, t->nb_ctl, t->nb_queue, nullptr,
+                0, tree_rows(t)};
+    for (; a.first < t->nleaf; a.first += kMaxGrid) {
+        k_neigh<true><<<(unsigned)std::min(kMaxGrid, t->nleaf - a.first), kWave, 0, s>>>(a);
+        RCB_LAUNCH_CHECK("k_neigh<slab>");
+    }
     st = scan_i64(t, offsets, offsets, t->n, s);   // in place
     if (st != RCB_OK) return st;
     int32_t ctl[4] = {0, 0, 0, 0};
@@ -612,7 +641,7 @@ rcb_status neighbours_count(rcb_tree *t, int64_t *offsets, int64_t *total, hipSt
     t->nb_total = *total;
     t->nb_over = ctl[0];
     t->nb_nq = ctl[1];
-    t->nb_long = ctl[3];
+    t->nb_long = ctl[2];
     return RCB_OK;
 }
 
@@ -635,28 +664,29 @@ rcb_status neighbours_fill(rcb_tree *t, const int64_t *offsets, int32_t *ids, in
         k_inv<<<(unsigned)((t->n + kBlock - 1) / kBlock), kBlock, 0, s>>>(t->n, t->pid, inv);
         RCB_LAUNCH_CHECK("k_inv");
     }
-    const unsigned gridc = (unsigned)((t->n * 8 + kBlock - 1) / kBlock);
-    k_nb_compact<<<gridc, kBlock, 0, s>>>(t->n, inv, offsets, t->nb_slab, ids);
-    RCB_LAUNCH_CHECK("k_nb_compact");
-    if (t->nb_long > 0) {
-        const unsigned gl = (unsigned)((t->nb_long + kWaves - 1) / kWaves);
-        k_nb_compact_long<<<gl, kBlock, 0, s>>>(t->nb_long, inv, t->nb_longq, offsets, t->nb_slab, t->nb_longc,
-                                                t->nb_pool, ids);
-        RCB_LAUNCH_CHECK("k_nb_compact_long");
+    // the lists that one workgroup each sorts: those of more than kNbWaveMax
+    // ids (copied by the compaction) and those searched again
+    int32_t *longq = nullptr, *nlong = nullptr;
+    const int64_t sorts = (int64_t)t->nb_long + t->nb_over;
+    if (sorts > 0) {
+        longq = (int32_t *)dalloc(t, sizeof(int32_t) * (sorts + 1), s, tmp);
+        if (!longq) return RCB_ENOMEM;
+        nlong = longq + sorts;
+        RCB_ZERO(nlong, sizeof(int32_t), s);
     }
+    const unsigned gridc = (unsigned)((t->n * 8 + kBlock - 1) / kBlock);
+    k_nb_compact<<<gridc, kBlock, 0, s>>>(t->n, inv, offsets, t->nb_slab, t->nb_head, t->nb_next, t->nb_pool, ids,
+                                          nlong, longq);
+    RCB_LAUNCH_CHECK("k_nb_compact");
     if (t->nb_nq > 0) {
-        int32_t *longq = (int32_t *)dalloc(t, sizeof(int32_t) * (size_t)t->nb_over, s, tmp);
-        int32_t *ctl = (int32_t *)dalloc(t, sizeof(int32_t), s, tmp);
-        if (!longq || !ctl) return RCB_ENOMEM;
-        RCB_ZERO(ctl, sizeof(int32_t), s);
         NeighArgs a{t->nleaf, t->gk, t->ngroup, t->wrec, t->nhnode, t->nfirst, t->ncount, t->gnear_beg,
                     t->gnear_end, t->gnear, t->px, t->py, t->pz, t->ph, t->pid, nullptr, offsets, ids,
-                    nullptr, nullptr, 0, t->nb_head, ctl, t->nb_queue, longq, t->nb_nq, false};
-        const unsigned grid = (unsigned)((t->nb_nq + kSearchWaves - 1) / kSearchWaves);
-        k_neigh<false><<<grid, kSearchWaves * kWave, 0, s>>>(a);
+                    nullptr, nullptr, 0, 0, t->nb_head, nlong, t->nb_queue, longq, 0, false};
+        k_neigh<false><<<(unsigned)t->nb_nq, kWave, 0, s>>>(a);
         RCB_LAUNCH_CHECK("k_neigh<fill>");
-        // exactly the nb_over lists the count call could not keep append themselves
-        k_nb_sort_long<<<(unsigned)t->nb_over, kBlock, 0, s>>>(longq, offsets, ids);
+    }
+    if (sorts > 0) {   // exactly this many lists appended themselves
+        k_nb_sort_long<<<(unsigned)std::min(kMaxGrid, sorts), kBlock, 0, s>>>(sorts, longq, offsets, ids);
         RCB_LAUNCH_CHECK("k_nb_sort_long");
     }
     return RCB_OK;

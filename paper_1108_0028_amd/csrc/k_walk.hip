@@ -73,6 +73,16 @@ struct WalkArgs {
     unsigned long long *stats;   // if given: [0] node records tested, [1] (node, leaf) tests
 };
 
+// what k_slab_ends estimates the neighbour lists' overflow from
+struct NbEstimate {
+    int64_t nleaf;
+    int gk;
+    double n;   // particles
+    const int32_t *ncount;
+    const double *nlo, *nhi, *hnode;
+    const double4 *rec;
+};
+
 // bit 8 s set iff byte s of x is non-zero (the lead lane of entry s)
 __device__ __forceinline__ uint64_t byte_any(uint64_t x) {
     x |= x >> 4;
@@ -379,18 +389,38 @@ __global__ __launch_bounds__(WAVES * kWave) void k_walk_wide(WalkArgs w, int32_t
     }
 }
 
-// ends of the slab lists: [g cap, g cap + count)
+// ends of the slab lists: [g cap, g cap + count). With est, also the neighbour
+// search's overflow chunks that the group will need: a cell of c particles in
+// volume V expects c / V 4 pi / 3 (2h)^3 neighbours each (2h: h_node - h_node_int),
+// and lists past 64 ids take chunks of 64. It only sizes a pool.
 __global__ __launch_bounds__(kBlock) void k_slab_ends(int64_t ngroup, int64_t near_cap, int64_t far_cap,
                                                       const int64_t *__restrict__ ncnt,
                                                       const int64_t *__restrict__ fcnt,
                                                       int64_t *__restrict__ nbeg, int64_t *__restrict__ nend,
-                                                      int64_t *__restrict__ fbeg, int64_t *__restrict__ fend) {
+                                                      int64_t *__restrict__ fbeg, int64_t *__restrict__ fend,
+                                                      const NbEstimate e, unsigned long long *__restrict__ est) {
     const int64_t g = blockIdx.x * (int64_t)kBlock + threadIdx.x;
-    if (g >= ngroup) return;
-    nbeg[g] = g * near_cap;
-    nend[g] = g * near_cap + ncnt[g];
-    fbeg[g] = g * far_cap;
-    fend[g] = g * far_cap + fcnt[g];
+    double chunks = 0.0;
+    if (g < ngroup) {
+        nbeg[g] = g * near_cap;
+        nend[g] = g * near_cap + ncnt[g];
+        fbeg[g] = g * far_cap;
+        fend[g] = g * far_cap + fcnt[g];
+        for (int i = 0; est && i < 1 << e.gk; ++i) {
+            const int64_t A = e.nleaf + (g << e.gk) + i;
+            const double c = e.ncount[A];
+            const double V = (e.nhi[3 * A] - e.nlo[3 * A]) * (e.nhi[3 * A + 1] - e.nlo[3 * A + 1]) *
+                             (e.nhi[3 * A + 2] - e.nlo[3 * A + 2]);
+            const double r = e.hnode[A] - e.rec[2 * A].w;
+            double nb = 4.19 * c / V * r * r * r * 1.1;   // (10% over the mean)
+            if (!(nb < e.n)) nb = e.n;                    // (also a cell without volume)
+            if (c > 0.0 && nb > 64.0) chunks += c * ceil((nb - 64.0) / 64.0);
+        }
+    }
+    if (est) {
+        chunks = wave_sum(chunks);
+        if (lane_id() == 0 && chunks > 0.0) atomicAdd(est, (unsigned long long)chunks);
+    }
 }
 
 // Sort the near lists of the groups walked by k_walk_group by label (bitonic
@@ -546,7 +576,7 @@ rcb_status ensure_walk(rcb_tree *t, hipStream_t s) {
     // per-group counts, the later tiers' queues and the statistics: one block
     // kept by the tree for its later walks (no frees between the walk's
     // kernels and the next call's)
-    const size_t ws_bytes = sizeof(int64_t) * 2 * NG + sizeof(int32_t) * 2 * NG + 2 * sizeof(unsigned long long) + 64;
+    const size_t ws_bytes = sizeof(int64_t) * 2 * NG + sizeof(int32_t) * 2 * NG + 3 * sizeof(unsigned long long) + 64;
     if (!t->walk_ws) {
         t->walk_ws = dalloc(t, ws_bytes, s, t->allocs);
         if (!t->walk_ws) return RCB_ENOMEM;
@@ -554,7 +584,7 @@ rcb_status ensure_walk(rcb_tree *t, hipStream_t s) {
     int64_t *ncnt = (int64_t *)t->walk_ws;
     int64_t *fcnt = ncnt + NG;
     unsigned long long *stats = (unsigned long long *)(fcnt + NG);
-    int32_t *queue = (int32_t *)(stats + 2);    // groups for the 2nd tier
+    int32_t *queue = (int32_t *)(stats + 3);    // groups for the 2nd tier
     int32_t *queue2 = queue + NG;               // and for k_walk_group
     int64_t cn = 0, cf = 0;
     std::vector<void *> slabs;
@@ -588,7 +618,7 @@ rcb_status ensure_walk(rcb_tree *t, hipStream_t s) {
     // the flags (errors, list counts, the tiers' queue lengths) and the
     // statistics, read once after each tier that runs
     int32_t flags[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    unsigned long long hstats[2] = {0, 0};
+    unsigned long long hstats[3] = {0, 0, 0};   // [2]: k_slab_ends' estimate
     auto read_flags = [&]() -> rcb_status {
         const HostRead r[2] = {{t->dflag, flags, (int)sizeof(flags)}, {stats, hstats, (int)sizeof(hstats)}};
         return read_small(s, r, 2, "rcb_walk");
@@ -598,9 +628,10 @@ rcb_status ensure_walk(rcb_tree *t, hipStream_t s) {
     // later tiers rewrote some counts
     int64_t *ends = (int64_t *)dalloc(t, sizeof(int64_t) * 4 * NG, s, t->list_allocs);
     if (!ends) return RCB_ENOMEM;
-    auto slab_ends = [&]() -> rcb_status {
+    const NbEstimate ne{t->nleaf, t->gk, (double)t->n, t->ncount, t->nlo, t->nhi, t->nhnode, t->wrec};
+    auto slab_ends = [&](unsigned long long *est) -> rcb_status {
         k_slab_ends<<<(unsigned)((NG + kBlock - 1) / kBlock), kBlock, 0, s>>>(NG, cn, cf, ncnt, fcnt, ends, ends + NG,
-                                                                              ends + 2 * NG, ends + 3 * NG);
+                                                                              ends + 2 * NG, ends + 3 * NG, ne, est);
         RCB_LAUNCH_CHECK("k_slab_ends");
         return RCB_OK;
     };
@@ -610,7 +641,7 @@ rcb_status ensure_walk(rcb_tree *t, hipStream_t s) {
         else k_walk_wide<false, kWQueue, kWaves><<<grid, kBlock, 0, s>>>(w, q1, t->dflag + 6, nullptr, 0, cap1);
         RCB_LAUNCH_CHECK("k_walk_wide");
         if (count_queues) {
-            rcb_status st = slab_ends();
+            rcb_status st = slab_ends(stats + 2);
             if (st != RCB_OK) return st;
             st = read_flags();
             if (st != RCB_OK) return st;
@@ -635,13 +666,14 @@ rcb_status ensure_walk(rcb_tree *t, hipStream_t s) {
     };
     RCB_ZERO(t->dflag, sizeof(int32_t) * 4, s);
     RCB_ZERO(t->dflag + 6, sizeof(int32_t) * 2, s);
-    RCB_ZERO(stats, sizeof(unsigned long long) * 2, s);
+    RCB_ZERO(stats, sizeof(unsigned long long) * 3, s);
     rcb_status wst = walk_tiers(true);
     if (wst != RCB_OK) return wst;
     w.stats = nullptr;   // a second walk (exact lists) does not count again
     t->walk_requeued = nq;
     t->walk_nodes = (int64_t)hstats[0];
     t->walk_tests = (int64_t)hstats[1];
+    t->nb_est = (int64_t)hstats[2];
     if (flags[0]) {
         set_error("walk: stack overflow (tree deeper than the walk stack supports)");
         return RCB_ECAPACITY;
@@ -653,7 +685,7 @@ rcb_status ensure_walk(rcb_tree *t, hipStream_t s) {
     const int32_t nlong = flags[1];
     if (flags[3] == 0) {
         if (nq > 0) {   // the later tiers rewrote the counts of their groups
-            rcb_status st = slab_ends();
+            rcb_status st = slab_ends(nullptr);
             if (st != RCB_OK) return st;
         }
         t->gnear_beg = ends;
@@ -762,8 +794,8 @@ void drop_lists(rcb_tree *t, hipStream_t s) {
     t->near_off = t->far_off = nullptr;
     t->near_list = t->far_list = nullptr;
     t->nb_total = -1;
-    t->nb_slab = t->nb_pool = t->nb_head = t->nb_longq = t->nb_longc = t->nb_queue = t->nb_ctl = nullptr;
-    t->nb_pool_cap = 0;
+    t->nb_slab = t->nb_pool = t->nb_head = t->nb_next = t->nb_queue = t->nb_ctl = nullptr;
+    t->nb_sub_cap = 0;
     t->nb_over = t->nb_long = t->nb_nq = 0;
     t->walk_requeued = 0;
     t->walk_nodes = t->walk_tests = -1;

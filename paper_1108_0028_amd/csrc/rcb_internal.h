@@ -27,6 +27,9 @@ constexpr int kLeafC = 22;   // doubles per leaf in rcb_tree::farc
 
 constexpr int kWave = 64;
 constexpr int kChunk = 512;          // elements per wave item of the big-node passes
+// a launch holds fewer than 2^32 work-items: kernels with a workgroup per
+// cell or group take at most this many of them per launch
+constexpr int64_t kMaxGrid = (int64_t)1 << 22;
 constexpr double kReachPad = 1.0 + 0x1p-32;
 
 struct BuildScratch {
@@ -89,14 +92,15 @@ struct rcb_tree {
     int64_t nb_total = -1;             // neighbour total of the last count call
     int32_t *nb_slab = nullptr;        // neighbour ids of the count call, kNbCap per particle
     int32_t *nb_pool = nullptr;        // overflow chunks of the slab rows
-    int32_t *nb_head = nullptr;        // per particle: its chunk (lists past the row)
-    int32_t *nb_longq = nullptr;       // particles whose list sits in row + chunks
-    int32_t *nb_longc = nullptr;       // the chunks of each nb_longq entry
+    int32_t *nb_head = nullptr;        // per particle: its first chunk (lists past the row)
+    int32_t *nb_next = nullptr;        // per chunk: the list's next one
     int32_t *nb_queue = nullptr;       // leaves holding a list that the fill call searches again
     int32_t *nb_ctl = nullptr;         // device counters of the count call
-    int64_t nb_pool_cap = 0;           // chunks in nb_pool
+    int32_t nb_subs = 1;               // sub-pools of nb_pool (a power of two)
+    int64_t nb_sub_cap = 0;            // chunks of each
+    int64_t nb_est = 0;                // overflow chunks expected (from the last walk)
     int32_t nb_over = 0;               // lists the fill call searches again
-    int32_t nb_long = 0;               // lists kept in row + chunk
+    int32_t nb_long = 0;               // kept lists that one workgroup each sorts
     int32_t nb_nq = 0;                 // entries of nb_queue
     // device flags: [0] 8-wide walk stack overflow, [1] long near lists, [2] their
     // queue, [3] groups outgrowing the list slabs, [4] particles outgrowing
