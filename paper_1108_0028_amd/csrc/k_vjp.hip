@@ -21,9 +21,10 @@
 //   dr_b += aR m_b / M + m_b (6 aQ d - 2 tr(aQ) d)
 //   dm_b += aM + aR . d / M + 3 d.aQ.d - |d|^2 tr(aQ)
 // (dQ/dCOM = 0 because sum m d = 0).
-// Kernels: moments (per group) -> far (per group) -> near (per group, leaf by
-// leaf) -> push.
+// Kernels: moments (per group) -> far (per group) -> near (per leaf) -> push.
+#include <algorithm>
 #include <cstdlib>
+#include <type_traits>
 
 #include "far_math.h"
 #include "near_tile.h"
@@ -81,6 +82,12 @@ struct VjpArgs {
     // deterministic form: the cotangents in tree order, 3 n values of the
     // output type (component c of tree position p at c * n + p)
     void *gtree;
+    // deterministic form: source-side near terms, 4 per (chunk of the cell's
+    // sink groups, particle of the cell) from row srcp[cell], chunk by chunk;
+    // the cell's chunks are srcc[cell] .. srcc[cell + 1]
+    double *srcpart;
+    const int64_t *srcc, *srcp;
+    int64_t first;   // this launch's first leaf, where a workgroup takes one
 };
 
 template <bool MIXED>
@@ -282,8 +289,8 @@ __global__ __launch_bounds__(kBlock) void k_vjp_far(VjpArgs a, AT *__restrict__ 
     }
 }
 
-// near field and the sink-side far terms: per group, the leaves in turn, lanes
-// (sink slot, slice) over the leaf's particles as in the forward kernel
+// near field and the sink-side far terms: per leaf, lanes (sink slot, slice)
+// over the leaf's particles as in the forward kernel
 // (near_tile.h). Sources of the leaf's near cells are staged 64 at a time in
 // LDS as T = ceil(nt / J) rows of J. Sink slot s visits the rows in the
 // rotated order (s + t) mod T, so at each step the lanes of one slice touch
@@ -304,159 +311,172 @@ struct VjpShared {
 
 // SRC = false (the deterministic form): sink-side terms only; the source-side
 // terms are summed per source cell by k_vjp_near_src instead.
-template <bool MIXED, bool SRC>
-__global__ __launch_bounds__(kBlock) void k_vjp_near(VjpArgs a) {
+// A workgroup of H waves per cell: wave w takes the chunks w, w + H, ... of 64
+// entries of the near list, and the sink sums of the waves are added in order.
+// (One wave per group of 8 cells: 491 us for 4096 particles, now 73.)
+template <bool MIXED, bool SRC, int H>
+__global__ __launch_bounds__(H * kWave) void k_vjp_near(VjpArgs a) {
     using T = typename std::conditional<MIXED, float, double>::type;
-    __shared__ VjpShared<T> sh_all[kWaves];
-    VjpShared<T> &sh = sh_all[threadIdx.x / kWave];
-    const int64_t gi = wave_index();
-    if (gi >= a.ngroup) return;
+    __shared__ VjpShared<T> sh_all[H];
+    __shared__ double red[H > 1 ? H : 1][3][kWave];
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    VjpShared<T> &sh = sh_all[wv];
+    const int64_t leaf = a.first + xcd_block();
+    const int64_t gi = leaf >> a.gk, A = a.nleaf + leaf;
+    const int li = (int)(leaf & ((1 << a.gk) - 1));
     const int lane = lane_id();
-    const int G = 1 << a.gk;
-    const int64_t GL = (a.nleaf >> a.gk) + gi;
-    if (a.ncount[GL] == 0) return;
+    const int32_t sA = a.nfirst[A], c = a.ncount[A];
+    if (c == 0) return;
     const int64_t n0 = a.gnear_beg[gi], n1 = a.gnear_end[gi];
-    for (int li = 0; li < G; ++li) {
-        const int64_t A = a.nleaf + gi * G + li;
-        const int32_t sA = a.nfirst[A], c = a.ncount[A];
-        if (c == 0) continue;
-        const LeafLanes L = leaf_lanes(c);
-        const double cA[3] = {a.ncom[3 * A], a.ncom[3 * A + 1], a.ncom[3 * A + 2]};
-        for (int g0 = 0; g0 < c; g0 += L.S) {
-            const int si = g0 + L.sslot;
-            const bool has_sink = L.sslot < L.S && si < c;
-            const int32_t pa = sA + (has_sink ? si : 0);
-            const int32_t oa = a.pid[pa];
-            T ga[3] = {(T)0, (T)0, (T)0};
-            double gd[3] = {0.0, 0.0, 0.0};
-            if (has_sink) {
-                gd[0] = load_g<MIXED>(a.gx, oa);
-                gd[1] = load_g<MIXED>(a.gy, oa);
-                gd[2] = load_g<MIXED>(a.gz, oa);
-                ga[0] = (T)gd[0];
-                ga[1] = (T)gd[1];
-                ga[2] = (T)gd[2];
-            }
-            T sx, sy, sz, ha;
-            if constexpr (MIXED) {   // leaf frame
-                sx = a.fdx[pa];
-                sy = a.fdy[pa];
-                sz = a.fdz[pa];
-                ha = a.fh[pa];
-            } else {
-                sx = a.px[pa];
-                sy = a.py[pa];
-                sz = a.pz[pa];
-                ha = a.ph[pa];
-            }
-            double acc[3] = {0.0, 0.0, 0.0};
-            for (int64_t e0 = n0; e0 < n1; e0 += kWave) {
-                const int tot = load_entry_chunk(a.gnear, a.nfirst, a.ncount, e0, n1, 1u << li, sh.ec);
-                for (int t = 0; t < tot; t += kWave) {
-                    const int q = t + lane;
-                    if (q < tot) {
-                        const int k = entry_of(sh.ec, q);
-                        const int32_t pb = sh.ec.fB[k] + (q - sh.ec.pos[k]);
+    const double cA[3] = {a.ncom[3 * A], a.ncom[3 * A + 1], a.ncom[3 * A + 2]};
+    for (int g0 = 0; g0 < c; g0 += kWave) {
+        const LeafLanes L = leaf_lanes(c - g0);
+        const int si = g0 + L.sslot;
+        const bool has_sink = L.sslot < L.S && si < c;
+        const int32_t pa = sA + (has_sink ? si : 0);
+        const int32_t oa = a.pid[pa];
+        T ga[3] = {(T)0, (T)0, (T)0};
+        double gd[3] = {0.0, 0.0, 0.0};
+        if (has_sink) {
+            gd[0] = load_g<MIXED>(a.gx, oa);
+            gd[1] = load_g<MIXED>(a.gy, oa);
+            gd[2] = load_g<MIXED>(a.gz, oa);
+            ga[0] = (T)gd[0];
+            ga[1] = (T)gd[1];
+            ga[2] = (T)gd[2];
+        }
+        T sx, sy, sz, ha;
+        if constexpr (MIXED) {   // leaf frame
+            sx = a.fdx[pa];
+            sy = a.fdy[pa];
+            sz = a.fdz[pa];
+            ha = a.fh[pa];
+        } else {
+            sx = a.px[pa];
+            sy = a.py[pa];
+            sz = a.pz[pa];
+            ha = a.ph[pa];
+        }
+        double acc[3] = {0.0, 0.0, 0.0};
+        for (int64_t e0 = n0 + wv * kWave; e0 < n1; e0 += H * kWave) {
+            const int tot = load_entry_chunk(a.gnear, a.nfirst, a.ncount, e0, n1, 1u << li, sh.ec);
+            for (int t = 0; t < tot; t += kWave) {
+                const int q = t + lane;
+                if (q < tot) {
+                    const int k = entry_of(sh.ec, q);
+                    const int32_t pb = sh.ec.fB[k] + (q - sh.ec.pos[k]);
+                    if constexpr (MIXED) {
+                        const int64_t B = sh.ec.label[k];
+                        sh.t.x[lane] = (float)(a.ncom[3 * B] - cA[0]) + a.fdx[pb];
+                        sh.t.y[lane] = (float)(a.ncom[3 * B + 1] - cA[1]) + a.fdy[pb];
+                        sh.t.z[lane] = (float)(a.ncom[3 * B + 2] - cA[2]) + a.fdz[pb];
+                        sh.t.m[lane] = a.fm[pb];
+                        sh.t.h[lane] = a.fh[pb];
+                    } else {
+                        sh.t.x[lane] = a.px[pb];
+                        sh.t.y[lane] = a.py[pb];
+                        sh.t.z[lane] = a.pz[pb];
+                        sh.t.m[lane] = a.pm[pb];
+                        sh.t.h[lane] = a.ph[pb];
+                    }
+                    sh.t.pb[lane] = pb;
+                }
+#pragma unroll
+                for (int cc = 0; cc < 4; ++cc) sh.t.acc[cc][lane] = 0.0;
+                tile_sync();
+                const int nt = tot - t < kWave ? tot - t : kWave;
+                const int rows = (nt + L.J - 1) / L.J;
+                // sink slot s starts at row s mod rows, so that the lanes of
+                // one step add into different sources
+                const int span = rows * L.J;
+                int j = (L.sslot % rows) * L.J + L.slice;
+                for (int st = 0; st < rows; ++st, j = j + L.J < span ? j + L.J : j + L.J - span) {
+                    // the deterministic form leaves out the self pair, whose sink and
+                    // source terms cancel exactly (v = 0) but would be computed in two
+                    // kernels there
+                    if (has_sink && j < nt && (SRC || sh.t.pb[j] != pa)) {
+                        const T v[3] = {sx - sh.t.x[j], sy - sh.t.y[j], sz - sh.t.z[j]};
+                        const T r2 = (v[0] * v[0] + v[1] * v[1]) + v[2] * v[2];
+                        const T hsum = ha + sh.t.h[j];
+                        const T ri = rsq_t(r2);
+                        const T ri2 = ri * ri;
+                        const T r3 = ri2 * ri;
+                        const T r5 = r3 * ri2;
+                        T F = r3, dFr = (T)-3 * r5;
+                        if (!soft_outside<T>(r2, hsum)) soft_FdF<T>(r2, ri, r3, r5, hsum, F, dFr);
+                        const T vg = v[0] * ga[0] + v[1] * ga[1] + v[2] * ga[2];
+                        const T mb = sh.t.m[j];
+#pragma unroll
+                        for (int cc = 0; cc < 3; ++cc) {
+                            const T Kg = mb * (F * ga[cc] + dFr * v[cc] * vg);
+                            acc[cc] -= (double)Kg;
+                            if (SRC) atomicAdd(&sh.t.acc[cc][j], (double)Kg);
+                        }
+                        if (SRC) atomicAdd(&sh.t.acc[3][j], (double)(-F * vg));
+                    }
+                }
+                tile_sync();
+                if (SRC && lane < nt) {
+                    const double s0 = sh.t.acc[0][lane], s1 = sh.t.acc[1][lane],
+                                 s2 = sh.t.acc[2][lane], s3 = sh.t.acc[3][lane];
+                    if (s0 != 0.0 || s1 != 0.0 || s2 != 0.0 || s3 != 0.0) {
+                        const int32_t pb = sh.t.pb[lane];
                         if constexpr (MIXED) {
-                            const int64_t B = sh.ec.label[k];
-                            sh.t.x[lane] = (float)(a.ncom[3 * B] - cA[0]) + a.fdx[pb];
-                            sh.t.y[lane] = (float)(a.ncom[3 * B + 1] - cA[1]) + a.fdy[pb];
-                            sh.t.z[lane] = (float)(a.ncom[3 * B + 2] - cA[2]) + a.fdz[pb];
-                            sh.t.m[lane] = a.fm[pb];
-                            sh.t.h[lane] = a.fh[pb];
+                            __hip_atomic_fetch_add(a.srcf + pb, (float)s0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            __hip_atomic_fetch_add(a.srcf + a.n + pb, (float)s1, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT);
+                            __hip_atomic_fetch_add(a.srcf + 2 * a.n + pb, (float)s2, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT);
+                            __hip_atomic_fetch_add(a.srcf + 3 * a.n + pb, (float)s3, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT);
                         } else {
-                            sh.t.x[lane] = a.px[pb];
-                            sh.t.y[lane] = a.py[pb];
-                            sh.t.z[lane] = a.pz[pb];
-                            sh.t.m[lane] = a.pm[pb];
-                            sh.t.h[lane] = a.ph[pb];
-                        }
-                        sh.t.pb[lane] = pb;
-                    }
-#pragma unroll
-                    for (int cc = 0; cc < 4; ++cc) sh.t.acc[cc][lane] = 0.0;
-                    tile_sync();
-                    const int nt = tot - t < kWave ? tot - t : kWave;
-                    const int rows = (nt + L.J - 1) / L.J;
-                    // sink slot s starts at row s mod rows, so that the lanes of
-                    // one step add into different sources
-                    const int span = rows * L.J;
-                    int j = (L.sslot % rows) * L.J + L.slice;
-                    for (int st = 0; st < rows; ++st, j = j + L.J < span ? j + L.J : j + L.J - span) {
-                        // the deterministic form leaves out the self pair, whose sink and
-                        // source terms cancel exactly (v = 0) but would be computed in two
-                        // kernels there
-                        if (has_sink && j < nt && (SRC || sh.t.pb[j] != pa)) {
-                            const T v[3] = {sx - sh.t.x[j], sy - sh.t.y[j], sz - sh.t.z[j]};
-                            const T r2 = (v[0] * v[0] + v[1] * v[1]) + v[2] * v[2];
-                            const T hsum = ha + sh.t.h[j];
-                            const T ri = rsq_t(r2);
-                            const T ri2 = ri * ri;
-                            const T r3 = ri2 * ri;
-                            const T r5 = r3 * ri2;
-                            T F = r3, dFr = (T)-3 * r5;
-                            if (!soft_outside<T>(r2, hsum)) soft_FdF<T>(r2, ri, r3, r5, hsum, F, dFr);
-                            const T vg = v[0] * ga[0] + v[1] * ga[1] + v[2] * ga[2];
-                            const T mb = sh.t.m[j];
-#pragma unroll
-                            for (int cc = 0; cc < 3; ++cc) {
-                                const T Kg = mb * (F * ga[cc] + dFr * v[cc] * vg);
-                                acc[cc] -= (double)Kg;
-                                if (SRC) atomicAdd(&sh.t.acc[cc][j], (double)Kg);
-                            }
-                            if (SRC) atomicAdd(&sh.t.acc[3][j], (double)(-F * vg));
+                            atomicAdd(a.src + pb, s0);
+                            atomicAdd(a.src + a.n + pb, s1);
+                            atomicAdd(a.src + 2 * a.n + pb, s2);
+                            atomicAdd(a.src + 3 * a.n + pb, s3);
                         }
                     }
-                    tile_sync();
-                    if (SRC && lane < nt) {
-                        const double s0 = sh.t.acc[0][lane], s1 = sh.t.acc[1][lane],
-                                     s2 = sh.t.acc[2][lane], s3 = sh.t.acc[3][lane];
-                        if (s0 != 0.0 || s1 != 0.0 || s2 != 0.0 || s3 != 0.0) {
-                            const int32_t pb = sh.t.pb[lane];
-                            if constexpr (MIXED) {
-                                __hip_atomic_fetch_add(a.srcf + pb, (float)s0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                                __hip_atomic_fetch_add(a.srcf + a.n + pb, (float)s1, __ATOMIC_RELAXED,
-                                                       __HIP_MEMORY_SCOPE_AGENT);
-                                __hip_atomic_fetch_add(a.srcf + 2 * a.n + pb, (float)s2, __ATOMIC_RELAXED,
-                                                       __HIP_MEMORY_SCOPE_AGENT);
-                                __hip_atomic_fetch_add(a.srcf + 3 * a.n + pb, (float)s3, __ATOMIC_RELAXED,
-                                                       __HIP_MEMORY_SCOPE_AGENT);
-                            } else {
-                                atomicAdd(a.src + pb, s0);
-                                atomicAdd(a.src + a.n + pb, s1);
-                                atomicAdd(a.src + 2 * a.n + pb, s2);
-                                atomicAdd(a.src + 3 * a.n + pb, s3);
-                            }
-                        }
-                    }
-                    tile_sync();
                 }
+                tile_sync();
             }
+        }
 #pragma unroll
-            for (int cc = 0; cc < 3; ++cc) acc[cc] = seg_sum(acc[cc], L.slice, L.J);
-            if (has_sink && L.slice == 0) {
-                const double *lc = a.leafc + (gi * G + li) * kLeafC;
-                const double d[3] = {a.px[pa] - cA[0], a.py[pa] - cA[1], a.pz[pa] - cA[2]};
-                const double ma = a.pm[pa];
-                const double MA = a.nM[A];
-                const double cot[3] = {lc[19], lc[20], lc[21]};
-                double out[3];
+        for (int cc = 0; cc < 3; ++cc) acc[cc] = seg_sum(acc[cc], L.slice, L.J);
+        if constexpr (H > 1) {
+            if (L.slice == 0) {
 #pragma unroll
-                for (int l = 0; l < 3; ++l) {
-                    double v = acc[l] + ma / MA * cot[l];
+                for (int cc = 0; cc < 3; ++cc) red[wv][cc][L.sslot] = acc[cc];
+            }
+            __syncthreads();
+            if (wv == 0 && L.slice == 0) {
+                for (int w = 1; w < H; ++w)
 #pragma unroll
-                    for (int i = 0; i < 3; ++i) {
-                        v += gd[i] * lc[3 + jidx(i, l)];
+                    for (int cc = 0; cc < 3; ++cc) acc[cc] += red[w][cc][L.sslot];
+            }
+            __syncthreads();
+        }
+        if (wv == 0 && has_sink && L.slice == 0) {
+            const double *lc = a.leafc + leaf * kLeafC;
+            const double d[3] = {a.px[pa] - cA[0], a.py[pa] - cA[1], a.pz[pa] - cA[2]};
+            const double ma = a.pm[pa];
+            const double MA = a.nM[A];
+            const double cot[3] = {lc[19], lc[20], lc[21]};
+            double out[3];
 #pragma unroll
-                        for (int m = 0; m < 3; ++m) v += gd[i] * lc[9 + hidx(i, l, m)] * d[m];
-                    }
-                    out[l] = v;
+            for (int l = 0; l < 3; ++l) {
+                double v = acc[l] + ma / MA * cot[l];
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    v += gd[i] * lc[3 + jidx(i, l)];
+#pragma unroll
+                    for (int m = 0; m < 3; ++m) v += gd[i] * lc[9 + hidx(i, l, m)] * d[m];
                 }
-                a.sink[pa] = out[0];
-                a.sink[a.n + pa] = out[1];
-                a.sink[2 * a.n + pa] = out[2];
-                a.sink[3 * a.n + pa] = (cot[0] * d[0] + cot[1] * d[1] + cot[2] * d[2]) / MA;
+                out[l] = v;
             }
+            a.sink[pa] = out[0];
+            a.sink[a.n + pa] = out[1];
+            a.sink[2 * a.n + pa] = out[2];
+            a.sink[3 * a.n + pa] = (cot[0] * d[0] + cot[1] * d[1] + cot[2] * d[2]) / MA;
         }
     }
 }
@@ -502,10 +522,20 @@ __global__ __launch_bounds__(kBlock) void k_vjp_push(VjpArgs a, const double *__
         const double mb = a.pm[p];
         double sr[4];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) sr[c] = MIXED ? (double)a.srcf[c * a.n + p] : a.src[c * a.n + p];
+        for (int c = 0; c < 4; ++c) sr[c] = 0.0;
+        const int64_t A = a.nleaf + gi * G + leaf_slot(lf, (int32_t)p);
+        if (a.srcpart) {   // the chunks' terms in order
+            const int64_t bl = A - a.nleaf, c1 = a.srcc[bl + 1] - a.srcc[bl];
+            const double *row = a.srcpart + 4 * (a.srcp[bl] + (p - a.nfirst[A]));
+            for (int64_t q = 0; q < c1; ++q, row += 4 * (int64_t)a.ncount[A])
+#pragma unroll
+                for (int c = 0; c < 4; ++c) sr[c] += row[c];
+        } else {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) sr[c] = MIXED ? (double)a.srcf[c * a.n + p] : a.src[c * a.n + p];
+        }
         double dr[3] = {a.sink[p] + sr[0], a.sink[a.n + p] + sr[1], a.sink[2 * a.n + p] + sr[2]};
         double dmb = a.sink[3 * a.n + p] + sr[3];
-        const int64_t A = a.nleaf + gi * G + leaf_slot(lf, (int32_t)p);
         for (int64_t B = A; B > GL; B >>= 1) {
             double ad[kAdj];
 #pragma unroll
@@ -768,7 +798,21 @@ __global__ void k_det_adj_sum(const double *__restrict__ part, const int64_t *__
     adj[i] = v;
 }
 
-// source-side near terms, one wave per lowest-level cell B: lanes (source
+// chunks of kSrcChunk sink groups per lowest-level cell, and their rows of
+// source terms (one per particle of the cell)
+constexpr int kSrcChunk = 64;
+__global__ void k_src_count(const int64_t *__restrict__ lb, const int64_t *__restrict__ le,
+                            const int32_t *__restrict__ ncount, int64_t nleaf, int64_t *__restrict__ nc,
+                            int64_t *__restrict__ nrow) {
+    const int64_t l = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (l >= nleaf) return;
+    const int64_t c = ncount[nleaf + l] > 0 ? (le[nleaf + l] - lb[nleaf + l] + kSrcChunk - 1) / kSrcChunk : 0;
+    nc[l] = c;
+    nrow[l] = c * ncount[nleaf + l];
+}
+
+// source-side near terms, one wave per chunk of kSrcChunk sink groups of a
+// lowest-level cell B: lanes (source
 // slot, slice) over B's particles as in leaf_lanes. The sink cells A whose
 // near list holds B (the groups ascending, then the cells of each group's
 // near mask) are taken 8 groups (64 cells) at a time; an exclusive scan of
@@ -776,8 +820,10 @@ __global__ void k_det_adj_sum(const double *__restrict__ part, const int64_t *__
 // time in LDS (near_tile.h's chunk layout), each slice taking every J-th.
 // In the mixed form a staged sink carries the FP32 shift from its cell's
 // centre of mass to B's, so the pair arithmetic is exactly that of
-// k_vjp_near. The slices' sums are combined by seg_sum and written (no
-// atomics: B owns its particles).
+// k_vjp_near. The slices' sums are combined by seg_sum and written to the
+// chunk's rows, which k_vjp_push adds in order.
+// A cell of a cloud's halo is near to thousands of cells: with one wave per
+// cell the longest of 250,000 Plummer particles held the launch for 5.2 ms.
 template <typename T>
 struct SinkTile {
     T x[kWave], y[kWave], z[kWave], h[kWave], g[3][kWave];
@@ -791,23 +837,25 @@ struct SrcShared {
 };
 
 template <bool MIXED>
-__global__ __launch_bounds__(kBlock) void k_vjp_near_src(VjpArgs a, const uint64_t *__restrict__ items,
-                                                         const int64_t *__restrict__ lb,
-                                                         const int64_t *__restrict__ le) {
+__global__ __launch_bounds__(kWave) void k_vjp_near_src(VjpArgs a, const uint64_t *__restrict__ items,
+                                                        const int64_t *__restrict__ lb,
+                                                        const int64_t *__restrict__ le,
+                                                        const int32_t *__restrict__ owner) {
     using T = typename std::conditional<MIXED, float, double>::type;
-    __shared__ SrcShared<T> sh_all[kWaves];
-    SrcShared<T> &sh = sh_all[threadIdx.x / kWave];
-    const int64_t bl = wave_index();
-    if (bl >= a.nleaf) return;
+    __shared__ SrcShared<T> sh;
+    const int64_t ci = a.first + xcd_block();
     const int lane = lane_id();
     const int G = 1 << a.gk;
+    const int64_t bl = __builtin_amdgcn_readfirstlane(owner[ci]);
     const int64_t B = a.nleaf + bl;
     const int32_t sB = a.nfirst[B], c = a.ncount[B];
-    if (c == 0) return;
-    const LeafLanes L = leaf_lanes(c);
-    const int64_t e_beg = lb[B], e_end = le[B];
+    const int64_t part = ci - a.srcc[bl];
+    double *const rows = a.srcpart + 4 * (a.srcp[bl] + part * c);
+    const int64_t e_beg = lb[B] + part * kSrcChunk;
+    const int64_t e_end = e_beg + kSrcChunk < le[B] ? e_beg + kSrcChunk : le[B];
     const double cB[3] = {a.ncom[3 * B], a.ncom[3 * B + 1], a.ncom[3 * B + 2]};
-    for (int g0 = 0; g0 < c; g0 += L.S) {
+    for (int g0 = 0; g0 < c; g0 += kWave) {
+        const LeafLanes L = leaf_lanes(c - g0);
         const int si = g0 + L.sslot;
         const bool has_src = L.sslot < L.S && si < c;
         const int32_t pb = sB + (has_src ? si : 0);
@@ -909,10 +957,7 @@ __global__ __launch_bounds__(kBlock) void k_vjp_near_src(VjpArgs a, const uint64
         for (int cc = 0; cc < 4; ++cc) acc[cc] = seg_sum(acc[cc], L.slice, L.J);
         if (has_src && L.slice == 0) {
 #pragma unroll
-            for (int cc = 0; cc < 4; ++cc) {
-                if constexpr (MIXED) a.srcf[cc * a.n + pb] = (float)acc[cc];
-                else a.src[cc * a.n + pb] = acc[cc];
-            }
+            for (int cc = 0; cc < 4; ++cc) rows[4 * (int64_t)si + cc] = acc[cc];
         }
     }
 }
@@ -970,7 +1015,7 @@ rcb_status det_sort(rcb_tree *t, const int64_t *beg, const int64_t *end, const u
 // and the source-side near terms. Each far entry's node adjoint is stored by
 // k_vjp_far and summed per node (72 B per entry); if that array cannot be had
 // (or RCB_VJP_DET_RECOMPUTE is set) k_vjp_far_node recomputes it per node.
-rcb_status vjp_det(rcb_tree *t, VjpArgs a, double *adj, bool mixed, Scratch &tmp, hipStream_t s) {
+rcb_status vjp_det(rcb_tree *t, VjpArgs &a, double *adj, bool mixed, Scratch &tmp, hipStream_t s) {
     const int64_t nlab = t->nlab;
     const unsigned gridg = (unsigned)((t->ngroup + kWaves - 1) / kWaves);
     DetLists far, near;
@@ -1021,9 +1066,32 @@ rcb_status vjp_det(rcb_tree *t, VjpArgs a, double *adj, bool mixed, Scratch &tmp
     if (mixed) k_det_gather_g<true><<<gp, 256, 0, s>>>(a);
     else k_det_gather_g<false><<<gp, 256, 0, s>>>(a);
     RCB_LAUNCH_CHECK("k_det_gather_g");
-    const unsigned gn = (unsigned)((t->nleaf + kWaves - 1) / kWaves);
-    if (mixed) k_vjp_near_src<true><<<gn, kBlock, 0, s>>>(a, near.items, near.lb, near.le);
-    else k_vjp_near_src<false><<<gn, kBlock, 0, s>>>(a, near.items, near.lb, near.le);
+    const int64_t NL = t->nleaf;
+    int64_t *sc = (int64_t *)dalloc(t, sizeof(int64_t) * 2 * (NL + 1), s, tmp), *sp = sc + NL + 1;
+    if (!sc) return RCB_ENOMEM;
+    const unsigned gs = (unsigned)((NL + 255) / 256);
+    k_src_count<<<gs, 256, 0, s>>>(near.lb, near.le, t->ncount, NL, sc, sp);
+    RCB_LAUNCH_CHECK("k_src_count");
+    st = scan_i64(t, sc, sc, NL, s);
+    if (st != RCB_OK) return st;
+    st = scan_i64(t, sp, sp, NL, s);
+    if (st != RCB_OK) return st;
+    int64_t tot[2] = {0, 0};   // chunks, rows
+    const HostRead rs[2] = {{sc + NL, &tot[0], (int)sizeof(int64_t)}, {sp + NL, &tot[1], (int)sizeof(int64_t)}};
+    st = read_small(s, rs, 2, "deterministic VJP: source chunks");
+    if (st != RCB_OK) return st;
+    int32_t *sown = (int32_t *)dalloc(t, sizeof(int32_t) * (tot[0] + 1), s, tmp);
+    a.srcpart = (double *)dalloc(t, sizeof(double) * 4 * (tot[1] + 1), s, tmp);
+    if (!sown || !a.srcpart) return RCB_ENOMEM;
+    a.srcc = sc;
+    a.srcp = sp;
+    k_det_owner<<<gs, 256, 0, s>>>(sc, NL, sown);
+    RCB_LAUNCH_CHECK("k_det_owner");
+    for (a.first = 0; a.first < tot[0]; a.first += kMaxGrid) {
+        const unsigned gn = (unsigned)std::min(kMaxGrid, tot[0] - a.first);
+        if (mixed) k_vjp_near_src<true><<<gn, kWave, 0, s>>>(a, near.items, near.lb, near.le, sown);
+        else k_vjp_near_src<false><<<gn, kWave, 0, s>>>(a, near.items, near.lb, near.le, sown);
+    }
     RCB_LAUNCH_CHECK("k_vjp_near_src");
     return RCB_OK;
 }
@@ -1038,8 +1106,8 @@ rcb_status gravity_vjp(rcb_tree *t, const void *gx, const void *gy, const void *
     const int64_t n = t->n;
     double *sink = (double *)dalloc(t, sizeof(double) * 4 * n, s, tmp);
     const bool mixed = t->p.precision == RCB_MIXED;
-    void *srcv = dalloc(t, (mixed ? sizeof(float) : sizeof(double)) * 4 * n, s, tmp);
     const bool det = t->p.deterministic != 0;
+    void *srcv = det ? (void *)sink : dalloc(t, (mixed ? sizeof(float) : sizeof(double)) * 4 * n, s, tmp);
     if (det && t->ngroup > (int64_t(1) << 24)) {
         set_error("rcb_gravity_vjp: the deterministic form takes at most 2^24 groups of 8 cells (k <= 27)");
         return RCB_ECAPACITY;
@@ -1059,15 +1127,16 @@ rcb_status gravity_vjp(rcb_tree *t, const void *gx, const void *gy, const void *
     }
     double *leafc = t->farc;   // 19 far coefficients + the leaf's cotangent sum per leaf
     if (!sink || !srcv || !adj || !adjc || !adjmc || !mom || !leafc) return RCB_ENOMEM;
-    RCB_ZERO(srcv, (mixed ? sizeof(float) : sizeof(double)) * 4 * n, s);
     if (!det) {
+        RCB_ZERO(srcv, (mixed ? sizeof(float) : sizeof(double)) * 4 * n, s);
         RCB_ZERO(adjc, (mixed ? sizeof(float) : sizeof(double)) * adj_n, s);
         RCB_ZERO(adjmc, (mixed ? sizeof(float) : sizeof(double)) * adjm_n, s);
     }
     VjpArgs a{t->nleaf, t->gk, t->ngroup, t->nfirst, t->ncount, t->ncom, t->nM, t->nQ,
               t->gnear_beg, t->gnear_end, t->gfar_beg, t->gfar_end, t->gnear, t->gfar, t->px, t->py, t->pz, t->pm, t->ph,
               t->fdx, t->fdy, t->fdz, t->fm, t->fh, t->pid, gx, gy, gz, mom, leafc, sink, mixed ? nullptr : (double *)srcv,
-              mixed ? (float *)srcv : nullptr, adj, nullptr, nmid, n, t->nlab};
+              mixed ? (float *)srcv : nullptr, adj, nullptr, nmid, n, t->nlab, nullptr, nullptr, nullptr, nullptr, nullptr,
+              nullptr, 0};
     const unsigned gridg = (unsigned)((t->ngroup + kWaves - 1) / kWaves);
     if (det && mixed) k_vjp_moments_det<true><<<gridg, kBlock, 0, s>>>(a);
     else if (det) k_vjp_moments_det<false><<<gridg, kBlock, 0, s>>>(a);
@@ -1080,6 +1149,25 @@ rcb_status gravity_vjp(rcb_tree *t, const void *gx, const void *gy, const void *
         t->farc_valid = true;
     }
 
+    // two waves per cell while the cells leave SIMDs idle (4096 particles, 512
+    // cells: 241 us the VJP with one, 199 with 2, 191 with 8; 32,768 cells 3.64
+    // and 3.56 ms), one from there on (131,072 cells: 8.65 and 8.80 ms)
+    auto near = [&](auto src) {
+        constexpr bool S = decltype(src)::value;
+        auto launch = [&](auto mixed_c, auto waves) {
+            constexpr bool M = decltype(mixed_c)::value;
+            constexpr int H = decltype(waves)::value;
+            k_vjp_near<M, S, H><<<(unsigned)std::min(kMaxGrid, t->nleaf - a.first), H * kWave, 0, s>>>(a);
+        };
+        auto sized = [&](auto mixed_c) {
+            if (t->nleaf <= 32768) launch(mixed_c, std::integral_constant<int, 2>{});
+            else launch(mixed_c, std::integral_constant<int, 1>{});
+        };
+        for (a.first = 0; a.first < t->nleaf; a.first += kMaxGrid) {
+            if (mixed) sized(std::true_type{});
+            else sized(std::false_type{});
+        }
+    };
     const int64_t alen = kAdj * t->nlab;
     const unsigned gridr = (unsigned)((alen + 255) / 256);
     if (det) {
@@ -1087,8 +1175,7 @@ rcb_status gravity_vjp(rcb_tree *t, const void *gx, const void *gy, const void *
         // per-node lists
         st = vjp_det(t, a, adj, mixed, tmp, s);
         if (st != RCB_OK) return st;
-        if (mixed) k_vjp_near<true, false><<<gridg, kBlock, 0, s>>>(a);
-        else k_vjp_near<false, false><<<gridg, kBlock, 0, s>>>(a);
+        near(std::false_type{});
         RCB_LAUNCH_CHECK("k_vjp_near");
     } else {
         if (mixed) {
@@ -1103,8 +1190,7 @@ rcb_status gravity_vjp(rcb_tree *t, const void *gx, const void *gy, const void *
                                                        nmid);
         }
         RCB_LAUNCH_CHECK("k_adj_reduce");
-        if (mixed) k_vjp_near<true, true><<<gridg, kBlock, 0, s>>>(a);
-        else k_vjp_near<false, true><<<gridg, kBlock, 0, s>>>(a);
+        near(std::true_type{});
         RCB_LAUNCH_CHECK("k_vjp_near");
     }
     if (mixed) k_vjp_push<true><<<gridg, kBlock, 0, s>>>(a, adj, t->ncom, t->nM, dx, dy, dz, dm);
