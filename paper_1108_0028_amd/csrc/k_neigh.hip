@@ -296,11 +296,11 @@ __global__ __launch_bounds__(kBlock) void k_inv(int64_t n, const int32_t *__rest
     if (p < n) inv[pid[p]] = (int32_t)p;
 }
 
-// Sorting network on 64 keys, all comparators ascending: for k = 2, 4, ..., 64
-// the first stage pairs i with i ^ (k - 1), the following ones i with i ^ d
-// (d = k/4, ..., 1); the smaller key goes to the lower index. Key i sits in
-// register i % 8 of lane i / 8 of an aligned group of 8 lanes, so strides
-// below 8 are exchanges between registers and the others between lanes.
+// Sorting network on 8 U keys, all comparators ascending: for k = 2, 4, ...,
+// 8 U the first stage pairs i with i ^ (k - 1), the following ones i with
+// i ^ d (d = k/4, ..., 1); the smaller key goes to the lower index. Key i sits
+// in register i % U of lane i / U of an aligned group of 8 lanes, so strides
+// below U are exchanges between registers and the others between lanes.
 __device__ __forceinline__ void cex(uint32_t &lo, uint32_t &hi) {
     const uint32_t a = lo, b = hi;
     lo = a < b ? a : b;
@@ -325,92 +325,101 @@ __device__ __forceinline__ uint32_t xor_lanes(uint32_t v) {
     return v;
 }
 
-template <int K>
-__device__ __forceinline__ void net64_flip(uint32_t (&v)[8], int j0) {
-    if constexpr (K <= 8) {
+template <int U, int K>
+__device__ __forceinline__ void net_flip(uint32_t (&v)[U], int j0) {
+    if constexpr (K <= U) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
+        for (int u = 0; u < U; ++u)
             if (u < (u ^ (K - 1))) cex(v[u], v[u ^ (K - 1)]);
     } else {
-        // partner: lane j0 ^ (K / 8 - 1), register 7 - u
-        const bool lower = (j0 & (K >> 4)) == 0;
-        uint32_t w[8];
+        // partner: lane j0 ^ (K / U - 1), register U - 1 - u
+        const bool lower = (j0 & (K / (2 * U))) == 0;
+        uint32_t w[U];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) w[u] = xor_lanes<(K >> 3) - 1>(v[7 - u]);
+        for (int u = 0; u < U; ++u) w[u] = xor_lanes<K / U - 1>(v[U - 1 - u]);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = lower ? (v[u] < w[u] ? v[u] : w[u]) : (v[u] < w[u] ? w[u] : v[u]);
+        for (int u = 0; u < U; ++u) v[u] = lower ? (v[u] < w[u] ? v[u] : w[u]) : (v[u] < w[u] ? w[u] : v[u]);
     }
 }
 
-template <int D>
-__device__ __forceinline__ void net64_stride(uint32_t (&v)[8], int j0) {
-    if constexpr (D < 8) {
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if ((u & D) == 0) cex(v[u], v[u | D]);
-    } else {
-        const bool lower = (j0 & (D >> 3)) == 0;   // partner: lane j0 ^ (D / 8)
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const uint32_t w = xor_lanes<(D >> 3)>(v[u]);
-            v[u] = lower ? (v[u] < w ? v[u] : w) : (v[u] < w ? w : v[u]);
-        }
-    }
-}
-
-template <int K>
-__device__ __forceinline__ void net64_merge(uint32_t (&v)[8], int j0) {
-    net64_flip<K>(v, j0);
-    if constexpr (K >= 4) net64_stride<K / 4>(v, j0);
-    if constexpr (K >= 8) net64_stride<K / 8>(v, j0);
-    if constexpr (K >= 16) net64_stride<K / 16>(v, j0);
-    if constexpr (K >= 32) net64_stride<K / 32>(v, j0);
-    if constexpr (K >= 64) net64_stride<K / 64>(v, j0);
-}
-
-// The same all-ascending network over 64 U keys held U per lane (key i in
-// register i % U of lane i / U): strides below U are exchanges between
-// registers, the others between lanes (shuffles).
-template <int U>
-__device__ __forceinline__ void net_lanes(uint32_t (&v)[U], int lane) {
-    for (int k = 2; k <= kWave * U; k <<= 1) {
-        if (k <= U) {
+template <int U, int D>
+__device__ __forceinline__ void net_strides(uint32_t (&v)[U], int j0) {   // D, D / 2, ..., 1
+    if constexpr (D >= 1) {
+        if constexpr (D < U) {
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                if (u < (u ^ (k - 1))) cex(v[u], v[u ^ (k - 1)]);
-        } else {   // partner: lane ^ (k / U - 1), register U - 1 - u
-            const bool lower = (lane & (k / (2 * U))) == 0;
-            uint32_t w[U];
+                if ((u & D) == 0) cex(v[u], v[u | D]);
+        } else {
+            const bool lower = (j0 & (D / U)) == 0;   // partner: lane j0 ^ (D / U)
 #pragma unroll
-            for (int u = 0; u < U; ++u) w[u] = (uint32_t)__shfl_xor((int)v[U - 1 - u], k / U - 1, kWave);
-#pragma unroll
-            for (int u = 0; u < U; ++u) v[u] = lower ? (v[u] < w[u] ? v[u] : w[u]) : (v[u] < w[u] ? w[u] : v[u]);
-        }
-        for (int d = k / 4; d >= 1; d >>= 1) {
-            if (d < U) {
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if ((u & d) == 0) cex(v[u], v[u | d]);
-            } else {   // partner: lane ^ (d / U), same register
-                const bool lower = (lane & (d / U)) == 0;
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const uint32_t w = (uint32_t)__shfl_xor((int)v[u], d / U, kWave);
-                    v[u] = lower ? (v[u] < w ? v[u] : w) : (v[u] < w ? w : v[u]);
-                }
+            for (int u = 0; u < U; ++u) {
+                const uint32_t w = xor_lanes<D / U>(v[u]);
+                v[u] = lower ? (v[u] < w ? v[u] : w) : (v[u] < w ? w : v[u]);
             }
         }
+        net_strides<U, D / 2>(v, j0);
     }
 }
 
-// slab rows -> the caller's CSR, in caller order: 8 lanes per particle, each
-// loading 8 consecutive slots of the row (keys past the count are 2^32 - 1,
-// i.e. last); the lists are sorted ascending, staged in LDS and stored one
-// particle at a time, each list by consecutive lanes. Then the wave takes its
-// particles' lists longer than the row, one after the other: up to kNbWaveMax
-// ids as 4 keys per lane (16-byte loads: lanes 0-15 read the row, every
-// further 16 lanes one chunk), sorted in registers; longer ones are copied
-// and queued for k_nb_sort_long. Lists searched again (head -1) are skipped.
+template <int U, int K = 2>
+__device__ __forceinline__ void net_sort(uint32_t (&v)[U], int j0) {
+    if constexpr (K <= 8 * U) {
+        net_flip<U, K>(v, j0);
+        net_strides<U, K / 4>(v, j0);
+        net_sort<U, 2 * K>(v, j0);
+    }
+}
+
+// One wave's 8 lists of at most 8 U ids (8 lanes each, this lane's with c ids,
+// 0: none here): the row and the chunks ch[] loaded 8 slots a lane at a time
+// (keys past the count are 2^32 - 1, i.e. last), sorted, and stored 64 keys of
+// each list at a time through LDS, each list by consecutive lanes.
+template <int U>
+__device__ __forceinline__ void compact_lists(int c, int64_t o, const int32_t *__restrict__ row,
+                                              const int32_t (&ch)[3], const int32_t *__restrict__ pool,
+                                              uint32_t *st, int32_t *__restrict__ ids) {
+    const int lane = lane_id(), j0 = lane % 8, p = lane / 8;
+    uint32_t v[U];
+#pragma unroll
+    for (int b = 0; b < U / 8; ++b) {
+        const int i0 = kNbCap * b + 8 * j0;
+        if (i0 < c) {
+            const int4 *src = reinterpret_cast<const int4 *>((b ? pool + (int64_t)ch[b ? b - 1 : 0] * kNbChunk : row) + 8 * j0);
+            const int4 x = src[0], y = src[1];
+            const int32_t k[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[8 * b + u] = i0 + u < c ? (uint32_t)k[u] : 0xffffffffu;
+        } else {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[8 * b + u] = 0xffffffffu;
+        }
+    }
+    net_sort<U>(v, j0);
+    constexpr int kLanes = kWave / U;   // lanes of a list that hold 64 of its keys
+#pragma unroll
+    for (int r = 0; r < U / 8; ++r) {
+        if (j0 / kLanes == r) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) st[p * kNbCap + (j0 % kLanes) * U + u] = v[u];
+        }
+        tile_sync();
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {   // list q of the wave
+            const int64_t oq = ((int64_t)__builtin_amdgcn_readlane((int)(o >> 32), 8 * q) << 32) |
+                               (uint32_t)__builtin_amdgcn_readlane((int)o, 8 * q);
+            const int cq = __builtin_amdgcn_readlane(c, 8 * q);
+            if (kNbCap * r + lane < cq) ids[oq + kNbCap * r + lane] = (int32_t)st[q * kNbCap + lane];
+        }
+        tile_sync();
+    }
+}
+
+// slab rows and chunks -> the caller's CSR, in caller order: 8 lanes per
+// particle, 8, 16 or 32 keys per lane by the wave's longest list (of up to
+// kNbWaveMax ids); longer lists are copied and queued for k_nb_sort_long.
+// Lists searched again (head -1) are skipped.
+// 500,000 particles with 102 neighbours each: 76 us; one list after the other,
+// 4 keys on each of the wave's lanes and shuffles between them, took 460.
 __global__ __launch_bounds__(kBlock) void k_nb_compact(int64_t n, const int32_t *__restrict__ inv,
                                                        const int64_t *__restrict__ offsets,
                                                        const int32_t *__restrict__ slab,
@@ -423,87 +432,47 @@ __global__ __launch_bounds__(kBlock) void k_nb_compact(int64_t n, const int32_t 
     uint32_t *st = stage[threadIdx.x / kWave];
     const int lane = lane_id();
     const int64_t a = (blockIdx.x * (int64_t)kBlock + threadIdx.x) / 8;
-    const int j0 = lane % 8, p = lane / 8;
-    int64_t o = 0, call = 0;
+    int64_t o = 0;
+    int call = 0;   // < n <= 2^31 - 1
     if (a < n) {
         o = offsets[a];
-        call = offsets[a + 1] - o;
+        call = (int)(offsets[a + 1] - o);
     }
-    const int c = call > kNbCap ? 0 : (int)call;
-    uint32_t v[8];
-    if (8 * j0 < c) {
-        const int64_t r = inv ? (int64_t)inv[a] : a;   // the particle's slab row
-        const int4 *src = reinterpret_cast<const int4 *>(slab + r * kNbCap + 8 * j0);
-        const int4 x = src[0], y = src[1];
-        v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
-        v[4] = y.x; v[5] = y.y; v[6] = y.z; v[7] = y.w;
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (8 * j0 + u >= c) v[u] = 0xffffffffu;
-    } else {
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = 0xffffffffu;
+    const int32_t *row = slab;
+    if (call > 0) row += (inv ? (int64_t)inv[a] : a) * kNbCap;
+    int32_t ch[3] = {-1, -1, -1};
+    if (ballot(call > kNbCap) == 0ull) {
+        compact_lists<8>(call, o, row, ch, pool, st, ids);
+        return;
     }
-    if (ballot(c > 1) != 0ull) {   // wave-uniform: every lane takes part in the exchanges
-        net64_merge<2>(v, j0);
-        net64_merge<4>(v, j0);
-        net64_merge<8>(v, j0);
-        net64_merge<16>(v, j0);
-        net64_merge<32>(v, j0);
-        net64_merge<64>(v, j0);
+    if (call > kNbCap) {
+        ch[0] = head[a];
+        if (call <= kNbWaveMax && ch[0] >= 0) {
+            if (call > kNbCap + kNbChunk) ch[1] = next[ch[0]];
+            if (call > kNbCap + 2 * kNbChunk) ch[2] = next[ch[1]];
+        }
     }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) st[p * kNbCap + 8 * j0 + u] = v[u];
-    tile_sync();
-    const auto list_start = [&](int l) {   // o of lane l (uniform)
-        return ((int64_t)__builtin_amdgcn_readlane((int)(o >> 32), l) << 32) |
-               (uint32_t)__builtin_amdgcn_readlane((int)o, l);
-    };
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {   // particle q of the wave: its list by lanes 0 .. c - 1
-        const int64_t oq = list_start(8 * q);
-        const int cq = __builtin_amdgcn_readlane(c, 8 * q);
-        if (lane < cq) ids[oq + lane] = (int32_t)st[q * kNbCap + lane];
-    }
-    uint64_t lm = ballot(j0 == 0 && call > kNbCap);
-    if (lm == 0) return;
-    const int64_t a0 = a - p;
+    const int c = call > kNbCap && (call > kNbWaveMax || ch[0] < 0) ? 0 : call;
+    if (ballot(c > 2 * kNbCap) != 0ull) compact_lists<32>(c, o, row, ch, pool, st, ids);
+    else if (ballot(c > kNbCap) != 0ull) compact_lists<16>(c, o, row, ch, pool, st, ids);
+    else compact_lists<8>(c, o, row, ch, pool, st, ids);
+    uint64_t lm = ballot(lane % 8 == 0 && call > kNbWaveMax && ch[0] >= 0);
+    const int64_t a0 = a - lane / 8;
     while (lm) {
         const int l = __ffsll((long long)lm) - 1;
         lm &= lm - 1;
-        const int64_t al = a0 + l / 8, ol = list_start(l);
-        const int cl = __builtin_amdgcn_readlane((int)call, l);   // < n <= 2^31 - 1
-        int32_t ch = head[al];
-        if (ch < 0) continue;
-        const int32_t *const row = slab + (inv ? (int64_t)inv[al] : al) * kNbCap;
-        if (cl <= kNbWaveMax) {
-            const int32_t c1 = cl > kNbCap + kNbChunk ? next[ch] : 0;
-            const int32_t c2 = cl > kNbCap + 2 * kNbChunk ? next[c1] : 0;
-            const int i0 = 4 * lane;
-            uint32_t w[4] = {0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu};
-            if (i0 < cl) {
-                const int32_t cq = i0 < kNbCap + kNbChunk ? ch : (i0 < kNbCap + 2 * kNbChunk ? c1 : c2);
-                const int32_t *src =
-                    i0 < kNbCap ? row + i0 : pool + (int64_t)cq * kNbChunk + (i0 - kNbCap) % kNbChunk;
-                const int4 x = *reinterpret_cast<const int4 *>(src);
-                w[0] = x.x; w[1] = x.y; w[2] = x.z; w[3] = x.w;
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (i0 + u >= cl) w[u] = 0xffffffffu;
-            }
-            net_lanes<4>(w, lane);
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (i0 + u < cl) ids[ol + i0 + u] = (int32_t)w[u];
-        } else {
-            ids[ol + lane] = row[lane];
-            for (int i = kNbCap;; i += kNbChunk) {
-                if (i + lane < cl) ids[ol + i + lane] = pool[(int64_t)ch * kNbChunk + lane];
-                if (i + kNbChunk >= cl) break;
-                ch = next[ch];
-            }
-            if (lane == 0) longq[atomicAdd(nlong, 1)] = (int32_t)al;
+        const int64_t al = a0 + l / 8;
+        const int64_t ol = ((int64_t)__builtin_amdgcn_readlane((int)(o >> 32), l) << 32) |
+                           (uint32_t)__builtin_amdgcn_readlane((int)o, l);
+        const int cl = __builtin_amdgcn_readlane(call, l);
+        int32_t cq = __builtin_amdgcn_readlane(ch[0], l);
+        ids[ol + lane] = slab[(inv ? (int64_t)inv[al] : al) * kNbCap + lane];
+        for (int i = kNbCap;; i += kNbChunk) {
+            if (i + lane < cl) ids[ol + i + lane] = pool[(int64_t)cq * kNbChunk + lane];
+            if (i + kNbChunk >= cl) break;
+            cq = next[cq];
         }
+        if (lane == 0) longq[atomicAdd(nlong, 1)] = (int32_t)al;
     }
 }
 
