@@ -220,27 +220,29 @@ __global__ __launch_bounds__(kBlock) void k_walk_group(WalkArgs w, const int32_t
     }
 }
 
-// Wide walk: lane j holds the j-th entry taken from the front of a FIFO ring
-// in LDS; its node record is loaded once and tested against each leaf of the
-// group (records in LDS), and the per-leaf decisions of the header become
-// 8-bit masks per lane. Children are appended in the order of their parents,
+// Wide walk: a FIFO ring in LDS holds the opened nodes, whose two children are
+// visited with the same masks: up to 32 are taken from the front per round,
+// lane j holding child j % 2 of entry j / 2 (the pair's records share one
+// 128-byte line). A child's record is loaded once and tested against each
+// leaf of the group (records in LDS), and the per-leaf decisions of the header
+// become 8-bit masks per lane. Opened children are appended in lane order,
 // so nodes are visited level by level and, within a level, by increasing
 // label: near entries (always lowest-level cells) come out sorted by label,
 // as the neighbour lists' tree order needs, with no sort. At 4M particles
-// the ring holds up to ~800 entries. A group whose appends would pass the
+// the ring holds up to ~400 entries. A group whose appends would pass the
 // ring stops: if queue is given its index is appended (flag[6] counts them)
 // for the next tier to walk again, writing counts and lists over whatever
 // this one wrote: the same kernel with a ring of kWQueue2 entries (one wave
 // per block), then k_walk_group (and k_sort_lists for its near lists).
 // only: if given, wave i walks group only[i] (i < nonly).
 constexpr int kWQueue = 1024;    // powers of two
-constexpr int kWQueue2 = 8192;
+constexpr int kWQueue2 = 4096;
 
 template <bool PURE, int QCAP, int WAVES>
 __global__ __launch_bounds__(WAVES * kWave) void k_walk_wide(WalkArgs w, int32_t *queue, int32_t *nqueue,
                                                              const int32_t *only, int64_t nonly, int cap) {
-    __shared__ uint32_t qlab_all[WAVES][QCAP];   // ring: node label
-    __shared__ uint16_t qmsk_all[WAVES][QCAP];   // and gravity | neighbour << 8 masks
+    __shared__ uint32_t qlab_all[WAVES][QCAP];   // ring: label of an opened node
+    __shared__ uint16_t qmsk_all[WAVES][QCAP];   // and its children's gravity | neighbour << 8 masks
     __shared__ double4 leaf_all[WAVES][16];      // per leaf: (g, h_node), (com, -)
     uint32_t *qlab = qlab_all[threadIdx.x / kWave];
     uint16_t *qmsk = qmsk_all[threadIdx.x / kWave];
@@ -273,25 +275,20 @@ __global__ __launch_bounds__(WAVES * kWave) void k_walk_wide(WalkArgs w, int32_t
     }
     const uint16_t root_masks = (uint16_t)(live_mask | (PURE ? live_mask << 8 : 0u));
     if (lane == 0) {
-        if (w.k == 0) {
-            qlab[0] = 1u;
-            qmsk[0] = root_masks;
-        } else {
-            qlab[0] = 2u;
-            qlab[1] = 3u;
-            qmsk[0] = qmsk[1] = root_masks;
-        }
+        qlab[0] = w.k == 0 ? 0u : 1u;   // (k = 0: the root alone, as child 1 of entry 0)
+        qmsk[0] = root_masks;
     }
-    int head = 0, cnt = w.k == 0 ? 1 : 2;   // ring [head, head + cnt), indices mod kWQueue
+    int head = 0, cnt = 1;   // ring [head, head + cnt), indices mod QCAP
     __builtin_amdgcn_wave_barrier();
     bool overflow = false;
     uint32_t n_nodes = 0, n_tests = 0;      // this lane's share of the walk statistics
     while (cnt > 0) {
-        const int b = cnt < kWave ? cnt : kWave;
-        const bool act = lane < b;
-        const int slot = (head + (act ? lane : 0)) & (QCAP - 1);
+        const int b = cnt < kWave / 2 ? cnt : kWave / 2;
+        const int slot = (head + (lane / 2 < b ? lane / 2 : 0)) & (QCAP - 1);
         const uint32_t qm = qmsk[slot];
-        const int32_t node = act ? (int32_t)qlab[slot] : 1;
+        const int32_t child = (int32_t)(2 * qlab[slot]) + (lane & 1);
+        const bool act = lane / 2 < b && child > 0;
+        const int32_t node = act ? child : 1;
         head = (head + b) & (QCAP - 1);
         cnt -= b;
         const int tail = (head + cnt) & (QCAP - 1);
@@ -337,24 +334,20 @@ __global__ __launch_bounds__(WAVES * kWave) void k_walk_wide(WalkArgs w, int32_t
         const bool op = (ogm | onm) != 0u;
         const uint64_t b_open = ballot(op);
         const int no = __popcll(b_open);
-        if (cnt + 2 * no > cap) {
+        if (cnt + no > cap) {
             overflow = true;
             break;
         }
-        // the appended slots lie outside [head, head + cnt) (cnt + 2 no <=
+        // the appended slots lie outside [head, head + cnt) (cnt + no <=
         // cap <= QCAP); some are the ones just taken, read above
         __builtin_amdgcn_wave_barrier();
         if (op) {
-            const int r = rank_below(b_open);
-            const uint16_t masks = (uint16_t)(ogm | (onm << 8));
-            const int s0 = (tail + 2 * r) & (QCAP - 1), s1 = (tail + 2 * r + 1) & (QCAP - 1);
-            qlab[s0] = (uint32_t)(2 * node);
-            qlab[s1] = (uint32_t)(2 * node + 1);
-            qmsk[s0] = masks;
-            qmsk[s1] = masks;
+            const int s0 = (tail + rank_below(b_open)) & (QCAP - 1);
+            qlab[s0] = (uint32_t)node;
+            qmsk[s0] = (uint16_t)(ogm | (onm << 8));
         }
         __builtin_amdgcn_wave_barrier();
-        cnt += 2 * no;
+        cnt += no;
         const bool hn = (nm | cm) != 0u;
         const uint64_t b_near = ballot(hn);
         if (hn) {
@@ -553,16 +546,19 @@ __global__ __launch_bounds__(kBlock) void k_expand(int64_t nleaf, int gk,
 
 }  // namespace
 
-// Slab capacities: 1024 near and up to 16384 far entries per group, within
-// a budget for both slabs of 8 GB or 480 bytes per particle, whichever is
-// larger. At 4M particles and theta = 0.7 the group lists average ~170 near
+// Slab capacities: 1024 near entries per group, up to 16384 (and no more than
+// there are cells) while the near slab stays within 1 GB: below a million
+// particles some groups of a cloud's halo are near to thousands of cells, and
+// one list past its slab means a second walk (250,000 Plummer particles: walk
+// 0.78 -> 0.39 ms). Up to 16384 far entries per group, within a budget for
+// both slabs of 8 GB or 480 bytes per particle, whichever is larger. At 4M particles and theta = 0.7 the group lists average ~170 near
 // and ~2150 far entries; at depth 23 (67M-1e8 particles, 2^20 groups) the
 // per-particle budget leaves 2816-4672 far entries per group, enough for the
 // clustered test cloud's lists, so that the walk runs once. n = 0 gives the
 // 8 GB budget alone (the fallback when the larger slabs cannot be had).
-static void slab_caps(int64_t ngroup, int64_t n, int64_t &cn, int64_t &cf) {
+static void slab_caps(int64_t ngroup, int64_t nleaf, int64_t n, int64_t &cn, int64_t &cf) {
     const int64_t budget = std::max<int64_t>((int64_t)8 << 30, 480 * n);
-    cn = 1024;
+    cn = std::max<int64_t>(1024, std::min<int64_t>({16384, nleaf, ((int64_t)1 << 30) / (8 * ngroup)}));
     cf = budget / (8 * ngroup) - cn;
     cf = std::min<int64_t>(16384, std::max<int64_t>(1024, cf & ~(int64_t)63));
 }
@@ -592,7 +588,7 @@ rcb_status ensure_walk(rcb_tree *t, hipStream_t s) {
     for (int attempt = 0; attempt < 2 && !(nslab && fslab); ++attempt) {
         for (void *p : slabs) dfree(t, p, s);
         slabs.clear();
-        slab_caps(NG, attempt == 0 ? t->n : 0, cn, cf);
+        slab_caps(NG, t->nleaf, attempt == 0 ? t->n : 0, cn, cf);
         nslab = (uint64_t *)dalloc(t, sizeof(uint64_t) * NG * cn, s, slabs);
         fslab = nslab ? (uint64_t *)dalloc(t, sizeof(uint64_t) * NG * cf, s, slabs) : nullptr;
     }
@@ -603,9 +599,9 @@ rcb_status ensure_walk(rcb_tree *t, hipStream_t s) {
     int cap1 = kWQueue, cap2 = kWQueue2;
     if (const char *e = getenv("RCB_WALK_WIDE_STACK")) {
         const int v = atoi(e);
-        if (v >= 2) {
-            cap1 = std::min(cap1, v);
-            cap2 = std::min(cap2, v);
+        if (v >= 2) {   // nodes: two per entry
+            cap1 = std::min(cap1, v / 2);
+            cap2 = std::min(cap2, v / 2);
         }
     }
     WalkArgs w{t->wrec, t->nhnode, t->k, t->gk, NG, t->p.theta * t->p.theta, ncnt, fcnt,
