@@ -22,7 +22,7 @@
 // the part that moves with the sink's centre of mass. far_pair_adjoint
 // carries dPsi/dR by forward-mode dual numbers through the forward closed
 // forms (a cross-check for the tests); far_pair_adjoint_sym, used by the
-// kernels, has every output in closed form over symmetrised moments.
+// kernels, has every output in closed form over symmetrised traceless moments.
 #pragma once
 
 #include <math.h>
@@ -377,128 +377,129 @@ RCB_HD void far_pair_adjoint(double x, double y, double z, double M, const doubl
 }
 
 
-// Symmetrised sink moments. Psi contracts G1 with the symmetric J and G2
-// with the fully symmetric H, so only sym(G1) and the full symmetrisation of
-// G2 enter Psi and all its derivatives:
-//   S1 = G0, S2_il = (G1_il + G1_li)/2, S3_ilm = (G2_ilm + G2_lim + G2_mil)/3,
-//   t1 = tr S2, sg_m = sum_i S3_iim.
+// Symmetrised sink moments without their traces. Psi contracts G1 with the
+// symmetric J and G2 with the fully symmetric H, both traceless (the field of
+// Eq. 5 is harmonic) at every R and for every traceless Q, so only the
+// symmetric traceless parts of G1 and G2 enter Psi and its derivatives:
+//   S1 = G0, S2_il = (G1_il + G1_li)/2 - d_il tr/3,
+//   S3_ilm = (G2_ilm + G2_lim + G2_mil)/3 =: T_ilm, less
+//            (d_il s_m + d_im s_l + d_lm s_i)/5 with s_m = sum_i T_iim.
 struct SymMoments {
     double S1[3];
     double S2[6];    // jidx order
     double S3[10];   // hidx order
-    double t1;
-    double sg[3];
 };
 
 RCB_HD void sym_moments(const double G0[3], const double G1[9], const double G2[18], SymMoments &S) {
     for (int i = 0; i < 3; ++i) S.S1[i] = G0[i];
+    const double t = (G1[0] + G1[4] + G1[8]) / 3.0;
     for (int i = 0; i < 3; ++i)
-        for (int l = i; l < 3; ++l) S.S2[jidx(i, l)] = 0.5 * (G1[3 * i + l] + G1[3 * l + i]);
+        for (int l = i; l < 3; ++l)
+            S.S2[jidx(i, l)] = 0.5 * (G1[3 * i + l] + G1[3 * l + i]) - (i == l ? t : 0.0);
+    double T[10], s[3];
     for (int i = 0; i < 3; ++i)
         for (int l = i; l < 3; ++l)
             for (int m = l; m < 3; ++m)
-                S.S3[hidx(i, l, m)] =
+                T[hidx(i, l, m)] =
                     (G2[6 * i + jidx(l, m)] + G2[6 * l + jidx(i, m)] + G2[6 * m + jidx(i, l)]) / 3.0;
-    S.t1 = S.S2[0] + S.S2[3] + S.S2[5];
-    for (int m = 0; m < 3; ++m) S.sg[m] = S.S3[hidx(0, 0, m)] + S.S3[hidx(1, 1, m)] + S.S3[hidx(2, 2, m)];
+    for (int m = 0; m < 3; ++m) s[m] = ((T[hidx(0, 0, m)] + T[hidx(1, 1, m)]) + T[hidx(2, 2, m)]) / 5.0;
+    for (int i = 0; i < 3; ++i)
+        for (int l = i; l < 3; ++l)
+            for (int m = l; m < 3; ++m)
+                S.S3[hidx(i, l, m)] = T[hidx(i, l, m)] - (((i == l ? s[m] : 0.0) + (i == m ? s[l] : 0.0)) +
+                                                          (l == m ? s[i] : 0.0));
 }
 
-// Closed form of the pair adjoint with symmetrised moments (no dual numbers).
-// With u0 = S1.x, v = S2 x, w11 = x.v, sx = sg.x, P_lm = S3_ilm x_i, p = P x,
+// Closed form of the pair adjoint with these moments (no dual numbers). With
+// u0 = S1.x, v = S2 x, w1 = x.v, P_lm = S3_ilm x_i (traceless), p = P x,
 // w2 = x.p, q = Q x, s = x.q and the scalars of the forward pass, the pair's
 // share of L is
-//   Psi = a1 K1 + b2 K2 + e3 w2/2 + c0 K3 + 2 c1 q.v + 3/2 c1 K4 + 3/2 c2 q.p,
-//   K1 = u0 + t1, K2 = w11 + 3/2 sx, K3 = S1.q + S2:Q, K4 = Q:P + sg.q.
+//   Psi = a1 u0 + b2 w1 + e3 w2/2 + c0 K3 + 2 c1 q.v + 3/2 c1 K4 + 3/2 c2 q.p,
+//   K3 = S1.q + S2:Q, K4 = Q:P.
 // Using dD_k/dx = D_(k+1) x, ds/dx = 2 q, dq_i/dx_n = Q_in and
 //   da1 = b2 x + c1 q, db2 = e3 x + c2 q, de3 = e4 x + c3 q, dc_k = c_(k+1) x
-// (e4 = M D4 + s D6/6, c3 = D5/3):
-//   dPsi/dM = D1 K1 + D2 K2 + D3 w2/2
-//   dPsi/dQ = sym[ ss x x^T + psq x^T ] + c0 S2 + 3/2 c1 P,
-//             ss = (D3 K1 + D4 K2 + D5 w2/2)/6,
-//             psq = c0 S1 + 2 c1 v + 3/2 c1 sg + 3/2 c2 p
-//   rho = dPsi/dR = ax x + aq q + a1 S1 + b2 (2 v + 3/2 sg) + 3/2 e3 p + Q psq
-//                   + 2 c1 S2 q + 3/2 c1 (S3:Q) + 3 c2 P q,
-//         ax = b2 K1 + e3 K2 + e4 w2/2 + c1 K3 + 2 c2 q.v + 3/2 c2 K4 + 3/2 c3 q.p,
-//         aq = c1 K1 + c2 K2 + c3 w2/2
-//   cot = d(S3:H/2)/dR = bx x + bq q + 3/2 b2 sg + 3/2 e3 p + 3/2 c1 (S3:Q)
-//                        + Q (3/2 c1 sg + 3/2 c2 p) + 3 c2 P q,
-//         bx = 3/2 e3 sx + 3/2 c2 K4 + e4 w2/2 + 3/2 c3 q.p, bq = 3/2 c2 sx + c3 w2/2
+// (e4 = M D4 + s D6/6, c3 = D5/3; below c4 = D6/3, so that b2 = 3 M c0 + s c2/2,
+// e3 = 3 M c1 + s c3/2, e4 = 3 M c2 + s c4/2):
+//   dPsi/dM = D1 u0 + D2 w1 + D3 w2/2
+//   dPsi/dQ = y x^T + x y^T + c0 S2 + 3/2 c1 P, y = (aq x/2 + z + zc)/2,
+//             z = c0 S1 + 2 c1 v, zc = 3/2 c2 p (traceless but for 2 x.y)
+//   cot = d(S3:H/2)/dR = bx x + bq q + Q zc + 3/2 e3 p + 3/2 c1 (S3:Q) + 3 c2 P q,
+//         bx = e4 w2/2 + 3/2 (c2 K4 + c3 q.p), bq = c3 w2/2
+//   rho = dPsi/dR = cot + (b2 u0 + e3 w1 + c1 K3 + 2 c2 q.v) x
+//                   + (c1 u0 + c2 w1) q + a1 S1 + 2 b2 v + Q z + 2 c1 S2 q,
+//         aq = bq + c1 u0 + c2 w1 (the q coefficient of rho)
 // where (S3:Q)_n = S3_nlm Q_lm.
+// ~280 FP64 instructions; with the traces kept in the moments it took ~360.
 RCB_HD void far_pair_adjoint_sym(double x, double y, double z, double M, const double qq[6],
                                  const SymMoments &S, double rho[3], double cot[3], double &adjM,
                                  double adjQ[6]) {
     const double X[3] = {x, y, z};
     const double r2 = (x * x + y * y) + z * z;
     const double ri = rsqrt64(r2);
-    const double ri2 = ri * ri;
-    const double D1 = -ri * ri2;
-    const double D2 = -3.0 * D1 * ri2;
-    const double D3 = -5.0 * D2 * ri2;
-    const double D4 = -7.0 * D3 * ri2;
-    const double D5 = -9.0 * D4 * ri2;
-    const double D6 = -11.0 * D5 * ri2;
+    const double w = ri * ri;
+    const double p3 = ri * w;
+    const double c0 = p3 * w;
+    const double p7 = c0 * w;
+    const double p9 = p7 * w;
+    const double p11 = p9 * w;
+    const double c1 = -5.0 * p7, c2 = 35.0 * p9, c3 = -315.0 * p11, c4 = 3465.0 * (p11 * w);
+    const double c1h = 1.5 * c1, c2h = 1.5 * c2, c1d = 2.0 * c1;
     double q[3];
     for (int i = 0; i < 3; ++i) q[i] = qq[jidx(i, 0)] * x + qq[jidx(i, 1)] * y + qq[jidx(i, 2)] * z;
-    const double s = q[0] * x + q[1] * y + q[2] * z;
-    const double sixth = 1.0 / 6.0, third = 1.0 / 3.0;
-    const double a1 = M * D1 + sixth * D3 * s;
-    const double b2 = M * D2 + sixth * D4 * s;
-    const double e3 = M * D3 + sixth * D5 * s;
-    const double e4 = M * D4 + sixth * D6 * s;
-    const double c0 = third * D2, c1 = third * D3, c2 = third * D4, c3 = third * D5;
+    const double hs = 0.5 * ((q[0] * x + q[1] * y) + q[2] * z);
+    const double M3 = 3.0 * M;
+    const double a1 = hs * c1 - M * p3;
+    const double b2 = hs * c2 + M3 * c0;
+    const double e3 = hs * c3 + M3 * c1;
+    const double e4 = hs * c4 + M3 * c2;
     // sink contractions with x
     const double u0 = S.S1[0] * x + S.S1[1] * y + S.S1[2] * z;
     double v[3];
     for (int i = 0; i < 3; ++i) v[i] = S.S2[jidx(i, 0)] * x + S.S2[jidx(i, 1)] * y + S.S2[jidx(i, 2)] * z;
-    const double w11 = v[0] * x + v[1] * y + v[2] * z;
-    const double sx = S.sg[0] * x + S.sg[1] * y + S.sg[2] * z;
+    const double w1 = v[0] * x + v[1] * y + v[2] * z;
     double P[6];
     for (int l = 0; l < 3; ++l)
         for (int m = l; m < 3; ++m)
-            P[jidx(l, m)] = S.S3[hidx(0, l, m)] * x + S.S3[hidx(1, l, m)] * y + S.S3[hidx(2, l, m)] * z;
+            if (l != 2)
+                P[jidx(l, m)] = S.S3[hidx(0, l, m)] * x + S.S3[hidx(1, l, m)] * y + S.S3[hidx(2, l, m)] * z;
+    P[5] = -(P[0] + P[3]);
     double p[3];
     for (int l = 0; l < 3; ++l) p[l] = P[jidx(l, 0)] * x + P[jidx(l, 1)] * y + P[jidx(l, 2)] * z;
-    const double w2 = p[0] * x + p[1] * y + p[2] * z;
+    const double w2h = 0.5 * (x * p[0] + y * p[1] + z * p[2]);
     // contractions with Q (symmetric: off-diagonal pairs counted twice)
     const double S2Q = (S.S2[0] * qq[0] + S.S2[3] * qq[3] + S.S2[5] * qq[5]) +
                        2.0 * (S.S2[1] * qq[1] + S.S2[2] * qq[2] + S.S2[4] * qq[4]);
-    const double QP = (P[0] * qq[0] + P[3] * qq[3] + P[5] * qq[5]) +
+    const double K4 = (P[0] * qq[0] + P[3] * qq[3] + P[5] * qq[5]) +
                       2.0 * (P[1] * qq[1] + P[2] * qq[2] + P[4] * qq[4]);
-    const double K1 = u0 + S.t1;
-    const double K2 = w11 + 1.5 * sx;
     const double K3 = (S.S1[0] * q[0] + S.S1[1] * q[1] + S.S1[2] * q[2]) + S2Q;
-    const double K4 = QP + (S.sg[0] * q[0] + S.sg[1] * q[1] + S.sg[2] * q[2]);
     const double qv = q[0] * v[0] + q[1] * v[1] + q[2] * v[2];
     const double qp = q[0] * p[0] + q[1] * p[1] + q[2] * p[2];
-    adjM = D1 * K1 + D2 * K2 + 0.5 * D3 * w2;
-    const double ss = sixth * (D3 * K1 + D4 * K2 + 0.5 * D5 * w2);
-    double psq[3], psc[3];
+    adjM = 3.0 * (c0 * w1 + c1 * w2h) - p3 * u0;
+    const double bq = c3 * w2h, dq = c1 * u0 + c2 * w1;
+    const double aqh = 0.5 * (bq + dq);
+    double zz[3], t[3];
     for (int j = 0; j < 3; ++j) {
-        psc[j] = 1.5 * (c1 * S.sg[j] + c2 * p[j]);
-        psq[j] = c0 * S.S1[j] + 2.0 * c1 * v[j] + psc[j];
+        zz[j] = c0 * S.S1[j] + c1d * v[j];
+        t[j] = 0.5 * (aqh * X[j] + (zz[j] + c2h * p[j]));
     }
     for (int j = 0; j < 3; ++j)
         for (int k = j; k < 3; ++k)
-            adjQ[jidx(j, k)] = ss * X[j] * X[k] + 0.5 * (psq[j] * X[k] + psq[k] * X[j]) +
-                               c0 * S.S2[jidx(j, k)] + 1.5 * c1 * P[jidx(j, k)];
-    const double ax = b2 * K1 + e3 * K2 + 0.5 * e4 * w2 + c1 * K3 + 2.0 * c2 * qv + 1.5 * c2 * K4 +
-                      1.5 * c3 * qp;
-    const double aq = c1 * K1 + c2 * K2 + 0.5 * c3 * w2;
-    const double bx = 1.5 * e3 * sx + 1.5 * c2 * K4 + 0.5 * e4 * w2 + 1.5 * c3 * qp;
-    const double bq = 1.5 * c2 * sx + 0.5 * c3 * w2;
+            adjQ[jidx(j, k)] = t[j] * X[k] + t[k] * X[j] + c0 * S.S2[jidx(j, k)] + c1h * P[jidx(j, k)];
+    const double bx = e4 * w2h + (c2h * K4 + 1.5 * (c3 * qp));
+    const double dx = b2 * u0 + e3 * w1 + c1 * K3 + 2.0 * (c2 * qv);
+    const double e3h = 1.5 * e3, c2t = 2.0 * c2h, b2d = 2.0 * b2;
     for (int n = 0; n < 3; ++n) {
-        double S3Q = 0.0, Pq = 0.0, S2q = 0.0, Qpsq = 0.0, Qpsc = 0.0;
+        const double S3Q = (S.S3[hidx(n, 0, 0)] * qq[0] + S.S3[hidx(n, 1, 1)] * qq[3] + S.S3[hidx(n, 2, 2)] * qq[5]) +
+                           2.0 * (S.S3[hidx(n, 0, 1)] * qq[1] + S.S3[hidx(n, 0, 2)] * qq[2] + S.S3[hidx(n, 1, 2)] * qq[4]);
+        double Pq = 0.0, S2q = 0.0, Qz = 0.0, Qp = 0.0;
         for (int m = 0; m < 3; ++m) {
-            for (int l = 0; l < 3; ++l) S3Q += S.S3[hidx(n, l, m)] * qq[jidx(l, m)];
             Pq += P[jidx(n, m)] * q[m];
             S2q += S.S2[jidx(n, m)] * q[m];
-            Qpsq += qq[jidx(n, m)] * psq[m];
-            Qpsc += qq[jidx(n, m)] * psc[m];
+            Qz += qq[jidx(n, m)] * zz[m];
+            Qp += qq[jidx(n, m)] * p[m];
         }
-        const double common = 1.5 * e3 * p[n] + 1.5 * c1 * S3Q + 3.0 * c2 * Pq;
-        cot[n] = bx * X[n] + bq * q[n] + 1.5 * b2 * S.sg[n] + Qpsc + common;
-        rho[n] = ax * X[n] + aq * q[n] + a1 * S.S1[n] + b2 * (2.0 * v[n] + 1.5 * S.sg[n]) + Qpsq +
-                 2.0 * c1 * S2q + common;
+        cot[n] = bx * X[n] + bq * q[n] + c2h * Qp + e3h * p[n] + c1h * S3Q + c2t * Pq;
+        rho[n] = cot[n] + dx * X[n] + dq * q[n] + a1 * S.S1[n] + b2d * v[n] + Qz + c1d * S2q;
     }
 }
 

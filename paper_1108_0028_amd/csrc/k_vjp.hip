@@ -9,7 +9,7 @@
 // Pairs are recomputed from the lists, not stored. The source-side terms
 // are summed over the wave's sinks and added with FP64 atomics.
 // Far field (Sec. 2.4.2, Eq. 6): per sink leaf the cotangent moments G0, G1,
-// G2, stored symmetrised (far_math.h: only their symmetric parts reach Psi),
+// G2, stored symmetrised and traceless (far_math.h: only those parts reach Psi),
 // then
 //   dr_a += J g_a + H[g_a, d_a]                       (d_a = r_a - com_A)
 //   com_A receives cot = sum_B d(G2:H/2)/dR  ->  dr_a += m_a/M_A cot,
@@ -48,7 +48,7 @@ constexpr int kAdjCopies = 8;   // node-adjoint copies filled by k_vjp_far
 constexpr int kMidLevel = 16;
 constexpr int kAdjMidCopies = 64;
 constexpr int kAcc = 30;    // G0(3), G1(9), G2(18) while accumulating
-constexpr int kMom = 23;    // S1(3), S2(6), S3(10), t1, sg(3): far_math.h SymMoments
+constexpr int kMom = 19;    // S1(3), S2(6), S3(10): far_math.h SymMoments
 
 using rcbfar::hidx;
 using rcbfar::jidx;
@@ -159,9 +159,6 @@ __global__ __launch_bounds__(kBlock) void k_vjp_moments(VjpArgs a) {
         for (int q = 0; q < 6; ++q) o[3 + q] = S.S2[q];
 #pragma unroll
         for (int q = 0; q < 10; ++q) o[9 + q] = S.S3[q];
-        o[19] = S.t1;
-#pragma unroll
-        for (int q = 0; q < 3; ++q) o[20 + q] = S.sg[q];
     }
 }
 
@@ -232,9 +229,6 @@ __global__ __launch_bounds__(kBlock) void k_vjp_far(VjpArgs a, AT *__restrict__ 
             for (int q = 0; q < 6; ++q) Sm.S2[q] = uniform_f64(mo[3 + q]);
 #pragma unroll
             for (int q = 0; q < 10; ++q) Sm.S3[q] = uniform_f64(mo[9 + q]);
-            Sm.t1 = uniform_f64(mo[19]);
-#pragma unroll
-            for (int q = 0; q < 3; ++q) Sm.sg[q] = uniform_f64(mo[20 + q]);
             const double cA[3] = {uniform_f64(sh.com[i][0]), uniform_f64(sh.com[i][1]),
                                   uniform_f64(sh.com[i][2])};
             double ct[3] = {0.0, 0.0, 0.0};
@@ -245,7 +239,7 @@ __global__ __launch_bounds__(kBlock) void k_vjp_far(VjpArgs a, AT *__restrict__ 
                 ad[0] += aM;
 #pragma unroll
                 for (int u = 0; u < 3; ++u) ad[1 + u] -= rho[u];
-                const double tq = (aQ[0] + aQ[3] + aQ[5]) / 3.0;
+                const double tq = (aQ[0] + aQ[3] + aQ[5]) * (1.0 / 3.0);
                 ad[4] += aQ[0] - tq;
                 ad[5] += aQ[1];
                 ad[6] += aQ[2];
@@ -644,9 +638,6 @@ __global__ __launch_bounds__(kBlock) void k_vjp_moments_det(VjpArgs a) {
             for (int q = 0; q < 6; ++q) o[3 + q] = S.S2[q];
 #pragma unroll
             for (int q = 0; q < 10; ++q) o[9 + q] = S.S3[q];
-            o[19] = S.t1;
-#pragma unroll
-            for (int q = 0; q < 3; ++q) o[20 + q] = S.sg[q];
         }
     }
 }
@@ -763,16 +754,13 @@ __global__ __launch_bounds__(kBlock) void k_vjp_far_node(VjpArgs a, const uint64
             for (int q = 0; q < 6; ++q) Sm.S2[q] = mo[3 + q];
 #pragma unroll
             for (int q = 0; q < 10; ++q) Sm.S3[q] = mo[9 + q];
-            Sm.t1 = mo[19];
-#pragma unroll
-            for (int q = 0; q < 3; ++q) Sm.sg[q] = mo[20 + q];
             double rho[3], ct[3] = {0.0, 0.0, 0.0}, aM, aQ[6];
             rcbfar::far_pair_adjoint_sym(a.ncom[3 * A] - cB[0], a.ncom[3 * A + 1] - cB[1],
                                          a.ncom[3 * A + 2] - cB[2], MB, qq, Sm, rho, ct, aM, aQ);
             ad[0] += aM;
 #pragma unroll
             for (int u = 0; u < 3; ++u) ad[1 + u] -= rho[u];
-            const double tq = (aQ[0] + aQ[3] + aQ[5]) / 3.0;
+            const double tq = (aQ[0] + aQ[3] + aQ[5]) * (1.0 / 3.0);
             ad[4] += aQ[0] - tq;
             ad[5] += aQ[1];
             ad[6] += aQ[2];
