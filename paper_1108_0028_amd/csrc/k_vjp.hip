@@ -41,12 +41,14 @@ constexpr int kWaves = kBlock / kWave;
 // adjoint's traceless part alone (6 aQ d - 2 tr(aQ) d = 6 (aQ - tr/3 I) d, and
 // likewise for dm), and one atomic per entry fewer goes out
 constexpr int kAdj = 9;
-constexpr int kAdjCopies = 8;   // node-adjoint copies filled by k_vjp_far
 // Nodes of the levels above kMidLevel sit in the far lists of many groups at
-// once, and the atomics on their adjoints contend: they get kAdjMidCopies
-// copies (kAdjCopies / XCD), in their own array of kAdj * 2^kMidLevel per copy.
+// once: their adjoints are added to several copies, in their own array of
+// kAdj * 2^kMidLevel per copy. FP64: 8 copies (with 64 and 8 of the deep nodes the
+// VJP of 300,000 particles took 2.88 ms, with 8 and one 2.74). FP32 (mixed
+// form): 64, which also keep each FP32 sum short. The deeper nodes have one.
 constexpr int kMidLevel = 16;
-constexpr int kAdjMidCopies = 64;
+template <typename AT>
+constexpr int kAdjMidCopies = sizeof(AT) == 4 ? 64 : 8;
 constexpr int kAcc = 30;    // G0(3), G1(9), G2(18) while accumulating
 constexpr int kMom = 19;    // S1(3), S2(6), S3(10): far_math.h SymMoments
 
@@ -70,9 +72,9 @@ struct VjpArgs {
     double *sink;   // 4 n, tree order: dx dy dz dm
     double *src;    // 4 n, tree order, atomics (FP64 form)
     float *srcf;    // the same in the mixed form (FP32 atomics, its contract's accumulation)
-    double *adj;    // kAdj per label (summed copies); component q of label B at q * nlab + B
+    double *adj;    // kAdj per label (summed copies); component q of label B at B * kAdj + q
     double *adjm;   // unused
-    int64_t nmid;   // labels below nmid have kAdjMidCopies adjoint copies, q * nmid + B
+    int64_t nmid;   // labels below nmid have kAdjMidCopies adjoint copies
     int64_t n;
     int64_t nlab;
     // deterministic form: each far entry's node adjoint (kAdj FP64) at row
@@ -162,15 +164,24 @@ __global__ __launch_bounds__(kBlock) void k_vjp_moments(VjpArgs a) {
     }
 }
 
-// far field: per group, lanes = far entries; the group's leaves are taken in
+// far field: a workgroup of kFarWaves waves per group, lanes = far entries (64
+// per window, the windows going to the waves in turn); the group's leaves are taken in
 // turn with their centre of mass and cotangent moments held uniform (scalar
 // registers), so each lane sums its entry's node adjoint over the leaves that
-// accepted it and issues one set of atomics. The sink-centre term is kept per
-// lane and leaf in LDS and summed over the lanes once per group.
+// accepted it. The sink-centre term is kept per four lanes and leaf in LDS and
+// summed over lanes and waves once per group. A window's adjoints are turned
+// round in LDS, so that consecutive lanes hold the kAdj components of one
+// entry and its atomics fall into one or two lines. Device-scope atomics run
+// past L2, so their number of lines is what they cost: component by component,
+// every lane's in a line of its own, this kernel took 5.5 ms for 1M particles
+// (mixed, 36M entries), now 3.2; one wave per group of a 64-group cloud 87 us,
+// four 23.
+constexpr int kFarWaves = 4;
+template <typename AT>
 struct VjpFarShared {
-    double cot[8][3][kWave / 2];   // per lane pair and leaf
-    double mom[8][kMom];       // the group's leaves: symmetrised moments
-    double com[8][3];          // and centres of mass
+    double cot[8][3][kWave / 4];   // per four lanes and leaf
+    AT rows[kWave * kAdj];         // the window's node adjoints
+    int32_t lab[kWave];            // and its labels (-1: past the end)
 };
 
 // AT: the type of the node-adjoint copies (FP64; FP32 in the mixed form, whose
@@ -182,20 +193,22 @@ struct VjpFarShared {
 // the node adjoints itself).
 constexpr int kFarAtomic = 0, kFarCot = 1, kFarStore = 2;
 template <typename AT, int MODE>
-__global__ __launch_bounds__(kBlock) void k_vjp_far(VjpArgs a, AT *__restrict__ adjc, AT *__restrict__ adjmc) {
-    __shared__ VjpFarShared sh_all[kWaves];
-    VjpFarShared &sh = sh_all[threadIdx.x / kWave];
-    double(*cotp)[3][kWave / 2] = sh.cot;
-    const int64_t gi = wave_index();
-    if (gi >= a.ngroup) return;
+__global__ __launch_bounds__(kFarWaves * kWave, sizeof(AT) == 4 ? 4 : 3) void k_vjp_far(VjpArgs a, AT *__restrict__ adjc,
+                                                               AT *__restrict__ adjmc) {
+    __shared__ VjpFarShared<AT> sh_all[kFarWaves];
+    __shared__ double mom[8][kMom];   // the group's leaves: symmetrised moments
+    __shared__ double com[8][3];      // and centres of mass
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    VjpFarShared<AT> &sh = sh_all[wv];
+    const int64_t gi = a.first + blockIdx.x;
     const int lane = lane_id();
     const int G = 1 << a.gk;
-    for (int i = lane; i < 8 * 3 * (kWave / 2); i += kWave) (&cotp[0][0][0])[i] = 0.0;
-    for (int i = lane; i < G * kMom; i += kWave) sh.mom[i / kMom][i % kMom] = a.mom[gi * G * kMom + i];
-    if (lane < 3 * G) sh.com[lane / 3][lane % 3] = a.ncom[3 * (a.nleaf + gi * G) + lane];
-    tile_sync();
+    for (int i = lane; i < 8 * 3 * (kWave / 4); i += kWave) (&sh.cot[0][0][0])[i] = 0.0;
+    for (int i = threadIdx.x; i < G * kMom; i += kFarWaves * kWave) mom[i / kMom][i % kMom] = a.mom[gi * G * kMom + i];
+    if ((int)threadIdx.x < 3 * G) com[threadIdx.x / 3][threadIdx.x % 3] = a.ncom[3 * (a.nleaf + gi * G) + threadIdx.x];
+    __syncthreads();
     const int64_t f0 = a.gfar_beg[gi], f1 = a.gfar_end[gi];
-    for (int64_t e0 = f0; e0 < f1; e0 += kWave) {
+    for (int64_t e0 = f0 + wv * kWave; e0 < f1; e0 += kFarWaves * kWave) {
         const int64_t e = e0 + lane;
         const uint64_t ent = e < f1 ? a.gfar[e] : 0ull;
         const uint32_t emask = (uint32_t)(ent >> 32) & 0xffu;
@@ -218,10 +231,8 @@ __global__ __launch_bounds__(kBlock) void k_vjp_far(VjpArgs a, AT *__restrict__ 
         for (int i = 0; i < G; ++i) {
             const bool mine = (emask >> i) & 1u;
             if (ballot(mine) == 0) continue;
-            const int64_t leaf = gi * G + i;
-            const int64_t A = a.nleaf + leaf;
             // the leaf's moments and centre are the same on every lane
-            const double *mo = sh.mom[i];
+            const double *mo = mom[i];
             rcbfar::SymMoments Sm;
 #pragma unroll
             for (int q = 0; q < 3; ++q) Sm.S1[q] = uniform_f64(mo[q]);
@@ -229,8 +240,7 @@ __global__ __launch_bounds__(kBlock) void k_vjp_far(VjpArgs a, AT *__restrict__ 
             for (int q = 0; q < 6; ++q) Sm.S2[q] = uniform_f64(mo[3 + q]);
 #pragma unroll
             for (int q = 0; q < 10; ++q) Sm.S3[q] = uniform_f64(mo[9 + q]);
-            const double cA[3] = {uniform_f64(sh.com[i][0]), uniform_f64(sh.com[i][1]),
-                                  uniform_f64(sh.com[i][2])};
+            const double cA[3] = {uniform_f64(com[i][0]), uniform_f64(com[i][1]), uniform_f64(com[i][2])};
             double ct[3] = {0.0, 0.0, 0.0};
             if (mine) {
                 double rho[3], aM, aQ[6];
@@ -246,39 +256,45 @@ __global__ __launch_bounds__(kBlock) void k_vjp_far(VjpArgs a, AT *__restrict__ 
                 ad[7] += aQ[3] - tq;
                 ad[8] += aQ[4];
             }
-            // lanes 2j and 2j + 1 add their terms, the even lane keeps the sum
+            // four lanes add their terms, the first of them keeps the sum
 #pragma unroll
             for (int u = 0; u < 3; ++u) {
-                const double t = ct[u] + swap_adjacent_lanes(ct[u]);
-                if (!(lane & 1)) cotp[i][u][lane >> 1] += t;
+                double t = ct[u] + swap_adjacent_lanes(ct[u]);
+                t += swap_lane_pairs(t);
+                if (!(lane & 3)) sh.cot[i][u][lane >> 2] += t;
             }
         }
-        if (MODE == kFarStore && emask) {
-            double *row = a.contrib + (a.cbase[gi] + (e - f0)) * kAdj;
+        if constexpr (MODE != kFarCot) {
 #pragma unroll
-            for (int q = 0; q < kAdj; ++q) row[q] = ad[q];
-        }
-        if (MODE == kFarAtomic && emask) {
-            // each copy takes the blocks of one residue mod the number of
+            for (int q = 0; q < kAdj; ++q) sh.rows[lane * kAdj + q] = (AT)ad[q];
+            sh.lab[lane] = emask ? (int32_t)B : -1;
+            tile_sync();
+            const int nw = (int)(f1 - e0 < kWave ? f1 - e0 : kWave);
+            AT *const out = MODE == kFarStore ? (AT *)a.contrib + (a.cbase[gi] + (e0 - f0)) * kAdj : nullptr;
+            // each copy takes the groups of one residue mod the number of
             // copies, i.e. of one XCD under round-robin dispatch (8 | copies)
-            if (B < a.nmid) {
-                AT *adj = adjmc + (int64_t)(blockIdx.x % kAdjMidCopies) * kAdj * a.nmid;
-#pragma unroll
-                for (int q = 0; q < kAdj; ++q)
-                    __hip_atomic_fetch_add(adj + q * a.nmid + B, (AT)ad[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            } else {
-                AT *adj = adjc + (int64_t)(blockIdx.x % kAdjCopies) * kAdj * a.nlab;
-#pragma unroll
-                for (int q = 0; q < kAdj; ++q)
-                    __hip_atomic_fetch_add(adj + q * a.nlab + B, (AT)ad[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            AT *const mid = adjmc + (int64_t)(blockIdx.x % kAdjMidCopies<AT>) * kAdj * a.nmid;
+#pragma unroll 1
+            for (int f = lane; f < nw * kAdj; f += kWave) {
+                const int r = f / kAdj;
+                if constexpr (MODE == kFarStore) {
+                    out[f] = sh.rows[f];
+                } else {
+                    const int32_t L = sh.lab[r];
+                    if (L < 0) continue;
+                    __hip_atomic_fetch_add((L < a.nmid ? mid : adjc) + (int64_t)L * kAdj + (f - r * kAdj), sh.rows[f],
+                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
             }
+            tile_sync();
         }
     }
-    tile_sync();
-    if (lane < 3 * G) {
-        const int i = lane / 3, u = lane % 3;
+    __syncthreads();
+    if ((int)threadIdx.x < 3 * G) {
+        const int i = threadIdx.x / 3, u = threadIdx.x % 3;
         double v = 0.0;
-        for (int l = 0; l < kWave / 2; ++l) v += cotp[i][u][l];
+        for (int w = 0; w < kFarWaves; ++w)
+            for (int l = 0; l < kWave / 4; ++l) v += sh_all[w].cot[i][u][l];
         a.leafc[(gi * G + i) * kLeafC + 19 + u] = v;
     }
 }
@@ -533,14 +549,14 @@ __global__ __launch_bounds__(kBlock) void k_vjp_push(VjpArgs a, const double *__
         for (int64_t B = A; B > GL; B >>= 1) {
             double ad[kAdj];
 #pragma unroll
-            for (int q = 0; q < kAdj; ++q) ad[q] = adj[q * a.nlab + B];
+            for (int q = 0; q < kAdj; ++q) ad[q] = adj[B * kAdj + q];
             const double cB[3] = {ncom[3 * B], ncom[3 * B + 1], ncom[3 * B + 2]};
             push_node(ad, nM[B], cB, r, mb, dr, dmb);
         }
         for (int64_t B = GL; B >= 1; B >>= 1) {   // wave-uniform
             double ad[kAdj];
 #pragma unroll
-            for (int q = 0; q < kAdj; ++q) ad[q] = adj[q * a.nlab + B];
+            for (int q = 0; q < kAdj; ++q) ad[q] = adj[B * kAdj + q];
             const double cB[3] = {ncom[3 * B], ncom[3 * B + 1], ncom[3 * B + 2]};
             push_node(ad, nM[B], cB, r, mb, dr, dmb);
         }
@@ -559,25 +575,20 @@ __global__ __launch_bounds__(kBlock) void k_vjp_push(VjpArgs a, const double *__
     }
 }
 
-// node adjoints: the copies summed in FP64 in a fixed order into out (labels
-// below nmid from the mid-level copies, the others from the kAdjCopies ones);
-// out may be copy 0 of adjc (each thread reads its own element first)
+// node adjoints into out, FP64: labels below nmid the sum of their copies in
+// order, the others from adjc, which may be out itself
 template <typename A>
 __global__ void k_adj_reduce(double *out, const A *adjc, const A *__restrict__ adjmc, int64_t nlab,
                              int64_t nmid) {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= kAdj * nlab) return;
-    const int64_t q = i / nlab, B = i % nlab;
-    double v;
-    if (B < nmid) {
-        const int64_t len = kAdj * nmid, k = q * nmid + B;
-        v = (double)adjmc[k];
-        for (int c = 1; c < kAdjMidCopies; ++c) v += (double)adjmc[(int64_t)c * len + k];
-    } else {
-        const int64_t len = kAdj * nlab;
-        v = (double)adjc[i];
-        for (int c = 1; c < kAdjCopies; ++c) v += (double)adjc[(int64_t)c * len + i];
+    if (i >= kAdj * nmid) {
+        if ((const void *)adjc != (const void *)out) out[i] = (double)adjc[i];
+        return;
     }
+    double v = (double)adjmc[i];
+#pragma unroll 8
+    for (int c = 1; c < kAdjMidCopies<A>; ++c) v += (double)adjmc[(int64_t)c * kAdj * nmid + i];
     out[i] = v;
 }
 
@@ -775,12 +786,12 @@ __global__ __launch_bounds__(kBlock) void k_vjp_far_node(VjpArgs a, const uint64
     }
 }
 
-// adj[q * nlab + B] = sum of the node's chunk sums in chunk order (0 if none)
+// adj[B * kAdj + q] = sum of the node's chunk sums in chunk order (0 if none)
 __global__ void k_det_adj_sum(const double *__restrict__ part, const int64_t *__restrict__ cb, int64_t nlab,
                               double *__restrict__ adj) {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= kAdj * nlab) return;
-    const int64_t q = i / nlab, B = i % nlab;
+    const int64_t B = i / kAdj, q = i % kAdj;
     double v = 0.0;
     for (int64_t c = cb[B]; c < cb[B + 1]; ++c) v += part[c * kAdj + q];
     adj[i] = v;
@@ -999,7 +1010,7 @@ rcb_status det_sort(rcb_tree *t, const int64_t *beg, const int64_t *end, const u
 }
 
 // The deterministic form after the cotangent moments and far coefficients:
-// sink-centre sums and node adjoints (FP64, q * nlab + B) of the far field,
+// sink-centre sums and node adjoints (FP64, B * kAdj + q) of the far field,
 // and the source-side near terms. Each far entry's node adjoint is stored by
 // k_vjp_far and summed per node (72 B per entry); if that array cannot be had
 // (or RCB_VJP_DET_RECOMPUTE is set) k_vjp_far_node recomputes it per node.
@@ -1014,9 +1025,12 @@ rcb_status vjp_det(rcb_tree *t, VjpArgs &a, double *adj, bool mixed, Scratch &tm
         contrib = (double *)dalloc(t, sizeof(double) * kAdj * far.total, s, tmp);
     a.contrib = contrib;
     a.cbase = far.base;
-    if (contrib) k_vjp_far<double, kFarStore><<<gridg, kBlock, 0, s>>>(a, nullptr, nullptr);
-    else k_vjp_far<double, kFarCot><<<gridg, kBlock, 0, s>>>(a, nullptr, nullptr);
-    RCB_LAUNCH_CHECK("k_vjp_far");
+    for (a.first = 0; a.first < t->ngroup; a.first += kMaxGrid) {
+        const unsigned gf = (unsigned)std::min(kMaxGrid, t->ngroup - a.first);
+        if (contrib) k_vjp_far<double, kFarStore><<<gf, kFarWaves * kWave, 0, s>>>(a, nullptr, nullptr);
+        else k_vjp_far<double, kFarCot><<<gf, kFarWaves * kWave, 0, s>>>(a, nullptr, nullptr);
+        RCB_LAUNCH_CHECK("k_vjp_far");
+    }
     st = det_sort(t, t->gfar_beg, t->gfar_end, t->gfar, contrib != nullptr, tmp, s, far);
     if (st != RCB_OK) return st;
     int64_t *cb = (int64_t *)dalloc(t, sizeof(int64_t) * (nlab + 1), s, tmp);
@@ -1101,11 +1115,11 @@ rcb_status gravity_vjp(rcb_tree *t, const void *gx, const void *gy, const void *
         return RCB_ECAPACITY;
     }
     const int64_t nmid = std::min<int64_t>(t->nlab, int64_t(1) << kMidLevel);
-    // node-adjoint copies: FP64 (summed into copy 0 of adj) or, in the mixed
-    // form, FP32 (summed into adj); the deterministic form writes adj alone
-    const size_t adj_n = det ? 0 : (size_t)kAdjCopies * kAdj * t->nlab;
-    const size_t adjm_n = det ? 0 : (size_t)kAdjMidCopies * kAdj * nmid;
-    double *adj = (double *)dalloc(t, sizeof(double) * (mixed || det ? (size_t)kAdj * t->nlab : adj_n), s, tmp);
+    // node adjoints as the far kernel adds them: FP64 in adj itself, FP32
+    // (mixed form) apart; the deterministic form writes adj alone
+    const size_t adj_n = det ? 0 : (size_t)kAdj * t->nlab;
+    const size_t adjm_n = det ? 0 : (size_t)(mixed ? kAdjMidCopies<float> : kAdjMidCopies<double>) * kAdj * nmid;
+    double *adj = (double *)dalloc(t, sizeof(double) * kAdj * t->nlab, s, tmp);
     void *adjc = det ? (void *)adj : mixed ? dalloc(t, sizeof(float) * adj_n, s, tmp) : (void *)adj;
     void *adjmc = det ? (void *)adj : dalloc(t, (mixed ? sizeof(float) : sizeof(double)) * adjm_n, s, tmp);
     double *mom = (double *)dalloc(t, sizeof(double) * kMom * t->nleaf, s, tmp);
@@ -1166,17 +1180,16 @@ rcb_status gravity_vjp(rcb_tree *t, const void *gx, const void *gy, const void *
         near(std::false_type{});
         RCB_LAUNCH_CHECK("k_vjp_near");
     } else {
-        if (mixed) {
-            k_vjp_far<float, kFarAtomic><<<gridg, kBlock, 0, s>>>(a, (float *)adjc, (float *)adjmc);
+        for (a.first = 0; a.first < t->ngroup; a.first += kMaxGrid) {
+            const unsigned gf = (unsigned)std::min(kMaxGrid, t->ngroup - a.first);
+            if (mixed) k_vjp_far<float, kFarAtomic><<<gf, kFarWaves * kWave, 0, s>>>(a, (float *)adjc, (float *)adjmc);
+            else k_vjp_far<double, kFarAtomic><<<gf, kFarWaves * kWave, 0, s>>>(a, (double *)adjc, (double *)adjmc);
             RCB_LAUNCH_CHECK("k_vjp_far");
-            k_adj_reduce<float><<<gridr, 256, 0, s>>>(adj, (const float *)adjc, (const float *)adjmc, t->nlab,
-                                                      nmid);
-        } else {
-            k_vjp_far<double, kFarAtomic><<<gridg, kBlock, 0, s>>>(a, (double *)adjc, (double *)adjmc);
-            RCB_LAUNCH_CHECK("k_vjp_far");
-            k_adj_reduce<double><<<gridr, 256, 0, s>>>(adj, (const double *)adjc, (const double *)adjmc, t->nlab,
-                                                       nmid);
         }
+        if (mixed)
+            k_adj_reduce<float><<<gridr, 256, 0, s>>>(adj, (const float *)adjc, (const float *)adjmc, t->nlab, nmid);
+        else
+            k_adj_reduce<double><<<gridr, 256, 0, s>>>(adj, (const double *)adjc, (const double *)adjmc, t->nlab, nmid);
         RCB_LAUNCH_CHECK("k_adj_reduce");
         near(std::true_type{});
         RCB_LAUNCH_CHECK("k_vjp_near");

@@ -290,17 +290,21 @@ __device__ __forceinline__ double uniform_f64(double v) {
     u.w[1] = __builtin_amdgcn_readfirstlane(u.w[1]);
     return u.d;
 }
-// The value of the other lane of this lane's pair (2j, 2j + 1), by DPP.
-__device__ __forceinline__ double swap_adjacent_lanes(double v) {
+// The value of another lane of this lane's four, by DPP quad permutation: the
+// other lane of the pair (2j, 2j + 1), and the same lane of the other pair.
+template <int PERM>
+__device__ __forceinline__ double quad_perm(double v) {
     union {
         double d;
         int w[2];
     } u, r;
     u.d = v;
-    r.w[0] = __builtin_amdgcn_mov_dpp(u.w[0], 0xB1, 0xF, 0xF, false);   // quad_perm [1,0,3,2]
-    r.w[1] = __builtin_amdgcn_mov_dpp(u.w[1], 0xB1, 0xF, 0xF, false);
+    r.w[0] = __builtin_amdgcn_mov_dpp(u.w[0], PERM, 0xF, 0xF, false);
+    r.w[1] = __builtin_amdgcn_mov_dpp(u.w[1], PERM, 0xF, 0xF, false);
     return r.d;
 }
+__device__ __forceinline__ double swap_adjacent_lanes(double v) { return quad_perm<0xB1>(v); }   // [1,0,3,2]
+__device__ __forceinline__ double swap_lane_pairs(double v) { return quad_perm<0x4E>(v); }       // [2,3,0,1]
 __device__ __forceinline__ uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 __device__ __forceinline__ int rank_below(uint64_t mask) {
     const int l = lane_id();
