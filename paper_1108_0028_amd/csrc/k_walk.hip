@@ -70,7 +70,7 @@ struct WalkArgs {
     int64_t near_cap, far_cap;
     uint64_t *near_list, *far_list;
     int32_t *flag;
-    unsigned long long *stats;   // if given: [0] node records tested, [1] (node, leaf) tests
+    uint2 *stats;   // if given, per group: node records tested, (node, leaf) tests
 };
 
 // what k_slab_ends estimates the neighbour lists' overflow from
@@ -270,6 +270,7 @@ __global__ __launch_bounds__(WAVES * kWave) void k_walk_wide(WalkArgs w, int32_t
         if (lane == 0) {
             w.near_cnt[gi] = 0;
             w.far_cnt[gi] = 0;
+            if (w.stats) w.stats[gi] = make_uint2(0u, 0u);
         }
         return;
     }
@@ -366,13 +367,14 @@ __global__ __launch_bounds__(WAVES * kWave) void k_walk_wide(WalkArgs w, int32_t
     }
     if (w.stats) {
         const int sn = wave_sum_i((int)n_nodes), st = wave_sum_i((int)n_tests);
-        if (lane == 0) {
-            atomicAdd(&w.stats[0], (unsigned long long)sn);
-            atomicAdd(&w.stats[1], (unsigned long long)st);
-        }
+        if (lane == 0) w.stats[gi] = make_uint2((uint32_t)sn, (uint32_t)st);
     }
     if (overflow) {
-        if (lane == 0 && queue) queue[atomicAdd(nqueue, 1)] = (int32_t)gi;
+        if (lane == 0 && queue) {   // (the counts are read before the next tier writes them)
+            queue[atomicAdd(nqueue, 1)] = (int32_t)gi;
+            w.near_cnt[gi] = 0;
+            w.far_cnt[gi] = 0;
+        }
         return;
     }
     if (lane == 0) {
@@ -382,24 +384,32 @@ __global__ __launch_bounds__(WAVES * kWave) void k_walk_wide(WalkArgs w, int32_t
     }
 }
 
-// ends of the slab lists: [g cap, g cap + count). With est, also the neighbour
-// search's overflow chunks that the group will need: a cell of c particles in
-// volume V expects c / V 4 pi / 3 (2h)^3 neighbours each (2h: h_node - h_node_int),
-// and lists past 64 ids take chunks of 64. It only sizes a pool.
+// ends of the slab lists: [g cap, g cap + count). With tot, also the totals
+// over the groups: [0] node records tested, [1] tests, [2] far entries and [3]
+// the overflow chunks that the neighbour search will need: a cell of c
+// particles in volume V expects c / V 4 pi / 3 (2h)^3 neighbours each (2h:
+// h_node - h_node_int), and lists past 64 ids take chunks of 64. [2] and [3]
+// only choose a launch and size a pool.
 __global__ __launch_bounds__(kBlock) void k_slab_ends(int64_t ngroup, int64_t near_cap, int64_t far_cap,
                                                       const int64_t *__restrict__ ncnt,
                                                       const int64_t *__restrict__ fcnt,
                                                       int64_t *__restrict__ nbeg, int64_t *__restrict__ nend,
                                                       int64_t *__restrict__ fbeg, int64_t *__restrict__ fend,
-                                                      const NbEstimate e, unsigned long long *__restrict__ est) {
+                                                      const NbEstimate e, const uint2 *__restrict__ stats,
+                                                      unsigned long long *__restrict__ tot) {
     const int64_t g = blockIdx.x * (int64_t)kBlock + threadIdx.x;
-    double chunks = 0.0;
+    double sum[4] = {0.0, 0.0, 0.0, 0.0};   // (exact: below 2^53)
     if (g < ngroup) {
         nbeg[g] = g * near_cap;
         nend[g] = g * near_cap + ncnt[g];
         fbeg[g] = g * far_cap;
         fend[g] = g * far_cap + fcnt[g];
-        for (int i = 0; est && i < 1 << e.gk; ++i) {
+        if (tot) {
+            sum[0] = stats[g].x;
+            sum[1] = stats[g].y;
+            sum[2] = (double)fcnt[g];
+        }
+        for (int i = 0; tot && i < 1 << e.gk; ++i) {
             const int64_t A = e.nleaf + (g << e.gk) + i;
             const double c = e.ncount[A];
             const double V = (e.nhi[3 * A] - e.nlo[3 * A]) * (e.nhi[3 * A + 1] - e.nlo[3 * A + 1]) *
@@ -407,12 +417,14 @@ __global__ __launch_bounds__(kBlock) void k_slab_ends(int64_t ngroup, int64_t ne
             const double r = e.hnode[A] - e.rec[2 * A].w;
             double nb = 4.19 * c / V * r * r * r * 1.1;   // (10% over the mean)
             if (!(nb < e.n)) nb = e.n;                    // (also a cell without volume)
-            if (c > 0.0 && nb > 64.0) chunks += c * ceil((nb - 64.0) / 64.0);
+            if (c > 0.0 && nb > 64.0) sum[3] += c * ceil((nb - 64.0) / 64.0);
         }
     }
-    if (est) {
-        chunks = wave_sum(chunks);
-        if (lane_id() == 0 && chunks > 0.0) atomicAdd(est, (unsigned long long)chunks);
+    if (!tot) return;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const double v = wave_sum(sum[q]);
+        if (lane_id() == 0 && v > 0.0) atomicAdd(tot + q, (unsigned long long)v);
     }
 }
 
@@ -572,15 +584,16 @@ rcb_status ensure_walk(rcb_tree *t, hipStream_t s) {
     // per-group counts, the later tiers' queues and the statistics: one block
     // kept by the tree for its later walks (no frees between the walk's
     // kernels and the next call's)
-    const size_t ws_bytes = sizeof(int64_t) * 2 * NG + sizeof(int32_t) * 2 * NG + 3 * sizeof(unsigned long long) + 64;
+    const size_t ws_bytes = sizeof(int64_t) * 2 * NG + sizeof(int32_t) * 2 * NG + sizeof(uint2) * NG + 4 * sizeof(unsigned long long) + 64;
     if (!t->walk_ws) {
         t->walk_ws = dalloc(t, ws_bytes, s, t->allocs);
         if (!t->walk_ws) return RCB_ENOMEM;
     }
     int64_t *ncnt = (int64_t *)t->walk_ws;
     int64_t *fcnt = ncnt + NG;
-    unsigned long long *stats = (unsigned long long *)(fcnt + NG);
-    int32_t *queue = (int32_t *)(stats + 3);    // groups for the 2nd tier
+    unsigned long long *tot = (unsigned long long *)(fcnt + NG);
+    uint2 *stats = (uint2 *)(tot + 4);
+    int32_t *queue = (int32_t *)(stats + NG);   // groups for the 2nd tier
     int32_t *queue2 = queue + NG;               // and for k_walk_group
     int64_t cn = 0, cf = 0;
     std::vector<void *> slabs;
@@ -612,11 +625,11 @@ rcb_status ensure_walk(rcb_tree *t, hipStream_t s) {
     // q1/q2 null: the queues are known (second pass) and are not appended to
     int64_t nq = 0, nq2 = 0;
     // the flags (errors, list counts, the tiers' queue lengths) and the
-    // statistics, read once after each tier that runs
+    // totals, read once after each tier that runs
     int32_t flags[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    unsigned long long hstats[3] = {0, 0, 0};   // [2]: k_slab_ends' estimate
+    unsigned long long htot[4] = {0, 0, 0, 0};   // k_slab_ends
     auto read_flags = [&]() -> rcb_status {
-        const HostRead r[2] = {{t->dflag, flags, (int)sizeof(flags)}, {stats, hstats, (int)sizeof(hstats)}};
+        const HostRead r[2] = {{t->dflag, flags, (int)sizeof(flags)}, {tot, htot, (int)sizeof(htot)}};
         return read_small(s, r, 2, "rcb_walk");
     };
     // the slab lists' ends per group (in the common case, that no list
@@ -625,9 +638,9 @@ rcb_status ensure_walk(rcb_tree *t, hipStream_t s) {
     int64_t *ends = (int64_t *)dalloc(t, sizeof(int64_t) * 4 * NG, s, t->list_allocs);
     if (!ends) return RCB_ENOMEM;
     const NbEstimate ne{t->nleaf, t->gk, (double)t->n, t->ncount, t->nlo, t->nhi, t->nhnode, t->wrec};
-    auto slab_ends = [&](unsigned long long *est) -> rcb_status {
+    auto slab_ends = [&](unsigned long long *out) -> rcb_status {
         k_slab_ends<<<(unsigned)((NG + kBlock - 1) / kBlock), kBlock, 0, s>>>(NG, cn, cf, ncnt, fcnt, ends, ends + NG,
-                                                                              ends + 2 * NG, ends + 3 * NG, ne, est);
+                                                                              ends + 2 * NG, ends + 3 * NG, ne, stats, out);
         RCB_LAUNCH_CHECK("k_slab_ends");
         return RCB_OK;
     };
@@ -636,8 +649,9 @@ rcb_status ensure_walk(rcb_tree *t, hipStream_t s) {
         if (pure) k_walk_wide<true, kWQueue, kWaves><<<grid, kBlock, 0, s>>>(w, q1, t->dflag + 6, nullptr, 0, cap1);
         else k_walk_wide<false, kWQueue, kWaves><<<grid, kBlock, 0, s>>>(w, q1, t->dflag + 6, nullptr, 0, cap1);
         RCB_LAUNCH_CHECK("k_walk_wide");
+        w.stats = nullptr;   // only the first tier of the first walk counts
         if (count_queues) {
-            rcb_status st = slab_ends(stats + 2);
+            rcb_status st = slab_ends(tot);
             if (st != RCB_OK) return st;
             st = read_flags();
             if (st != RCB_OK) return st;
@@ -662,14 +676,14 @@ rcb_status ensure_walk(rcb_tree *t, hipStream_t s) {
     };
     RCB_ZERO(t->dflag, sizeof(int32_t) * 4, s);
     RCB_ZERO(t->dflag + 6, sizeof(int32_t) * 2, s);
-    RCB_ZERO(stats, sizeof(unsigned long long) * 3, s);
+    RCB_ZERO(tot, sizeof(unsigned long long) * 4, s);
     rcb_status wst = walk_tiers(true);
     if (wst != RCB_OK) return wst;
-    w.stats = nullptr;   // a second walk (exact lists) does not count again
     t->walk_requeued = nq;
-    t->walk_nodes = (int64_t)hstats[0];
-    t->walk_tests = (int64_t)hstats[1];
-    t->nb_est = (int64_t)hstats[2];
+    t->walk_nodes = (int64_t)htot[0];
+    t->walk_tests = (int64_t)htot[1];
+    t->far_entries = (int64_t)htot[2];
+    t->nb_est = (int64_t)htot[3];
     if (flags[0]) {
         set_error("walk: stack overflow (tree deeper than the walk stack supports)");
         return RCB_ECAPACITY;

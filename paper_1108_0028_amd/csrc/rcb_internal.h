@@ -111,6 +111,7 @@ struct rcb_tree {
     int64_t walk_requeued = 0;         // groups of the last walk that outgrew the first ring
     int64_t walk_nodes = -1;           // node records the first walk tier tested (per group)
     int64_t walk_tests = -1;           // (node, visiting leaf) tests of the first tier
+    int64_t far_entries = 0;           // entries of all groups' far lists after the first tier
     // per leaf: the 19 far-field coefficients of the current moments (written
     // by rcb_gravity, or by the VJP if no gravity call has) and 3 VJP scratch values
     double *farc = nullptr;
@@ -306,10 +307,9 @@ __device__ __forceinline__ double quad_perm(double v) {
 __device__ __forceinline__ double swap_adjacent_lanes(double v) { return quad_perm<0xB1>(v); }   // [1,0,3,2]
 __device__ __forceinline__ double swap_lane_pairs(double v) { return quad_perm<0x4E>(v); }       // [2,3,0,1]
 __device__ __forceinline__ uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+// set bits of mask below this lane
 __device__ __forceinline__ int rank_below(uint64_t mask) {
-    const int l = lane_id();
-    uint64_t below = l ? (mask & ((~0ull) >> (64 - l))) : 0ull;
-    return __popcll(below);
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 __device__ __forceinline__ double dist2(double ax, double ay, double az, double bx, double by,
                                         double bz) {
