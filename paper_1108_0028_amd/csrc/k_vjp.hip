@@ -1146,7 +1146,7 @@ rcb_status gravity_vjp(rcb_tree *t, const void *gx, const void *gy, const void *
     else k_vjp_moments<false><<<gridg, kBlock, 0, s>>>(a);
     RCB_LAUNCH_CHECK("k_vjp_moments");
     if (!t->farc_valid) {   // else kept by the last rcb_gravity on these moments
-        st = far_coefficients(t, leafc, kLeafC, s);
+        st = far_coefficients(t, leafc, s);
         if (st != RCB_OK) return st;
         t->farc_valid = true;
     }
