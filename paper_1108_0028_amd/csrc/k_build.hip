@@ -179,21 +179,6 @@ struct PartIn {
     const double *x, *y, *z, *m, *h;
 };
 
-// Sum and max over the LANES lanes of this lane's group (xor butterfly: the
-// canonical pairwise tree across lanes, as for the whole wave).
-template <int LANES>
-__device__ __forceinline__ double group_sum(double v) {
-#pragma unroll
-    for (int o = 1; o < LANES; o <<= 1) v += __shfl_xor(v, o, kWave);
-    return v;
-}
-template <int LANES>
-__device__ __forceinline__ double group_max(double v) {
-#pragma unroll
-    for (int o = 1; o < LANES; o <<= 1) v = fmax(v, __shfl_xor(v, o, kWave));
-    return v;
-}
-
 // LANES = 64: one node per wave (512 elements); LANES = 8: one node per 8-lane
 // group (64 elements). Narrower trees padded with zeros give the same bits.
 // Wave-private LDS staging of one 512-element chunk: elements are loaded
@@ -259,35 +244,32 @@ __device__ __forceinline__ void chunk_sums_regs(const double (&X)[8], const doub
     constexpr int NS = Pay<P>::NS;
     double v[8][NS];
     double ml = -1.0;
+    // (no branches: past the end the mass is zero, and so is every term)
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
-        const int64_t i = p0 + t;
-        if (i < end) {
-            const double xi = X[t], yi = Y[t], zi = Z[t], mi = Mm[t];
-            if constexpr (P == 0) {
-                v[t][0] = mi;
-                v[t][1] = mi * xi;
-                v[t][2] = mi * yi;
-                v[t][3] = mi * zi;
-                ml = fmax(ml, dist2(xi, yi, zi, g[0], g[1], g[2]));
-            } else {
-                const double d0 = xi - c[0], d1 = yi - c[1], d2 = zi - c[2];
-                const double r2 = (d0 * d0 + d1 * d1) + d2 * d2;
-                const double m3 = 3.0 * mi;
-                const double mr2 = mi * r2;
-                v[t][0] = (m3 * d0) * d0 - mr2;
-                v[t][1] = (m3 * d0) * d1;
-                v[t][2] = (m3 * d0) * d2;
-                v[t][3] = (m3 * d1) * d1 - mr2;
-                v[t][4] = (m3 * d1) * d2;
-                v[t][5] = (m3 * d2) * d2 - mr2;
-                const double rg = sqrt(dist2(xi, yi, zi, g[0], g[1], g[2]));
-                ml = fmax(ml, rg + 2.0 * H[t]);
-            }
+        const double xi = X[t], yi = Y[t], zi = Z[t], mi = Mm[t];
+        double far;
+        if constexpr (P == 0) {
+            v[t][0] = mi;
+            v[t][1] = mi * xi;
+            v[t][2] = mi * yi;
+            v[t][3] = mi * zi;
+            far = dist2(xi, yi, zi, g[0], g[1], g[2]);
         } else {
-#pragma unroll
-            for (int s = 0; s < NS; ++s) v[t][s] = 0.0;
+            const double d0 = xi - c[0], d1 = yi - c[1], d2 = zi - c[2];
+            const double r2 = (d0 * d0 + d1 * d1) + d2 * d2;
+            const double m3 = 3.0 * mi;
+            const double mr2 = mi * r2;
+            v[t][0] = (m3 * d0) * d0 - mr2;
+            v[t][1] = (m3 * d0) * d1;
+            v[t][2] = (m3 * d0) * d2;
+            v[t][3] = (m3 * d1) * d1 - mr2;
+            v[t][4] = (m3 * d1) * d2;
+            v[t][5] = (m3 * d2) * d2 - mr2;
+            far = sqrt(dist2(xi, yi, zi, g[0], g[1], g[2])) + 2.0 * H[t];
         }
+        far = fmax(ml, far);
+        ml = p0 + t < end ? far : ml;
     }
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
@@ -1130,26 +1112,45 @@ __global__ void k_outside(int64_t nleaf, const int32_t *__restrict__ nfirst,
 }
 
 // ---------------------------------------------------------------------------
-// Subtrees. A node is "big" while it holds more than kSubMax particles or
-// lies more than kSubDepth levels above the lowest; big nodes go through the
-// device-wide chunk passes above, one level per launch. Every node that is
-// not big but whose parent is (or the root, if it is not big) is a subtree
-// root: one wave finishes its whole subtree down to level k with everything
-// in wave-private LDS -- the particles, and per node its range, box, mass,
-// centre of mass and quadrupole. Each level's canonical sums, split and
-// stable partition run there; node data, each level's particle order and
-// the final particle arrays are written to global memory and never read
-// back, and the quadrupoles are summed upwards (Eq. 2) from LDS. Roots come
-// from a queue filled by the level passes; a persistent grid takes them one
-// at a time, so every wave ends when the queue is empty.
+// Subtrees. A node is "big" while it holds more than SubSize<W>::max particles
+// or lies more than SubSize<W>::depth levels above the lowest; big nodes go
+// through the device-wide chunk passes above, one level per launch. Every node
+// that is not big but whose parent is (or the root, if it is not big) is a
+// subtree root: one workgroup of W waves finishes its whole subtree down to
+// level k with everything in LDS -- the particles, and per node its range, box,
+// mass, centre of mass and quadrupole. Each level's canonical sums, split and
+// stable partition run there, the level's nodes shared out to the waves and a
+// node of more than kChunk particles cut into chunks of a wave each; node data,
+// each level's particle order and the final particle arrays are written to
+// global memory and never read back, and the quadrupoles are summed upwards
+// (Eq. 2) from LDS. Roots come from a queue filled by the level passes; a
+// persistent grid takes them one at a time, so every workgroup ends when the
+// queue is empty.
+//
+// What bounds it is a chain: a level's passes need the level above, and a pass
+// is some 2 us of FP64 sums, LDS gathers and barriers whatever its size. So a
+// subtree is as large as the LDS holds (a device-wide level costs five launches,
+// some 30 us), its waves share a level, the sums go by DPP moves instead of
+// shuffles, loads have no branches, and barriers order the LDS alone.
 // ---------------------------------------------------------------------------
-constexpr int kSubMax = kChunk;                 // particles of a subtree root
-constexpr int kSubDepth = 6;                    // levels below a subtree root
-constexpr int kSubSlots = kSubMax + kSubMax / 8;
-constexpr int kSubNodes = (2 << kSubDepth) - 1; // nodes of a subtree: level d, index j at 2^d - 1 + j
-
-__device__ __forceinline__ bool is_big(int32_t c, int k, int lvl) {
-    return c > 0 && (c > kSubMax || k - lvl > kSubDepth);
+template <int W>   // waves of the workgroup
+struct SubSize {
+    static constexpr int threads = W * kWave;
+    static constexpr int max = W / 2 * kChunk;      // particles of a subtree root
+    static constexpr int depth = W == 8 ? 8 : 7;    // levels below a subtree root
+    static constexpr int slots = max + max / 8;
+    static constexpr int nodes = (2 << depth) - 1;   // level d, index j at 2^d - 1 + j
+    static constexpr int leaves = 1 << depth;
+    // the nodes of a level that hold more than kChunk particles have at most
+    // this many chunks together: a wave each
+    static_assert(max / kChunk + max / (kChunk + 1) <= W, "a wave per chunk");
+};
+// the build's choice of W: what a subtree may hold
+struct SubRule {
+    int max, depth;
+};
+__host__ __device__ __forceinline__ bool is_big(const SubRule &r, int64_t c, int k, int lvl) {
+    return c > 0 && (c > r.max || k - lvl > r.depth);
 }
 
 // One lane per node of the level (a wave per 64 nodes): the children of the
@@ -1160,7 +1161,8 @@ __device__ __forceinline__ bool is_big(int32_t c, int k, int lvl) {
 __global__ __launch_bounds__(kBlock) void k_level_classify(int lvl, int k, NodeOut o, BigCtl bc,
                                                            int32_t *__restrict__ roots,
                                                            int32_t *__restrict__ nroots, int max_big,
-                                                           int max_items, int32_t *__restrict__ flag) {
+                                                           int max_items, int32_t *__restrict__ flag,
+                                                           SubRule sr) {
     const int64_t w = wave_index();
     const int64_t nodes = (int64_t)1 << lvl;
     if (w * kWave >= nodes) return;
@@ -1168,9 +1170,9 @@ __global__ __launch_bounds__(kBlock) void k_level_classify(int lvl, int k, NodeO
     const int64_t j = w * kWave + lane;
     const bool valid = j < nodes;
     const int64_t lab = nodes + (valid ? j : 0);
-    bool consider = valid && (lvl == 0 || is_big(o.ncount[lab >> 1], k, lvl - 1));
+    bool consider = valid && (lvl == 0 || is_big(sr, o.ncount[lab >> 1], k, lvl - 1));
     const int32_t c = consider ? o.ncount[lab] : 0;
-    const bool big = consider && is_big(c, k, lvl);
+    const bool big = consider && is_big(sr, c, k, lvl);
     const bool root = consider && !big;
     const uint64_t br = ballot(root);
     int rbase = 0;
@@ -1214,6 +1216,7 @@ struct ClassifyArgs {
     int32_t *roots, *nroots;
     int max_big, max_items;
     int32_t *flag;
+    SubRule sr;
 };
 
 // w: the wave's index among the nblocks workgroups that classify
@@ -1230,7 +1233,7 @@ __device__ __forceinline__ void classify_children(const ClassifyArgs &ca, const 
     const bool valid = t < 2 * (int64_t)np;
     const int64_t lab = valid ? 2 * (int64_t)bp.big_node[t >> 1] + (t & 1) : 0;
     const int32_t c = valid ? o.ncount[lab] : 0;
-    const bool big = valid && is_big(c, k, lvl);
+    const bool big = valid && is_big(ca.sr, c, k, lvl);
     const bool root = valid && !big;
     const uint64_t br = ballot(root);
     // one atomic per wave and counter: the roots, the big nodes and their
@@ -1307,14 +1310,38 @@ struct SubArgs {
     NodeOut o;
 };
 
+template <int W>
 struct SubLds {
-    double x[kSubSlots], y[kSubSlots], z[kSubSlots], m[kSubSlots];
-    int32_t id[kSubSlots];
+    using S = SubSize<W>;
+    double x[S::slots], y[S::slots], z[S::slots], m[S::slots];
+    int32_t id[S::slots];
     // per node of the subtree (slot 2^d - 1 + j for level l0 + d, label R0 2^d + j)
-    int32_t first[kSubNodes], count[kSubNodes];   // first: subtree-relative
-    double lo[kSubNodes][3], hi[kSubNodes][3];
-    double mass[kSubNodes], com[kSubNodes][3], q[kSubNodes][6];
+    int32_t first[S::nodes], count[S::nodes];   // first: subtree-relative
+    double mass[S::nodes], com[S::nodes][3], q[S::nodes][6];
+    // boxes (lo, hi) of the level's nodes, by level parity
+    double box[2][S::leaves][6];
+    // per wave: its chunk's payload A sums, max, payload B sums and max, and left count
+    double part[W][12];
+    int32_t left[W];
+    int32_t next;   // the next root's queue slot
 };
+
+// Particle e of the subtree, or zeros (no branch: a load under a condition of
+// its own waits for itself, and forty of them in a row held a level's pass for
+// some 10 us).
+template <int W>
+__device__ __forceinline__ void load_slot(const SubLds<W> &sh, bool ok, int e, double &x, double &y, double &z,
+                                          double &m, int32_t &id) {
+    const int sl = stage_slot(ok ? e : 0);
+    const double vx = sh.x[sl], vy = sh.y[sl], vz = sh.z[sl], vm = sh.m[sl];
+    const int32_t vi = sh.id[sl];
+    x = ok ? vx : 0.0;
+    y = ok ? vy : 0.0;
+    z = ok ? vz : 0.0;
+    m = ok ? vm : 0.0;
+    id = ok ? vi : 0;
+}
+constexpr int kNoSlot = 8;   // a padding slot (stage_slot never gives it): stores that go nowhere
 
 // All descendants of the empty node E (level lvl, first particle `first`,
 // box lo/hi) down to level k: empty, with E's box; E's own range and box
@@ -1356,22 +1383,29 @@ __device__ __forceinline__ void fill_empty_subtree(const NodeOut o, int64_t E, i
 // the pass's nodes are read completely before any element moves); the
 // children's ranges and boxes go to their LDS slots.
 // Sum and max over the GW lanes of this lane's group, GW a run-time power
-// of two (the same xor butterfly as group_sum / group_max)
+// of two (as group_sum / group_max)
 __device__ __forceinline__ double gsum(double v, int GW) {
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1)
-        if (o < GW) v += __shfl_xor(v, o, kWave);
+    if (GW > 1) v = pair_sum<1>(v);
+    if (GW > 2) v = pair_sum<2>(v);
+    if (GW > 4) v = pair_sum<4>(v);
+    if (GW > 8) v = pair_sum<8>(v);
+    if (GW > 16) v = pair_sum<16>(v);
+    if (GW > 32) v = pair_sum<32>(v);
     return v;
 }
 __device__ __forceinline__ double gmax(double v, int GW) {
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1)
-        if (o < GW) v = fmax(v, __shfl_xor(v, o, kWave));
+    if (GW > 1) v = pair_max<1>(v);
+    if (GW > 2) v = pair_max<2>(v);
+    if (GW > 4) v = pair_max<4>(v);
+    if (GW > 8) v = pair_max<8>(v);
+    if (GW > 16) v = pair_max<16>(v);
+    if (GW > 32) v = pair_max<32>(v);
     return v;
 }
 
+template <int W>
 __device__ __forceinline__ void sub_pass(const NodeOut o, int k, const double *__restrict__ hin,
-                                         double *__restrict__ ph, SubLds &sh, int64_t R0, int d, int p,
+                                         double *__restrict__ ph, SubLds<W> &sh, int64_t R0, int d, int p,
                                          int lvl, int64_t s0, float *fdx, float *fdy, float *fdz, float *fm,
                                          float *fh, const int GW) {
     const bool leaf = lvl == k;
@@ -1380,15 +1414,16 @@ __device__ __forceinline__ void sub_pass(const NodeOut o, int k, const double *_
     const int nd = 1 << d;
     const int j = p + gslot;
     const int slot = nd - 1 + (j < nd ? j : 0);
-    const int c = j < nd ? sh.count[slot] : 0;
+    const int cj = j < nd ? sh.count[slot] : 0;
+    const int c = cj <= kChunk ? cj : 0;   // (larger ones: sub_big)
     const bool valid = c > 0;
     const int f = sh.first[slot];
     const int64_t lab = (R0 << d) + j;
     double lo[3], hi[3];
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
-        lo[q] = sh.lo[slot][q];
-        hi[q] = sh.hi[slot][q];
+        lo[q] = sh.box[d & 1][j < nd ? j : 0][q];
+        hi[q] = sh.box[d & 1][j < nd ? j : 0][3 + q];
     }
     const double g[3] = {0.5 * (lo[0] + hi[0]), 0.5 * (lo[1] + hi[1]), 0.5 * (lo[2] + hi[2])};
     double X[8], Y[8], Z[8], Mm[8], H[8];
@@ -1397,12 +1432,7 @@ __device__ __forceinline__ void sub_pass(const NodeOut o, int k, const double *_
     for (int t = 0; t < 8; ++t) {
         const int e = 8 * gl + t;
         const bool ok = valid && e < c;
-        const int sl = stage_slot(ok ? f + e : 0);
-        X[t] = ok ? sh.x[sl] : 0.0;
-        Y[t] = ok ? sh.y[sl] : 0.0;
-        Z[t] = ok ? sh.z[sl] : 0.0;
-        Mm[t] = ok ? sh.m[sl] : 0.0;
-        I[t] = ok ? sh.id[sl] : 0;
+        load_slot(sh, ok, f + e, X[t], Y[t], Z[t], Mm[t], I[t]);
     }
     // the leaves' smoothing lengths: gathered first, used after payload A
     // (I is 0 past the node)
@@ -1415,22 +1445,19 @@ __device__ __forceinline__ void sub_pass(const NodeOut o, int k, const double *_
     }
     // payload A: m, m x, m y, m z summed by the canonical tree (8 in the
     // lane, then across the group), and max |r - g|^2 (as chunk_sums_regs<0>)
+    // (no branches: past the node the mass is zero, and so is every term)
     double sa[4], mx;
     {
         double v[8][4];
         double ml = -1.0;
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
-            if (valid && 8 * gl + t < c) {
-                v[t][0] = Mm[t];
-                v[t][1] = Mm[t] * X[t];
-                v[t][2] = Mm[t] * Y[t];
-                v[t][3] = Mm[t] * Z[t];
-                ml = fmax(ml, dist2(X[t], Y[t], Z[t], g[0], g[1], g[2]));
-            } else {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) v[t][q] = 0.0;
-            }
+            v[t][0] = Mm[t];
+            v[t][1] = Mm[t] * X[t];
+            v[t][2] = Mm[t] * Y[t];
+            v[t][3] = Mm[t] * Z[t];
+            const double far = fmax(ml, dist2(X[t], Y[t], Z[t], g[0], g[1], g[2]));
+            ml = valid && 8 * gl + t < c ? far : ml;
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -1461,8 +1488,8 @@ __device__ __forceinline__ void sub_pass(const NodeOut o, int k, const double *_
         double ml = -1.0;
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
-            const bool ok = valid && 8 * gl + t < c;
-            if (ok) ml = fmax(ml, sqrt(dist2(X[t], Y[t], Z[t], g[0], g[1], g[2])) + 2.0 * H[t]);
+            const double far = fmax(ml, sqrt(dist2(X[t], Y[t], Z[t], g[0], g[1], g[2])) + 2.0 * H[t]);
+            ml = valid && 8 * gl + t < c ? far : ml;
         }
 #pragma unroll
         for (int t = 0; t < 8; ++t)
@@ -1473,16 +1500,13 @@ __device__ __forceinline__ void sub_pass(const NodeOut o, int k, const double *_
             double v[8];
 #pragma unroll
             for (int t = 0; t < 8; ++t) {
-                if (valid && 8 * gl + t < c) {
-                    const double d0 = X[t] - com[0], d1 = Y[t] - com[1], d2 = Z[t] - com[2];
-                    const double r2 = (d0 * d0 + d1 * d1) + d2 * d2;
-                    const double m3 = 3.0 * Mm[t];
-                    const double mr2 = Mm[t] * r2;
-                    v[t] = q == 0 ? (m3 * d0) * d0 - mr2 : q == 1 ? (m3 * d0) * d1 : q == 2 ? (m3 * d0) * d2
-                         : q == 3 ? (m3 * d1) * d1 - mr2 : q == 4 ? (m3 * d1) * d2 : (m3 * d2) * d2 - mr2;
-                } else {
-                    v[t] = 0.0;
-                }
+                const double d0 = X[t] - com[0], d1 = Y[t] - com[1], d2 = Z[t] - com[2];
+                const double r2 = (d0 * d0 + d1 * d1) + d2 * d2;
+                const double m3 = 3.0 * Mm[t];
+                const double mr2 = Mm[t] * r2;
+                const double u = q == 0 ? (m3 * d0) * d0 - mr2 : q == 1 ? (m3 * d0) * d1 : q == 2 ? (m3 * d0) * d2
+                               : q == 3 ? (m3 * d1) * d1 - mr2 : q == 4 ? (m3 * d1) * d2 : (m3 * d2) * d2 - mr2;
+                v[t] = valid ? u : 0.0;   // (a lane without a node has no centre of mass)
             }
             const double sq = gsum(((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7])), GW) + 0.0;
             if (lead) {
@@ -1538,20 +1562,18 @@ __device__ __forceinline__ void sub_pass(const NodeOut o, int k, const double *_
     for (int t = 0; t < 8; ++t) {
         const int e = 8 * gl + t;
         const int lbefore = excl + __popc(lb & ((1u << t) - 1u));
-        dst[t] = valid && e < c ? ((lb >> t) & 1u ? f + lbefore : f + nleft + (e - lbefore)) : -1;
+        const int to = (lb >> t) & 1u ? f + lbefore : f + nleft + (e - lbefore);
+        dst[t] = valid && e < c ? stage_slot(to) : kNoSlot;
     }
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
-        if (dst[t] >= 0) {
-            const int sl = stage_slot(dst[t]);
-            sh.x[sl] = X[t];
-            sh.y[sl] = Y[t];
-            sh.z[sl] = Z[t];
-            sh.m[sl] = Mm[t];
-            sh.id[sl] = I[t];
-        }
+        sh.x[dst[t]] = X[t];
+        sh.y[dst[t]] = Y[t];
+        sh.z[dst[t]] = Z[t];
+        sh.m[dst[t]] = Mm[t];
+        sh.id[dst[t]] = I[t];
     }
     if (lead) {
         const int64_t L = 2 * lab, R = 2 * lab + 1;
@@ -1571,75 +1593,241 @@ __device__ __forceinline__ void sub_pass(const NodeOut o, int k, const double *_
             o.nhi[3 * L + q] = lh;
             o.nlo[3 * R + q] = rl;
             o.nhi[3 * R + q] = hi[q];
-            sh.lo[cs][q] = lo[q];
-            sh.hi[cs][q] = lh;
-            sh.lo[cs + 1][q] = rl;
-            sh.hi[cs + 1][q] = hi[q];
+            double(*nb)[6] = sh.box[(d & 1) ^ 1];   // the children's boxes
+            nb[2 * j][q] = lo[q];
+            nb[2 * j][3 + q] = lh;
+            nb[2 * j + 1][q] = rl;
+            nb[2 * j + 1][3 + q] = hi[q];
         }
     }
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
 }
 
-// The next subtree root of a wave, fetched in four stages while the wave
-// builds the current one, so that each stage's memory latency hides under a
-// level of the current build: 0 takes a queue slot, 1 reads its label, 2 the
-// root's range and box, 3 issues the loads of its particles (lane l holds
-// elements l + 64 q), which the wave puts into LDS when it starts the root.
-constexpr int kSubPer = kSubMax / kWave;
-struct SubNext {
-    int rv;          // lane 0: the queue slot from the atomic
-    int r;           // the queue slot (uniform)
-    int64_t R0, s0;
-    int c0;
-    double lo[3], hi[3];
-    double vx[kSubPer], vy[kSubPer], vz[kSubPer], vm[kSubPer];
-    int32_t vi[kSubPer];
-};
+// The nodes of subtree level d that hold more than kChunk particles: a wave
+// per chunk, with the payloads and the partition of sub_pass. The chunks' sums
+// are combined pairwise as k_big_finalize does (at most four: zeros pad them),
+// and a chunk's left count is added to those before it. Every wave of the
+// workgroup takes part in the barriers.
+__device__ __forceinline__ double sum_chunks(const double (*part)[12], int w0, int nch, int q) {
+    double p[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) p[i] = i < nch ? part[w0 + i][q] : 0.0;
+    return (p[0] + p[1]) + (p[2] + p[3]);
+}
 
-__device__ __forceinline__ void next_root_stage(const SubArgs &a, int nq, int stage, SubNext &nx) {
-    const int lane = lane_id();
-    if (stage == 0) {
-        nx.rv = 0;
-        if (lane == 0) nx.rv = atomicAdd(a.qhead, 1);
-    } else if (stage == 1) {
-        nx.r = __builtin_amdgcn_readlane(nx.rv, 0);
-        nx.R0 = nx.r < nq ? a.roots[nx.r] : 1;
-    } else if (stage == 2) {
-        if (nx.r >= nq) return;
-        const int64_t R0 = nx.R0;
-        nx.s0 = a.o.nfirst[R0];
-        nx.c0 = a.o.ncount[R0];
+template <int W>
+__device__ __forceinline__ void sub_big(const NodeOut o, int k, const double *__restrict__ hin,
+                                        double *__restrict__ ph, SubLds<W> &sh, int64_t R0, int d, int lvl,
+                                        int64_t s0, float *fdx, float *fdy, float *fdz, float *fm, float *fh) {
+    const bool leaf = lvl == k;
+    const int lane = lane_id(), nd = 1 << d;
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    int j = -1, ch = 0, nch = 0, w0 = 0, cum = 0;   // this wave's node, chunk, and the node's first wave
+    for (int b = 0; b < nd; b += kWave) {
+        uint64_t bm = ballot(b + lane < nd && sh.count[nd - 1 + (b + lane < nd ? b + lane : 0)] > kChunk);
+        while (bm) {
+            const int jj = b + __ffsll((long long)bm) - 1;
+            bm &= bm - 1;
+            const int n = (sh.count[nd - 1 + jj] + kChunk - 1) / kChunk;
+            if (wv >= cum && wv < cum + n) {
+                j = jj;
+                ch = wv - cum;
+                nch = n;
+                w0 = cum;
+            }
+            cum += n;
+        }
+    }
+    j = __builtin_amdgcn_readfirstlane(j);
+    const bool act = j >= 0;
+    const int slot = nd - 1 + (act ? j : 0);
+    const int c = act ? sh.count[slot] : 0;
+    const int f = sh.first[slot];
+    const int64_t lab = (R0 << d) + j;
+    const int e0 = ch * kChunk + 8 * lane;
+    double lo[3], hi[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        lo[q] = sh.box[d & 1][act ? j : 0][q];
+        hi[q] = sh.box[d & 1][act ? j : 0][3 + q];
+    }
+    const double g[3] = {0.5 * (lo[0] + hi[0]), 0.5 * (lo[1] + hi[1]), 0.5 * (lo[2] + hi[2])};
+    double X[8], Y[8], Z[8], Mm[8], H[8];
+    int32_t I[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        load_slot(sh, e0 + t < c, f + e0 + t, X[t], Y[t], Z[t], Mm[t], I[t]);
+        H[t] = leaf ? hin[I[t]] : 0.0;
+    }
+    const double none[3] = {0.0, 0.0, 0.0};
+    double ps[4], mx;
+    chunk_sums_regs<0>(X, Y, Z, Mm, H, e0, c, g, none, ps, mx);
+    if (lane == 0) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sh.part[wv][q] = ps[q];
+        sh.part[wv][4] = mx;
+    }
+    lds_barrier();
+    double sa[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) sa[q] = sum_chunks(sh.part, w0, nch, q);
+    const double M = sa[0] + 0.0;
+    double com[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) com[q] = (sa[1 + q] + 0.0) / M;
+    const bool lead = act && ch == 0 && lane == 0;
+    if (lead) {
+        for (int w = 1; w < nch; ++w) mx = fmax(mx, sh.part[w0 + w][4]);
+        o.nM[lab] = M;
+        sh.mass[slot] = M;
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
-            nx.lo[q] = a.o.nlo[3 * R0 + q];
-            nx.hi[q] = a.o.nhi[3 * R0 + q];
+            o.ncom[3 * lab + q] = com[q];
+            sh.com[slot][q] = com[q];
         }
-    } else {
-        if (nx.r >= nq || nx.c0 == 0) return;
-        const int l0 = 63 - __clzll((unsigned long long)nx.R0);
-        const bool par = l0 & 1;   // buffers chosen by select, not by a dynamic index
-        const bool top = l0 == 0;
-        const double *ix = top ? a.x0 : (par ? a.bx[1] : a.bx[0]), *iy = top ? a.y0 : (par ? a.by[1] : a.by[0]);
-        const double *iz = top ? a.z0 : (par ? a.bz[1] : a.bz[0]), *im = top ? a.m0 : (par ? a.bm[1] : a.bm[0]);
-        const int32_t *idl = a.lvl_id + (int64_t)l0 * a.n;
+        o.nhint[lab] = sqrt(mx);
+        o.nhnode[lab] = -1.0;
+    }
+    if (leaf) {
+        double pb[6], hm;
+        chunk_sums_regs<1>(X, Y, Z, Mm, H, e0, c, g, com, pb, hm);
+        if (lane == 0) {
 #pragma unroll
-        for (int q = 0; q < kSubPer; ++q) {
-            const int i = lane + kWave * q;
-            const int64_t src = nx.s0 + (i < nx.c0 ? i : 0);
-            nx.vx[q] = ix[src];
-            nx.vy[q] = iy[src];
-            nx.vz[q] = iz[src];
-            nx.vm[q] = im[src];
-            nx.vi[q] = idl[src];
+            for (int q = 0; q < 6; ++q) sh.part[wv][5 + q] = pb[q];
+            sh.part[wv][11] = hm;
+        }
+        lds_barrier();
+        if (lead) {
+            for (int w = 1; w < nch; ++w) hm = fmax(hm, sh.part[w0 + w][11]);
+#pragma unroll
+            for (int q = 0; q < 6; ++q) {
+                const double sq = sum_chunks(sh.part, w0, nch, 5 + q) + 0.0;
+                o.nQ[6 * lab + q] = sq;
+                sh.q[slot][q] = sq;
+            }
+            o.nhnode[lab] = hm;
+        }
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            if (e0 + t < c) {
+                const int64_t i = s0 + f + e0 + t;
+                ph[i] = H[t];
+                if (fdx) {
+                    fdx[i] = (float)(X[t] - com[0]);
+                    fdy[i] = (float)(Y[t] - com[1]);
+                    fdz[i] = (float)(Z[t] - com[2]);
+                    fm[i] = (float)Mm[t];
+                    fh[i] = (float)H[t];
+                }
+            }
+        }
+        return;
+    }
+    int ax = 0;
+    double best = hi[0] - lo[0];
+    if (hi[1] - lo[1] > best) {
+        best = hi[1] - lo[1];
+        ax = 1;
+    }
+    if (hi[2] - lo[2] > best) ax = 2;
+    const double plane = ax == 0 ? com[0] : (ax == 1 ? com[1] : com[2]);
+    uint32_t lb = 0;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        const double xv = ax == 0 ? X[t] : (ax == 1 ? Y[t] : Z[t]);
+        if (e0 + t < c && xv < plane) lb |= 1u << t;
+    }
+    const int nl = __popc(lb);
+    int before = wave_excl_scan(nl);
+    if (lane == kWave - 1) sh.left[wv] = before + nl;
+    lds_barrier();
+    int nleft = 0;
+    for (int w = 0; w < nch; ++w) {
+        const int n = sh.left[w0 + w];
+        nleft += n;
+        if (w < ch) before += n;
+    }
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        const int lbefore = before + __popc(lb & ((1u << t) - 1u));
+        const int to = (lb >> t) & 1u ? f + lbefore : f + nleft + (e0 + t - lbefore);
+        const int sl = e0 + t < c ? stage_slot(to) : kNoSlot;
+        sh.x[sl] = X[t];
+        sh.y[sl] = Y[t];
+        sh.z[sl] = Z[t];
+        sh.m[sl] = Mm[t];
+        sh.id[sl] = I[t];
+    }
+    if (lead) {
+        const int64_t L = 2 * lab, R = 2 * lab + 1;
+        const int cs = 2 * nd - 1 + 2 * j;   // the children's slots
+        double(*nb)[6] = sh.box[(d & 1) ^ 1];
+        o.nfirst[L] = (int32_t)(s0 + f);
+        o.ncount[L] = nleft;
+        o.nfirst[R] = (int32_t)(s0 + f + nleft);
+        o.ncount[R] = c - nleft;
+        sh.first[cs] = f;
+        sh.count[cs] = nleft;
+        sh.first[cs + 1] = f + nleft;
+        sh.count[cs + 1] = c - nleft;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            const double lh = q == ax ? plane : hi[q], rl = q == ax ? plane : lo[q];
+            o.nlo[3 * L + q] = lo[q];
+            o.nhi[3 * L + q] = lh;
+            o.nlo[3 * R + q] = rl;
+            o.nhi[3 * R + q] = hi[q];
+            nb[2 * j][q] = lo[q];
+            nb[2 * j][3 + q] = lh;
+            nb[2 * j + 1][q] = rl;
+            nb[2 * j + 1][3 + q] = hi[q];
         }
     }
 }
 
-__global__ __launch_bounds__(kWave) void k_subtree(SubArgs a, float *fdx, float *fdy, float *fdz, float *fm,
-                                                      float *fh) {
-    __shared__ SubLds sh;
+// The next subtree root of a workgroup, fetched in four stages while it builds
+// the current one, so that each stage's memory latency hides under a
+// level of the current build: 0 takes a queue slot, 1 hands it to the other
+// waves (read in stage 2, a barrier later), 2 reads its label, 3 the root's
+// range and, in the first six threads, its box. The first roots are the
+// workgroups' numbers; a grid that covers the queue fetches no others.
+constexpr int kSubStages = 4;
+struct SubNext {
+    int rv;          // thread 0: the queue slot from the atomic
+    int r;           // the queue slot (uniform)
+    int64_t R0, s0;
+    int c0;
+    double box;      // thread t < 6: lo, hi
+};
+
+template <int W>
+__device__ __forceinline__ void next_root_stage(const SubArgs &a, int nq, int stage, SubNext &nx, SubLds<W> &sh) {
+    if (stage == 0) {
+        nx.rv = nq;
+        if (threadIdx.x == 0 && nq > (int)gridDim.x) nx.rv = (int)gridDim.x + atomicAdd(a.qhead, 1);
+    } else if (stage == 1) {
+        if (threadIdx.x == 0) sh.next = nx.rv;
+    } else if (stage == 2) {
+        nx.r = __builtin_amdgcn_readfirstlane(sh.next);
+        nx.R0 = nx.r < nq ? a.roots[nx.r] : 1;
+    } else {
+        if (nx.r >= nq) return;
+        const int64_t R0 = nx.R0;
+        nx.s0 = a.o.nfirst[R0];
+        nx.c0 = a.o.ncount[R0];
+        const int q = threadIdx.x % 3;
+        nx.box = (threadIdx.x < 3 ? a.o.nlo : a.o.nhi)[3 * R0 + q];
+    }
+}
+
+template <int W>
+__global__ __launch_bounds__(SubSize<W>::threads, 2) void k_subtree(SubArgs a, float *fdx, float *fdy, float *fdz,
+                                                                 float *fm, float *fh) {
+    constexpr int kThreads = SubSize<W>::threads;
+    __shared__ SubLds<W> sh;
     const int lane = lane_id();
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     const NodeOut o = a.o;
     const int k = a.k;
     const double *__restrict__ hin = a.h;
@@ -1649,93 +1837,114 @@ __global__ __launch_bounds__(kWave) void k_subtree(SubArgs a, float *fdx, float 
     double *oz = kp ? a.bz[1] : a.bz[0], *om = kp ? a.bm[1] : a.bm[0];
     const int nq = a.qctl[0];
     SubNext nx;
-    for (int st = 0; st < 4; ++st) next_root_stage(a, nq, st, nx);   // the first root
-    for (;;) {
+    nx.r = blockIdx.x;   // the first root
+    nx.R0 = nx.r < nq ? a.roots[nx.r] : 1;
+    next_root_stage(a, nq, 3, nx, sh);
+    for (;;) {   // (the same number of barriers for every wave)
         if (nx.r >= nq) break;
         const int64_t R0 = nx.R0;
         const int l0 = 63 - __clzll((unsigned long long)R0);
         const int64_t s0 = nx.s0;
         const int c0 = nx.c0;
-        double rlo[3], rhi[3];
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            rlo[q] = nx.lo[q];
-            rhi[q] = nx.hi[q];
-        }
+        // (opaque to the compiler: the addresses made from it are not kept
+        // in registers from root to root, which spilled them)
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        if (tid < 6) sh.box[0][0][tid] = nx.box;
         if (c0 == 0) {   // an empty root (at any depth): its whole subtree
-            fill_empty_subtree(o, R0, l0, k, (int32_t)s0, rlo, rhi);
-            for (int st = 0; st < 4; ++st) next_root_stage(a, nq, st, nx);
+            lds_barrier();
+            if (wv == 0) {
+                double rlo[3], rhi[3];
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    rlo[q] = sh.box[0][0][q];
+                    rhi[q] = sh.box[0][0][3 + q];
+                }
+                fill_empty_subtree(o, R0, l0, k, (int32_t)s0, rlo, rhi);
+            }
+            for (int st = 0; st < kSubStages; ++st) {
+                next_root_stage(a, nq, st, nx, sh);
+                lds_barrier();
+            }
             continue;
         }
+        {   // the root's particles (buffers chosen by select, not by a dynamic index)
+            const bool par = l0 & 1, top = l0 == 0;
+            const double *ix = top ? a.x0 : (par ? a.bx[1] : a.bx[0]), *iy = top ? a.y0 : (par ? a.by[1] : a.by[0]);
+            const double *iz = top ? a.z0 : (par ? a.bz[1] : a.bz[0]), *im = top ? a.m0 : (par ? a.bm[1] : a.bm[0]);
+            const int32_t *idl = a.lvl_id + (int64_t)l0 * a.n;
 #pragma unroll
-        for (int q = 0; q < kSubPer; ++q) {   // the root's particles, loaded while the last root was built
-            const int i = lane + kWave * q;
-            if (i < c0) {
-                const int sl = stage_slot(i);
-                sh.x[sl] = nx.vx[q];
-                sh.y[sl] = nx.vy[q];
-                sh.z[sl] = nx.vz[q];
-                sh.m[sl] = nx.vm[q];
-                sh.id[sl] = nx.vi[q];
+            for (int q = 0; q < SubSize<W>::max / kThreads; ++q) {
+                const int i = tid + kThreads * q;
+                if (i < c0) {
+                    const int sl = stage_slot(i);
+                    sh.x[sl] = ix[s0 + i];
+                    sh.y[sl] = iy[s0 + i];
+                    sh.z[sl] = iz[s0 + i];
+                    sh.m[sl] = im[s0 + i];
+                    sh.id[sl] = idl[s0 + i];
+                }
             }
         }
         int nst = 0;   // the next root's fetch: one stage now, one after each level's passes
-        next_root_stage(a, nq, nst++, nx);
-        if (lane == 0) {
+        next_root_stage(a, nq, nst++, nx, sh);
+        if (tid == 0) {
             sh.first[0] = 0;
             sh.count[0] = c0;
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                sh.lo[0][q] = rlo[q];
-                sh.hi[0][q] = rhi[q];
-            }
         }
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        lds_barrier();
         const int D = k - l0;
         for (int d = 0; d <= D; ++d) {
             const int lvl = l0 + d, nd = 1 << d;
             // empty nodes of this level (their parent sent every element to
             // the other side): their subtrees are filled; nodes below them
             // carry count -1 and are skipped from here on
-            const int cl = lane < nd ? sh.count[nd - 1 + lane] : 1;
-            uint64_t emp = ballot(d > 0 && cl == 0);
-            while (emp) {
-                const int j = __ffsll((long long)emp) - 1;
-                emp &= emp - 1;
-                const int sl = nd - 1 + j;
-                double clo[3], chi[3];
+            for (int b = kWave * wv; d > 0 && b < nd; b += kThreads) {
+                const int jl = b + lane;
+                uint64_t emp = ballot(jl < nd && sh.count[nd - 1 + (jl < nd ? jl : 0)] == 0);
+                while (emp) {
+                    const int j = b + __ffsll((long long)emp) - 1;
+                    emp &= emp - 1;
+                    double clo[3], chi[3];
 #pragma unroll
-                for (int q = 0; q < 3; ++q) {
-                    clo[q] = sh.lo[sl][q];
-                    chi[q] = sh.hi[sl][q];
+                    for (int q = 0; q < 3; ++q) {
+                        clo[q] = sh.box[d & 1][j][q];
+                        chi[q] = sh.box[d & 1][j][3 + q];
+                    }
+                    fill_empty_subtree(o, (R0 << d) + j, lvl, k, (int32_t)(s0 + sh.first[nd - 1 + j]), clo, chi);
                 }
-                fill_empty_subtree(o, (R0 << d) + j, lvl, k, (int32_t)(s0 + sh.first[sl]), clo, chi);
             }
             int cm = 0;
             for (int j = lane; j < nd; j += kWave) cm = max(cm, sh.count[nd - 1 + j]);
 #pragma unroll
             for (int off = 1; off < kWave; off <<= 1) cm = max(cm, __shfl_xor(cm, off, kWave));
+            cm = __builtin_amdgcn_readfirstlane(cm);
             const int gw = cm <= 8 ? 1 : cm <= 16 ? 2 : cm <= 32 ? 4 : cm <= 64 ? 8 : cm <= 128 ? 16
                          : cm <= 256 ? 32 : 64;
             const int npg = kWave / gw;
             float *f0 = lvl == k ? fdx : nullptr;
-            if (lvl < k) {   // the next level's slots: -1 unless a non-empty parent sets them
-                for (int i = lane; i < 2 * nd; i += kWave) sh.count[2 * nd - 1 + i] = -1;
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            }
-            for (int p = 0; p < nd; p += npg)
+            if (lvl < k)   // the next level's slots: -1 unless a non-empty parent sets them
+                for (int i = tid; i < 2 * nd; i += kThreads) sh.count[2 * nd - 1 + i] = -1;
+            lds_barrier();
+            if (cm > kChunk)
+                sub_big(o, k, hin, ph, sh, R0, d, lvl, s0, f0, fdy, fdz, fm, fh);
+            for (int p = wv * npg; p < nd; p += W * npg)
                 sub_pass(o, k, hin, ph, sh, R0, d, p, lvl, s0, f0, fdy, fdz, fm, fh, gw);
-            if (nst < 4) next_root_stage(a, nq, nst++, nx);
+            if (nst < kSubStages) next_root_stage(a, nq, nst++, nx, sh);
+            lds_barrier();
             if (lvl == k) break;
             // this level's partition is complete: the next level's order
-            for (int i = lane; i < c0; i += kWave)
+            // (the next passes move ids only after another barrier)
+            asm volatile("" : "+v"(tid));
+            for (int i = tid; i < c0; i += kThreads)
                 a.lvl_id[(int64_t)(lvl + 1) * a.n + s0 + i] = sh.id[stage_slot(i)];
         }
-        while (nst < 4) next_root_stage(a, nq, nst++, nx);
+        while (nst < kSubStages) {
+            next_root_stage(a, nq, nst++, nx, sh);
+            lds_barrier();
+        }
         // final particle arrays (level k order)
-        for (int i = lane; i < c0; i += kWave) {
+        for (int i = tid; i < c0; i += kThreads) {
             const int sl = stage_slot(i);
             ox[s0 + i] = sh.x[sl];
             oy[s0 + i] = sh.y[sl];
@@ -1745,7 +1954,7 @@ __global__ __launch_bounds__(kWave) void k_subtree(SubArgs a, float *fdx, float 
         // Eq. 2 upwards through the subtree's internal levels, from LDS
         for (int d = D - 1; d >= 0; --d) {
             const int nd = 1 << d;
-            for (int j = lane; j < nd; j += kWave) {
+            for (int j = tid; j < nd; j += kThreads) {
                 const int sl = nd - 1 + j;
                 if (sh.count[sl] <= 0) continue;   // Q = 0, written with the empty subtree
                 double acc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
@@ -1772,21 +1981,19 @@ __global__ __launch_bounds__(kWave) void k_subtree(SubArgs a, float *fdx, float 
                     o.nQ[6 * lab + q6] = acc[q6];
                 }
             }
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            lds_barrier();
         }
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        lds_barrier();   // the next root overwrites the particles
     }
 }
 
-// Eq. 2 for the big nodes of one level (the others are done by their subtree's wave)
-__global__ void k_upward_big(int lvl, int k, NodeOut o) {
+// Eq. 2 for the big nodes of one level (the others are done by their subtree's workgroup)
+__global__ void k_upward_big(int lvl, int k, NodeOut o, SubRule sr) {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     const int64_t nodes = (int64_t)1 << lvl;
     if (i >= nodes) return;
     const int64_t lab = nodes + i;
-    if (!is_big(o.ncount[lab], k, lvl)) return;
+    if (!is_big(sr, o.ncount[lab], k, lvl)) return;
     const double pc[3] = {o.ncom[3 * lab], o.ncom[3 * lab + 1], o.ncom[3 * lab + 2]};
     double acc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     for (int ch = 0; ch < 2; ++ch) {
@@ -1810,12 +2017,12 @@ __global__ void k_upward_big(int lvl, int k, NodeOut o) {
 // k_upward_big for the levels top .. 0 in one launch: one workgroup, the
 // levels in turn (a level reads only the one below it, written before the
 // barrier by this workgroup)
-__global__ __launch_bounds__(1024) void k_upward_levels(int top, int k, NodeOut o) {
+__global__ __launch_bounds__(1024) void k_upward_levels(int top, int k, NodeOut o, SubRule sr) {
     for (int lvl = top; lvl >= 0; --lvl) {
         const int64_t nodes = (int64_t)1 << lvl;
         for (int64_t i = threadIdx.x; i < nodes; i += blockDim.x) {
             const int64_t lab = nodes + i;
-            if (!is_big(o.ncount[lab], k, lvl)) continue;
+            if (!is_big(sr, o.ncount[lab], k, lvl)) continue;
             const double pc[3] = {o.ncom[3 * lab], o.ncom[3 * lab + 1], o.ncom[3 * lab + 2]};
             double acc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
             for (int ch = 0; ch < 2; ++ch) {
@@ -2152,11 +2359,6 @@ static rcb_status big_chain(rcb_tree *t, BuildScratch &b, const NodeOut &o, cons
 // failed, ends the wait with an error.
 static thread_local int32_t g_level_seq = 0;
 
-
-static inline bool is_big_host(int64_t c, int k, int lvl) {
-    return c > 0 && (c > kSubMax || k - lvl > kSubDepth);
-}
-
 static rcb_status finish_build(rcb_tree *t, BuildScratch &b, const NodeOut &o, Scratch &tmp, int cur,
                                hipStream_t s);
 
@@ -2170,6 +2372,17 @@ static rcb_status alloc_mixed(rcb_tree *t, hipStream_t s) {
     t->fh = (float *)dalloc(t, bytes, s, t->allocs);
     if (!t->fdx || !t->fdy || !t->fdz || !t->fm || !t->fh) return RCB_ENOMEM;
     return RCB_OK;
+}
+
+// Subtrees by eight waves while half the chip's compute units hold them all at
+// once, else by four, two workgroups per compute unit, which hide each other's
+// barriers. Build of uniform and clustered clouds, eight / four waves: 2k
+// particles 123 / 143 us, 4k 180 / 183, 37k 310 / 307, 300k 481 / 486, 1M
+// 764 / 759, 4M 2311 / 2257, 16M 9843 / 9642 (one wave and 512 particles per
+// subtree: 214, 224, 367, 523, 787, 2296, 9858).
+static SubRule sub_rule(int64_t n) {
+    if (n <= (1 << 18)) return SubRule{SubSize<8>::max, SubSize<8>::depth};
+    return SubRule{SubSize<4>::max, SubSize<4>::depth};
 }
 
 rcb_status build_tree(rcb_tree *t, const double *x, const double *y, const double *z,
@@ -2201,8 +2414,9 @@ rcb_status build_tree(rcb_tree *t, const double *x, const double *y, const doubl
         b.m[i] = (double *)A(sizeof(double) * n, tmp);
     }
     // big nodes of one level: those of more than kChunk particles, and (fused
-    // build) every non-empty node more than kSubDepth levels above the lowest
-    const int64_t depth_big = t->k > kSubDepth ? (int64_t)1 << (t->k - kSubDepth - 1) : 0;
+    // build) every non-empty node more than sr.depth levels above the lowest
+    const SubRule sr = sub_rule(t->n);
+    const int64_t depth_big = t->k > sr.depth ? (int64_t)1 << (t->k - sr.depth - 1) : 0;
     b.max_big = std::min<int64_t>(t->nleaf, std::max<int64_t>(n / (kChunk + 1) + 1, depth_big));
     b.max_items = n / kChunk + b.max_big + 1;
     b.ctl = (int32_t *)A(sizeof(int32_t) * 4, tmp);
@@ -2238,7 +2452,7 @@ rcb_status build_tree(rcb_tree *t, const double *x, const double *y, const doubl
     // levels whose nodes exceed kSelSmall (at most n / kSelSmall nodes)
     const bool median = t->p.split == RCB_SPLIT_MEDIAN;
     // splits through a centre (mass or number): big nodes level by level,
-    // then every subtree of at most kSubMax particles by one wave; level 0
+    // then every subtree of at most sr.max particles by one workgroup; level 0
     // reads the caller's arrays, whose order is the identity
     const bool fused = !median && getenv("RCB_BUILD_LEVELS") == nullptr;
     // control words cleared by k_bounds_final: the roots queue (2), and the
@@ -2306,9 +2520,9 @@ rcb_status build_tree(rcb_tree *t, const double *x, const double *y, const doubl
         // level's lists are read by its passes while the next level's are made
         const BigCtl bcs[2] = {BigCtl{clr + 2, b.big_node, b.big_base, b.item_big}, BigCtl{clr + 6, bn2, bb2, ib2}};
         k_level_classify<<<1, kBlock, 0, s>>>(0, t->k, o, bcs[0], roots, qctl, (int)b.max_big, (int)b.max_items,
-                                              t->dflag + 5);
+                                              t->dflag + 5, sr);
         RCB_LAUNCH_CHECK("k_level_classify");
-        int64_t nbig = is_big_host((int64_t)n, t->k, 0) ? 1 : 0;
+        int64_t nbig = is_big(sr, n, t->k, 0) ? 1 : 0;
         int64_t nitems = nbig ? (n + kChunk - 1) / kChunk : 0;
         int64_t maxnch = nitems;   // chunks of the level's largest big node
         int cur = 0, last_big = -1;
@@ -2344,7 +2558,7 @@ rcb_status build_tree(rcb_tree *t, const double *x, const double *y, const doubl
             RCB_LAUNCH_CHECK("k_part_scan");
             const int ncls = (int)blocks_for_waves((2 * nb + kWave - 1) / kWave);
             const ClassifyArgs ca{lvl + 1, t->k, bl, (int)nb, bnx, roots, qctl, (int)b.max_big, (int)b.max_items,
-                                  t->dflag + 5};
+                                  t->dflag + 5, sr};
             k_scatter_classify<<<ncls + gi, kBlock, 0, s>>>(in, id_cur, out, o, bl, b.part_left, ncls, ca);
             RCB_LAUNCH_CHECK("k_scatter_classify");
             return RCB_OK;
@@ -2417,19 +2631,26 @@ rcb_status build_tree(rcb_tree *t, const double *x, const double *y, const doubl
                 RCB_LAUNCH_CHECK("k_mixed_big");
             }
         }
-        const unsigned gsub = (unsigned)std::min<int64_t>(2048, t->nleaf);
-        k_subtree<<<gsub, kWave, 0, s>>>(sa, t->fdx, t->fdy, t->fdz, t->fm, t->fh);
+        // as many workgroups as their LDS leaves room for on the chip
+        auto subtree = [&](auto w) {
+            constexpr int W = decltype(w)::value;
+            const int64_t per_cu = std::max<int64_t>(1, (160 << 10) / (int64_t)sizeof(SubLds<W>));
+            const unsigned g = (unsigned)std::min<int64_t>(256 * per_cu, t->nleaf);
+            k_subtree<W><<<g, SubSize<W>::threads, 0, s>>>(sa, t->fdx, t->fdy, t->fdz, t->fm, t->fh);
+        };
+        if (sr.max == SubSize<8>::max) subtree(std::integral_constant<int, 8>{});
+        else subtree(std::integral_constant<int, 4>{});
         RCB_LAUNCH_CHECK("k_subtree");
         // Eq. 2 for the big nodes: the wide levels one launch each, the
         // levels of at most kUpwardOne nodes in one workgroup
         int lvl = std::min(last_big, t->k - 1);
         for (; lvl >= 0 && ((int64_t)1 << lvl) > kUpwardOne; --lvl) {
             const int64_t nodes = (int64_t)1 << lvl;
-            k_upward_big<<<(unsigned)((nodes + 255) / 256), 256, 0, s>>>(lvl, t->k, o);
+            k_upward_big<<<(unsigned)((nodes + 255) / 256), 256, 0, s>>>(lvl, t->k, o, sr);
             RCB_LAUNCH_CHECK("k_upward_big");
         }
         if (lvl >= 0) {
-            k_upward_levels<<<1, 1024, 0, s>>>(lvl, t->k, o);
+            k_upward_levels<<<1, 1024, 0, s>>>(lvl, t->k, o, sr);
             RCB_LAUNCH_CHECK("k_upward_levels");
         }
         return finish_build(t, b, o, tmp, cur, s);

@@ -237,18 +237,74 @@ __device__ __forceinline__ int64_t xcd_wave_index() {
     return (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)w);
 }
 
-// Canonical sum of the 64 lane values: adjacent lanes first, then pairs of
-// pairs (xor butterfly; both partners of a pair get the same, commutative sum).
-__device__ __forceinline__ double wave_sum(double v) {
+// Exchanges of a butterfly whose step o pairs aligned groups of o lanes that
+// hold one value each (true after the steps 1 .. o/2): any lane of the partner
+// group will do. Steps 1 and 2 are quad permutations, 4 and 8 the mirrors of
+// half a row and a row (DPP moves); 16 and 32 swap rows and halves between two
+// copies, which leaves the lower group's value in one and the higher's in the
+// other. No LDS path, unlike shuffles.
+template <int O>
+__device__ __forceinline__ void pair_values(double v, double &lo, double &hi) {
+    union {
+        double d;
+        uint32_t w[2];
+    } u, x, y;
+    u.d = v;
+    if constexpr (O <= 8) {
+        constexpr int ctl = O == 1 ? 0xB1 : O == 2 ? 0x4E : O == 4 ? 0x141 : 0x140;
+        x.d = v;
 #pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) v += __shfl_xor(v, o, kWave);
+        for (int i = 0; i < 2; ++i) y.w[i] = (uint32_t)__builtin_amdgcn_mov_dpp((int)u.w[i], ctl, 0xF, 0xF, false);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const auto r = O == 16 ? __builtin_amdgcn_permlane16_swap(u.w[i], u.w[i], false, false)
+                                   : __builtin_amdgcn_permlane32_swap(u.w[i], u.w[i], false, false);
+            x.w[i] = r[0];
+            y.w[i] = r[1];
+        }
+    }
+    lo = x.d;
+    hi = y.d;
+}
+template <int O>
+__device__ __forceinline__ double pair_sum(double v) {
+    double a, b;
+    pair_values<O>(v, a, b);
+    return a + b;
+}
+template <int O>
+__device__ __forceinline__ double pair_max(double v) {
+    double a, b;
+    pair_values<O>(v, a, b);
+    return fmax(a, b);
+}
+
+// Canonical sum of the values of LANES adjacent lanes (a power of two, aligned):
+// adjacent lanes first, then pairs of pairs; every lane gets the same,
+// commutative sum.
+template <int LANES>
+__device__ __forceinline__ double group_sum(double v) {
+    if constexpr (LANES > 1) v = pair_sum<1>(v);
+    if constexpr (LANES > 2) v = pair_sum<2>(v);
+    if constexpr (LANES > 4) v = pair_sum<4>(v);
+    if constexpr (LANES > 8) v = pair_sum<8>(v);
+    if constexpr (LANES > 16) v = pair_sum<16>(v);
+    if constexpr (LANES > 32) v = pair_sum<32>(v);
     return v;
 }
-__device__ __forceinline__ double wave_max(double v) {
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) v = fmax(v, __shfl_xor(v, o, kWave));
+template <int LANES>
+__device__ __forceinline__ double group_max(double v) {
+    if constexpr (LANES > 1) v = pair_max<1>(v);
+    if constexpr (LANES > 2) v = pair_max<2>(v);
+    if constexpr (LANES > 4) v = pair_max<4>(v);
+    if constexpr (LANES > 8) v = pair_max<8>(v);
+    if constexpr (LANES > 16) v = pair_max<16>(v);
+    if constexpr (LANES > 32) v = pair_max<32>(v);
     return v;
 }
+__device__ __forceinline__ double wave_sum(double v) { return group_sum<kWave>(v); }
+__device__ __forceinline__ double wave_max(double v) { return group_max<kWave>(v); }
 __device__ __forceinline__ float wave_sumf(float v) {
 #pragma unroll
     for (int o = 1; o < kWave; o <<= 1) v += __shfl_xor(v, o, kWave);
@@ -306,6 +362,13 @@ __device__ __forceinline__ double quad_perm(double v) {
 }
 __device__ __forceinline__ double swap_adjacent_lanes(double v) { return quad_perm<0xB1>(v); }   // [1,0,3,2]
 __device__ __forceinline__ double swap_lane_pairs(double v) { return quad_perm<0x4E>(v); }       // [2,3,0,1]
+// Barrier of a workgroup that orders its LDS accesses only: stores to global
+// memory stay in flight (a __syncthreads waits for them).
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
 __device__ __forceinline__ uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 // set bits of mask below this lane
 __device__ __forceinline__ int rank_below(uint64_t mask) {
