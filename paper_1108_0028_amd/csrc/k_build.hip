@@ -1052,9 +1052,8 @@ __global__ void k_mixed_prep(int64_t nleaf, const int32_t *__restrict__ nfirst,
                              const int32_t *__restrict__ ncount, const double *__restrict__ ncom,
                              const double *__restrict__ px, const double *__restrict__ py,
                              const double *__restrict__ pz, const double *__restrict__ pm,
-                             const double *__restrict__ ph, float *__restrict__ fdx,
-                             float *__restrict__ fdy, float *__restrict__ fdz,
-                             float *__restrict__ fm, float *__restrict__ fh) {
+                             const double *__restrict__ ph, float4 *__restrict__ fd,
+                             float *__restrict__ fh) {
     const int64_t w = wave_index();
     const int64_t L0 = 8 * w;
     if (L0 >= nleaf) return;
@@ -1069,10 +1068,8 @@ __global__ void k_mixed_prep(int64_t nleaf, const int32_t *__restrict__ nfirst,
 #pragma unroll
         for (int q = 1; q < 8; ++q) j += f[q] <= i;
         const int64_t lab = nleaf + L0 + j;
-        fdx[i] = (float)(px[i] - ncom[3 * lab]);
-        fdy[i] = (float)(py[i] - ncom[3 * lab + 1]);
-        fdz[i] = (float)(pz[i] - ncom[3 * lab + 2]);
-        fm[i] = (float)pm[i];
+        fd[i] = make_float4((float)(px[i] - ncom[3 * lab]), (float)(py[i] - ncom[3 * lab + 1]),
+                            (float)(pz[i] - ncom[3 * lab + 2]), (float)pm[i]);
         fh[i] = (float)ph[i];
     }
 }
@@ -1406,8 +1403,7 @@ __device__ __forceinline__ double gmax(double v, int GW) {
 template <int W>
 __device__ __forceinline__ void sub_pass(const NodeOut o, int k, const double *__restrict__ hin,
                                          double *__restrict__ ph, SubLds<W> &sh, int64_t R0, int d, int p,
-                                         int lvl, int64_t s0, float *fdx, float *fdy, float *fdz, float *fm,
-                                         float *fh, const int GW) {
+                                         int lvl, int64_t s0, float4 *fd, float *fh, const int GW) {
     const bool leaf = lvl == k;
     const int lane = lane_id();
     const int gslot = lane / GW, gl = lane % GW;
@@ -1515,16 +1511,14 @@ __device__ __forceinline__ void sub_pass(const NodeOut o, int k, const double *_
             }
         }
         if (lead) o.nhnode[lab] = hn;
-        if (fdx) {   // mixed form: FP32 offsets from the leaf's centre of mass
+        if (fd) {   // mixed form: FP32 offsets from the leaf's centre of mass
 #pragma unroll
             for (int t = 0; t < 8; ++t) {
                 const int e = 8 * gl + t;
                 if (valid && e < c) {
                     const int64_t i = s0 + f + e;
-                    fdx[i] = (float)(X[t] - com[0]);
-                    fdy[i] = (float)(Y[t] - com[1]);
-                    fdz[i] = (float)(Z[t] - com[2]);
-                    fm[i] = (float)Mm[t];
+                    fd[i] = make_float4((float)(X[t] - com[0]), (float)(Y[t] - com[1]), (float)(Z[t] - com[2]),
+                                        (float)Mm[t]);
                     fh[i] = (float)H[t];
                 }
             }
@@ -1619,7 +1613,7 @@ __device__ __forceinline__ double sum_chunks(const double (*part)[12], int w0, i
 template <int W>
 __device__ __forceinline__ void sub_big(const NodeOut o, int k, const double *__restrict__ hin,
                                         double *__restrict__ ph, SubLds<W> &sh, int64_t R0, int d, int lvl,
-                                        int64_t s0, float *fdx, float *fdy, float *fdz, float *fm, float *fh) {
+                                        int64_t s0, float4 *fd, float *fh) {
     const bool leaf = lvl == k;
     const int lane = lane_id(), nd = 1 << d;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
@@ -1713,11 +1707,9 @@ __device__ __forceinline__ void sub_big(const NodeOut o, int k, const double *__
             if (e0 + t < c) {
                 const int64_t i = s0 + f + e0 + t;
                 ph[i] = H[t];
-                if (fdx) {
-                    fdx[i] = (float)(X[t] - com[0]);
-                    fdy[i] = (float)(Y[t] - com[1]);
-                    fdz[i] = (float)(Z[t] - com[2]);
-                    fm[i] = (float)Mm[t];
+                if (fd) {
+                    fd[i] = make_float4((float)(X[t] - com[0]), (float)(Y[t] - com[1]), (float)(Z[t] - com[2]),
+                                        (float)Mm[t]);
                     fh[i] = (float)H[t];
                 }
             }
@@ -1822,8 +1814,7 @@ __device__ __forceinline__ void next_root_stage(const SubArgs &a, int nq, int st
 }
 
 template <int W>
-__global__ __launch_bounds__(SubSize<W>::threads, 2) void k_subtree(SubArgs a, float *fdx, float *fdy, float *fdz,
-                                                                 float *fm, float *fh) {
+__global__ __launch_bounds__(SubSize<W>::threads, 2) void k_subtree(SubArgs a, float4 *fd, float *fh) {
     constexpr int kThreads = SubSize<W>::threads;
     __shared__ SubLds<W> sh;
     const int lane = lane_id();
@@ -1922,14 +1913,14 @@ __global__ __launch_bounds__(SubSize<W>::threads, 2) void k_subtree(SubArgs a, f
             const int gw = cm <= 8 ? 1 : cm <= 16 ? 2 : cm <= 32 ? 4 : cm <= 64 ? 8 : cm <= 128 ? 16
                          : cm <= 256 ? 32 : 64;
             const int npg = kWave / gw;
-            float *f0 = lvl == k ? fdx : nullptr;
+            float4 *f0 = lvl == k ? fd : nullptr;
             if (lvl < k)   // the next level's slots: -1 unless a non-empty parent sets them
                 for (int i = tid; i < 2 * nd; i += kThreads) sh.count[2 * nd - 1 + i] = -1;
             lds_barrier();
             if (cm > kChunk)
-                sub_big(o, k, hin, ph, sh, R0, d, lvl, s0, f0, fdy, fdz, fm, fh);
+                sub_big(o, k, hin, ph, sh, R0, d, lvl, s0, f0, fh);
             for (int p = wv * npg; p < nd; p += W * npg)
-                sub_pass(o, k, hin, ph, sh, R0, d, p, lvl, s0, f0, fdy, fdz, fm, fh, gw);
+                sub_pass(o, k, hin, ph, sh, R0, d, p, lvl, s0, f0, fh, gw);
             if (nst < kSubStages) next_root_stage(a, nq, nst++, nx, sh);
             lds_barrier();
             if (lvl == k) break;
@@ -2067,9 +2058,7 @@ __global__ __launch_bounds__(kBlock) void k_gather_h_big(const double *__restric
 __global__ __launch_bounds__(kBlock) void k_mixed_big(NodeOut o, BigCtl bc, const double *__restrict__ px,
                                                       const double *__restrict__ py, const double *__restrict__ pz,
                                                       const double *__restrict__ pm, const double *__restrict__ ph,
-                                                      float *__restrict__ fdx, float *__restrict__ fdy,
-                                                      float *__restrict__ fdz, float *__restrict__ fm,
-                                                      float *__restrict__ fh) {
+                                                      float4 *__restrict__ fd, float *__restrict__ fh) {
     const int64_t w = wave_index();
     if (w >= bc.ctl[1]) return;
     const int bi = bc.item_big[w];
@@ -2080,10 +2069,7 @@ __global__ __launch_bounds__(kBlock) void k_mixed_big(NodeOut o, BigCtl bc, cons
     const int64_t end = min(base + kChunk, s + c);
     const double cx = o.ncom[3 * lab], cy = o.ncom[3 * lab + 1], cz = o.ncom[3 * lab + 2];
     for (int64_t i = base + lane_id(); i < end; i += kWave) {
-        fdx[i] = (float)(px[i] - cx);
-        fdy[i] = (float)(py[i] - cy);
-        fdz[i] = (float)(pz[i] - cz);
-        fm[i] = (float)pm[i];
+        fd[i] = make_float4((float)(px[i] - cx), (float)(py[i] - cy), (float)(pz[i] - cz), (float)pm[i]);
         fh[i] = (float)ph[i];
     }
 }
@@ -2364,13 +2350,9 @@ static rcb_status finish_build(rcb_tree *t, BuildScratch &b, const NodeOut &o, S
 
 // The mixed form's FP32 particle arrays (tree-owned)
 static rcb_status alloc_mixed(rcb_tree *t, hipStream_t s) {
-    const size_t bytes = sizeof(float) * t->n;
-    t->fdx = (float *)dalloc(t, bytes, s, t->allocs);
-    t->fdy = (float *)dalloc(t, bytes, s, t->allocs);
-    t->fdz = (float *)dalloc(t, bytes, s, t->allocs);
-    t->fm = (float *)dalloc(t, bytes, s, t->allocs);
-    t->fh = (float *)dalloc(t, bytes, s, t->allocs);
-    if (!t->fdx || !t->fdy || !t->fdz || !t->fm || !t->fh) return RCB_ENOMEM;
+    t->fd = (float4 *)dalloc(t, sizeof(float4) * t->n, s, t->allocs);
+    t->fh = (float *)dalloc(t, sizeof(float) * t->n, s, t->allocs);
+    if (!t->fd || !t->fh) return RCB_ENOMEM;
     return RCB_OK;
 }
 
@@ -2626,8 +2608,7 @@ rcb_status build_tree(rcb_tree *t, const double *x, const double *y, const doubl
             if (last_big == t->k) {
                 const BigCtl &bl = bcs[t->k & 1];
                 k_mixed_big<<<blocks_for_waves(nitems), kBlock, 0, s>>>(o, bl, b.x[cur], b.y[cur], b.z[cur],
-                                                                      b.m[cur], t->ph, t->fdx, t->fdy, t->fdz,
-                                                                      t->fm, t->fh);
+                                                                      b.m[cur], t->ph, t->fd, t->fh);
                 RCB_LAUNCH_CHECK("k_mixed_big");
             }
         }
@@ -2636,7 +2617,7 @@ rcb_status build_tree(rcb_tree *t, const double *x, const double *y, const doubl
             constexpr int W = decltype(w)::value;
             const int64_t per_cu = std::max<int64_t>(1, (160 << 10) / (int64_t)sizeof(SubLds<W>));
             const unsigned g = (unsigned)std::min<int64_t>(256 * per_cu, t->nleaf);
-            k_subtree<W><<<g, SubSize<W>::threads, 0, s>>>(sa, t->fdx, t->fdy, t->fdz, t->fm, t->fh);
+            k_subtree<W><<<g, SubSize<W>::threads, 0, s>>>(sa, t->fd, t->fh);
         };
         if (sr.max == SubSize<8>::max) subtree(std::integral_constant<int, 8>{});
         else subtree(std::integral_constant<int, 4>{});
@@ -2717,12 +2698,12 @@ static rcb_status finish_build(rcb_tree *t, BuildScratch &b, const NodeOut &o, S
         t->allocs.push_back(p);
         tmp.keep(p);
     }
-    if (t->p.precision == RCB_MIXED && !t->fdx) {   // (the fused build wrote them already)
+    if (t->p.precision == RCB_MIXED && !t->fd) {   // (the fused build wrote them already)
         rcb_status st = alloc_mixed(t, s);
         if (st != RCB_OK) return st;
         k_mixed_prep<<<blocks_for_waves((t->nleaf + 7) / 8), kBlock, 0, s>>>(
-            t->nleaf, t->nfirst, t->ncount, t->ncom, t->px, t->py, t->pz, t->pm, t->ph, t->fdx,
-            t->fdy, t->fdz, t->fm, t->fh);
+            t->nleaf, t->nfirst, t->ncount, t->ncom, t->px, t->py, t->pz, t->pm, t->ph, t->fd,
+            t->fh);
         RCB_LAUNCH_CHECK("k_mixed_prep");
     }
     return RCB_OK;
@@ -2830,8 +2811,8 @@ static rcb_status refresh_core(rcb_tree *t, const double *x, const double *y, co
     RCB_LAUNCH_CHECK("k_records");
     if (t->p.precision == RCB_MIXED) {
         k_mixed_prep<<<blocks_for_waves((t->nleaf + 7) / 8), kBlock, 0, s>>>(
-            t->nleaf, t->nfirst, t->ncount, t->ncom, t->px, t->py, t->pz, t->pm, t->ph, t->fdx,
-            t->fdy, t->fdz, t->fm, t->fh);
+            t->nleaf, t->nfirst, t->ncount, t->ncom, t->px, t->py, t->pz, t->pm, t->ph, t->fd,
+            t->fh);
         RCB_LAUNCH_CHECK("k_mixed_prep");
     }
     t->nb_total = -1;   // neighbour counts belong to the old positions

@@ -22,8 +22,10 @@
 // Both are bound by VALU issue (k_far at 90% of it at the clock the card holds
 // under FP64, ~1.85 GHz). One kernel for both, a wave per group of 8 leaves,
 // left the chip idle where groups are few and waiting for the longest: 2,000
-// particles 478 us, now 51; 500,000 in cells of 61 8.1 ms, now 0.89; 300,000
-// clumpy 2.19 ms, now 0.55; 4M 7.4 ms as now.
+// particles 478 us, now 47; 500,000 in cells of 61 8.1 ms, now 0.82; 300,000
+// clumpy 2.19 ms, now 0.48. At 4M in cells of 8 k_near's staging was nearly half of
+// its instructions: 3.0 ms with a search of the entries for every source, five
+// arrays of particles and a division per tile, now 2.5.
 //        L2P: a_a += f + J d + H[d, d] / 2,  d = r_a - com_A  (Eq. 6).
 // FP64 form: everything in FP64. Mixed form: the sink leaf's frame. Sinks
 // are their FP32 offsets from the leaf centre of mass; a source of cell B is
@@ -53,7 +55,8 @@ struct GravArgs {
     const int64_t *gnear_beg, *gnear_end, *gfar_beg, *gfar_end;
     const uint64_t *gnear, *gfar;
     const double *px, *py, *pz, *pm, *ph;
-    const float *fdx, *fdy, *fdz, *fm, *fh;
+    const float4 *fd;
+    const float *fh;
     const int32_t *pid;
     void *ax, *ay, *az;
     double *farc;   // if given: each leaf's far coefficients at farc[leaf * kLeafC]
@@ -179,19 +182,15 @@ __global__ __launch_bounds__(W * kWave) void k_far(GravArgs g) {
     }
 }
 
-struct alignas(16) SrcF {
-    float x, y, z, m, h;
-};
-struct alignas(16) SrcD {
-    double x, y, z, m, h;
-};
-
 // tile: 64 staged sources, then 64 zero-mass sources that pad the last
 // partial row of slices, so the pair loop needs no bounds test
 template <bool MIXED>
 struct NearStage {
-    EntryChunk ec;
+    using T = typename std::conditional<MIXED, float, double>::type;
+    typename std::conditional<MIXED, EntF, EntD>::type ent[kWave];
     typename std::conditional<MIXED, SrcF, SrcD>::type tile[2 * kWave];
+    T h[2 * kWave];
+    uint32_t mark[kWave];
 };
 // Near field and L2P, a workgroup of H waves per leaf: the tiles go to the
 // waves in turn and the waves' sums are added in order.
@@ -209,10 +208,10 @@ __global__ __launch_bounds__(H * kWave, MIXED ? 6 : 5) void k_near(GravArgs g) {
     const int32_t sA = g.nfirst[A], c = g.ncount[A];
     if (c == 0) return;
     using Src = typename std::conditional<MIXED, SrcF, SrcD>::type;
-    Src dummy;
-    dummy.x = dummy.y = dummy.z = dummy.m = 0;
-    dummy.h = 1;
-    np.tile[kWave + lane] = dummy;
+    np.tile[kWave + lane] = Src{0, 0, 0, 0};
+    np.h[kWave + lane] = 1;
+    np.mark[lane] = 0;
+    uint32_t gen = 0;
     const int64_t n0 = g.gnear_beg[gi], n1 = g.gnear_end[gi];
     const double cA[3] = {g.ncom[3 * A], g.ncom[3 * A + 1], g.ncom[3 * A + 2]};
     for (int g0 = 0; g0 < c; g0 += kWave) {
@@ -222,9 +221,10 @@ __global__ __launch_bounds__(H * kWave, MIXED ? 6 : 5) void k_near(GravArgs g) {
         const int32_t pa = sA + (has_sink ? si : 0);
         T xa, ya, za, ha;
         if constexpr (MIXED) {   // leaf frame
-            xa = g.fdx[pa];
-            ya = g.fdy[pa];
-            za = g.fdz[pa];
+            const float4 f = g.fd[pa];
+            xa = f.x;
+            ya = f.y;
+            za = f.z;
             ha = g.fh[pa];
         } else {
             xa = g.px[pa];
@@ -246,54 +246,65 @@ __global__ __launch_bounds__(H * kWave, MIXED ? 6 : 5) void k_near(GravArgs g) {
         T ax = 0, ay = 0, az = 0;
         int turn = 0;   // H > 1: the wave that takes the next tile
         for (int64_t e0 = n0; e0 < n1; e0 += kWave) {
-            const int tot = load_entry_chunk(g.gnear, g.nfirst, g.ncount, e0, n1, 1u << li, np.ec);
+            const ChunkEntry ce = load_chunk(g.gnear, g.nfirst, g.ncount, e0, n1, 1u << li);
+            const int tot = ce.tot;
+            if (ce.has()) {
+                if constexpr (MIXED) {
+                    const double *cB = g.ncom + 3 * (int64_t)ce.label;
+                    np.ent[ce.rank] = EntF{(float)(cB[0] - cA[0]), (float)(cB[1] - cA[1]), (float)(cB[2] - cA[2]),
+                                           ce.off()};
+                } else {
+                    np.ent[ce.rank].off = ce.off();
+                }
+            }
             for (int t = 0; t < tot; t += kWave) {
                 if constexpr (H > 1) {
                     const bool mine = turn == wv;
                     turn = turn + 1 < H ? turn + 1 : 0;
                     if (!mine) continue;
                 }
-                const int q = t + lane;
-                Src s = dummy;
-                T bx = 0, by = 0, bz = 0;   // from the leaf's centre of mass
-                if (q < tot) {
-                    const int k = entry_of(np.ec, q);
-                    const int64_t pb = (int64_t)np.ec.fB[k] + (q - np.ec.pos[k]);
-                    if constexpr (MIXED) {
-                        const int64_t B = np.ec.label[k];
-                        s.x = (float)(g.ncom[3 * B] - cA[0]) + g.fdx[pb];
-                        s.y = (float)(g.ncom[3 * B + 1] - cA[1]) + g.fdy[pb];
-                        s.z = (float)(g.ncom[3 * B + 2] - cA[2]) + g.fdz[pb];
-                        s.m = g.fm[pb];
-                        s.h = g.fh[pb];
-                        bx = s.x;
-                        by = s.y;
-                        bz = s.z;
-                    } else {
-                        s.x = g.px[pb];
-                        s.y = g.py[pb];
-                        s.z = g.pz[pb];
-                        s.m = g.pm[pb];
-                        s.h = g.ph[pb];
-                        bx = s.x - cA[0];
-                        by = s.y - cA[1];
-                        bz = s.z - cA[2];
-                    }
-                }
-                // sources outside the support of every sink go behind the others
-                const T lim = ((T)reach + s.h) * (T)1.001;
-                const bool out = (bx * bx + by * by) + bz * bz > lim * lim;
-                const uint64_t cb = ballot(q < tot && !out), ob = ballot(q < tot && out);
-                const int nc = __popcll(cb);
-                np.tile[q >= tot ? lane : out ? nc + rank_below(ob) : rank_below(cb)] = s;
-                tile_sync();
                 const int nt = tot - t < kWave ? tot - t : kWave;
-                const int full = nt / L.J, soft = (nc + L.J - 1) / L.J;
+                const uint64_t valid = ~0ull >> (kWave - nt);
+                const auto en = np.ent[tile_entry(ce, t, np.mark, gen)];
+                // (lanes past the end take the last source with no mass)
+                const int64_t pb = (int64_t)en.off + (t + (lane < nt ? lane : nt - 1));
+                Src s;
+                T sh, bx, by, bz;   // b: from the leaf's centre of mass
+                if constexpr (MIXED) {
+                    const float4 f = g.fd[pb];
+                    sh = g.fh[pb];
+                    s.x = bx = en.x + f.x;
+                    s.y = by = en.y + f.y;
+                    s.z = bz = en.z + f.z;
+                    s.m = f.w;
+                } else {
+                    s.x = g.px[pb];
+                    s.y = g.py[pb];
+                    s.z = g.pz[pb];
+                    s.m = g.pm[pb];
+                    sh = g.ph[pb];
+                    bx = s.x - cA[0];
+                    by = s.y - cA[1];
+                    bz = s.z - cA[2];
+                }
+                s.m = lane < nt ? s.m : (T)0;
+                // sources outside the support of every sink go behind the others
+                // (those past the end last)
+                const T lim = ((T)reach + sh) * (T)1.001;
+                const bool out = (bx * bx + by * by) + bz * bz > lim * lim;
+                const uint64_t cb = ~ballot(out) & valid;
+                const int nc = __popcll(cb), before = rank_below(cb);
+                const int at = (cb >> lane) & 1 ? before : nc + lane - before;
+                np.tile[at] = s;
+                np.h[at] = sh;
+                tile_sync();
+                const int full = L.rows(nt), soft = L.rows(nc + L.J - 1);
                 auto row = [&](int r) {
-                    const auto s = np.tile[r * L.J + L.slice];
+                    const int i = r * L.J + L.slice;
+                    const Src s = np.tile[i];
                     const T vx = xa - s.x, vy = ya - s.y, vz = za - s.z;
                     const T r2 = (vx * vx + vy * vy) + vz * vz;
-                    const T hsum = ha + s.h;
+                    const T hsum = ha + np.h[i];
                     const T ri = rsq_t(r2);
                     const T r3 = ri * ri * ri;
                     T F = r3;
@@ -303,9 +314,7 @@ __global__ __launch_bounds__(H * kWave, MIXED ? 6 : 5) void k_near(GravArgs g) {
                     ay -= F * vy;
                     az -= F * vz;
                 };
-                for (int r = 0; r < soft; ++r) row(r);
-                for (int r = soft; r < full; ++r) {
-                    const auto s = np.tile[r * L.J + L.slice];
+                auto plain = [&](const Src &s) {
                     const T vx = xa - s.x, vy = ya - s.y, vz = za - s.z;
                     const T r2 = (vx * vx + vy * vy) + vz * vz;
                     const T ri = rsq_t(r2);
@@ -313,7 +322,16 @@ __global__ __launch_bounds__(H * kWave, MIXED ? 6 : 5) void k_near(GravArgs g) {
                     ax -= F * vx;
                     ay -= F * vy;
                     az -= F * vz;
+                };
+                for (int r = 0; r < soft; ++r) row(r);
+                int r = soft;
+                for (; r + 1 < full; r += 2) {   // (two rows per step: their LDS reads overlap)
+                    const Src *p = np.tile + (r * L.J + L.slice);
+                    const Src s0 = p[0], s1 = p[L.J];
+                    plain(s0);
+                    plain(s1);
                 }
+                if (r < full) plain(np.tile[r * L.J + L.slice]);
                 if (soft <= full && full * L.J < nt) row(full);   // the last, padded row
                 tile_sync();
             }
@@ -365,7 +383,7 @@ __global__ __launch_bounds__(H * kWave, MIXED ? 6 : 5) void k_near(GravArgs g) {
 GravArgs grav_args(const rcb_tree *t, void *ax, void *ay, void *az, double *farc) {
     return GravArgs{t->nleaf, t->gk, t->ngroup, t->nfirst, t->ncount, t->ncom, t->nM, t->nQ,
                     t->gnear_beg, t->gnear_end, t->gfar_beg, t->gfar_end, t->gnear, t->gfar, t->px, t->py, t->pz, t->pm, t->ph,
-                    t->fdx, t->fdy, t->fdz, t->fm, t->fh, t->pid, ax, ay, az, farc, 0};
+                    t->fd, t->fh, t->pid, ax, ay, az, farc, 0};
 }
 
 // Waves per group: 4 where groups are few (SIMDs to fill) or their lists long

@@ -95,7 +95,8 @@ struct alignas(16) SrcN {
 // chunks, by parity (the slots that one row hands to a sink are at most 64
 // consecutive ones and touch at most two chunks).
 struct NeighShared {
-    EntryChunk ec;
+    int32_t off[kWave];     // of the chunk's entries with sources
+    uint32_t mark[kWave];
     SrcN tile[2 * kWave];
     int32_t cnt[kWave];
     int32_t chunk[kWave][2];
@@ -134,6 +135,8 @@ __global__ __launch_bounds__(kWave) void k_neigh(NeighArgs a) {
     const double4 gA = a.rec[2 * A];
     const double rA = a.hnode[A] * kReachPad;
     const double rA2 = rA * rA;
+    sh.mark[lane] = 0;
+    uint32_t gen = 0;
     for (int g0 = 0; g0 < c; g0 += kWave) {
         const LeafLanes L = leaf_lanes(c - g0);   // the last pass of a big leaf spreads its rest
         const int si = g0 + L.sslot;
@@ -220,22 +223,16 @@ __global__ __launch_bounds__(kWave) void k_neigh(NeighArgs a) {
         };
         int fill = 0;   // kept sources waiting in the ring from head
         for (int64_t e0 = n0; e0 < n1; e0 += kWave) {
-            const int tot =
-                load_entry_chunk(a.gnear, a.nfirst, a.ncount, e0, n1, 1u << (8 + li), sh.ec);
+            const ChunkEntry ce = load_chunk(a.gnear, a.nfirst, a.ncount, e0, n1, 1u << (8 + li));
+            const int tot = ce.tot;
+            if (ce.has()) sh.off[ce.rank] = ce.off();
             for (int t = 0; t < tot; t += kWave) {
-                const int q = t + lane;
-                double sx = 0.0, sy = 0.0, sz = 0.0;
-                int32_t spb = -1, sid = -1;
-                if (q < tot) {
-                    const int k = entry_of(sh.ec, q);
-                    const int32_t pb = sh.ec.fB[k] + (q - sh.ec.pos[k]);
-                    sx = a.px[pb];
-                    sy = a.py[pb];
-                    sz = a.pz[pb];
-                    spb = pb;
-                    sid = a.pid[pb];
-                }
-                const bool keep = q < tot && dist2(gA.x, gA.y, gA.z, sx, sy, sz) < rA2;
+                const int nt = tot - t < kWave ? tot - t : kWave;
+                // (lanes past the end read the last source again)
+                const int32_t spb = sh.off[tile_entry(ce, t, sh.mark, gen)] + (t + (lane < nt ? lane : nt - 1));
+                const double sx = a.px[spb], sy = a.py[spb], sz = a.pz[spb];
+                const int32_t sid = a.pid[spb];
+                const bool keep = lane < nt && dist2(gA.x, gA.y, gA.z, sx, sy, sz) < rA2;
                 const uint64_t kb = ballot(keep);
                 if (keep) {   // appended in order after the waiting ones
                     SrcN &dst = sh.tile[(head + fill + rank_below(kb)) & kRingMask];

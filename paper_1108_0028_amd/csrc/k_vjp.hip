@@ -64,7 +64,8 @@ struct VjpArgs {
     const int64_t *gnear_beg, *gnear_end, *gfar_beg, *gfar_end;
     const uint64_t *gnear, *gfar;
     const double *px, *py, *pz, *pm, *ph;
-    const float *fdx, *fdy, *fdz, *fm, *fh;
+    const float4 *fd;
+    const float *fh;
     const int32_t *pid;
     const void *gx, *gy, *gz;
     double *mom;    // kMom per leaf: symmetrised cotangent moments
@@ -307,16 +308,15 @@ __global__ __launch_bounds__(kFarWaves * kWave, sizeof(AT) == 4 ? 4 : 3) void k_
 // different sources and the source-side terms are summed with LDS atomics
 // without conflicts; each tile's sums then go out with one set of FP64
 // atomics per source.
-template <typename T>
-struct VjpTile {
-    T x[kWave], y[kWave], z[kWave], m[kWave], h[kWave];
+template <bool MIXED>
+struct VjpShared {
+    using T = typename std::conditional<MIXED, float, double>::type;
+    typename std::conditional<MIXED, EntF, EntD>::type ent[kWave];
+    typename std::conditional<MIXED, SrcF, SrcD>::type src[kWave];
+    T h[kWave];
     int32_t pb[kWave];
     double acc[4][kWave];
-};
-template <typename T>
-struct VjpShared {
-    EntryChunk ec;
-    VjpTile<T> t;
+    uint32_t mark[kWave];
 };
 
 // SRC = false (the deterministic form): sink-side terms only; the source-side
@@ -327,10 +327,10 @@ struct VjpShared {
 template <bool MIXED, bool SRC, int H>
 __global__ __launch_bounds__(H * kWave) void k_vjp_near(VjpArgs a) {
     using T = typename std::conditional<MIXED, float, double>::type;
-    __shared__ VjpShared<T> sh_all[H];
+    __shared__ VjpShared<MIXED> sh_all[H];
     __shared__ double red[H > 1 ? H : 1][3][kWave];
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-    VjpShared<T> &sh = sh_all[wv];
+    VjpShared<MIXED> &sh = sh_all[wv];
     const int64_t leaf = a.first + xcd_block();
     const int64_t gi = leaf >> a.gk, A = a.nleaf + leaf;
     const int li = (int)(leaf & ((1 << a.gk) - 1));
@@ -339,6 +339,8 @@ __global__ __launch_bounds__(H * kWave) void k_vjp_near(VjpArgs a) {
     if (c == 0) return;
     const int64_t n0 = a.gnear_beg[gi], n1 = a.gnear_end[gi];
     const double cA[3] = {a.ncom[3 * A], a.ncom[3 * A + 1], a.ncom[3 * A + 2]};
+    sh.mark[lane] = 0;
+    uint32_t gen = 0;
     for (int g0 = 0; g0 < c; g0 += kWave) {
         const LeafLanes L = leaf_lanes(c - g0);
         const int si = g0 + L.sslot;
@@ -357,9 +359,10 @@ __global__ __launch_bounds__(H * kWave) void k_vjp_near(VjpArgs a) {
         }
         T sx, sy, sz, ha;
         if constexpr (MIXED) {   // leaf frame
-            sx = a.fdx[pa];
-            sy = a.fdy[pa];
-            sz = a.fdz[pa];
+            const float4 f = a.fd[pa];
+            sx = f.x;
+            sy = f.y;
+            sz = f.z;
             ha = a.fh[pa];
         } else {
             sx = a.px[pa];
@@ -369,33 +372,36 @@ __global__ __launch_bounds__(H * kWave) void k_vjp_near(VjpArgs a) {
         }
         double acc[3] = {0.0, 0.0, 0.0};
         for (int64_t e0 = n0 + wv * kWave; e0 < n1; e0 += H * kWave) {
-            const int tot = load_entry_chunk(a.gnear, a.nfirst, a.ncount, e0, n1, 1u << li, sh.ec);
+            const ChunkEntry ce = load_chunk(a.gnear, a.nfirst, a.ncount, e0, n1, 1u << li);
+            const int tot = ce.tot;
+            if (ce.has()) {
+                if constexpr (MIXED) {
+                    const double *cB = a.ncom + 3 * (int64_t)ce.label;
+                    sh.ent[ce.rank] = EntF{(float)(cB[0] - cA[0]), (float)(cB[1] - cA[1]), (float)(cB[2] - cA[2]),
+                                           ce.off()};
+                } else {
+                    sh.ent[ce.rank].off = ce.off();
+                }
+            }
             for (int t = 0; t < tot; t += kWave) {
-                const int q = t + lane;
-                if (q < tot) {
-                    const int k = entry_of(sh.ec, q);
-                    const int32_t pb = sh.ec.fB[k] + (q - sh.ec.pos[k]);
+                const int nt = tot - t < kWave ? tot - t : kWave;
+                const auto en = sh.ent[tile_entry(ce, t, sh.mark, gen)];
+                {   // (lanes past the end stage the last source again: no sink reads it)
+                    const int32_t pb = en.off + (t + (lane < nt ? lane : nt - 1));
                     if constexpr (MIXED) {
-                        const int64_t B = sh.ec.label[k];
-                        sh.t.x[lane] = (float)(a.ncom[3 * B] - cA[0]) + a.fdx[pb];
-                        sh.t.y[lane] = (float)(a.ncom[3 * B + 1] - cA[1]) + a.fdy[pb];
-                        sh.t.z[lane] = (float)(a.ncom[3 * B + 2] - cA[2]) + a.fdz[pb];
-                        sh.t.m[lane] = a.fm[pb];
-                        sh.t.h[lane] = a.fh[pb];
+                        const float4 f = a.fd[pb];
+                        sh.src[lane] = SrcF{en.x + f.x, en.y + f.y, en.z + f.z, f.w};
+                        sh.h[lane] = a.fh[pb];
                     } else {
-                        sh.t.x[lane] = a.px[pb];
-                        sh.t.y[lane] = a.py[pb];
-                        sh.t.z[lane] = a.pz[pb];
-                        sh.t.m[lane] = a.pm[pb];
-                        sh.t.h[lane] = a.ph[pb];
+                        sh.src[lane] = SrcD{a.px[pb], a.py[pb], a.pz[pb], a.pm[pb]};
+                        sh.h[lane] = a.ph[pb];
                     }
-                    sh.t.pb[lane] = pb;
+                    sh.pb[lane] = pb;
                 }
 #pragma unroll
-                for (int cc = 0; cc < 4; ++cc) sh.t.acc[cc][lane] = 0.0;
+                for (int cc = 0; cc < 4; ++cc) sh.acc[cc][lane] = 0.0;
                 tile_sync();
-                const int nt = tot - t < kWave ? tot - t : kWave;
-                const int rows = (nt + L.J - 1) / L.J;
+                const int rows = L.rows(nt + L.J - 1);
                 // sink slot s starts at row s mod rows, so that the lanes of
                 // one step add into different sources
                 const int span = rows * L.J;
@@ -404,10 +410,11 @@ __global__ __launch_bounds__(H * kWave) void k_vjp_near(VjpArgs a) {
                     // the deterministic form leaves out the self pair, whose sink and
                     // source terms cancel exactly (v = 0) but would be computed in two
                     // kernels there
-                    if (has_sink && j < nt && (SRC || sh.t.pb[j] != pa)) {
-                        const T v[3] = {sx - sh.t.x[j], sy - sh.t.y[j], sz - sh.t.z[j]};
+                    if (has_sink && j < nt && (SRC || sh.pb[j] != pa)) {
+                        const auto s = sh.src[j];
+                        const T v[3] = {sx - s.x, sy - s.y, sz - s.z};
                         const T r2 = (v[0] * v[0] + v[1] * v[1]) + v[2] * v[2];
-                        const T hsum = ha + sh.t.h[j];
+                        const T hsum = ha + sh.h[j];
                         const T ri = rsq_t(r2);
                         const T ri2 = ri * ri;
                         const T r3 = ri2 * ri;
@@ -415,22 +422,22 @@ __global__ __launch_bounds__(H * kWave) void k_vjp_near(VjpArgs a) {
                         T F = r3, dFr = (T)-3 * r5;
                         if (!soft_outside<T>(r2, hsum)) soft_FdF<T>(r2, ri, r3, r5, hsum, F, dFr);
                         const T vg = v[0] * ga[0] + v[1] * ga[1] + v[2] * ga[2];
-                        const T mb = sh.t.m[j];
+                        const T mb = s.m;
 #pragma unroll
                         for (int cc = 0; cc < 3; ++cc) {
                             const T Kg = mb * (F * ga[cc] + dFr * v[cc] * vg);
                             acc[cc] -= (double)Kg;
-                            if (SRC) atomicAdd(&sh.t.acc[cc][j], (double)Kg);
+                            if (SRC) atomicAdd(&sh.acc[cc][j], (double)Kg);
                         }
-                        if (SRC) atomicAdd(&sh.t.acc[3][j], (double)(-F * vg));
+                        if (SRC) atomicAdd(&sh.acc[3][j], (double)(-F * vg));
                     }
                 }
                 tile_sync();
                 if (SRC && lane < nt) {
-                    const double s0 = sh.t.acc[0][lane], s1 = sh.t.acc[1][lane],
-                                 s2 = sh.t.acc[2][lane], s3 = sh.t.acc[3][lane];
+                    const double s0 = sh.acc[0][lane], s1 = sh.acc[1][lane], s2 = sh.acc[2][lane],
+                                 s3 = sh.acc[3][lane];
                     if (s0 != 0.0 || s1 != 0.0 || s2 != 0.0 || s3 != 0.0) {
-                        const int32_t pb = sh.t.pb[lane];
+                        const int32_t pb = sh.pb[lane];
                         if constexpr (MIXED) {
                             __hip_atomic_fetch_add(a.srcf + pb, (float)s0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                             __hip_atomic_fetch_add(a.srcf + a.n + pb, (float)s1, __ATOMIC_RELAXED,
@@ -829,10 +836,11 @@ struct SinkTile {
     float sx[kWave], sy[kWave], sz[kWave];   // mixed form: (float)(com_B - com_A)
     int32_t pa[kWave];                       // tree position (the self pair is left out)
 };
-template <typename T>
+template <bool MIXED>
 struct SrcShared {
-    EntryChunk ec;
-    SinkTile<T> t;
+    typename std::conditional<MIXED, EntF, EntD>::type ent[kWave];
+    SinkTile<typename std::conditional<MIXED, float, double>::type> t;
+    uint32_t mark[kWave];
 };
 
 template <bool MIXED>
@@ -841,7 +849,7 @@ __global__ __launch_bounds__(kWave) void k_vjp_near_src(VjpArgs a, const uint64_
                                                         const int64_t *__restrict__ le,
                                                         const int32_t *__restrict__ owner) {
     using T = typename std::conditional<MIXED, float, double>::type;
-    __shared__ SrcShared<T> sh;
+    __shared__ SrcShared<MIXED> sh;
     const int64_t ci = a.first + xcd_block();
     const int lane = lane_id();
     const int G = 1 << a.gk;
@@ -853,6 +861,8 @@ __global__ __launch_bounds__(kWave) void k_vjp_near_src(VjpArgs a, const uint64_
     const int64_t e_beg = lb[B] + part * kSrcChunk;
     const int64_t e_end = e_beg + kSrcChunk < le[B] ? e_beg + kSrcChunk : le[B];
     const double cB[3] = {a.ncom[3 * B], a.ncom[3 * B + 1], a.ncom[3 * B + 2]};
+    sh.mark[lane] = 0;
+    uint32_t gen = 0;
     for (int g0 = 0; g0 < c; g0 += kWave) {
         const LeafLanes L = leaf_lanes(c - g0);
         const int si = g0 + L.sslot;
@@ -860,11 +870,12 @@ __global__ __launch_bounds__(kWave) void k_vjp_near_src(VjpArgs a, const uint64_
         const int32_t pb = sB + (has_src ? si : 0);
         T mb, hb, bx, by, bz;   // bx..: FP64 position, or the FP32 offset from com_B
         if constexpr (MIXED) {
-            mb = a.fm[pb];
+            const float4 f = a.fd[pb];
+            mb = f.w;
             hb = a.fh[pb];
-            bx = a.fdx[pb];
-            by = a.fdy[pb];
-            bz = a.fdz[pb];
+            bx = f.x;
+            by = f.y;
+            bz = f.z;
         } else {
             mb = a.pm[pb];
             hb = a.ph[pb];
@@ -886,28 +897,32 @@ __global__ __launch_bounds__(kWave) void k_vjp_near_src(VjpArgs a, const uint64_
                     cA = a.ncount[A];
                 }
             }
-            const int p = wave_excl_scan(cA);
-            sh.ec.fB[lane] = fA;
-            sh.ec.pos[lane] = p;
-            sh.ec.label[lane] = A;
-            if (lane == kWave - 1) sh.ec.pos[kWave] = p + cA;
-            tile_sync();
-            const int tot = __builtin_amdgcn_readfirstlane(sh.ec.pos[kWave]);
+            const ChunkEntry ce = chunk_entry(A, fA, cA);
+            const int tot = ce.tot;
+            if (ce.has()) {
+                if constexpr (MIXED) {
+                    const double *cK = a.ncom + 3 * (int64_t)ce.label;
+                    sh.ent[ce.rank] = EntF{(float)(cB[0] - cK[0]), (float)(cB[1] - cK[1]), (float)(cB[2] - cK[2]),
+                                           ce.off()};
+                } else {
+                    sh.ent[ce.rank].off = ce.off();
+                }
+            }
             for (int t = 0; t < tot; t += kWave) {
-                const int q = t + lane;
-                if (q < tot) {
-                    const int k = entry_of(sh.ec, q);
-                    const int32_t pa = sh.ec.fB[k] + (q - sh.ec.pos[k]);
+                const int nt = tot - t < kWave ? tot - t : kWave;
+                const auto en = sh.ent[tile_entry(ce, t, sh.mark, gen)];
+                {   // (lanes past the end stage the last sink again: no source reads it)
+                    const int32_t pa = en.off + (t + (lane < nt ? lane : nt - 1));
                     sh.t.pa[lane] = pa;
                     if constexpr (MIXED) {
-                        const int64_t Ak = sh.ec.label[k];
-                        sh.t.x[lane] = a.fdx[pa];
-                        sh.t.y[lane] = a.fdy[pa];
-                        sh.t.z[lane] = a.fdz[pa];
+                        const float4 f = a.fd[pa];
+                        sh.t.x[lane] = f.x;
+                        sh.t.y[lane] = f.y;
+                        sh.t.z[lane] = f.z;
                         sh.t.h[lane] = a.fh[pa];
-                        sh.t.sx[lane] = (float)(cB[0] - a.ncom[3 * Ak]);
-                        sh.t.sy[lane] = (float)(cB[1] - a.ncom[3 * Ak + 1]);
-                        sh.t.sz[lane] = (float)(cB[2] - a.ncom[3 * Ak + 2]);
+                        sh.t.sx[lane] = en.x;
+                        sh.t.sy[lane] = en.y;
+                        sh.t.sz[lane] = en.z;
                     } else {
                         sh.t.x[lane] = a.px[pa];
                         sh.t.y[lane] = a.py[pa];
@@ -920,7 +935,6 @@ __global__ __launch_bounds__(kWave) void k_vjp_near_src(VjpArgs a, const uint64_
                     sh.t.g[2][lane] = gt[2 * a.n + pa];
                 }
                 tile_sync();
-                const int nt = tot - t < kWave ? tot - t : kWave;
                 if (has_src) {
                     for (int j = L.slice; j < nt; j += L.J) {
                         if (sh.t.pa[j] == pb) continue;   // the self pair: v = 0, no term
@@ -1136,7 +1150,7 @@ rcb_status gravity_vjp(rcb_tree *t, const void *gx, const void *gy, const void *
     }
     VjpArgs a{t->nleaf, t->gk, t->ngroup, t->nfirst, t->ncount, t->ncom, t->nM, t->nQ,
               t->gnear_beg, t->gnear_end, t->gfar_beg, t->gfar_end, t->gnear, t->gfar, t->px, t->py, t->pz, t->pm, t->ph,
-              t->fdx, t->fdy, t->fdz, t->fm, t->fh, t->pid, gx, gy, gz, mom, leafc, sink, mixed ? nullptr : (double *)srcv,
+              t->fd, t->fh, t->pid, gx, gy, gz, mom, leafc, sink, mixed ? nullptr : (double *)srcv,
               mixed ? (float *)srcv : nullptr, adj, nullptr, nmid, n, t->nlab, nullptr, nullptr, nullptr, nullptr, nullptr,
               nullptr, 0};
     const unsigned gridg = (unsigned)((t->ngroup + kWaves - 1) / kWaves);

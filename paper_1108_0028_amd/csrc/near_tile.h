@@ -3,70 +3,94 @@
 // The sources of a group are the particles of the cells on its union near
 // list (ascending labels; within a cell, tree order). A wave takes the list
 // 64 entries at a time: lane j reads entry j, and an exclusive scan of the
-// cell sizes gives each entry's first source index in the chunk. Sources are
-// then staged 64 at a time: lane j loads source t + j (its entry found by a
-// binary search over the chunk's prefix) into the LDS tile, and every sink
-// lane reads the tile back as broadcasts. Entries that the caller does not
-// need (for example cells with no candidate bit, for the neighbour search)
-// are given zero sources.
+// cell sizes gives each entry's first source in the chunk. The entries that
+// have sources stand in LDS by their rank among them. Sources are then staged
+// 64 at a time: lane j of a tile finds its entry by counting the entries that
+// start at or before it (a mark at each start inside the tile, read back as a
+// ballot), and every sink lane reads the tile back as broadcasts. Entries that
+// the caller does not need (for example cells with no candidate bit, for the
+// neighbour search) are given zero sources.
+// The staging is a good part of a tile's instructions where cells are small
+// (cells of 8: 64 sources are 8 rows of a dozen instructions). A binary search
+// of the prefix for each source and centres of mass read and converted per
+// source, not per entry, made it 140 instructions of 316.
 #pragma once
 
 #include "rcb_internal.h"
 
 namespace rcb {
 
-struct EntryChunk {
-    int32_t fB[kWave];
-    int32_t pos[kWave + 1];
-    uint32_t mask[kWave];     // near mask (bits 0-7) | candidate mask (bits 8-15)
-    int32_t label[kWave];
-};
-
-// Loads entries [e0, min(e0 + 64, n1)) into ec; returns the number of sources.
-// keep_mask: entries whose (near|cand) mask has no bit of keep_mask count as
-// empty.
-__device__ __forceinline__ int load_entry_chunk(const uint64_t *__restrict__ gnear,
-                                                const int32_t *__restrict__ nfirst,
-                                                const int32_t *__restrict__ ncount, int64_t e0,
-                                                int64_t n1, uint32_t keep_mask, EntryChunk &ec) {
-    const int lane = lane_id();
-    const int64_t e = e0 + lane;
-    uint64_t ent = 0;
-    int32_t cB = 0, fB = 0, lab = 0;
-    uint32_t m = 0;
-    if (e < n1) {
-        ent = gnear[e];
-        lab = (int32_t)((uint32_t)ent & 0x7fffffffu);
-        m = (uint32_t)(ent >> 32) & 0xffffu;
-        if (m & keep_mask) {
-            fB = nfirst[lab];
-            cB = ncount[lab];
-        }
-    }
-    const int p = wave_excl_scan(cB);
-    ec.fB[lane] = fB;
-    ec.pos[lane] = p;
-    ec.mask[lane] = m;
-    ec.label[lane] = lab;
-    if (lane == kWave - 1) ec.pos[kWave] = p + cB;
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    return __builtin_amdgcn_readfirstlane(ec.pos[kWave]);   // the same on every lane
-}
-
-// entry k of the chunk holding source q (largest k with pos[k] <= q)
-__device__ __forceinline__ int entry_of(const EntryChunk &ec, int q) {
-    int lo = 0;
-#pragma unroll
-    for (int step = 32; step > 0; step >>= 1)
-        if (ec.pos[lo + step] <= q) lo += step;
-    return lo;
-}
-
 __device__ __forceinline__ void tile_sync() {
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
 }
+
+// One lane's entry of a chunk
+struct ChunkEntry {
+    int32_t label, first;   // the cell and its first particle
+    int32_t pos;            // its first source in the chunk (INT32_MAX: no sources)
+    int rank;               // among the entries with sources
+    int tot;                // sources of the chunk (the same on every lane)
+    __device__ __forceinline__ bool has() const { return pos != INT32_MAX; }
+    // particle of source q of this entry: q + off()
+    __device__ __forceinline__ int32_t off() const { return first - pos; }
+};
+// Entries from cell sizes (0: not wanted)
+__device__ __forceinline__ ChunkEntry chunk_entry(int32_t label, int32_t first, int32_t count) {
+    ChunkEntry ce;
+    const int incl = wave_incl_scan(count);
+    ce.label = label;
+    ce.first = first;
+    ce.pos = count > 0 ? incl - count : INT32_MAX;
+    ce.rank = rank_below(ballot(count > 0));
+    ce.tot = __builtin_amdgcn_readlane(incl, kWave - 1);
+    return ce;
+}
+// Entries [e0, min(e0 + 64, n1)) of a near list; those whose (near|cand) mask
+// has no bit of keep_mask count as empty.
+__device__ __forceinline__ ChunkEntry load_chunk(const uint64_t *__restrict__ gnear,
+                                                 const int32_t *__restrict__ nfirst,
+                                                 const int32_t *__restrict__ ncount, int64_t e0, int64_t n1,
+                                                 uint32_t keep_mask) {
+    const int64_t e = e0 + lane_id();
+    const uint64_t ent = gnear[e < n1 ? e : n1 - 1];
+    const int32_t lab = (int32_t)((uint32_t)ent & 0x7fffffffu);
+    const bool want = e < n1 && ((uint32_t)(ent >> 32) & 0xffffu & keep_mask);
+    int32_t f = 0, c = 0;
+    if (want) {
+        f = nfirst[lab];
+        c = ncount[lab];
+    }
+    return chunk_entry(lab, f, c);
+}
+// The entry (by rank) of this lane's source of the tile of sources
+// [t, t + 64). mark: 64 words of the wave's LDS, zero before the first tile;
+// gen: counts the wave's tiles.
+__device__ __forceinline__ int tile_entry(const ChunkEntry &ce, int t, uint32_t *mark, uint32_t &gen) {
+    ++gen;
+    const uint32_t o = (uint32_t)ce.pos - (uint32_t)t;
+    if (o < (uint32_t)kWave) mark[o] = gen;
+    tile_sync();
+    const bool start = mark[lane_id()] == gen;
+    tile_sync();
+    return __popcll(ballot(ce.pos < t)) + rank_below(ballot(start)) + (start ? 1 : 0) - 1;
+}
+
+// a staged source, and what a chunk's entry adds to its particles: in the mixed
+// form the FP32 shift from the entry's centre of mass to the leaf's
+struct alignas(16) SrcF {
+    float x, y, z, m;
+};
+struct alignas(16) SrcD {
+    double x, y, z, m;
+};
+struct alignas(16) EntF {
+    float x, y, z;
+    int32_t off;
+};
+struct EntD {
+    int32_t off;
+};
 
 // Lanes of a wave over the sinks of one leaf of c > 0 particles: S = min(c, 64)
 // sinks per pass, J = 64 / S slices per sink, lane = sslot * J + slice. Lanes
@@ -74,11 +98,14 @@ __device__ __forceinline__ void tile_sync() {
 // j, j + J, j + 2J, ...
 struct LeafLanes {
     int S, J, sslot, slice;
+    uint32_t inv;   // of J, for rows(): exact for n < 65536 / J
+    __device__ __forceinline__ int rows(int n) const { return (int)(((uint32_t)n * inv) >> 16); }   // n / J
 };
 __device__ __forceinline__ LeafLanes leaf_lanes(int c) {
     LeafLanes L;
     L.S = c < kWave ? c : kWave;
-    L.J = kWave / L.S;
+    L.J = __builtin_amdgcn_readfirstlane(kWave / L.S);
+    L.inv = __builtin_amdgcn_readfirstlane(65536 / L.J + 1);
     L.sslot = lane_id() / L.J;
     L.slice = lane_id() - L.sslot * L.J;
     return L;

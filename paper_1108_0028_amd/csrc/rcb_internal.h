@@ -3,8 +3,8 @@
 // Layout in HBM (all arrays owned by the tree, allocated stream-ordered):
 //   particles, tree order (a node's particles are contiguous, Sec. 2.1
 //   "Particle sorting"): px py pz pm ph (FP64), pid (int32 caller index);
-//   mixed form adds fdx fdy fdz (FP32 offset from the leaf centre of mass),
-//   fm fh (FP32).
+//   mixed form adds fd (FP32: offset from the leaf centre of mass, mass) and
+//   fh (FP32).
 //   nodes, indexed by label (root 1, children 2n and 2n+1, Sec. 2.1 "Node
 //   labelling"): nfirst ncount (int32), nlo nhi ncom (3 FP64 per label),
 //   nM nhint nhnode (FP64), nQ (6 FP64 per label), nplane + naxis (split).
@@ -64,7 +64,8 @@ struct rcb_tree {
     double *px = nullptr, *py = nullptr, *pz = nullptr, *pm = nullptr, *ph = nullptr;
     int32_t *pid = nullptr;            // tree position -> caller index (= lvl_id of level k)
     int32_t *lvl_id = nullptr;         // (k + 1) x n: the order at each level of the build
-    float *fdx = nullptr, *fdy = nullptr, *fdz = nullptr, *fm = nullptr, *fh = nullptr;
+    float4 *fd = nullptr;
+    float *fh = nullptr;
 
     int32_t *nfirst = nullptr, *ncount = nullptr;
     double *nlo = nullptr, *nhi = nullptr, *ncom = nullptr, *nM = nullptr, *nQ = nullptr;
@@ -315,17 +316,20 @@ __device__ __forceinline__ int wave_sum_i(int v) {
     for (int o = 1; o < kWave; o <<= 1) v += __shfl_xor(v, o, kWave);
     return v;
 }
-// exclusive prefix sum over lanes
-__device__ __forceinline__ int wave_excl_scan(int v) {
-    int x = v;
-    const int l = lane_id();
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        int y = __shfl_up(x, o, kWave);
-        if (l >= o) x += y;
-    }
-    return x - v;
+// inclusive prefix sum over lanes, by DPP moves: shifts by 1, 2, 4 and 8 lanes
+// within rows of 16 (lanes with no source add 0), then each odd row adds the
+// last lane of the row before it, and the upper half that of the lower
+__device__ __forceinline__ int wave_incl_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
+    return v;
 }
+// exclusive prefix sum over lanes
+__device__ __forceinline__ int wave_excl_scan(int v) { return wave_incl_scan(v) - v; }
 __device__ __forceinline__ int64_t wave_excl_scan64(int64_t v) {
     int64_t x = v;
     const int l = lane_id();
