@@ -353,16 +353,25 @@ __device__ __forceinline__ double uniform_f64(double v) {
 }
 // The value of another lane of this lane's four, by DPP quad permutation: the
 // other lane of the pair (2j, 2j + 1), and the same lane of the other pair.
-template <int PERM>
-__device__ __forceinline__ double quad_perm(double v) {
+template <int CTRL, typename T>
+__device__ __forceinline__ T dpp_move(T v) {
     union {
-        double d;
-        int w[2];
+        T t;
+        int w[sizeof(T) / 4];
     } u, r;
-    u.d = v;
-    r.w[0] = __builtin_amdgcn_mov_dpp(u.w[0], PERM, 0xF, 0xF, false);
-    r.w[1] = __builtin_amdgcn_mov_dpp(u.w[1], PERM, 0xF, 0xF, false);
-    return r.d;
+    u.t = v;
+#pragma unroll
+    for (int i = 0; i < (int)sizeof(T) / 4; ++i) r.w[i] = __builtin_amdgcn_mov_dpp(u.w[i], CTRL, 0xF, 0xF, false);
+    return r.t;
+}
+template <int PERM, typename T>
+__device__ __forceinline__ T quad_perm(T v) {
+    return dpp_move<PERM>(v);
+}
+// v of the lane N below in this lane's row of 16, cyclically
+template <int N, typename T>
+__device__ __forceinline__ T row_rotate(T v) {
+    return dpp_move<0x120 + N>(v);
 }
 __device__ __forceinline__ double swap_adjacent_lanes(double v) { return quad_perm<0xB1>(v); }   // [1,0,3,2]
 __device__ __forceinline__ double swap_lane_pairs(double v) { return quad_perm<0x4E>(v); }       // [2,3,0,1]

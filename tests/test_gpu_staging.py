@@ -40,3 +40,30 @@ def test_tiles(n, nll, prec, coincident):
         for x, r in zip(gt.vjp(*[_t(v, dt) for v in g]), ot.vjp(*g)):
             assert np.abs(_np(x).astype(np.float64) - r).max() <= VTOL[prec] * max(np.abs(r).max(), 1e-300)
     gt.destroy()
+
+
+@pytest.mark.parametrize("c", [2, 11, 12, 13, 23, 24, 25, 47, 48, 49, 64, 65])
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("det", [False, True])
+def test_vjp_by_leaf_size(c, prec, det):
+    """Leaves at the limits of the VJP's two forms and of the first one's one,
+    two and four segments: four mirrored quarters, so that every leaf has
+    exactly c particles, half of each in reach of the others' support."""
+    import torch
+    from paper_1108_0028_amd import Tree
+    _say("leaf size", c, prec, det)
+    q = W.small_random(c, 70 + c, "uniform", h_scale=4.0)
+    x, y = 2.0 + np.abs(q.x), 1.0 + np.abs(q.y)
+    X = np.concatenate([x, -x, x, -x])
+    Y = np.concatenate([y, y, -y, -y])
+    Z, m, h = (np.tile(v, 4) for v in (q.z, q.m, q.h))
+    ot = O.OracleTree(X, Y, Z, m, h, n_ll=c)
+    cnt = ot.topology()["count"]
+    assert ot.n_leaves == 4 and (cnt[4:8] == c).all()
+    ot.walk(0.0)
+    g = W.cotangents(4 * c, seed=5)
+    dt = torch.float32 if prec == "mixed" else torch.float64
+    gt = Tree(*[_t(v) for v in (X, Y, Z, m, h)], n_ll=c, theta=0.0, precision=prec, deterministic=det)
+    for a, r in zip(gt.vjp(*[_t(v, dt) for v in g]), ot.vjp(*g)):
+        assert np.abs(_np(a).astype(np.float64) - r).max() <= VTOL[prec] * np.abs(r).max()
+    gt.destroy()
