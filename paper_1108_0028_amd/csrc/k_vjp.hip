@@ -27,7 +27,7 @@
 #include <type_traits>
 
 #include "far_math.h"
-#include "near_tile.h"
+#include "near_rows.h"
 #include "rcb_internal.h"
 #include "soft.h"
 
@@ -300,57 +300,17 @@ __global__ __launch_bounds__(kFarWaves * kWave, sizeof(AT) == 4 ? 4 : 3) void k_
     }
 }
 
-// near field and the sink-side far terms, per leaf, in one of two forms.
-//
-// Leaves of at most kRowLeaf particles: lanes are sources. The staged sources
-// wait in two stacks in LDS, those that may lie in the support of a sink and
-// those that cannot (k_near's test), until one holds a pass of 64 >> kk; the
-// lanes are 1 << kk segments, and segment s takes the pass's sources against
-// the sinks s per .. s per + per - 1, per <= kRowSinks, one sink a row. A
-// source's terms then stay in its lane's registers for the whole pass, and the
-// sinks' sums in each lane's until the end, so no sum goes through LDS.
-// Larger leaves: lanes (sink slot, slice) as in the forward kernel
-// (near_tile.h). Sources of the leaf's near cells are staged 64 at a time in
-// LDS as T = ceil(nt / J) rows of J. Sink slot s visits the rows in the
-// rotated order (s + t) mod T, so at each step the lanes of one slice touch
-// different sources and the source-side terms are summed with LDS atomics
-// without conflicts.
-// Either way a pass's sums go out with one set of atomics per source, four
+// near field and the sink-side far terms, per leaf, by rows (near_rows.h). A
+// pass's source-side sums go out with one set of atomics per source, four
 // consecutive lanes to a source's four and 16 sources at a time: atomics are
 // bound by the cache lines they touch. 1M particles, mixed: 0.68 ms for them
 // with a particle's four in four arrays, now 0.45.
-// The rows form spares the LDS traffic of every pair, the slices form the
-// registers; both are bound by VALU issue. FP64 VJP, slices and rows: 250,000
-// particles deterministic 3349 and 3114 us, 300,000 in cells of up to 24 3215 and
-// 2634, of up to 64 2434 and 2164 (rows up to 12 or 24 only: 2429, 2258); mixed,
-// 1M in cells of 8 the same, 300,000 in cells of up to 40 3488 and 3371. More than four
-// segments would cut a source's row short.
-constexpr int kRowSinks = 12;             // 72 registers of sink sums
-constexpr int kRowLeaf = 4 * kRowSinks;
-constexpr int kRowWait = 3 * kWave;       // at most 63 wait in either stack, and a tile joins them
+constexpr int kRowSinks = 8;   // 48 registers of sink sums (12: 250,000 particles deterministic 3117 us, with 8 3000)
 template <bool MIXED>
-struct VjpShared {
+struct VjpShared : RowLds<MIXED, kRowSinks> {
     using T = typename std::conditional<MIXED, float, double>::type;
-    using Src = typename std::conditional<MIXED, SrcF, SrcD>::type;
-    typename std::conditional<MIXED, EntF, EntD>::type ent[kWave];
-    uint32_t mark[kWave];
-    union {
-        struct {   // rows form: sources that may be in reach from the front, others from the back
-            Src src[kRowWait];
-            T h[kRowWait];
-            int32_t pb[kRowWait];
-            Src sink[kRowLeaf];             // position, h
-            T g[kRowLeaf][4];
-            int32_t pa[kRowLeaf];
-        } r;
-        struct {   // slices form
-            Src src[kWave];
-            T h[kWave];
-            int32_t pb[kWave];
-            double acc[4][kWave];
-        } s;
-        double out[4][kRowSinks][3];        // rows form, after its passes: by row of 16 lanes
-    };
+    T g[kWave][4];         // the sinks' cotangents
+    int32_t pa[kWave];     // and tree positions
 };
 
 // The source-side sums of n <= 64 staged sources (value(j, c): component c of
@@ -369,224 +329,18 @@ __device__ __forceinline__ void source_atomics(const VjpArgs &a, int n, V value,
     }
 }
 
-// The pair's terms: F and dF/dr / r, or -- SOFT = false -- those outside the
-// kernel support.
-template <bool SOFT, typename T>
-__device__ __forceinline__ void pair_FdF(T r2, T hsum, T &F, T &dFr) {
-    const T ri = rsq_t(r2);
-    const T ri2 = ri * ri;
-    const T r3 = ri2 * ri;
-    const T r5 = r3 * ri2;
-    F = r3;
-    dFr = (T)-3 * r5;
-    if (SOFT && !soft_outside<T>(r2, hsum)) soft_FdF<T>(r2, ri, r3, r5, hsum, F, dFr);
-}
-
-// The rows form: the near-field sums of the leaf's sinks over this wave's
-// chunks, acc[s][..] of sink s in sh.out on return (see above), and the
-// sources' terms.
-template <bool MIXED, bool SRC, int H>
-__device__ __forceinline__ void near_rows(const VjpArgs &a, VjpShared<MIXED> &sh, int wv, int li, int64_t n0,
-                                          int64_t n1, int32_t sA, int c, int kk, int per, const double (&cA)[3],
-                                          uint32_t &gen) {
-    using T = typename std::conditional<MIXED, float, double>::type;
-    using Src = typename std::conditional<MIXED, SrcF, SrcD>::type;
-    const int lane = lane_id();
-    const int P = kWave >> kk;   // sources of a pass
-    float reach;                 // as in k_near
-    {
-        const bool real = lane < c;
-        const int32_t pa = sA + (real ? lane : 0);
-        const int32_t oa = a.pid[pa];
-        Src s;
-        float rx, ry, rz;
-        if constexpr (MIXED) {   // leaf frame
-            const float4 f = a.fd[pa];
-            s = Src{f.x, f.y, f.z, a.fh[pa]};
-            rx = s.x;
-            ry = s.y;
-            rz = s.z;
-        } else {
-            s = Src{a.px[pa], a.py[pa], a.pz[pa], a.ph[pa]};
-            rx = (float)(s.x - cA[0]);
-            ry = (float)(s.y - cA[1]);
-            rz = (float)(s.z - cA[2]);
-        }
-        // (slots past the leaf's particles: the first particle with no cotangent)
-        if (lane < kRowLeaf) {
-            sh.r.sink[lane] = s;
-            sh.r.g[lane][0] = real ? (T)load_g<MIXED>(a.gx, oa) : (T)0;
-            sh.r.g[lane][1] = real ? (T)load_g<MIXED>(a.gy, oa) : (T)0;
-            sh.r.g[lane][2] = real ? (T)load_g<MIXED>(a.gz, oa) : (T)0;
-            sh.r.pa[lane] = real ? pa : -1;
-        }
-        reach = sqrtf((rx * rx + ry * ry) + rz * rz) + (float)s.m;
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) reach = fmaxf(reach, __shfl_xor(reach, o, kWave));
-    }
-    tile_sync();
-    double acc[kRowSinks][3];
-#pragma unroll
-    for (int i = 0; i < kRowSinks; ++i) acc[i][0] = acc[i][1] = acc[i][2] = 0.0;
-    const int seg = lane >> (6 - kk), in_seg = lane & (P - 1);
-    const int sink0 = seg * per;
-    // one pass: the first cnt lanes of each segment take the sources at slot(0),
-    // slot(1), ..., whose slots then hold their sums
-    auto pass = [&](auto soft, int cnt, auto slot) {
-        constexpr bool SOFT = decltype(soft)::value;
-        const int at = slot(in_seg < cnt ? in_seg : 0);
-        Src s = sh.r.src[at];
-        const T hb = SOFT ? sh.r.h[at] : (T)0;
-        const int32_t pb = sh.r.pb[at];
-        const bool live = in_seg < cnt;
-        s.m = live ? s.m : (T)0;
-        double src[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int i = 0; i < kRowSinks; ++i) {
-            if (i < per) {
-                const Src k = sh.r.sink[sink0 + i];
-                const T *g = sh.r.g[sink0 + i];
-                const T ga[3] = {g[0], g[1], g[2]};
-                const T v[3] = {k.x - s.x, k.y - s.y, k.z - s.z};
-                const T r2 = (v[0] * v[0] + v[1] * v[1]) + v[2] * v[2];
-                T F, dFr;
-                pair_FdF<SOFT, T>(r2, k.m + hb, F, dFr);
-                const T vg = v[0] * ga[0] + v[1] * ga[1] + v[2] * ga[2];
-                // the deterministic form leaves out the self pair, whose sink and
-                // source terms cancel exactly (v = 0) but would be computed in two
-                // kernels there
-                const T mb = !SRC && SOFT && pb == sh.r.pa[sink0 + i] ? (T)0 : s.m;
-                const T Fm = F * mb, vm = dFr * vg * mb;
-#pragma unroll
-                for (int cc = 0; cc < 3; ++cc) {
-                    const T Kg = Fm * ga[cc] + vm * v[cc];
-                    acc[i][cc] -= (double)Kg;
-                    if (SRC) src[cc] += (double)Kg;
-                }
-                if (SRC) src[3] += (double)(-F * vg);
-            }
-        }
-        if constexpr (SRC) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {   // the segments' sums of the same source
-                if (kk > 0) src[q] = pair_sum<32>(src[q]);
-                if (kk > 1) src[q] = pair_sum<16>(src[q]);
-            }
-            if (live && seg == 0) sh.r.src[at] = Src{(T)src[0], (T)src[1], (T)src[2], (T)src[3]};
-            tile_sync();
-            source_atomics<MIXED>(
-                a, cnt, [&](int j, int c) { return ((const T *)&sh.r.src[slot(j)])[c]; },
-                [&](int j) { return sh.r.pb[slot(j)]; });
-            tile_sync();
-        }
-    };
-    int64_t e0 = n0 + wv * kWave;
-    ChunkEntry ce{};
-    int t = 0, nc = 0, no = 0;   // nc, no: waiting in the stacks
-    for (;;) {
-        while (t >= ce.tot && e0 < n1) {
-            ce = load_chunk(a.gnear, a.nfirst, a.ncount, e0, n1, 1u << li);
-            if (ce.has()) {
-                if constexpr (MIXED) {
-                    const double *cB = a.ncom + 3 * (int64_t)ce.label;
-                    sh.ent[ce.rank] = EntF{(float)(cB[0] - cA[0]), (float)(cB[1] - cA[1]), (float)(cB[2] - cA[2]),
-                                           ce.off()};
-                } else {
-                    sh.ent[ce.rank].off = ce.off();
-                }
-            }
-            t = 0;
-            e0 += H * kWave;
-        }
-        const bool more = t < ce.tot;
-        if (more) {
-            const int nt = ce.tot - t < kWave ? ce.tot - t : kWave;
-            const uint64_t valid = ~0ull >> (kWave - nt);
-            const auto en = sh.ent[tile_entry(ce, t, sh.mark, gen)];
-            const int32_t pb = en.off + (t + (lane < nt ? lane : nt - 1));
-            Src s;
-            T h, bx, by, bz;   // b: from the leaf's centre of mass
-            if constexpr (MIXED) {
-                const float4 f = a.fd[pb];
-                h = a.fh[pb];
-                s = Src{en.x + f.x, en.y + f.y, en.z + f.z, f.w};
-                bx = s.x;
-                by = s.y;
-                bz = s.z;
-            } else {
-                s = Src{a.px[pb], a.py[pb], a.pz[pb], a.pm[pb]};
-                h = a.ph[pb];
-                bx = s.x - cA[0];
-                by = s.y - cA[1];
-                bz = s.z - cA[2];
-            }
-            const T lim = ((T)reach + h) * (T)1.001;
-            const bool out = (bx * bx + by * by) + bz * bz > lim * lim;
-            const uint64_t cb = ~ballot(out) & valid, ob = ballot(out) & valid;
-            const int at = out ? kRowWait - 1 - (no + rank_below(ob)) : nc + rank_below(cb);
-            if (lane < nt) {
-                sh.r.src[at] = s;
-                sh.r.h[at] = h;
-                sh.r.pb[at] = pb;
-            }
-            nc += __popcll(cb);
-            no += __popcll(ob);
-            t += kWave;
-            tile_sync();
-        }
-        const int need = more ? P : 1;
-        while (nc >= need) {
-            const int cnt = nc < P ? nc : P;
-            nc -= cnt;
-            // at the end the others join the last pass if they fit
-            const int join = !more && nc == 0 && no > 0 && cnt + no <= P ? no : 0;
-            no -= join;
-            pass(std::true_type{}, cnt + join,
-                 [&](int i) { return i < cnt ? nc + i : kRowWait - 1 - (i - cnt); });
-        }
-        while (no >= need) {
-            const int cnt = no < P ? no : P;
-            no -= cnt;
-            pass(std::false_type{}, cnt, [&](int i) { return kRowWait - 1 - (no + i); });
-        }
-        if (!more) break;
-        tile_sync();
-    }
-    tile_sync();
-    // sums over each row of 16 lanes: the rows of sums are halved twice between
-    // the lanes of a quad (lane l keeps rows 6 (l & 1) + 3 (l >> 1 & 1) + i),
-    // then the four quads are added
-    const bool odd = lane & 1, pair = lane & 2;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int cc = 0; cc < 3; ++cc) {
-            double v[2];
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const double lo = acc[i + 3 * j][cc], hi = acc[i + 3 * j + 6][cc];
-                v[j] = (odd ? hi : lo) + quad_perm<0xB1>(odd ? lo : hi);
-            }
-            double w = (pair ? v[1] : v[0]) + quad_perm<0x4E>(pair ? v[0] : v[1]);
-            w += row_rotate<4>(w);
-            w += row_rotate<8>(w);
-            if ((lane & 15) < 4) sh.out[lane >> 4][6 * (lane & 1) + 3 * ((lane >> 1) & 1) + i][cc] = w;
-        }
-    tile_sync();
-}
-
 // SRC = false (the deterministic form): sink-side terms only; the source-side
 // terms are summed per source cell by k_vjp_near_src instead.
-// A workgroup of H waves per cell: wave w takes the chunks w, w + H, ... of 64
-// entries of the near list, and the sink sums of the waves are added in order.
+// A workgroup of H waves per cell, whose sink sums are added in order.
 // (One wave per group of 8 cells: 491 us for 4096 particles, now 73.)
 template <bool MIXED, bool SRC, int H>
 __global__ __launch_bounds__(H * kWave, MIXED ? 4 : 3) void k_vjp_near(VjpArgs a) {
     using T = typename std::conditional<MIXED, float, double>::type;
+    using Src = typename std::conditional<MIXED, SrcF, SrcD>::type;
+    constexpr int SB = kRowSinks;
     __shared__ VjpShared<MIXED> sh_all[H];
-    __shared__ double red[H > 1 ? H : 1][3][kWave];
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-    VjpShared<MIXED> &sh = sh_all[wv];
+    auto &sh = sh_all[wv];
     const int64_t leaf = a.first + xcd_block();
     const int64_t gi = leaf >> a.gk, A = a.nleaf + leaf;
     const int li = (int)(leaf & ((1 << a.gk) - 1));
@@ -623,129 +377,98 @@ __global__ __launch_bounds__(H * kWave, MIXED ? 4 : 3) void k_vjp_near(VjpArgs a
         a.sink[2 * a.n + pa] = out[2];
         a.sink[3 * a.n + pa] = (cot[0] * d[0] + cot[1] * d[1] + cot[2] * d[2]) / MA;
     };
-    if (c <= kRowLeaf) {
-        const int kk = c <= kRowSinks ? 0 : c <= 2 * kRowSinks ? 1 : 2;
-        const int per = (c + (1 << kk) - 1) >> kk;
-        near_rows<MIXED, SRC, H>(a, sh, wv, li, n0, n1, sA, c, kk, per, cA, gen);
-        if constexpr (H > 1) __syncthreads();
-        if (wv == 0 && lane < c) {
-            const int seg = lane / per, i = lane - seg * per, r0 = seg << (2 - kk);   // its rows of 16 lanes
-            double acc[3] = {0.0, 0.0, 0.0};
-            for (int w = 0; w < H; ++w)
-                for (int r = r0; r < r0 + (4 >> kk); ++r)
-#pragma unroll
-                    for (int cc = 0; cc < 3; ++cc) acc[cc] += sh_all[w].out[r][i][cc];
-            finish(sA + lane, acc);
-        }
-        return;
-    }
     for (int g0 = 0; g0 < c; g0 += kWave) {
-        const LeafLanes L = leaf_lanes(c - g0);
-        const int si = g0 + L.sslot;
-        const bool has_sink = L.sslot < L.S && si < c;
-        const int32_t pa = sA + (has_sink ? si : 0);
-        const int32_t oa = a.pid[pa];
-        T ga[3] = {(T)0, (T)0, (T)0};
-        if (has_sink) {
-            ga[0] = (T)load_g<MIXED>(a.gx, oa);
-            ga[1] = (T)load_g<MIXED>(a.gy, oa);
-            ga[2] = (T)load_g<MIXED>(a.gz, oa);
-        }
-        T sx, sy, sz, ha;
+        const int cs = c - g0 < kWave ? c - g0 : kWave;
+        const RowShape rs = row_shape<SB>(cs);
+        const bool real = lane < cs;
+        const int32_t pa = sA + g0 + (real ? lane : 0);
+        // (slots past the sinks: the first one, with no cotangent)
+        Src me;
         if constexpr (MIXED) {   // leaf frame
             const float4 f = a.fd[pa];
-            sx = f.x;
-            sy = f.y;
-            sz = f.z;
-            ha = a.fh[pa];
+            me = Src{f.x, f.y, f.z, a.fh[pa]};
         } else {
-            sx = a.px[pa];
-            sy = a.py[pa];
-            sz = a.pz[pa];
-            ha = a.ph[pa];
+            me = Src{a.px[pa], a.py[pa], a.pz[pa], a.ph[pa]};
         }
-        double acc[3] = {0.0, 0.0, 0.0};
-        for (int64_t e0 = n0 + wv * kWave; e0 < n1; e0 += H * kWave) {
-            const ChunkEntry ce = load_chunk(a.gnear, a.nfirst, a.ncount, e0, n1, 1u << li);
-            const int tot = ce.tot;
-            if (ce.has()) {
-                if constexpr (MIXED) {
-                    const double *cB = a.ncom + 3 * (int64_t)ce.label;
-                    sh.ent[ce.rank] = EntF{(float)(cB[0] - cA[0]), (float)(cB[1] - cA[1]), (float)(cB[2] - cA[2]),
-                                           ce.off()};
-                } else {
-                    sh.ent[ce.rank].off = ce.off();
-                }
-            }
-            for (int t = 0; t < tot; t += kWave) {
-                const int nt = tot - t < kWave ? tot - t : kWave;
-                const auto en = sh.ent[tile_entry(ce, t, sh.mark, gen)];
-                {   // (lanes past the end stage the last source again: no sink reads it)
-                    const int32_t pb = en.off + (t + (lane < nt ? lane : nt - 1));
-                    if constexpr (MIXED) {
-                        const float4 f = a.fd[pb];
-                        sh.s.src[lane] = SrcF{en.x + f.x, en.y + f.y, en.z + f.z, f.w};
-                        sh.s.h[lane] = a.fh[pb];
-                    } else {
-                        sh.s.src[lane] = SrcD{a.px[pb], a.py[pb], a.pz[pb], a.pm[pb]};
-                        sh.s.h[lane] = a.ph[pb];
-                    }
-                    sh.s.pb[lane] = pb;
-                }
+        const int32_t oa = a.pid[pa];
+        sh.sink[lane] = me;
+        sh.g[lane][0] = real ? (T)load_g<MIXED>(a.gx, oa) : (T)0;
+        sh.g[lane][1] = real ? (T)load_g<MIXED>(a.gy, oa) : (T)0;
+        sh.g[lane][2] = real ? (T)load_g<MIXED>(a.gz, oa) : (T)0;
+        sh.pa[lane] = real ? pa : -1;
+        const float reach = sink_reach<MIXED>(me, cA);
+        double acc[SB][3];
 #pragma unroll
-                for (int cc = 0; cc < 4; ++cc) sh.s.acc[cc][lane] = 0.0;
-                tile_sync();
-                const int rows = L.rows(nt + L.J - 1);
-                // sink slot s starts at row s mod rows, so that the lanes of
-                // one step add into different sources
-                const int span = rows * L.J;
-                int j = (L.sslot % rows) * L.J + L.slice;
-                for (int st = 0; st < rows; ++st, j = j + L.J < span ? j + L.J : j + L.J - span) {
+        for (int i = 0; i < SB; ++i) acc[i][0] = acc[i][1] = acc[i][2] = 0.0;
+        // a pass; the sources' slots then hold their sums
+        auto pass = [&](auto soft, int n, auto slot) {
+            const int at = slot(rs.in_seg < n ? rs.in_seg : 0);
+            Src s = sh.src[at];
+            const T hb = soft ? sh.h[at] : (T)0;
+            const int32_t pb = sh.pb[at];
+            s.m = rs.in_seg < n ? s.m : (T)0;
+            double src[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int i = 0; i < SB; ++i) {
+                if (i < rs.per) {
+                    const Src k = sh.sink[rs.sink0 + i];
+                    const T *gp = sh.g[rs.sink0 + i];
+                    const T ga[3] = {gp[0], gp[1], gp[2]};
+                    const T v[3] = {k.x - s.x, k.y - s.y, k.z - s.z};
+                    const T r2 = (v[0] * v[0] + v[1] * v[1]) + v[2] * v[2];
+                    const T ri = rsq_t(r2);
+                    const T ri2 = ri * ri;
+                    const T r3 = ri2 * ri;
+                    const T r5 = r3 * ri2;
+                    T F = r3, dFr = (T)-3 * r5;
+                    if constexpr (soft) {
+                        const T hsum = k.m + hb;
+                        if (!soft_outside<T>(r2, hsum)) soft_FdF<T>(r2, ri, r3, r5, hsum, F, dFr);
+                    }
+                    const T vg = v[0] * ga[0] + v[1] * ga[1] + v[2] * ga[2];
                     // the deterministic form leaves out the self pair, whose sink and
                     // source terms cancel exactly (v = 0) but would be computed in two
                     // kernels there
-                    if (has_sink && j < nt && (SRC || sh.s.pb[j] != pa)) {
-                        const auto s = sh.s.src[j];
-                        const T v[3] = {sx - s.x, sy - s.y, sz - s.z};
-                        const T r2 = (v[0] * v[0] + v[1] * v[1]) + v[2] * v[2];
-                        const T hsum = ha + sh.s.h[j];
-                        T F, dFr;
-                        pair_FdF<true, T>(r2, hsum, F, dFr);
-                        const T vg = v[0] * ga[0] + v[1] * ga[1] + v[2] * ga[2];
-                        const T mb = s.m;
+                    const T mb = !SRC && soft && pb == sh.pa[rs.sink0 + i] ? (T)0 : s.m;
+                    const T Fm = F * mb, vm = dFr * vg * mb;
 #pragma unroll
-                        for (int cc = 0; cc < 3; ++cc) {
-                            const T Kg = mb * (F * ga[cc] + dFr * v[cc] * vg);
-                            acc[cc] -= (double)Kg;
-                            if (SRC) atomicAdd(&sh.s.acc[cc][j], (double)Kg);
-                        }
-                        if (SRC) atomicAdd(&sh.s.acc[3][j], (double)(-F * vg));
+                    for (int cc = 0; cc < 3; ++cc) {
+                        const T Kg = Fm * ga[cc] + vm * v[cc];
+                        acc[i][cc] -= (double)Kg;
+                        if (SRC) src[cc] += (double)Kg;
                     }
+                    if (SRC) src[3] += (double)(-F * vg);
                 }
-                tile_sync();
-                if constexpr (SRC) {
-                    source_atomics<MIXED>(
-                        a, nt, [&](int j, int c) { return sh.s.acc[c][j]; }, [&](int j) { return sh.s.pb[j]; });
+            }
+            if constexpr (SRC) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {   // the segments' sums of the same source
+                    if (rs.kk > 0) src[q] = pair_sum<32>(src[q]);
+                    if (rs.kk > 1) src[q] = pair_sum<16>(src[q]);
+                    if (rs.kk > 2) src[q] += row_rotate<8>(src[q]);
                 }
+                if (lane < n) sh.src[at] = Src{(T)src[0], (T)src[1], (T)src[2], (T)src[3]};
+                tile_sync();
+                source_atomics<MIXED>(
+                    a, n, [&](int j, int q) { return ((const T *)&sh.src[slot(j)])[q]; },
+                    [&](int j) { return sh.pb[slot(j)]; });
                 tile_sync();
             }
+        };
+        tile_sync();
+        list_rows<MIXED, H>(
+            a, sh, wv, li, n0, n1, cA, reach, rs.P, gen,
+            [&](int n, auto slot) { pass(std::true_type{}, n, slot); },
+            [&](int n, auto slot) { pass(std::false_type{}, n, slot); });
+        sum_rows<SB>(rs, acc, sh.out);
+        if constexpr (H > 1) __syncthreads();
+        if (wv == 0 && real) {
+            double sum[3] = {0.0, 0.0, 0.0};
+            for (int w = 0; w < H; ++w) row_total<SB>(rs, lane, sh_all[w].out, sum);
+            finish(pa, sum);
         }
-#pragma unroll
-        for (int cc = 0; cc < 3; ++cc) acc[cc] = seg_sum(acc[cc], L.slice, L.J);
-        if constexpr (H > 1) {
-            if (L.slice == 0) {
-#pragma unroll
-                for (int cc = 0; cc < 3; ++cc) red[wv][cc][L.sslot] = acc[cc];
-            }
-            __syncthreads();
-            if (wv == 0 && L.slice == 0) {
-                for (int w = 1; w < H; ++w)
-#pragma unroll
-                    for (int cc = 0; cc < 3; ++cc) acc[cc] += red[w][cc][L.sslot];
-            }
-            __syncthreads();
-        }
-        if (wv == 0 && has_sink && L.slice == 0) finish(pa, acc);
+        if constexpr (H > 1) __syncthreads();
+        else tile_sync();
     }
 }
 

@@ -42,13 +42,13 @@ def test_tiles(n, nll, prec, coincident):
     gt.destroy()
 
 
-@pytest.mark.parametrize("c", [2, 11, 12, 13, 23, 24, 25, 47, 48, 49, 64, 65])
+@pytest.mark.parametrize("c", [2, 7, 8, 9, 11, 13, 16, 17, 25, 32, 33, 49, 57, 64, 65, 130])
 @pytest.mark.parametrize("prec", ["fp64", "mixed"])
 @pytest.mark.parametrize("det", [False, True])
 def test_vjp_by_leaf_size(c, prec, det):
-    """Leaves at the limits of the VJP's two forms and of the first one's one,
-    two and four segments: four mirrored quarters, so that every leaf has
-    exactly c particles, half of each in reach of the others' support."""
+    """Leaves at the limits of the one, two, four and eight segments that the
+    VJP's rows take, and of one pass of sinks: four mirrored quarters, every leaf with
+    exactly c particles, some of them in reach of the others' support."""
     import torch
     from paper_1108_0028_amd import Tree
     _say("leaf size", c, prec, det)
