@@ -546,6 +546,85 @@ __global__ __launch_bounds__(kBlock) void k_nb_sort_long(int64_t nsort, const in
     }
 }
 
+// The same for clouds of at most kBitsMax particles: the ids of a list, all
+// different, are set in a bitmap of the caller's indices in LDS, and an id's
+// place is the number of bits below it -- the sum before its group of 8 words,
+// kept from one scan, and the bits of the group. A network is a chain of some 60
+// stages with a barrier each.
+// rcb_neighbours_fill in us, network and bitmap: 2000 particles, 134 lists of up
+// to 1999 ids 91 and 58; 37,000, 2600 lists of up to 875 95 and 69; 300,000, 7200 of
+// up to 1476 219 and 221 (the bitmap's words are cleared and scanned for every
+// list), hence the limit.
+constexpr int kBitsMax = 1 << 18;
+constexpr int kBitsOwn = 16;   // ids a thread keeps; of longer lists they are read from the bitmap
+__global__ __launch_bounds__(kBlock) void k_nb_sort_bits(int64_t nsort, const int32_t *__restrict__ longq,
+                                                         const int64_t *__restrict__ offsets,
+                                                         int32_t *__restrict__ ids, int n) {
+    extern __shared__ uint32_t bits[];
+    const int tid = threadIdx.x, lane = lane_id(), wv = tid / kWave;
+    const int ng = (n + 255) / 256;          // groups of 8 words
+    uint32_t *const before = bits + 8 * ng;   // set bits before each group
+    uint32_t *const wsum = before + ng;       // per wave
+    const int per = (ng + kBlock - 1) / kBlock;
+    const int gb = tid * per < ng ? tid * per : ng, ge = gb + per < ng ? gb + per : ng;   // this thread's groups
+    auto group_bits = [&](int g, int words) {
+        int c = 0;
+        for (int w = 0; w < words; ++w) c += __popc(bits[8 * g + w]);
+        return c;
+    };
+    for (int64_t i = blockIdx.x; i < nsort; i += gridDim.x) {
+        const int32_t q = longq[i];
+        const int64_t b = offsets[q];
+        const int len = (int)(offsets[q + 1] - b);
+        int32_t *const list = ids + b;
+        for (int w = tid; w < 8 * ng; w += kBlock) bits[w] = 0;
+        const bool own = len <= kBitsOwn * kBlock;
+        int32_t v[kBitsOwn];
+        __syncthreads();
+        if (own) {
+#pragma unroll
+            for (int u = 0; u < kBitsOwn; ++u) {
+                v[u] = tid + u * kBlock < len ? list[tid + u * kBlock] : -1;
+                if (v[u] >= 0) atomicOr(&bits[v[u] >> 5], 1u << (v[u] & 31));
+            }
+        } else {
+            for (int j = tid; j < len; j += kBlock) {
+                const int32_t x = list[j];
+                atomicOr(&bits[x >> 5], 1u << (x & 31));
+            }
+        }
+        __syncthreads();
+        int c = 0;
+        for (int g = gb; g < ge; ++g) c += group_bits(g, 8);
+        const int incl = wave_incl_scan(c);
+        if (lane == kWave - 1) wsum[wv] = incl;
+        __syncthreads();
+        int at = incl - c;
+        for (int w = 0; w < wv; ++w) at += wsum[w];
+        for (int g = gb; g < ge; ++g) {
+            before[g] = at;
+            if (own) {
+                at += group_bits(g, 8);
+            } else {
+                for (int w = 0; w < 8; ++w)
+                    for (uint32_t m = bits[8 * g + w]; m; m &= m - 1) list[at++] = 256 * g + 32 * w + __ffs(m) - 1;
+            }
+        }
+        __syncthreads();
+        if (own) {
+#pragma unroll
+            for (int u = 0; u < kBitsOwn; ++u) {
+                if (v[u] >= 0) {
+                    const int g = v[u] >> 8, w = (v[u] >> 5) & 7;
+                    list[before[g] + group_bits(g, w) + __popc(bits[v[u] >> 5] & ((1u << (v[u] & 31)) - 1u))] = v[u];
+                }
+            }
+        }
+        __syncthreads();
+    }
+}
+inline size_t bits_lds(int64_t n) { return sizeof(uint32_t) * (9 * ((n + 255) / 256) + kWaves); }
+
 // Slab rows go by caller index, so that the fill call streams them in the
 // CSR's order; past 4 GiB of slab (16.7M particles) by tree position instead,
 // where a wave's rows are contiguous: the search's scattered stores into a
@@ -571,11 +650,16 @@ rcb_status neighbours_count(rcb_tree *t, int64_t *offsets, int64_t *total, hipSt
         // overflow chunks: one for every 8th particle (lists past 64 ids are 3%
         // (Plummer) to 8% (clumps) at ~50 neighbours on average), and the number
         // that the walk's estimate of each cell's neighbour count asks for (at
-        // most 4 per particle; at 105 neighbours, one for nearly each)
+        // most 4 per particle; at 105 neighbours, one for nearly each), and for
+        // small clouds what the longest lists possible take, up to 16 MiB: a few
+        // lists of thousands searched again cost 2000 particles 38 of 380 us
         t->nb_subs = 1;
         while (t->nb_subs < kSubMax && t->nb_subs * 8 < t->ngroup) t->nb_subs *= 2;
+        const int64_t all = t->n > kNbCap ? t->n * ((t->n - kNbCap + kNbChunk - 1) / kNbChunk) : 0;
+        const int64_t small = std::min<int64_t>(all, (int64_t)1 << 16);
         const int64_t base = t->n / 8 + 1;
-        const int64_t more = std::min<int64_t>({t->nb_est, 4 * t->n, ((int64_t)1 << 30) - base});   // (int32 chunk ids)
+        const int64_t more = std::max<int64_t>(
+            small, std::min<int64_t>({t->nb_est, 4 * t->n, ((int64_t)1 << 30) - base}));   // (int32 chunk ids)
         t->nb_slab = (int32_t *)dalloc(t, sizeof(int32_t) * t->n * kNbCap, s, t->list_allocs);
         for (int64_t want : {base + more, base}) {   // the smaller pool if the larger cannot be had
             t->nb_sub_cap = (want + t->nb_subs - 1) / t->nb_subs + 8;
@@ -652,8 +736,14 @@ rcb_status neighbours_fill(rcb_tree *t, const int64_t *offsets, int32_t *ids, in
         RCB_LAUNCH_CHECK("k_neigh<fill>");
     }
     if (sorts > 0) {   // exactly this many lists appended themselves
-        k_nb_sort_long<<<(unsigned)std::min(kMaxGrid, sorts), kBlock, 0, s>>>(sorts, longq, offsets, ids);
-        RCB_LAUNCH_CHECK("k_nb_sort_long");
+        const unsigned g = (unsigned)std::min(kMaxGrid, sorts);
+        if (t->n <= kBitsMax) {
+            k_nb_sort_bits<<<g, kBlock, bits_lds(t->n), s>>>(sorts, longq, offsets, ids, (int)t->n);
+            RCB_LAUNCH_CHECK("k_nb_sort_bits");
+        } else {
+            k_nb_sort_long<<<g, kBlock, 0, s>>>(sorts, longq, offsets, ids);
+            RCB_LAUNCH_CHECK("k_nb_sort_long");
+        }
     }
     return RCB_OK;
 }
