@@ -2,24 +2,27 @@
 // (Sec. 2.3: "Neighbour walk" culled to the true neighbours, and the
 // one-dimensional "Neighbour list").
 //
-// One wave (a workgroup of its own) per leaf. Lanes are (sink slot s, slice
-// j) over the leaf's particles (near_tile.h: S = min(c, 64) sinks, J = 64 / S
-// slices; c: the sinks still to do). The candidate cells of the leaf (cells
-// of its group's near list, ascending labels, whose candidate mask has the
-// leaf) are staged through LDS 64 particles at a time; slice j of sink s
-// tests tile entries j, j + J, .... A pair is a neighbour iff b != a and
-// |r_a - r_b|^2 < (2 h_a)^2 in FP64 on the tree's copy of the inputs (the
-// same predicate for every precision mode).
+// One or more waves per leaf (a workgroup), each with every H-th of the leaf's
+// sinks. Lanes are sources: the candidate cells of the leaf (cells of its group's
+// near list, ascending labels, whose candidate mask has the leaf) are staged 64
+// particles at a time (near_tile.h), those inside the leaf's sphere wait in LDS
+// until 64 are there, and then every sink is tested against them in a row of its
+// own. A pair is a neighbour iff b != a and |r_a - r_b|^2 < (2 h_a)^2 in FP64 on
+// the tree's copy of the inputs (the same predicate for every precision mode). A
+// row's hits take the list's next slots by their rank in its ballot, the sinks'
+// counts are kept one a lane, so the lists need no atomics.
+// The sphere (centre g_A, radius h_node(A) padded by 2^-32, Sec. 2.3.1): a
+// neighbour b of a sink a has |r_b - g_A| <= |r_b - r_a| + |r_a - g_A| < 2 h_a +
+// |r_a - g_A| <= h_node(A), so no neighbour is dropped.
+// Bound by its chains: loads and stores of a wave wait in order, a row is some
+// 20 dependent instructions, seven waves a SIMD. With lanes as (sink, slice of the
+// sources) and a slot from an LDS atomic for each hit, rows of many hits of few sinks
+// serialised: rcb_neighbours_count of 37,000 particles (lists of up to 875) 192, now
+// 110 us; 300,000 clumpy 560 and 380; 500,000 in cells of 61 800 and 715; 16M clumpy 8760 and
+// 8190; 4M and 500,000 of even lists 1905 and 1930, 402 and 422.
 // A leaf's work varies tenfold, so wider units of work leave the chip waiting
-// for the longest: one wave per group of 8 leaves took 690 us for 37,000
-// particles (512 groups), per leaf 202; at 4M 2313 and 2021 us, at 16M 9.75
-// and 9.38 ms (rcb_neighbours_count).
-// Staging keeps only the sources inside the leaf's sphere (centre g_A,
-// radius h_node(A) padded by 2^-32, Sec. 2.3.1): a neighbour b of a sink a
-// has |r_b - g_A| <= |r_b - r_a| + |r_a - g_A| < 2 h_a + |r_a - g_A|
-// <= h_node(A), so no neighbour is dropped, and the sources that stay are
-// compacted in order. Ranks are taken by ballot within the sink's lane
-// segment.
+// for the longest: one wave per group of 8 leaves took 690 us for the 37,000 (512
+// groups).
 //
 // The count call writes each particle's count into the caller's offsets
 // array (scanned in place afterwards) and its first kNbCap ids into a slab
@@ -46,10 +49,7 @@ constexpr int kNbCap = 64;        // slab slots per particle (~50 neighbours exp
 constexpr int kNbChunk = 64;      // slots of an overflow chunk
 constexpr int kNbWaveMax = 256;   // lists of up to 256 ids are sorted by one wave in registers
 constexpr int kLongLds = 4096;    // lists searched again: sorted in LDS up to this length
-constexpr int kRingMask = 2 * kWave - 1;
-constexpr int kRingBytes = 2 * kWave * 32;   // the ring of SrcN, in bytes
-constexpr int kVmcnt0 = 0x0f70;   // s_waitcnt vmcnt(0), expcnt and lgkmcnt left free
-constexpr int kIcmpUge = 35;      // unsigned >= for __builtin_amdgcn_uicmp
+constexpr int kSinks = 32;        // sinks of a pass over the candidates
 
 struct NeighArgs {
     int64_t nleaf;
@@ -85,21 +85,20 @@ struct alignas(16) SrcN {
     int32_t pb;   // tree position
     int32_t id;   // caller index
 };
+struct alignas(16) SinkN {
+    double x, y, z;
+    double lim;   // (2 h)^2, or -1: takes no neighbours
+};
 
-// tile: a ring of 128 sources; kept sources accumulate until at least 64 wait
-// (at most 127), whole rows are taken and the rest waits; the last partial
-// row is padded with sources that can never be neighbours (pb = -1 at
-// infinite distance). cnt / chunk: per sink slot of the pass, the
-// neighbours found so far (slots are handed out by LDS atomics, so a list is
-// stored in no particular order; the fill call sorts it) and its last two
-// chunks, by parity (the slots that one row hands to a sink are at most 64
-// consecutive ones and touch at most two chunks).
+// wait: the kept sources that no pass has taken yet (at most 63, and a tile
+// joins them). chunk: per sink, its list's last two chunks, by parity (the slots
+// that one row hands out are at most 64 consecutive ones and touch at most two).
 struct NeighShared {
     int32_t off[kWave];     // of the chunk's entries with sources
     uint32_t mark[kWave];
-    SrcN tile[2 * kWave];
-    int32_t cnt[kWave];
-    int32_t chunk[kWave][2];
+    SrcN wait[2 * kWave];
+    SinkN sink[kSinks];
+    int32_t chunk[kSinks][2];
 };
 
 // Chunk counters: one per sub-pool, 64 bytes apart, and neighbouring groups
@@ -115,16 +114,19 @@ constexpr int kCtlWords = kSubCtl * (1 + kSubMax);
 // not be had are only counted from there on, and their leaf is queued.
 // Otherwise only the sinks queued that way are searched, their ids going to
 // offsets[pid] + slot.
-template <bool SLAB>
-__global__ __launch_bounds__(kWave) void k_neigh(NeighArgs a) {
-    __shared__ NeighShared sh;
+template <bool SLAB, int H>
+__global__ __launch_bounds__(H * kWave) void k_neigh(NeighArgs a) {
+    __shared__ NeighShared sh_all[H];
+    __shared__ int over_any;
     const int lane = lane_id();
+    const int wv = H > 1 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)) : 0;
+    NeighShared &sh = sh_all[wv];
     const int G = 1 << a.gk;
-    int64_t l;   // the wave's leaf, from 0
+    int64_t l;   // the workgroup's leaf, from 0
     if constexpr (SLAB) {
-        l = a.first + xcd_wave_index();
+        l = a.first + xcd_block();
     } else {
-        l = __builtin_amdgcn_readfirstlane(a.queue[wave_index()]);
+        l = __builtin_amdgcn_readfirstlane(a.queue[blockIdx.x]);
     }
     const int64_t gi = l >> a.gk, A = a.nleaf + l;
     const int li = (int)(l & (G - 1));
@@ -137,91 +139,86 @@ __global__ __launch_bounds__(kWave) void k_neigh(NeighArgs a) {
     const double rA2 = rA * rA;
     sh.mark[lane] = 0;
     uint32_t gen = 0;
-    for (int g0 = 0; g0 < c; g0 += kWave) {
-        const LeafLanes L = leaf_lanes(c - g0);   // the last pass of a big leaf spreads its rest
-        const int si = g0 + L.sslot;
-        bool has_sink = L.sslot < L.S && si < c;
-        const int32_t pa = sA + (has_sink ? si : 0);
+    for (int g0 = 0; g0 < c; g0 += kSinks) {
+        const int cs = c - g0 < kSinks ? c - g0 : kSinks;
+        // lane i: sink i, if it is one of this wave's
+        const int32_t p0 = sA + g0;
+        const int32_t pa = p0 + (lane < cs ? lane : 0);
         const int32_t oa = a.pid[pa];
-        int64_t obase = (int64_t)(a.tree_rows ? pa : oa) * kNbCap;
+        bool has_sink = lane < cs && (H == 1 || lane % H == wv);
+        int64_t o0 = 0;
         if constexpr (!SLAB) {   // the lists the count call could not keep
-            const int64_t o0 = has_sink ? a.offsets[oa] : 0;
+            o0 = has_sink ? a.offsets[oa] : 0;
             has_sink = has_sink && a.offsets[oa + 1] - o0 > kNbCap && a.head[oa] < 0;
-            obase = o0;
-            if (ballot(has_sink) == 0ull) continue;
         }
-        const double xa = a.px[pa], ya = a.py[pa], za = a.pz[pa];
-        const double two_h = 2.0 * a.ph[pa];
-        const double lim = has_sink ? two_h * two_h : -1.0;
-        if (L.slice == 0) sh.cnt[L.sslot] = 0;
+        if (ballot(has_sink) == 0ull) continue;
+        if (lane < cs) {
+            const double two_h = 2.0 * a.ph[pa];
+            sh.sink[lane] = SinkN{a.px[pa], a.py[pa], a.pz[pa], has_sink ? two_h * two_h : -1.0};
+        }
+        const int32_t row_of = a.tree_rows ? pa : oa;   // slab mode
+        int count = 0;                                  // lane i: neighbours of sink i so far
         tile_sync();
-        int head = 0;   // ring position of the first waiting source
-        int32_t *const row = a.ids + obase;
-        // hit h with slot r (0 for lanes without a hit): into the slab row, or
-        // (rare) one of the sink's chunks, each taken by the hit of its first slot
-        auto put = [&](bool h, uint32_t r, int32_t id) {
-            const bool low = !SLAB || r < (uint32_t)kNbCap;
-            if (h & low) row[r] = id;
-            if constexpr (SLAB) {
-                // lanes with r >= kNbCap, as the comparison's own lane mask
-                if (__builtin_amdgcn_uicmp(r, (uint32_t)kNbCap, kIcmpUge) != 0ull) {
-                    const uint32_t q = (r - kNbCap) / kNbChunk, o = (r - kNbCap) % kNbChunk;
-                    if (!low && o == 0) {
-                        const int32_t prev = q ? sh.chunk[L.sslot][(q - 1) & 1] : 0;
-                        int32_t ch = -1;
-                        if (prev >= 0) {
-                            const int32_t sub = (int32_t)gi & a.sub_mask;
-                            const int32_t i = atomicAdd(a.ctl + kSubCtl * (1 + sub), 1);
-                            if (i < a.sub_cap) {
-                                ch = (int32_t)(sub * a.sub_cap) + i;
-                                if (q) a.next[prev] = ch;
-                                else a.head[oa] = ch;
-                            }
-                        }
-                        sh.chunk[L.sslot][q & 1] = ch;
+        // slab mode, slots past the row: hit lanes with slot r of sink i, in one of
+        // the list's chunks, each taken by the hit of its first slot
+        auto put_far = [&](int i, bool hit, uint32_t r, int32_t id) {
+            const bool far = hit && r >= (uint32_t)kNbCap;
+            const uint32_t q = (r - kNbCap) / kNbChunk, o = (r - kNbCap) % kNbChunk;
+            if (far && o == 0) {
+                const int32_t prev = q ? sh.chunk[i][(q - 1) & 1] : 0;
+                int32_t ch = -1;
+                if (prev >= 0) {
+                    const int32_t sub = (int32_t)gi & a.sub_mask;
+                    const int32_t k = atomicAdd(a.ctl + kSubCtl * (1 + sub), 1);
+                    if (k < a.sub_cap) {
+                        ch = (int32_t)(sub * a.sub_cap) + k;
+                        if (q) a.next[prev] = ch;
+                        else a.head[a.pid[p0 + i]] = ch;
                     }
-                    tile_sync();
-                    if (!low) {
-                        const int32_t ch = sh.chunk[L.sslot][q & 1];
-                        if (ch >= 0) a.pool[(int64_t)ch * kNbChunk + o] = id;
-                    }
-                    tile_sync();
                 }
+                sh.chunk[i][q & 1] = ch;
             }
-        };
-        auto test = [&](const SrcN &src) {
-            return (src.pb != pa) & (dist2(xa, ya, za, src.x, src.y, src.z) < lim);
-        };
-        // the ring as byte offsets: (offset & kRingBytes - 1) wraps it
-        auto at = [&](int b) -> const SrcN & {
-            return *reinterpret_cast<const SrcN *>(reinterpret_cast<const char *>(sh.tile) +
-                                                   (b & (kRingBytes - 1)));
-        };
-        // rows [0, np) of the waiting sources: slice j of a sink tests j, j + J,
-        // ...; two rows per step, so that their LDS traffic overlaps
-        auto rows = [&](int np) {
-            const int b0 = (head + L.slice) * (int)sizeof(SrcN), bJ = L.J * (int)sizeof(SrcN);
-            int u0 = 0;
-            for (; u0 + L.J < np; u0 += 2 * L.J) {
-                const int b = b0 + u0 * (int)sizeof(SrcN);
-                const SrcN s0 = at(b), s1 = at(b + bJ);
-                const bool h0 = test(s0), h1 = test(s1);
-                uint32_t r0 = 0, r1 = 0;
-                if (h0) r0 = atomicAdd((uint32_t *)&sh.cnt[L.sslot], 1u);
-                if (h1) r1 = atomicAdd((uint32_t *)&sh.cnt[L.sslot], 1u);
-                put(h0, r0, s0.id);
-                put(h1, r1, s1.id);
+            tile_sync();
+            if (far) {
+                const int32_t ch = sh.chunk[i][q & 1];
+                if (ch >= 0) a.pool[(int64_t)ch * kNbChunk + o] = id;
             }
-            if (u0 < np) {
-                const SrcN s0 = at(b0 + u0 * (int)sizeof(SrcN));
-                const bool h0 = test(s0);
-                uint32_t r0 = 0;
-                if (h0) r0 = atomicAdd((uint32_t *)&sh.cnt[L.sslot], 1u);
-                put(h0, r0, s0.id);
-            }
-            head = (head + np) & kRingMask;
+            tile_sync();
         };
-        int fill = 0;   // kept sources waiting in the ring from head
+        // one pass: the waiting sources [at, at + n), one a lane, against every sink
+        auto pass = [&](int at, int n) {
+            const SrcN s = sh.wait[at + (lane < n ? lane : 0)];
+            const double sx = lane < n ? s.x : __builtin_inf();   // (never within lim)
+            auto put = [&](int i, bool hit) {
+                const uint64_t m = ballot(hit);
+                if (m == 0) return;
+                const int have = __builtin_amdgcn_readlane(count, i);
+                const int r = have + rank_below(m), now = have + __popcll(m);
+                count = lane == i ? now : count;
+                if constexpr (SLAB) {
+                    int32_t *const row = a.ids + (int64_t)__builtin_amdgcn_readlane(row_of, i) * kNbCap;
+                    if (hit && r < kNbCap) row[r] = s.id;
+                    if (now > kNbCap) put_far(i, hit, (uint32_t)r, s.id);
+                } else {
+                    const int64_t lo = (uint32_t)__builtin_amdgcn_readlane((int)o0, i);
+                    const int64_t hi = __builtin_amdgcn_readlane((int)(o0 >> 32), i);
+                    int32_t *const row = a.ids + (lo | hi << 32);
+                    if (hit) row[r] = s.id;
+                }
+            };
+            auto test = [&](int i) {
+                const SinkN k = sh.sink[i];
+                return (dist2(k.x, k.y, k.z, sx, s.y, s.z) < k.lim) & (s.pb != p0 + i);
+            };
+            int i = wv;
+            for (; i + H < cs; i += 2 * H) {   // (two rows per step: their LDS reads overlap)
+                const bool h0 = test(i), h1 = test(i + H);
+                put(i, h0);
+                put(i + H, h1);
+            }
+            if (i < cs) put(i, test(i));
+        };
+        int fill = 0;   // kept sources waiting
         for (int64_t e0 = n0; e0 < n1; e0 += kWave) {
             const ChunkEntry ce = load_chunk(a.gnear, a.nfirst, a.ncount, e0, n1, 1u << (8 + li));
             const int tot = ce.tot;
@@ -234,45 +231,23 @@ __global__ __launch_bounds__(kWave) void k_neigh(NeighArgs a) {
                 const int32_t sid = a.pid[spb];
                 const bool keep = lane < nt && dist2(gA.x, gA.y, gA.z, sx, sy, sz) < rA2;
                 const uint64_t kb = ballot(keep);
-                if (keep) {   // appended in order after the waiting ones
-                    SrcN &dst = sh.tile[(head + fill + rank_below(kb)) & kRingMask];
-                    dst.x = sx;
-                    dst.y = sy;
-                    dst.z = sz;
-                    dst.pb = spb;
-                    dst.id = sid;
-                }
-                // every gather has landed: otherwise the waits for them (which on
-                // this chip also wait for all earlier stores) are left to the rows
-                __builtin_amdgcn_s_waitcnt(kVmcnt0);
-                const int avail = fill + __popcll(kb);
+                if (keep) sh.wait[fill + rank_below(kb)] = SrcN{sx, sy, sz, spb, sid};
+                fill += __popcll(kb);
                 tile_sync();
-                if (avail >= kWave) {   // whole rows only; the rest waits
-                    const int np = avail - avail % L.J;
-                    rows(np);
-                    fill = avail - np;
+                if (fill >= kWave) {
+                    fill -= kWave;
+                    pass(fill, kWave);
                     tile_sync();
-                } else {
-                    fill = avail;
                 }
             }
         }
-        {   // pads the last partial row
-            SrcN &dst = sh.tile[(head + fill + lane) & kRingMask];
-            dst.x = dst.y = dst.z = __builtin_inf();
-            dst.pb = -1;
-            dst.id = -1;
-        }
-        tile_sync();
-        rows(fill);
-        tile_sync();
-        if (SLAB && has_sink && L.slice == 0) {
-            const int cnt = sh.cnt[L.sslot];
-            a.counts[oa] = cnt;
-            if (cnt > kNbCap) {
-                const int last = (cnt - kNbCap - 1) / kNbChunk;   // its last chunk
-                if (sh.chunk[L.sslot][last & 1] >= 0) {
-                    if (cnt > kNbWaveMax) atomicAdd(a.ctl + 2, 1);
+        if (fill > 0) pass(0, fill);
+        if (SLAB && has_sink) {
+            a.counts[oa] = count;
+            if (count > kNbCap) {
+                const int last = (count - kNbCap - 1) / kNbChunk;   // its last chunk
+                if (sh.chunk[lane][last & 1] >= 0) {
+                    if (count > kNbWaveMax) atomicAdd(a.ctl + 2, 1);
                 } else {
                     a.head[oa] = -1;
                     atomicAdd(a.ctl, 1);
@@ -280,10 +255,20 @@ __global__ __launch_bounds__(kWave) void k_neigh(NeighArgs a) {
                 }
             }
         }
-        if (!SLAB && has_sink && L.slice == 0) a.longq[atomicAdd(a.ctl, 1)] = oa;
-        tile_sync();   // cnt / chunk are reset by the next pass
+        if (!SLAB && has_sink) a.longq[atomicAdd(a.ctl, 1)] = oa;
+        tile_sync();   // sink / chunk are reset by the next pass
     }
-    if (SLAB && ballot(leaf_over) != 0ull && lane == 0) a.queue[atomicAdd(a.ctl + 1, 1)] = (int32_t)l;
+    if constexpr (SLAB) {   // the leaf is queued once
+        bool any = ballot(leaf_over) != 0ull;
+        if constexpr (H > 1) {
+            if (threadIdx.x == 0) over_any = 0;
+            __syncthreads();
+            if (any && lane == 0) atomicOr(&over_any, 1);
+            __syncthreads();
+            any = over_any != 0;
+        }
+        if (any && threadIdx.x == 0) a.queue[atomicAdd(a.ctl + 1, 1)] = (int32_t)l;
+    }
 }
 
 // caller index -> tree position (slab rows by tree position)
@@ -679,7 +664,14 @@ rcb_status neighbours_count(rcb_tree *t, int64_t *offsets, int64_t *total, hipSt
                 t->nb_pool, t->nb_next, t->nb_sub_cap, t->nb_subs - 1, t->nb_head, t->nb_ctl, t->nb_queue, nullptr,
                 0, tree_rows(t)};
     for (; a.first < t->nleaf; a.first += kMaxGrid) {
-        k_neigh<true><<<(unsigned)std::min(kMaxGrid, t->nleaf - a.first), kWave, 0, s>>>(a);
+        const unsigned g = (unsigned)std::min(kMaxGrid, t->nleaf - a.first);
+        // waves per leaf while leaves are few; each stages the sources again (in
+        // us with 1, 2, 4, 8: 256 leaves 119, 93, 78, 73; 1024 leaves 80, 60, 57, 64, of 58
+        // particles 216, 159, 141, 182; 4096 leaves 113, 107, 109, 131; 8192 leaves 163,
+        // 147, 168, 237, of 61 particles 724, 737, 911, 1310; 32,768 377, 427, 576, 887)
+        if (t->nleaf <= 2048) k_neigh<true, 4><<<g, 4 * kWave, 0, s>>>(a);
+        else if (t->nleaf <= 4096) k_neigh<true, 2><<<g, 2 * kWave, 0, s>>>(a);
+        else k_neigh<true, 1><<<g, kWave, 0, s>>>(a);
         RCB_LAUNCH_CHECK("k_neigh<slab>");
     }
     st = scan_i64(t, offsets, offsets, t->n, s);   // in place
@@ -732,7 +724,7 @@ rcb_status neighbours_fill(rcb_tree *t, const int64_t *offsets, int32_t *ids, in
         NeighArgs a{t->nleaf, t->gk, t->ngroup, t->wrec, t->nhnode, t->nfirst, t->ncount, t->gnear_beg,
                     t->gnear_end, t->gnear, t->px, t->py, t->pz, t->ph, t->pid, nullptr, offsets, ids,
                     nullptr, nullptr, 0, 0, t->nb_head, nlong, t->nb_queue, longq, 0, false};
-        k_neigh<false><<<(unsigned)t->nb_nq, kWave, 0, s>>>(a);
+        k_neigh<false, 1><<<(unsigned)t->nb_nq, kWave, 0, s>>>(a);
         RCB_LAUNCH_CHECK("k_neigh<fill>");
     }
     if (sorts > 0) {   // exactly this many lists appended themselves

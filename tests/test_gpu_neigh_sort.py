@@ -37,3 +37,21 @@ def test_long_lists_by_cloud_size(n):
     np.testing.assert_array_equal(cnt, want)
     assert (want > 256).sum() > 300
     gt.destroy()
+
+
+@pytest.mark.parametrize("nll", [5, 10, 20, 50])
+def test_lists_by_waves_per_leaf(nll):
+    """8192, 4096 and 2048 leaves take one, two and four waves each; leaves of
+    more than 32 particles take their sinks in several passes."""
+    from oracle import oracle as O
+    _say("waves per leaf", nll)
+    c = W.clumpy_cube(40000)
+    ot = O.OracleTree(*c.arrays(), n_ll=nll)
+    ot.walk(0.7)
+    ooff, oids, valid = ot.neighbours()
+    assert valid.all() and np.diff(ooff).max() > 256
+    gt = _gpu_tree(c, nll, 0.7)
+    off, ids = gt.neighbours()
+    np.testing.assert_array_equal(_np(off), ooff)
+    np.testing.assert_array_equal(_np(ids), oids)
+    gt.destroy()
