@@ -1379,25 +1379,23 @@ __device__ __forceinline__ void fill_empty_subtree(const NodeOut o, int64_t E, i
 // split and the stable partition of the node's elements in LDS (in place:
 // the pass's nodes are read completely before any element moves); the
 // children's ranges and boxes go to their LDS slots.
-// Sum and max over the GW lanes of this lane's group, GW a run-time power
-// of two (as group_sum / group_max)
-__device__ __forceinline__ double gsum(double v, int GW) {
-    if (GW > 1) v = pair_sum<1>(v);
-    if (GW > 2) v = pair_sum<2>(v);
-    if (GW > 4) v = pair_sum<4>(v);
-    if (GW > 8) v = pair_sum<8>(v);
-    if (GW > 16) v = pair_sum<16>(v);
-    if (GW > 32) v = pair_sum<32>(v);
-    return v;
+// v summed and mx maximised over the GW lanes of this lane's group, GW a
+// run-time power of two (as group_sum / group_max), all in one cascade: a
+// branch a step and not a value, and N + 1 independent chains
+template <int O, int N>
+__device__ __forceinline__ void gstep(double (&v)[N], double &mx, int GW) {
+    if constexpr (O < kWave) {
+        if (GW > O) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) v[i] = pair_sum<O>(v[i]);
+            mx = pair_max<O>(mx);
+            gstep<2 * O, N>(v, mx, GW);
+        }
+    }
 }
-__device__ __forceinline__ double gmax(double v, int GW) {
-    if (GW > 1) v = pair_max<1>(v);
-    if (GW > 2) v = pair_max<2>(v);
-    if (GW > 4) v = pair_max<4>(v);
-    if (GW > 8) v = pair_max<8>(v);
-    if (GW > 16) v = pair_max<16>(v);
-    if (GW > 32) v = pair_max<32>(v);
-    return v;
+template <int N>
+__device__ __forceinline__ void gsums(double (&v)[N], double &mx, int GW) {
+    gstep<1, N>(v, mx, GW);
 }
 
 template <int W>
@@ -1412,6 +1410,7 @@ __device__ __forceinline__ void sub_pass(const NodeOut o, int k, const double *_
     const int slot = nd - 1 + (j < nd ? j : 0);
     const int cj = j < nd ? sh.count[slot] : 0;
     const int c = cj <= kChunk ? cj : 0;   // (larger ones: sub_big)
+    if (ballot(c > 0) == 0ull) return;
     const bool valid = c > 0;
     const int f = sh.first[slot];
     const int64_t lab = (R0 << d) + j;
@@ -1459,9 +1458,10 @@ __device__ __forceinline__ void sub_pass(const NodeOut o, int k, const double *_
         for (int q = 0; q < 4; ++q) {
             const double a0 = (v[0][q] + v[1][q]) + (v[2][q] + v[3][q]);
             const double b0 = (v[4][q] + v[5][q]) + (v[6][q] + v[7][q]);
-            sa[q] = gsum(a0 + b0, GW);
+            sa[q] = a0 + b0;
         }
-        mx = gmax(ml, GW);
+        mx = ml;
+        gsums(sa, mx, GW);
     }
     const double M = sa[0] + 0.0;
     double com[3];
@@ -1487,10 +1487,7 @@ __device__ __forceinline__ void sub_pass(const NodeOut o, int k, const double *_
             const double far = fmax(ml, sqrt(dist2(X[t], Y[t], Z[t], g[0], g[1], g[2])) + 2.0 * H[t]);
             ml = valid && 8 * gl + t < c ? far : ml;
         }
-#pragma unroll
-        for (int t = 0; t < 8; ++t)
-            if (valid && 8 * gl + t < c) ph[s0 + f + 8 * gl + t] = H[t];
-        const double hn = gmax(ml, GW);
+        double sq[6];
 #pragma unroll
         for (int q = 0; q < 6; ++q) {
             double v[8];
@@ -1504,19 +1501,25 @@ __device__ __forceinline__ void sub_pass(const NodeOut o, int k, const double *_
                                : q == 3 ? (m3 * d1) * d1 - mr2 : q == 4 ? (m3 * d1) * d2 : (m3 * d2) * d2 - mr2;
                 v[t] = valid ? u : 0.0;   // (a lane without a node has no centre of mass)
             }
-            const double sq = gsum(((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7])), GW) + 0.0;
-            if (lead) {
-                o.nQ[6 * lab + q] = sq;
-                sh.q[slot][q] = sq;
-            }
+            sq[q] = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
         }
-        if (lead) o.nhnode[lab] = hn;
-        if (fd) {   // mixed form: FP32 offsets from the leaf's centre of mass
+        double hn = ml;
+        gsums(sq, hn, GW);
+        if (lead) {
 #pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                const int e = 8 * gl + t;
-                if (valid && e < c) {
-                    const int64_t i = s0 + f + e;
+            for (int q = 0; q < 6; ++q) {
+                sh.q[slot][q] = sq[q] + 0.0;
+                o.nQ[6 * lab + q] = sq[q] + 0.0;
+            }
+            o.nhnode[lab] = hn;
+        }
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const int e = 8 * gl + t;
+            if (valid && e < c) {
+                const int64_t i = s0 + f + e;
+                ph[i] = H[t];
+                if (fd) {   // mixed form: FP32 offsets from the leaf's centre of mass
                     fd[i] = make_float4((float)(X[t] - com[0]), (float)(Y[t] - com[1]), (float)(Z[t] - com[2]),
                                         (float)Mm[t]);
                     fh[i] = (float)H[t];
@@ -1541,16 +1544,11 @@ __device__ __forceinline__ void sub_pass(const NodeOut o, int k, const double *_
         if (valid && 8 * gl + t < c && xv < plane) lb |= 1u << t;
     }
     const int nl = __popc(lb);
-    int incl = nl;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        if (off < GW) {
-            const int y = __shfl_up(incl, off, kWave);
-            if (gl >= off) incl += y;
-        }
-    }
-    const int excl = incl - nl;
-    const int nleft = __shfl(incl, gslot * GW + GW - 1, kWave);
+    // the lefts before this lane in its group, and the group's
+    const int incl = wave_incl_scan(nl);
+    const int before = __shfl(incl - nl, gslot * GW, kWave);
+    const int excl = incl - nl - before;
+    const int nleft = __shfl(incl, gslot * GW + GW - 1, kWave) - before;
     int dst[8];
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
