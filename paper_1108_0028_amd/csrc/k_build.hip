@@ -1321,6 +1321,9 @@ struct SubLds {
     double part[W][12];
     int32_t left[W];
     int32_t next;   // the next root's queue slot
+    // a packed level: each lane's node and the logarithm of its lanes
+    uint16_t map[2 * S::threads];
+    int32_t lanes;   // lanes taken
 };
 
 // Particle e of the subtree, or zeros (no branch: a load under a condition of
@@ -1382,31 +1385,39 @@ __device__ __forceinline__ void fill_empty_subtree(const NodeOut o, int64_t E, i
 // v summed and mx maximised over the GW lanes of this lane's group, GW a
 // run-time power of two (as group_sum / group_max), all in one cascade: a
 // branch a step and not a value, and N + 1 independent chains
-template <int O, int N>
-__device__ __forceinline__ void gstep(double (&v)[N], double &mx, int GW) {
+// PACKED: GW differs between the lanes' groups, at most gmax.
+template <bool PACKED, int O, int N>
+__device__ __forceinline__ void gstep(double (&v)[N], double &mx, int GW, int gmax) {
     if constexpr (O < kWave) {
-        if (GW > O) {
+        if (gmax > O) {
+            const bool in = !PACKED || GW > O;
 #pragma unroll
-            for (int i = 0; i < N; ++i) v[i] = pair_sum<O>(v[i]);
-            mx = pair_max<O>(mx);
-            gstep<2 * O, N>(v, mx, GW);
+            for (int i = 0; i < N; ++i) {
+                const double w = pair_sum<O>(v[i]);
+                v[i] = in ? w : v[i];
+            }
+            const double m = pair_max<O>(mx);
+            mx = in ? m : mx;
+            gstep<PACKED, 2 * O, N>(v, mx, GW, gmax);
         }
     }
 }
-template <int N>
-__device__ __forceinline__ void gsums(double (&v)[N], double &mx, int GW) {
-    gstep<1, N>(v, mx, GW);
+template <bool PACKED, int N>
+__device__ __forceinline__ void gsums(double (&v)[N], double &mx, int GW, int gmax) {
+    gstep<PACKED, 1, N>(v, mx, GW, gmax);
 }
 
-template <int W>
+// j: this lane's node (nd: none), GW lanes of it (gmax: the most of any; not
+// PACKED: the same for all)
+template <bool PACKED, int W>
 __device__ __forceinline__ void sub_pass(const NodeOut o, int k, const double *__restrict__ hin,
-                                         double *__restrict__ ph, SubLds<W> &sh, int64_t R0, int d, int p,
-                                         int lvl, int64_t s0, float4 *fd, float *fh, const int GW) {
+                                         double *__restrict__ ph, SubLds<W> &sh, int64_t R0, int d, int j,
+                                         int lvl, int64_t s0, float4 *fd, float *fh, const int GW,
+                                         const int gmax) {
     const bool leaf = lvl == k;
     const int lane = lane_id();
-    const int gslot = lane / GW, gl = lane % GW;
+    const int gl = lane & (GW - 1), gstart = lane - gl;
     const int nd = 1 << d;
-    const int j = p + gslot;
     const int slot = nd - 1 + (j < nd ? j : 0);
     const int cj = j < nd ? sh.count[slot] : 0;
     const int c = cj <= kChunk ? cj : 0;   // (larger ones: sub_big)
@@ -1461,7 +1472,7 @@ __device__ __forceinline__ void sub_pass(const NodeOut o, int k, const double *_
             sa[q] = a0 + b0;
         }
         mx = ml;
-        gsums(sa, mx, GW);
+        gsums<PACKED>(sa, mx, GW, gmax);
     }
     const double M = sa[0] + 0.0;
     double com[3];
@@ -1504,7 +1515,7 @@ __device__ __forceinline__ void sub_pass(const NodeOut o, int k, const double *_
             sq[q] = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
         }
         double hn = ml;
-        gsums(sq, hn, GW);
+        gsums<PACKED>(sq, hn, GW, gmax);
         if (lead) {
 #pragma unroll
             for (int q = 0; q < 6; ++q) {
@@ -1546,9 +1557,9 @@ __device__ __forceinline__ void sub_pass(const NodeOut o, int k, const double *_
     const int nl = __popc(lb);
     // the lefts before this lane in its group, and the group's
     const int incl = wave_incl_scan(nl);
-    const int before = __shfl(incl - nl, gslot * GW, kWave);
+    const int before = __shfl(incl - nl, gstart, kWave);
     const int excl = incl - nl - before;
-    const int nleft = __shfl(incl, gslot * GW + GW - 1, kWave) - before;
+    const int nleft = __shfl(incl, gstart + GW - 1, kWave) - before;
     int dst[8];
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
@@ -1776,6 +1787,55 @@ __device__ __forceinline__ void sub_big(const NodeOut o, int k, const double *__
     }
 }
 
+// Gives each node of a level of nd <= 256 nodes the lanes its size needs
+// (a power of two), the largest first, so that a group stays in its aligned
+// lanes: sh.map and sh.lanes, by wave 0. A level's rounds are otherwise those of
+// its largest node: 37,000 clustered particles 294 us, levels of more than two
+// rounds packed 277 (all of more than one 274, but 500,000 even ones 474 and 495: a
+// larger cloud's workgroups, of four waves, leave it).
+constexpr uint16_t kNoNode = 0xffff;
+template <int W>
+__device__ __forceinline__ void pack_level(SubLds<W> &sh, int nd, int wv) {
+    if (wv != 0) return;
+    constexpr int PER = SubSize<W>::leaves / kWave;   // nodes of a lane: consecutive ones
+    const int lane = lane_id();
+    int cl[PER];
+    // counts of the sizes 2^0 .. 2^2 lanes (10 bits each), and 2^3 .. 2^6 (8 bits each)
+    int w0 = 0, w1 = 0;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int j = PER * lane + u;
+        const int c = j < nd ? sh.count[nd - 1 + j] : 0;
+        const int need = (c + 7) >> 3;
+        cl[u] = c > 0 && c <= kChunk ? (need > 1 ? 32 - __clz(need - 1) : 0) : -1;
+        w0 += cl[u] >= 0 && cl[u] < 3 ? 1 << (10 * cl[u]) : 0;
+        w1 += cl[u] >= 3 ? 1 << (8 * (cl[u] - 3)) : 0;
+    }
+    const int i0 = wave_incl_scan(w0), i1 = wave_incl_scan(w1);
+    const int t0 = __builtin_amdgcn_readlane(i0, kWave - 1), t1 = __builtin_amdgcn_readlane(i1, kWave - 1);
+    int b0 = i0 - w0, b1 = i1 - w1;
+    int start[7], at = 0;   // first lane of each size
+#pragma unroll
+    for (int q = 6; q >= 0; --q) {
+        start[q] = at;
+        at += (q < 3 ? (t0 >> (10 * q)) & 1023 : (t1 >> (8 * (q - 3))) & 255) << q;
+    }
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        if (cl[u] < 0) continue;
+        int st = 0;
+#pragma unroll
+        for (int q = 0; q < 7; ++q)
+            st = cl[u] == q ? start[q] + ((q < 3 ? (b0 >> (10 * q)) & 1023 : (b1 >> (8 * (q - 3))) & 255) << q) : st;
+        b0 += cl[u] < 3 ? 1 << (10 * cl[u]) : 0;
+        b1 += cl[u] >= 3 ? 1 << (8 * (cl[u] - 3)) : 0;
+        for (int l = 0; l < 1 << cl[u]; ++l) sh.map[st + l] = (uint16_t)((PER * lane + u) << 3 | cl[u]);
+    }
+    const int pad = (at + kWave - 1) & ~(kWave - 1);
+    if (at + lane < pad) sh.map[at + lane] = kNoNode;
+    if (lane == 0) sh.lanes = pad;
+}
+
 // The next subtree root of a workgroup, fetched in four stages while it builds
 // the current one, so that each stage's memory latency hides under a
 // level of the current build: 0 takes a queue slot, 1 hands it to the other
@@ -1911,14 +1971,27 @@ __global__ __launch_bounds__(SubSize<W>::threads, 2) void k_subtree(SubArgs a, f
             const int gw = cm <= 8 ? 1 : cm <= 16 ? 2 : cm <= 32 ? 4 : cm <= 64 ? 8 : cm <= 128 ? 16
                          : cm <= 256 ? 32 : 64;
             const int npg = kWave / gw;
+            // more than two rounds for the largest node: each node its own lanes
+            const bool packed = W == 8 && nd > 2 * W * npg;
             float4 *f0 = lvl == k ? fd : nullptr;
             if (lvl < k)   // the next level's slots: -1 unless a non-empty parent sets them
                 for (int i = tid; i < 2 * nd; i += kThreads) sh.count[2 * nd - 1 + i] = -1;
             lds_barrier();
             if (cm > kChunk)
                 sub_big(o, k, hin, ph, sh, R0, d, lvl, s0, f0, fh);
-            for (int p = wv * npg; p < nd; p += W * npg)
-                sub_pass(o, k, hin, ph, sh, R0, d, p, lvl, s0, f0, fh, gw);
+            if (packed) {
+                pack_level(sh, nd, wv);
+                lds_barrier();
+                for (int u = wv * kWave; u < sh.lanes; u += W * kWave) {
+                    const uint16_t m = sh.map[u + lane];
+                    const bool none = m == kNoNode;
+                    sub_pass<true>(o, k, hin, ph, sh, R0, d, none ? nd : m >> 3, lvl, s0, f0, fh,
+                                   1 << (none ? 0 : m & 7), gw);
+                }
+            } else {
+                for (int p = wv * npg; p < nd; p += W * npg)
+                    sub_pass<false>(o, k, hin, ph, sh, R0, d, p + lane / gw, lvl, s0, f0, fh, gw, gw);
+            }
             if (nst < kSubStages) next_root_stage(a, nq, nst++, nx, sh);
             lds_barrier();
             if (lvl == k) break;

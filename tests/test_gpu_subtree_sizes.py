@@ -55,3 +55,20 @@ def test_subtree_rule(n, nll):
     gt = _gpu_tree(c, nll, 0.7)
     compare_trees(gt, ot)
     gt.destroy()
+
+
+@pytest.mark.parametrize("n,nll,sigma", [(2040, 8, 0.3), (2040, 8, 0.6), (2040, 8, 1.0), (2040, 8, 2.0), (5000, 6, 0.6)])
+def test_subtree_uneven(n, nll, sigma):
+    """Coordinates with a long tail: the nodes of a level hold from none to
+    hundreds of particles, and take lanes each to its size."""
+    _say("uneven", n, nll, sigma)
+    rng = np.random.default_rng(int(100 * sigma) + n)
+    x, y, z = np.exp(sigma * rng.normal(size=(3, n)))
+    c = W.Cloud("uneven", x, y, z, rng.uniform(0.5, 1.5, n) / n, rng.uniform(0.05, 0.15, n))
+    ot = O.OracleTree(*c.arrays(), n_ll=nll)
+    ot.walk(0.7)
+    for prec in ("fp64", "mixed"):
+        gt = _gpu_tree(c, nll, 0.7, prec)
+        compare_trees(gt, ot)
+        compare_lists(gt, ot)
+        gt.destroy()
