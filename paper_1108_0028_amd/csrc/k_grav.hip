@@ -392,10 +392,10 @@ GravArgs grav_args(const rcb_tree *t, void *ax, void *ay, void *az, double *farc
 // entries 1051, 986, 1073; 8192 of ~1700 entries 1021, 1040, 945; 16384 of ~3000
 // 3240, 3100, 3032; 65,536 of ~2100 entries 7160, 6862, 6907).
 template <bool RB>
-rcb_status launch_far(const rcb_tree *t, GravArgs g, hipStream_t s) {
+rcb_status launch_far(const rcb_tree *t, GravArgs g, int64_t g0, int64_t g1, hipStream_t s) {   // groups [g0, g1)
     const bool four = t->ngroup <= 2048 || (t->ngroup < 65536 && t->far_entries >= 1024 * t->ngroup);
-    for (g.first = 0; g.first < t->ngroup; g.first += kMaxGrid) {
-        const unsigned n = (unsigned)std::min(kMaxGrid, t->ngroup - g.first);
+    for (g.first = g0; g.first < g1; g.first += kMaxGrid) {
+        const unsigned n = (unsigned)std::min(kMaxGrid, g1 - g.first);
         if (four) k_far<RB, 4><<<n, 4 * kWave, 0, s>>>(g);
         else k_far<RB, 2><<<n, 2 * kWave, 0, s>>>(g);
         RCB_LAUNCH_CHECK("k_far");
@@ -408,9 +408,10 @@ rcb_status launch_far(const rcb_tree *t, GravArgs g, hipStream_t s) {
 // particles 1362, 1102, 988, 1000; 32,768 clumpy 629, 574, 570, 712; 131,072
 // 1887, 2000, 2072, 2607).
 template <bool MIXED>
-rcb_status launch_near(const rcb_tree *t, GravArgs g, hipStream_t s) {
-    for (g.first = 0; g.first < t->nleaf; g.first += kMaxGrid) {
-        const unsigned n = (unsigned)std::min(kMaxGrid, t->nleaf - g.first);
+rcb_status launch_near(const rcb_tree *t, GravArgs g, int64_t g0, int64_t g1, hipStream_t s) {   // of groups [g0, g1)
+    const int64_t end = g1 << t->gk;
+    for (g.first = g0 << t->gk; g.first < end; g.first += kMaxGrid) {
+        const unsigned n = (unsigned)std::min(kMaxGrid, end - g.first);
         if (t->nleaf <= 4096) k_near<MIXED, 8><<<n, 8 * kWave, 0, s>>>(g);
         else if (t->nleaf <= 16384) k_near<MIXED, 4><<<n, 4 * kWave, 0, s>>>(g);
         else if (t->nleaf <= 32768) k_near<MIXED, 2><<<n, 2 * kWave, 0, s>>>(g);
@@ -425,20 +426,35 @@ rcb_status launch_near(const rcb_tree *t, GravArgs g, hipStream_t s) {
 rcb_status far_coefficients(rcb_tree *t, double *out, hipStream_t s) {
     rcb_status st = ensure_walk(t, s);
     if (st != RCB_OK) return st;
-    return launch_far<false>(t, grav_args(t, nullptr, nullptr, nullptr, out), s);
+    return launch_far<false>(t, grav_args(t, nullptr, nullptr, nullptr, out), 0, t->ngroup, s);
 }
 
 rcb_status gravity(rcb_tree *t, void *ax, void *ay, void *az, hipStream_t s) {
     rcb_status st = ensure_walk(t, s);
     if (st != RCB_OK) return st;
     const bool rb = t->p.taylor_reading == RCB_READING_B;
-    if (!t->farc) t->farc = (double *)dalloc(t, sizeof(double) * kLeafC * t->nleaf, s, t->list_allocs);
-    if (!t->farc) return RCB_ENOMEM;
-    const GravArgs g = grav_args(t, ax, ay, az, t->farc);
-    st = rb ? launch_far<true>(t, g, s) : launch_far<false>(t, g, s);
-    if (st != RCB_OK) return st;
-    t->farc_valid = !rb;   // kept for a VJP on the same moments
-    return t->p.precision == RCB_MIXED ? launch_near<true>(t, g, s) : launch_near<false>(t, g, s);
+    const int64_t per_group = (int64_t)kLeafC << t->gk;   // doubles
+    // the far coefficients of all leaves, kept for a VJP on the same moments; if
+    // they cannot be had, of ranges of groups in turn
+    if (!t->farc) t->farc = (double *)dalloc(t, sizeof(double) * per_group * t->ngroup, s, t->list_allocs);
+    Scratch tmp(t, s);
+    double *buf = t->farc;
+    int64_t range = t->ngroup;
+    while (!buf && range > 1) {
+        range = (range + 7) / 8;
+        buf = (double *)dalloc(t, sizeof(double) * per_group * range, s, tmp);
+    }
+    if (!buf) return RCB_ENOMEM;
+    for (int64_t g0 = 0; g0 < t->ngroup; g0 += range) {
+        const int64_t g1 = std::min(g0 + range, t->ngroup);
+        const GravArgs g = grav_args(t, ax, ay, az, buf - per_group * g0);
+        st = rb ? launch_far<true>(t, g, g0, g1, s) : launch_far<false>(t, g, g0, g1, s);
+        if (st != RCB_OK) return st;
+        st = t->p.precision == RCB_MIXED ? launch_near<true>(t, g, g0, g1, s) : launch_near<false>(t, g, g0, g1, s);
+        if (st != RCB_OK) return st;
+    }
+    t->farc_valid = !rb && t->farc;
+    return RCB_OK;
 }
 
 }  // namespace rcb
