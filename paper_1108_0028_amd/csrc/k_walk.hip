@@ -238,6 +238,13 @@ __global__ __launch_bounds__(kBlock) void k_walk_group(WalkArgs w, const int32_t
 constexpr int kWQueue = 1024;    // powers of two
 constexpr int kWQueue2 = 4096;
 
+// the walk's flags (not [4] and [5], the build's) and totals, in one launch
+__global__ void k_walk_clear(int32_t *__restrict__ flags, unsigned long long *__restrict__ tot) {
+    const int i = threadIdx.x;
+    if (i < 4 || i == 6 || i == 7) flags[i] = 0;
+    if (i < 4) tot[i] = 0;
+}
+
 template <bool PURE, int QCAP, int WAVES>
 __global__ __launch_bounds__(WAVES * kWave) void k_walk_wide(WalkArgs w, int32_t *queue, int32_t *nqueue,
                                                              const int32_t *only, int64_t nonly, int cap) {
@@ -674,9 +681,8 @@ rcb_status ensure_walk(rcb_tree *t, hipStream_t s) {
         if (count_queues) return read_flags();
         return RCB_OK;
     };
-    RCB_ZERO(t->dflag, sizeof(int32_t) * 4, s);
-    RCB_ZERO(t->dflag + 6, sizeof(int32_t) * 2, s);
-    RCB_ZERO(tot, sizeof(unsigned long long) * 4, s);
+    k_walk_clear<<<1, kWave, 0, s>>>(t->dflag, tot);
+    RCB_LAUNCH_CHECK("k_walk_clear");
     rcb_status wst = walk_tiers(true);
     if (wst != RCB_OK) return wst;
     t->walk_requeued = nq;
