@@ -11,7 +11,7 @@ Prints ONE JSON line. Besides the contract fields: the FP64 form's
 throughput, the mixed form's error against the FP64 form, per-phase times
 (HIP events on the library's stream inside the timed region) with each
 phase's algorithmic work against its own bound, the roofline of the dominant
-kernel (k_gravity, one launch per step), the VJP's time against the
+kernels (k_far and k_near, one launch of each per step), the VJP's time against the
 forward's, the device memory a step holds, the force error against the
 direct sum on sampled particles, and the oracle's CPU baseline.
 """
@@ -314,17 +314,19 @@ def _rooflines(c, phases, prec, n, k):
     near_f = FLOP_P2P * c["pairs"] + FLOP_L2P * n
     far_f = FLOP_M2L * c["far_pairs"]
     g = alu(near_f if mixed else 0, far_f + (0 if mixed else near_f), phases["gravity"])
-    kname = "k_gravity<true, false>" if mixed else "k_gravity<false, false>"
-    g.update({"kernel": kname, "kernel_ms": phases["gravity"], "traffic": _profiled(kname),
+    kname = ["k_far<false, 2>", "k_near<true, 1>" if mixed else "k_near<false, 1>"]
+    traffic = [_profiled(k_) for k_ in kname]
+    g.update({"kernel": " + ".join(kname), "kernel_ms": phases["gravity"],
+              "traffic": None if None in traffic else sum(traffic),
               "basis": f"{FLOP_P2P} flop per near pair ({c['pairs']}), {FLOP_M2L} per far pair "
-                       f"({c['far_pairs']}), {FLOP_L2P} per sink ({n}); one launch per step, timed by "
-                       "HIP events on its stream"})
+                       f"({c['far_pairs']}), {FLOP_L2P} per sink ({n}); one launch of each per "
+                       "step, timed together by HIP events on their stream"})
     # build: compulsory HBM bytes N (48 k + 100) (each of the k levels reads
     # and writes the node's particle data and order; the leaf level, bounds,
     # gather and records the rest)
     b = hbm(n * (48 * k + 100), phases["build"])
     b["basis"] = f"N (48 k + 100) bytes, k = {k}"
-    b["traffic"] = {k_: _profiled(k_) for k_ in ("k_subtree", "k_scatter_classify", "k_chunk_reduce<0>",
+    b["traffic"] = {k_: _profiled(k_) for k_ in ("k_subtree<4>", "k_scatter_classify", "k_chunk_reduce<0>",
                                                  "k_part_count<false>", "k_part_count<true>")}
     # walk: FP64 tests of (node, visiting cell) pairs; also the node records it loads
     w = alu(0, FLOP_TEST * c["walk_tests"], phases["walk"])
@@ -341,7 +343,7 @@ def _rooflines(c, phases, prec, n, k):
     nb["hbm_frac"] = nbytes / (phases["neighbours"] * 1e-3) / (PEAK_HBM_GBS * 1e9)
     nb["basis"] = (f"{FLOP_CULL} FP64 flop per candidate pair ({c['cand_pairs']}); 28 B per candidate "
                    f"particle of a cell ({c['cand_particles']}), 12 B per neighbour id, 16 B per particle")
-    nb["traffic"] = {k_: _profiled(k_) for k_ in ("k_neigh<true>", "k_nb_compact", "k_nb_compact_long")}
+    nb["traffic"] = {k_: _profiled(k_) for k_ in ("k_neigh<true, 1>", "k_nb_compact")}
     g["counts"] = c
     return g, {"build": b, "walk": w, "neighbours": nb, "gravity": {k_: v for k_, v in g.items()
                                                                      if k_ != "counts"}}
@@ -366,7 +368,7 @@ def _vjp_timing(t, n, phases, prec):
     ms = ev[0].elapsed_time(ev[1]) / reps
     fwd = phases["build"] + phases["walk"] + phases["gravity"]
     far = "k_vjp_far<float, 0>" if prec == "mixed" else "k_vjp_far<double, 0>"
-    near = "k_vjp_near<true, true>" if prec == "mixed" else "k_vjp_near<false, true>"
+    near = "k_vjp_near<true, true, 1>" if prec == "mixed" else "k_vjp_near<false, true, 1>"
     return {"ms": ms, "forward_ms": fwd, "vjp_over_forward": ms / fwd,
             "basis": "forward = build + walk + gravity of the timed steps; the VJP reuses the tree, its "
                      "lists and the far coefficients kept by the gravity call",

@@ -38,7 +38,7 @@
  *    overlap.
  *  - Two environment variables select equivalent code paths, for tests:
  *    RCB_BUILD_LEVELS (any value) makes rcb_build() run every level as one
- *    device-wide pass instead of finishing small subtrees in one wave each
+ *    device-wide pass instead of finishing small subtrees in one workgroup each
  *    (same tree, bit for bit); RCB_WALK_WIDE_STACK=n caps the walk's
  *    first-tier node queue at n entries, so that more groups go to the later
  *    tiers (same lists); RCB_VJP_DET_RECOMPUTE (any value) makes the
@@ -245,10 +245,12 @@ rcb_status rcb_neighbours_count(rcb_tree *t, int64_t *offsets, int64_t *total, v
  *  offsets:  the array filled by rcb_neighbours_count() for this tree.
  *  ids:      device int32[capacity]; capacity >= total, else RCB_ECAPACITY.
  * The count call keeps each list in scratch owned by the tree (freed with
- * the interaction lists): a 64-slot row per particle (256 bytes) and, for
- * lists of up to 256, chunks of 64 slots from a pool of N/8 chunks (32 bytes
- * per particle); the cells holding a list that fit neither are searched
- * again here.
+ * the interaction lists): a 64-slot row per particle (256 bytes) and, past
+ * it, a chain of chunks of 64 slots from a pool of N/8 chunks (36 bytes per
+ * particle) and as many more as the walk's estimate of the neighbour counts
+ * asks for (at most 4 per particle; clouds of a few thousand particles get up to
+ * 16 MiB; the N/8 alone if the larger pool cannot be allocated). The cells
+ * holding a list for which the pool had no chunk left are searched again here.
  */
 rcb_status rcb_neighbours_fill(rcb_tree *t, const int64_t *offsets, int32_t *ids,
                                int64_t capacity, void *stream);
@@ -264,7 +266,8 @@ rcb_status rcb_neighbours_fill(rcb_tree *t, const int64_t *offsets, int32_t *ids
  * parts only). ax, ay, az: n values, FP64 for RCB_FP64, FP32 for RCB_MIXED.
  * The tree keeps f_A, J_A, H_A of every lowest-level cell (22 doubles per
  * cell, allocated on the first call) for a later rcb_gravity_vjp on the same
- * moments; rcb_refresh discards them.
+ * moments; rcb_refresh discards them. If they cannot be allocated, ranges of
+ * cells are taken in turn with a smaller buffer, and nothing is kept.
  */
 rcb_status rcb_gravity(rcb_tree *t, void *ax, void *ay, void *az, void *stream);
 
@@ -302,7 +305,7 @@ typedef struct {
     int64_t far_total;
     double theta;
     int64_t walk_requeued; /* groups of 8 lowest-level cells whose walk outgrew the first
-                              FIFO (1024 nodes) and was redone with a larger one or, past
+                              FIFO (2048 nodes) and was redone with a larger one or, past
                               8192 nodes, by the 8-wide walk (same lists); -1 before the walk */
     int64_t walk_nodes;    /* node records the breadth-first walk loaded: one per node per group
                               of 8 sibling cells (groups walked again by a later tier count only

@@ -2122,7 +2122,7 @@ __global__ __launch_bounds__(1024) void k_upward_levels(int top, int k, NodeOut 
 }
 
 // h in tree order for the big leaves (their order at level k is final);
-// the subtree waves write it for their own particles
+// the subtrees write it for their own particles
 __global__ __launch_bounds__(kBlock) void k_gather_h_big(const double *__restrict__ h,
                                                          const int32_t *__restrict__ id, NodeOut o, BigCtl bc,
                                                          double *__restrict__ ph) {
@@ -2137,7 +2137,7 @@ __global__ __launch_bounds__(kBlock) void k_gather_h_big(const double *__restric
     for (int64_t i = base + lane_id(); i < end; i += kWave) ph[i] = h[id[i]];
 }
 
-// k_mixed_prep for the big leaves only (the subtree waves write the FP32
+// k_mixed_prep for the big leaves only (the subtrees write the FP32
 // arrays of their own leaves), one wave per chunk of a big leaf
 __global__ __launch_bounds__(kBlock) void k_mixed_big(NodeOut o, BigCtl bc, const double *__restrict__ px,
                                                       const double *__restrict__ py, const double *__restrict__ pz,
@@ -2541,7 +2541,7 @@ rcb_status build_tree(rcb_tree *t, const double *x, const double *y, const doubl
         bb2 = (int32_t *)A(sizeof(int32_t) * b.max_big, tmp);
         ib2 = (int32_t *)A(sizeof(int32_t) * b.max_items, tmp);
         if (!roots || !bn2 || !bb2 || !ib2) return RCB_ENOMEM;
-        if (t->p.precision == RCB_MIXED) {   // written by the subtree waves
+        if (t->p.precision == RCB_MIXED) {   // written by the subtrees
             rcb_status st = alloc_mixed(t, s);
             if (st != RCB_OK) return st;
         }
@@ -2686,7 +2686,7 @@ rcb_status build_tree(rcb_tree *t, const double *x, const double *y, const doubl
         cur = t->k & 1;
         SubArgs sa{t->k, n, roots, qctl, qctl + 1, {b.x[0], b.x[1]}, {b.y[0], b.y[1]}, {b.z[0], b.z[1]},
                    {b.m[0], b.m[1]}, x, y, z, m, t->lvl_id, h, t->ph, o};
-        // mixed form: the subtree waves write the FP32 leaf-frame arrays of
+        // mixed form: the subtrees write the FP32 leaf-frame arrays of
         // their leaves as they finish them, k_mixed_big those of big leaves
         const bool mixed = t->p.precision == RCB_MIXED;
         if (mixed) {
