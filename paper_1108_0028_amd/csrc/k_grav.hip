@@ -158,7 +158,7 @@ __global__ __launch_bounds__(W * kWave) void k_far(GravArgs g) {
         FarWindow fw;
         FarPart part;   // (after its windows)
     } sh[W];
-    const int64_t gi = g.first + xcd_block();
+    const int64_t gi = g.first + xcd_block<kXcdGroups>();
     const int G = 1 << g.gk;
     if (g.ncount[(g.nleaf >> g.gk) + gi] == 0) return;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
@@ -201,7 +201,7 @@ __global__ __launch_bounds__(H * kWave, MIXED ? 6 : 5) void k_near(GravArgs g) {
     __shared__ T red[H > 1 ? H : 1][3][kWave];
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     NearStage<MIXED> &np = sh_all[wv];
-    const int64_t leaf = g.first + xcd_block();
+    const int64_t leaf = g.first + xcd_block<kXcdLeaves>();
     const int64_t gi = leaf >> g.gk, A = g.nleaf + leaf;
     const int li = (int)(leaf & ((1 << g.gk) - 1));
     const int lane = lane_id();

@@ -124,7 +124,7 @@ __global__ __launch_bounds__(H * kWave) void k_neigh(NeighArgs a) {
     const int G = 1 << a.gk;
     int64_t l;   // the workgroup's leaf, from 0
     if constexpr (SLAB) {
-        l = a.first + xcd_block();
+        l = a.first + xcd_block<kXcdLeaves>();
     } else {
         l = __builtin_amdgcn_readfirstlane(a.queue[blockIdx.x]);
     }

@@ -341,7 +341,7 @@ __global__ __launch_bounds__(H * kWave, MIXED ? 4 : 3) void k_vjp_near(VjpArgs a
     __shared__ VjpShared<MIXED> sh_all[H];
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     auto &sh = sh_all[wv];
-    const int64_t leaf = a.first + xcd_block();
+    const int64_t leaf = a.first + xcd_block<kXcdLeaves>();
     const int64_t gi = leaf >> a.gk, A = a.nleaf + leaf;
     const int li = (int)(leaf & ((1 << a.gk) - 1));
     const int lane = lane_id();
@@ -824,7 +824,7 @@ __global__ __launch_bounds__(kWave) void k_vjp_near_src(VjpArgs a, const uint64_
                                                         const int32_t *__restrict__ owner) {
     using T = typename std::conditional<MIXED, float, double>::type;
     __shared__ SrcShared<MIXED> sh;
-    const int64_t ci = a.first + xcd_block();
+    const int64_t ci = a.first + xcd_block<kXcdLeaves>();
     const int lane = lane_id();
     const int G = 1 << a.gk;
     const int64_t bl = __builtin_amdgcn_readfirstlane(owner[ci]);

@@ -20,6 +20,7 @@
 #include <vector>
 
 #include "rcb.h"
+#include "xcd_map.h"
 
 namespace rcb {
 
@@ -222,20 +223,10 @@ __device__ __forceinline__ int64_t wave_index() {
     return (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)w);
 }
 
-// Workgroups are handed to the 8 XCDs in turn (workgroup b to XCD b mod 8),
-// and each XCD has its own L2. xcd_block() renumbers them so that XCD x takes
-// one contiguous range of logical workgroups: neighbouring groups of cells,
-// which share sources and tree nodes, then meet in the same L2. A bijection
-// on [0, gridDim.x) for any grid size.
-constexpr uint32_t kXcds = 8;
+// the logical workgroup of this one, renumbered for the XCDs' L2s
+template <uint32_t RUN>
 __device__ __forceinline__ uint32_t xcd_block() {
-    const uint32_t b = blockIdx.x, nb = gridDim.x;
-    const uint32_t q = nb / kXcds, r = nb % kXcds, x = b % kXcds;
-    return x * q + (x < r ? x : r) + b / kXcds;
-}
-__device__ __forceinline__ int64_t xcd_wave_index() {
-    const uint32_t w = xcd_block() * (blockDim.x / kWave) + threadIdx.x / kWave;
-    return (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)w);
+    return xcd_slot(blockIdx.x, gridDim.x, RUN);
 }
 
 // Exchanges of a butterfly whose step o pairs aligned groups of o lanes that
