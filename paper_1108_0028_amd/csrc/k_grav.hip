@@ -232,17 +232,8 @@ __global__ __launch_bounds__(H * kWave, MIXED ? 6 : 5) void k_near(GravArgs g) {
             za = g.pz[pa];
             ha = g.ph[pa];
         }
-        // how far from the leaf's centre of mass the pass's sinks reach with their
-        // own h: a source b farther from it than reach + h_b is farther than
-        // h_a + h_b from every sink a (the 0.1% below is far above the rounding)
-        float reach;
-        {
-            const float rx = (float)(MIXED ? xa : xa - (T)cA[0]), ry = (float)(MIXED ? ya : ya - (T)cA[1]),
-                        rz = (float)(MIXED ? za : za - (T)cA[2]);
-            reach = sqrtf((rx * rx + ry * ry) + rz * rz) + (float)ha;
-#pragma unroll
-            for (int o = 1; o < kWave; o <<= 1) reach = fmaxf(reach, __shfl_xor(reach, o, kWave));
-        }
+        const T reach = MIXED ? sink_reach(xa, ya, za, ha)
+                              : sink_reach(T(xa - cA[0]), T(ya - cA[1]), T(za - cA[2]), ha);
         T ax = 0, ay = 0, az = 0;
         int turn = 0;   // H > 1: the wave that takes the next tile
         for (int64_t e0 = n0; e0 < n1; e0 += kWave) {
@@ -290,7 +281,7 @@ __global__ __launch_bounds__(H * kWave, MIXED ? 6 : 5) void k_near(GravArgs g) {
                 s.m = lane < nt ? s.m : (T)0;
                 // sources outside the support of every sink go behind the others
                 // (those past the end last)
-                const T lim = ((T)reach + sh) * (T)1.001;
+                const T lim = (reach + sh) * (T)1.001;
                 const bool out = (bx * bx + by * by) + bz * bz > lim * lim;
                 const uint64_t cb = ~ballot(out) & valid;
                 const int nc = __popcll(cb), before = rank_below(cb);

@@ -396,7 +396,8 @@ __global__ __launch_bounds__(H * kWave, MIXED ? 4 : 3) void k_vjp_near(VjpArgs a
         sh.g[lane][1] = real ? (T)load_g<MIXED>(a.gy, oa) : (T)0;
         sh.g[lane][2] = real ? (T)load_g<MIXED>(a.gz, oa) : (T)0;
         sh.pa[lane] = real ? pa : -1;
-        const float reach = sink_reach<MIXED>(me, cA);
+        const T reach = MIXED ? sink_reach(me.x, me.y, me.z, me.m)
+                              : sink_reach(T(me.x - cA[0]), T(me.y - cA[1]), T(me.z - cA[2]), me.m);
         double acc[SB][3];
 #pragma unroll
         for (int i = 0; i < SB; ++i) acc[i][0] = acc[i][1] = acc[i][2] = 0.0;

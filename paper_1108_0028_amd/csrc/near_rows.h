@@ -54,27 +54,13 @@ struct RowLds {
     };
 };
 
-// How far the leaf's sinks (lane's own: s, its position, h in s.m) reach from
-// its centre of mass cA with their own h: a source b farther from it than
-// reach + h_b is farther than h_a + h_b from every sink a (the 0.1% in
-// list_rows is far above the rounding).
-template <bool MIXED, typename Src>
-__device__ __forceinline__ float sink_reach(const Src &s, const double (&cA)[3]) {
-    const float x = MIXED ? (float)s.x : (float)(s.x - cA[0]), y = MIXED ? (float)s.y : (float)(s.y - cA[1]),
-                z = MIXED ? (float)s.z : (float)(s.z - cA[2]);
-    float reach = sqrtf((x * x + y * y) + z * z) + (float)s.m;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) reach = fmaxf(reach, __shfl_xor(reach, o, kWave));
-    return reach;
-}
-
 // Takes the near list [n0, n1) of the leaf with mask bit li and centre of mass
 // cA through the stacks; tiles go to the H waves in turn. near(n, slot) and
 // far(n, slot) take a pass of n <= P sources, number j at sh.src[slot(j)]
 // (far: none in the support of a sink). sh.mark: as tile_entry.
 template <bool MIXED, int H, typename A, typename Lds, typename Near, typename Far>
 __device__ __forceinline__ void list_rows(const A &a, Lds &sh, int wv, int li, int64_t n0, int64_t n1,
-                                          const double (&cA)[3], float reach, int P, uint32_t &gen, Near near,
+                                          const double (&cA)[3], typename Lds::T reach, int P, uint32_t &gen, Near near,
                                           Far far) {
     using T = typename Lds::T;
     using Src = typename Lds::Src;
@@ -123,7 +109,7 @@ __device__ __forceinline__ void list_rows(const A &a, Lds &sh, int wv, int li, i
                 by = s.y - cA[1];
                 bz = s.z - cA[2];
             }
-            const T lim = ((T)reach + h) * (T)1.001;
+            const T lim = (reach + h) * (T)1.001;
             const bool out = (bx * bx + by * by) + bz * bz > lim * lim;
             const uint64_t ob = ballot(out) & valid, cb = ~ballot(out) & valid;
             const int at = out ? kRowWait - 1 - (no + rank_below(ob)) : nc + rank_below(cb);

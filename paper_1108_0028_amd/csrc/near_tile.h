@@ -123,6 +123,22 @@ __device__ __forceinline__ T seg_sum(T v, int slice, int J) {
     return v;
 }
 
+// How far a leaf's sinks (this lane's: x, y, z from the leaf's centre of mass,
+// its smoothing length h) reach from that centre: a source b farther from it
+// than reach + h_b is farther than h_a + h_b from every sink a (the callers add
+// 0.1%, far above the rounding). In the form's own type: squares of offsets of
+// 1e-22 and below are nothing in FP32, and sources within the support would
+// count as outside it.
+__device__ __forceinline__ float sink_reach(float x, float y, float z, float h) {
+    float reach = sqrtf((x * x + y * y) + z * z) + h;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) reach = fmaxf(reach, __shfl_xor(reach, o, kWave));
+    return reach;
+}
+__device__ __forceinline__ double sink_reach(double x, double y, double z, double h) {
+    return uniform_f64(wave_max(sqrt((x * x + y * y) + z * z) + h));
+}
+
 // ballot bits of the lanes of this lane's segment
 __device__ __forceinline__ uint64_t seg_mask(const LeafLanes &L) {
     return L.J == kWave ? ~0ull : (((1ull << L.J) - 1ull) << (L.sslot * L.J));
