@@ -43,12 +43,17 @@ constexpr int kWaves = kBlock / kWave;
 constexpr int kAdj = 9;
 // Nodes of the levels above kMidLevel sit in the far lists of many groups at
 // once: their adjoints are added to several copies, in their own array of
-// kAdj * 2^kMidLevel per copy. FP64: 8 copies (with 64 and 8 of the deep nodes the
-// VJP of 300,000 particles took 2.88 ms, with 8 and one 2.74). FP32 (mixed
-// form): 64, which also keep each FP32 sum short. The deeper nodes have one.
+// kAdj * 2^kMidLevel per copy. FP64: 8 copies, and one of the deeper nodes (with
+// 64 and 8 the VJP of 300,000 particles took 2.88 ms, so 2.74). FP32 (mixed
+// form): 64, and 8 of the deeper nodes, added in FP64 by k_adj_reduce: they keep
+// each FP32 sum short. A node that all 16,384 groups of a cloud accept has its
+// mass adjoint to 2.4e-7 from 8 copies, to 1.9e-6 from one (1M particles: the VJP takes
+// the same time, 8.54 ms with the forward).
 constexpr int kMidLevel = 16;
 template <typename AT>
 constexpr int kAdjMidCopies = sizeof(AT) == 4 ? 64 : 8;
+template <typename AT>
+constexpr int kAdjCopies = sizeof(AT) == 4 ? 8 : 1;
 constexpr int kAcc = 30;    // G0(3), G1(9), G2(18) while accumulating
 constexpr int kMom = 19;    // S1(3), S2(6), S3(10): far_math.h SymMoments
 
@@ -75,7 +80,7 @@ struct VjpArgs {
     float *srcf;    // the same in the mixed form (FP32 atomics, its contract's accumulation)
     double *adj;    // kAdj per label (summed copies); component q of label B at B * kAdj + q
     double *adjm;   // unused
-    int64_t nmid;   // labels below nmid have kAdjMidCopies adjoint copies
+    int64_t nmid;   // labels below nmid have kAdjMidCopies adjoint copies, the others kAdjCopies
     int64_t n;
     int64_t nlab;
     // deterministic form: each far entry's node adjoint (kAdj FP64) at row
@@ -275,6 +280,7 @@ __global__ __launch_bounds__(kFarWaves * kWave, sizeof(AT) == 4 ? 4 : 3) void k_
             // each copy takes the groups of one residue mod the number of
             // copies, i.e. of one XCD under round-robin dispatch (8 | copies)
             AT *const mid = adjmc + (int64_t)(blockIdx.x % kAdjMidCopies<AT>) * kAdj * a.nmid;
+            AT *const deep = adjc + (int64_t)(blockIdx.x % kAdjCopies<AT>) * kAdj * (a.nlab - a.nmid);
 #pragma unroll 1
             for (int f = lane; f < nw * kAdj; f += kWave) {
                 const int r = f / kAdj;
@@ -283,8 +289,9 @@ __global__ __launch_bounds__(kFarWaves * kWave, sizeof(AT) == 4 ? 4 : 3) void k_
                 } else {
                     const int32_t L = sh.lab[r];
                     if (L < 0) continue;
-                    __hip_atomic_fetch_add((L < a.nmid ? mid : adjc) + (int64_t)L * kAdj + (f - r * kAdj), sh.rows[f],
-                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    AT *const node = L < a.nmid ? mid + (int64_t)L * kAdj : deep + (L - a.nmid) * kAdj;
+                    __hip_atomic_fetch_add(node + (f - r * kAdj), sh.rows[f], __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
                 }
             }
             tile_sync();
@@ -557,20 +564,26 @@ __global__ __launch_bounds__(kBlock) void k_vjp_push(VjpArgs a, const double *__
     }
 }
 
-// node adjoints into out, FP64: labels below nmid the sum of their copies in
-// order, the others from adjc, which may be out itself
+// node adjoints into out, FP64: the sum of each label's copies in order, of the
+// labels below nmid in adjmc, of the others in adjc (from label nmid on; a single
+// copy may stand in out itself)
 template <typename A>
 __global__ void k_adj_reduce(double *out, const A *adjc, const A *__restrict__ adjmc, int64_t nlab,
                              int64_t nmid) {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= kAdj * nlab) return;
+    double v;
     if (i >= kAdj * nmid) {
-        if ((const void *)adjc != (const void *)out) out[i] = (double)adjc[i];
-        return;
-    }
-    double v = (double)adjmc[i];
+        const int64_t j = i - kAdj * nmid;
+        if ((const void *)(adjc + j) == (const void *)(out + i)) return;
+        v = (double)adjc[j];
+#pragma unroll
+        for (int c = 1; c < kAdjCopies<A>; ++c) v += (double)adjc[(int64_t)c * kAdj * (nlab - nmid) + j];
+    } else {
+        v = (double)adjmc[i];
 #pragma unroll 8
-    for (int c = 1; c < kAdjMidCopies<A>; ++c) v += (double)adjmc[(int64_t)c * kAdj * nmid + i];
+        for (int c = 1; c < kAdjMidCopies<A>; ++c) v += (double)adjmc[(int64_t)c * kAdj * nmid + i];
+    }
     out[i] = v;
 }
 
@@ -1106,10 +1119,10 @@ rcb_status gravity_vjp(rcb_tree *t, const void *gx, const void *gy, const void *
     const int64_t nmid = std::min<int64_t>(t->nlab, int64_t(1) << kMidLevel);
     // node adjoints as the far kernel adds them: FP64 in adj itself, FP32
     // (mixed form) apart; the deterministic form writes adj alone
-    const size_t adj_n = det ? 0 : (size_t)kAdj * t->nlab;
+    const size_t adj_n = det ? 0 : (size_t)(mixed ? kAdjCopies<float> : kAdjCopies<double>) * kAdj * (t->nlab - nmid);
     const size_t adjm_n = det ? 0 : (size_t)(mixed ? kAdjMidCopies<float> : kAdjMidCopies<double>) * kAdj * nmid;
     double *adj = (double *)dalloc(t, sizeof(double) * kAdj * t->nlab, s, tmp);
-    void *adjc = det ? (void *)adj : mixed ? dalloc(t, sizeof(float) * adj_n, s, tmp) : (void *)adj;
+    void *adjc = det ? (void *)adj : mixed ? dalloc(t, sizeof(float) * adj_n, s, tmp) : (void *)(adj + kAdj * nmid);
     void *adjmc = det ? (void *)adj : dalloc(t, (mixed ? sizeof(float) : sizeof(double)) * adjm_n, s, tmp);
     double *mom = (double *)dalloc(t, sizeof(double) * kMom * t->nleaf, s, tmp);
     if (!t->farc) {
