@@ -336,6 +336,18 @@ __device__ __forceinline__ void source_atomics(const VjpArgs &a, int n, V value,
     }
 }
 
+// A pair's term m_b K g_a, K = F I + (dF/dr / r) v v^T, which the sink loses and
+// the source gains, and F (v . g_a): one form for k_vjp_near and k_vjp_near_src,
+// so that the two sides of a pair are the same bits and cancel in a sum.
+template <typename T>
+__device__ __forceinline__ void pair_term(const T (&v)[3], const T (&ga)[3], T F, T dFr, T mb, T (&K)[3], T &Fvg) {
+    const T vg = v[0] * ga[0] + v[1] * ga[1] + v[2] * ga[2];
+    const T Fm = F * mb, vm = dFr * vg * mb;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) K[c] = Fm * ga[c] + vm * v[c];
+    Fvg = F * vg;
+}
+
 // SRC = false (the deterministic form): sink-side terms only; the source-side
 // terms are summed per source cell by k_vjp_near_src instead.
 // A workgroup of H waves per cell, whose sink sums are added in order.
@@ -433,19 +445,18 @@ __global__ __launch_bounds__(H * kWave, MIXED ? 4 : 3) void k_vjp_near(VjpArgs a
                         const T hsum = k.m + hb;
                         if (!soft_outside<T>(r2, hsum)) soft_FdF<T>(r2, ri, r3, r5, hsum, F, dFr);
                     }
-                    const T vg = v[0] * ga[0] + v[1] * ga[1] + v[2] * ga[2];
                     // the deterministic form leaves out the self pair, whose sink and
                     // source terms cancel exactly (v = 0) but would be computed in two
                     // kernels there
                     const T mb = !SRC && soft && pb == sh.pa[rs.sink0 + i] ? (T)0 : s.m;
-                    const T Fm = F * mb, vm = dFr * vg * mb;
+                    T Kg[3], Fvg;
+                    pair_term<T>(v, ga, F, dFr, mb, Kg, Fvg);
 #pragma unroll
                     for (int cc = 0; cc < 3; ++cc) {
-                        const T Kg = Fm * ga[cc] + vm * v[cc];
-                        acc[i][cc] -= (double)Kg;
-                        if (SRC) src[cc] += (double)Kg;
+                        acc[i][cc] -= (double)Kg[cc];
+                        if (SRC) src[cc] += (double)Kg[cc];
                     }
-                    if (SRC) src[3] += (double)(-F * vg);
+                    if (SRC) src[3] -= (double)Fvg;
                 }
             }
             if constexpr (SRC) {
@@ -945,10 +956,11 @@ __global__ __launch_bounds__(kWave) void k_vjp_near_src(VjpArgs a, const uint64_
                         T F = r3, dFr = (T)-3 * r5;
                         if (!soft_outside<T>(r2, hsum)) soft_FdF<T>(r2, ri, r3, r5, hsum, F, dFr);
                         const T ga[3] = {sh.t.g[0][j], sh.t.g[1][j], sh.t.g[2][j]};
-                        const T vg = v[0] * ga[0] + v[1] * ga[1] + v[2] * ga[2];
+                        T Kg[3], Fvg;
+                        pair_term<T>(v, ga, F, dFr, mb, Kg, Fvg);
 #pragma unroll
-                        for (int cc = 0; cc < 3; ++cc) acc[cc] += (double)(mb * (F * ga[cc] + dFr * v[cc] * vg));
-                        acc[3] += (double)(-F * vg);
+                        for (int cc = 0; cc < 3; ++cc) acc[cc] += (double)Kg[cc];
+                        acc[3] -= (double)Fvg;
                     }
                 }
                 tile_sync();
