@@ -257,10 +257,12 @@ __device__ __forceinline__ void chunk_sums_regs(const double (&X)[8], const doub
     constexpr int NS = Pay<P>::NS;
     double v[8][NS];
     double ml = -1.0;
-    // (no branches: past the end the mass is zero, and so is every term)
+    // (no branches: past the end the mass is zero, and so is every term; not r2,
+    // the centre of mass's distance from zero, which may have no square)
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
         const double xi = X[t], yi = Y[t], zi = Z[t], mi = Mm[t];
+        const bool in = p0 + t < end;
         double far;
         if constexpr (P == 0) {
             v[t][0] = mi;
@@ -270,7 +272,7 @@ __device__ __forceinline__ void chunk_sums_regs(const double (&X)[8], const doub
             far = dist2(xi, yi, zi, g[0], g[1], g[2]);
         } else {
             const double d0 = xi - c[0], d1 = yi - c[1], d2 = zi - c[2];
-            const double r2 = (d0 * d0 + d1 * d1) + d2 * d2;
+            const double r2 = in ? (d0 * d0 + d1 * d1) + d2 * d2 : 0.0;
             const double m3 = 3.0 * mi;
             const double mr2 = mi * r2;
             v[t][0] = (m3 * d0) * d0 - mr2;
@@ -282,7 +284,7 @@ __device__ __forceinline__ void chunk_sums_regs(const double (&X)[8], const doub
             far = sqrt(dist2(xi, yi, zi, g[0], g[1], g[2])) + 2.0 * H[t];
         }
         far = fmax(ml, far);
-        ml = p0 + t < end ? far : ml;
+        ml = in ? far : ml;
     }
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
@@ -1523,7 +1525,9 @@ __device__ __forceinline__ void sub_pass(const NodeOut o, int k, const double *_
                 const double mr2 = Mm[t] * r2;
                 const double u = q == 0 ? (m3 * d0) * d0 - mr2 : q == 1 ? (m3 * d0) * d1 : q == 2 ? (m3 * d0) * d2
                                : q == 3 ? (m3 * d1) * d1 - mr2 : q == 4 ? (m3 * d1) * d2 : (m3 * d2) * d2 - mr2;
-                v[t] = valid ? u : 0.0;   // (a lane without a node has no centre of mass)
+                // (a lane without a node has no centre of mass, and the centre's
+                // distance from zero, past the node, may have no square)
+                v[t] = valid && 8 * gl + t < c ? u : 0.0;
             }
             sq[q] = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
         }
