@@ -565,19 +565,21 @@ __global__ __launch_bounds__(kBlock) void k_expand(int64_t nleaf, int gk,
 
 }  // namespace
 
-// Slab capacities: 1024 near entries per group, up to 16384 (and no more than
-// there are cells) while the near slab stays within 1 GB: below a million
-// particles some groups of a cloud's halo are near to thousands of cells, and
-// one list past its slab means a second walk (250,000 Plummer particles: walk
+// Slab capacities: 1024 near entries per group, with `wide` up to 16384 (and no
+// more than there are cells) while the near slab stays within 1 GB: below a
+// million particles some groups of a cloud's halo are near to thousands of cells,
+// and one list past its slab means a second walk (250,000 Plummer particles: walk
 // 0.78 -> 0.39 ms). Up to 16384 far entries per group, within a budget for
-// both slabs of 8 GB or 480 bytes per particle, whichever is larger. At 4M particles and theta = 0.7 the group lists average ~170 near
+// both slabs of 8 GB or 480 bytes per particle, whichever is larger. At 4M
+// particles and theta = 0.7 the group lists average ~170 near
 // and ~2150 far entries; at depth 23 (67M-1e8 particles, 2^20 groups) the
 // per-particle budget leaves 2816-4672 far entries per group, enough for the
 // clustered test cloud's lists, so that the walk runs once. n = 0 gives the
-// 8 GB budget alone (the fallback when the larger slabs cannot be had).
-static void slab_caps(int64_t ngroup, int64_t nleaf, int64_t n, int64_t &cn, int64_t &cf) {
+// 8 GB budget alone.
+static void slab_caps(int64_t ngroup, int64_t nleaf, int64_t n, bool wide, int64_t &cn, int64_t &cf) {
     const int64_t budget = std::max<int64_t>((int64_t)8 << 30, 480 * n);
-    cn = std::max<int64_t>(1024, std::min<int64_t>({16384, nleaf, ((int64_t)1 << 30) / (8 * ngroup)}));
+    cn = 1024;
+    if (wide) cn = std::max<int64_t>(cn, std::min<int64_t>({16384, nleaf, ((int64_t)1 << 30) / (8 * ngroup)}));
     cf = budget / (8 * ngroup) - cn;
     cf = std::min<int64_t>(16384, std::max<int64_t>(1024, cf & ~(int64_t)63));
 }
@@ -605,10 +607,12 @@ rcb_status ensure_walk(rcb_tree *t, hipStream_t s) {
     int64_t cn = 0, cf = 0;
     std::vector<void *> slabs;
     uint64_t *nslab = nullptr, *fslab = nullptr;
-    for (int attempt = 0; attempt < 2 && !(nslab && fslab); ++attempt) {
+    // the next smaller slabs where these cannot be had: the narrow near slab, then
+    // the 8 GB budget
+    for (int attempt = 0; attempt < 3 && !(nslab && fslab); ++attempt) {
         for (void *p : slabs) dfree(t, p, s);
         slabs.clear();
-        slab_caps(NG, t->nleaf, attempt == 0 ? t->n : 0, cn, cf);
+        slab_caps(NG, t->nleaf, attempt < 2 ? t->n : 0, attempt == 0, cn, cf);
         nslab = (uint64_t *)dalloc(t, sizeof(uint64_t) * NG * cn, s, slabs);
         fslab = nslab ? (uint64_t *)dalloc(t, sizeof(uint64_t) * NG * cf, s, slabs) : nullptr;
     }
