@@ -394,9 +394,11 @@ __global__ __launch_bounds__(WAVES * kWave) void k_walk_wide(WalkArgs w, int32_t
 // ends of the slab lists: [g cap, g cap + count). With tot, also the totals
 // over the groups: [0] node records tested, [1] tests, [2] far entries and [3]
 // the overflow chunks that the neighbour search will need: a cell of c
-// particles in volume V expects c / V 4 pi / 3 (2h)^3 neighbours each (2h:
-// h_node - h_node_int), and lists past 64 ids take chunks of 64. [2] and [3]
-// only choose a launch and size a pool.
+// particles in volume V expects c / V 4 pi / 3 r^3 neighbours each (r = 2h:
+// h_node - h_node_int), r on no axis past the root's side, beyond which there are
+// none (a flat cloud's cells have no volume: taken as full of particles, they asked
+// for 1 KB a particle, now 0.2), and lists past 64 ids take chunks of 64. [2] and
+// [3] only choose a launch and size a pool.
 __global__ __launch_bounds__(kBlock) void k_slab_ends(int64_t ngroup, int64_t near_cap, int64_t far_cap,
                                                       const int64_t *__restrict__ ncnt,
                                                       const int64_t *__restrict__ fcnt,
@@ -416,15 +418,25 @@ __global__ __launch_bounds__(kBlock) void k_slab_ends(int64_t ngroup, int64_t ne
             sum[1] = stats[g].y;
             sum[2] = (double)fcnt[g];
         }
-        for (int i = 0; tot && i < 1 << e.gk; ++i) {
-            const int64_t A = e.nleaf + (g << e.gk) + i;
-            const double c = e.ncount[A];
-            const double V = (e.nhi[3 * A] - e.nlo[3 * A]) * (e.nhi[3 * A + 1] - e.nlo[3 * A + 1]) *
-                             (e.nhi[3 * A + 2] - e.nlo[3 * A + 2]);
-            const double r = e.hnode[A] - e.rec[2 * A].w;
-            double nb = 4.19 * c / V * r * r * r * 1.1;   // (10% over the mean)
-            if (!(nb < e.n)) nb = e.n;                    // (also a cell without volume)
-            if (c > 0.0 && nb > 64.0) sum[3] += c * ceil((nb - 64.0) / 64.0);
+        if (tot) {
+            double all[3];
+#pragma unroll
+            for (int q = 0; q < 3; ++q) all[q] = e.nhi[3 + q] - e.nlo[3 + q];
+            const int G = 1 << e.gk;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {   // (all loads at once)
+                const int64_t A = e.nleaf + (g << e.gk) + (i < G ? i : 0);
+                const double c = i < G ? e.ncount[A] : 0;
+                const double r = e.hnode[A] - e.rec[2 * A].w;
+                double nb = 1.1 * 4.19 * c;   // (10% over the mean)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    const double side = e.nhi[3 * A + q] - e.nlo[3 * A + q];
+                    nb *= side > 0.0 ? (r < all[q] ? r : all[q]) * __builtin_amdgcn_rcp(side) : 1.0;
+                }
+                if (!(nb < e.n)) nb = e.n;
+                if (c > 0.0 && nb > 64.0) sum[3] += c * ceil((nb - 64.0) / 64.0);
+            }
         }
     }
     if (!tot) return;
