@@ -107,7 +107,7 @@ struct NeighShared {
 // lists cost 5.0 of the search's 5.7 ms, about 10 ns each.
 constexpr int kSubMax = 64;
 constexpr int kSubCtl = 16;
-constexpr int kCtlWords = kSubCtl * (1 + kSubMax);
+inline size_t ctl_bytes(int subs) { return sizeof(int32_t) * kSubCtl * (1 + subs); }
 
 // SLAB: ids go to slab row (caller index) while it has room, then to a chain
 // of chunks, each taken by the hit of its first slot; lists whose chunk could
@@ -617,6 +617,33 @@ inline size_t bits_lds(int64_t n) { return sizeof(uint32_t) * (9 * ((n + 255) / 
 // the inverse permutation (1e8 particles: 83 -> 73 ms).
 bool tree_rows(const rcb_tree *t) { return t->n * kNbCap * (int64_t)sizeof(int32_t) > ((int64_t)4 << 30); }
 
+// The count call's scratch with `subs` sub-pools of `cap` chunks each: all of it,
+// or nothing.
+bool take_scratch(rcb_tree *t, int32_t subs, int64_t cap, hipStream_t s) {
+    Scratch tmp(t, s);
+    bool all = true;
+    auto A = [&](size_t bytes) -> int32_t * {
+        void *p = all ? dalloc(t, bytes, s, tmp) : nullptr;
+        all = all && p;
+        return (int32_t *)p;
+    };
+    int32_t *slab = A(sizeof(int32_t) * t->n * kNbCap), *pool = A(sizeof(int32_t) * cap * subs * kNbChunk);
+    int32_t *next = A(sizeof(int32_t) * cap * subs), *head = A(sizeof(int32_t) * t->n);
+    int32_t *queue = A(sizeof(int32_t) * t->nleaf), *ctl = A(ctl_bytes(subs));
+    if (!all) return false;
+    t->list_allocs.insert(t->list_allocs.end(), tmp.begin(), tmp.end());
+    tmp.clear();
+    t->nb_slab = slab;
+    t->nb_pool = pool;
+    t->nb_next = next;
+    t->nb_head = head;
+    t->nb_queue = queue;
+    t->nb_ctl = ctl;
+    t->nb_subs = subs;
+    t->nb_sub_cap = cap;
+    return true;
+}
+
 }  // namespace
 
 // Count: one search that writes every particle's count into offsets (then
@@ -638,27 +665,18 @@ rcb_status neighbours_count(rcb_tree *t, int64_t *offsets, int64_t *total, hipSt
         // most 4 per particle; at 105 neighbours, one for nearly each), and for
         // small clouds what the longest lists possible take, up to 16 MiB: a few
         // lists of thousands searched again cost 2000 particles 38 of 380 us
-        t->nb_subs = 1;
-        while (t->nb_subs < kSubMax && t->nb_subs * 8 < t->ngroup) t->nb_subs *= 2;
+        // (the N/8 chunks alone, in one sub-pool, where that cannot be had)
+        int32_t subs = 1;
+        while (subs < kSubMax && subs * 8 < t->ngroup) subs *= 2;
         const int64_t all = t->n > kNbCap ? t->n * ((t->n - kNbCap + kNbChunk - 1) / kNbChunk) : 0;
         const int64_t small = std::min<int64_t>(all, (int64_t)1 << 16);
         const int64_t base = t->n / 8 + 1;
         const int64_t more = std::max<int64_t>(
             small, std::min<int64_t>({t->nb_est, 4 * t->n, ((int64_t)1 << 30) - base}));   // (int32 chunk ids)
-        t->nb_slab = (int32_t *)dalloc(t, sizeof(int32_t) * t->n * kNbCap, s, t->list_allocs);
-        for (int64_t want : {base + more, base}) {   // the smaller pool if the larger cannot be had
-            t->nb_sub_cap = (want + t->nb_subs - 1) / t->nb_subs + 8;
-            t->nb_pool = (int32_t *)dalloc(t, sizeof(int32_t) * t->nb_sub_cap * t->nb_subs * kNbChunk, s, t->list_allocs);
-            if (t->nb_pool || more == 0) break;
-        }
-        t->nb_next = (int32_t *)dalloc(t, sizeof(int32_t) * t->nb_sub_cap * t->nb_subs, s, t->list_allocs);
-        t->nb_head = (int32_t *)dalloc(t, sizeof(int32_t) * t->n, s, t->list_allocs);
-        t->nb_queue = (int32_t *)dalloc(t, sizeof(int32_t) * t->nleaf, s, t->list_allocs);
-        t->nb_ctl = (int32_t *)dalloc(t, sizeof(int32_t) * kCtlWords, s, t->list_allocs);
-        if (!t->nb_slab || !t->nb_pool || !t->nb_next || !t->nb_head || !t->nb_queue || !t->nb_ctl)
+        if (!take_scratch(t, subs, (base + more + subs - 1) / subs + 8, s) && !take_scratch(t, 1, base, s))
             return RCB_ENOMEM;
     }
-    RCB_ZERO(t->nb_ctl, sizeof(int32_t) * kCtlWords, s);
+    RCB_ZERO(t->nb_ctl, ctl_bytes(t->nb_subs), s);
     NeighArgs a{t->nleaf, t->gk, t->ngroup, t->wrec, t->nhnode, t->nfirst, t->ncount, t->gnear_beg,
                 t->gnear_end, t->gnear, t->px, t->py, t->pz, t->ph, t->pid, offsets, nullptr, t->nb_slab,
                 t->nb_pool, t->nb_next, t->nb_sub_cap, t->nb_subs - 1, t->nb_head, t->nb_ctl, t->nb_queue, nullptr,

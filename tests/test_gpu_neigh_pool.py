@@ -64,3 +64,56 @@ def test_units(log2s, monkeypatch):
     np.testing.assert_array_equal(soff, off)
     np.testing.assert_array_equal(sids, ids)
     assert sheld == held
+
+
+def _oracle_lists(c, nll):
+    from oracle import oracle as O
+    ot = O.OracleTree(*c.arrays(), n_ll=nll)
+    ot.walk(0.7)
+    off, ids, _ = ot.neighbours()
+    return off, ids
+
+
+@pytest.mark.parametrize("n,kind,hs", [(20000, "plummer", 1.0), (40000, "clumpy", 1.0), (3000, "uniform", 40.0)])
+def test_smallest_scratch(n, kind, hs, monkeypatch):
+    """the rows and the N/8 chunks are enough for a count: the lists that find no
+    chunk are searched again by the fill call"""
+    _say("smallest neighbour scratch", n, kind)
+    c = W.clumpy_cube(n) if kind == "clumpy" else W.small_random(n, 11 + n, kind, h_scale=hs)
+    off, ids = _oracle_lists(c, 12)
+    lim = LimitedAlloc()
+    t = lim.tree(monkeypatch, [_t(a) for a in c.arrays()], n_ll=12, theta=0.7)
+    t.walk()
+    # row, head; pool of n / 8 + 1 chunks with 16 bytes each of bookkeeping; a word
+    # per cell; the scan of the counts
+    lim.budget = lim.live + 260 * n + 272 * (n // 8 + 1) + 4 * (1 << t.info()["k"]) + 8 * (n // 2048 + 1) + 256
+    got = t.neighbours_count(_t(np.zeros(n + 1, np.int64)))
+    assert lim.refused > 0 and got == len(ids)
+    lim.budget = 1 << 62
+    o, i = t.neighbours()
+    np.testing.assert_array_equal(_np(o), off)
+    np.testing.assert_array_equal(_np(i), ids)
+    t.destroy()
+
+
+def test_count_after_a_refused_count(monkeypatch):
+    """a count without memory leaves nothing half made: the next one, with memory,
+    is as the first"""
+    from paper_1108_0028_amd import RcbError
+    _say("count after a refused count")
+    c = W.small_random(20000, 20011, "plummer")
+    off, ids = _oracle_lists(c, 12)
+    lim = LimitedAlloc()
+    t = lim.tree(monkeypatch, [_t(a) for a in c.arrays()], n_ll=12, theta=0.7)
+    t.walk()
+    live = lim.live
+    for room in (0, 256 * c.n, 292 * c.n):   # (the smallest scratch takes 293 bytes a particle)
+        lim.budget = live + room
+        with pytest.raises(RcbError) as e:
+            t.neighbours_count(_t(np.zeros(c.n + 1, np.int64)))
+        assert e.value.status == 2 and lim.live == live
+    lim.budget = 1 << 62
+    o, i = t.neighbours()
+    np.testing.assert_array_equal(_np(o), off)
+    np.testing.assert_array_equal(_np(i), ids)
+    t.destroy()
