@@ -116,8 +116,10 @@ typedef struct {
        for reuse on the stream that freed them). alloc(bytes, stream, ctx) returns device
        memory usable in stream order on `stream`, or NULL (the call then fails
        with RCB_ENOMEM); free(ptr, stream, ctx) releases it in stream order.
-       Every block is freed by the call that allocated it or by
-       rcb_destroy(). */
+       Every block is freed by a call on the tree, at the latest by
+       rcb_destroy(). A call that lacks memory is made again after the tree has
+       given back what its lists hold beyond their need (the unused part of
+       the near lists' slab and of the neighbour pool). */
     void *(*alloc)(size_t bytes, void *stream, void *ctx);
     void (*free)(void *ptr, void *stream, void *ctx);
     void *alloc_ctx;

@@ -644,6 +644,28 @@ bool take_scratch(rcb_tree *t, int32_t subs, int64_t cap, hipStream_t s) {
     return true;
 }
 
+// chunk ids of sub-pools of `cap` chunks -> of `to` (-1 stays; heads that were not
+// written are not read)
+__device__ __forceinline__ int32_t moved_chunk(int32_t ch, int64_t cap, int64_t to) {
+    return ch < 0 ? ch : (int32_t)(ch / cap * to + ch % cap);
+}
+__global__ __launch_bounds__(kBlock) void k_nb_move_heads(int64_t n, int64_t cap, int64_t to,
+                                                          int32_t *__restrict__ head) {
+    const int64_t a = blockIdx.x * (int64_t)kBlock + threadIdx.x;
+    if (a < n) head[a] = moved_chunk(head[a], cap, to);
+}
+// one wave per chunk of the new pool
+__global__ __launch_bounds__(kBlock) void k_nb_move_chunks(int64_t chunks, int64_t cap, int64_t to,
+                                                           const int32_t *__restrict__ pool,
+                                                           const int32_t *__restrict__ next,
+                                                           int32_t *__restrict__ npool, int32_t *__restrict__ nnext) {
+    const int64_t w = wave_index();
+    if (w >= chunks) return;
+    const int64_t from = w / to * cap + w % to;
+    npool[w * kNbChunk + lane_id()] = pool[from * kNbChunk + lane_id()];
+    if (lane_id() == 0) nnext[w] = moved_chunk(next[from], cap, to);
+}
+
 }  // namespace
 
 // Count: one search that writes every particle's count into offsets (then
@@ -703,6 +725,41 @@ rcb_status neighbours_count(rcb_tree *t, int64_t *offsets, int64_t *total, hipSt
     t->nb_nq = ctl[1];
     t->nb_long = ctl[2];
     return RCB_OK;
+}
+
+bool shrink_neigh_pool(rcb_tree *t, hipStream_t s) {
+    if (!t->nb_slab) return false;
+    if (t->nb_total < 0) {   // no count to fill from
+        for (int32_t **p : {&t->nb_slab, &t->nb_pool, &t->nb_next, &t->nb_head, &t->nb_queue, &t->nb_ctl}) {
+            free_list_block(t, *p, s);
+            *p = nullptr;
+        }
+        return true;
+    }
+    int32_t ctl[kSubCtl * (1 + kSubMax)];
+    if (hipMemcpyAsync(ctl, t->nb_ctl, ctl_bytes(t->nb_subs), hipMemcpyDeviceToHost, s) != hipSuccess ||
+        hipStreamSynchronize(s) != hipSuccess)
+        return false;
+    int64_t used = 1;   // chunks of the fullest sub-pool
+    for (int i = 0; i < t->nb_subs; ++i) used = std::max<int64_t>(used, ctl[kSubCtl * (1 + i)]);
+    if (used >= t->nb_sub_cap) return false;
+    const int64_t chunks = used * t->nb_subs;
+    Scratch tmp(t, s);
+    int32_t *pool = (int32_t *)dalloc(t, sizeof(int32_t) * chunks * kNbChunk, s, tmp);
+    int32_t *next = (int32_t *)dalloc(t, sizeof(int32_t) * chunks, s, tmp);
+    if (!pool || !next) return false;
+    k_nb_move_heads<<<(unsigned)((t->n + kBlock - 1) / kBlock), kBlock, 0, s>>>(t->n, t->nb_sub_cap, used, t->nb_head);
+    k_nb_move_chunks<<<(unsigned)((chunks + kWaves - 1) / kWaves), kBlock, 0, s>>>(chunks, t->nb_sub_cap, used,
+                                                                                   t->nb_pool, t->nb_next, pool, next);
+    for (int32_t **p : {&t->nb_pool, &t->nb_next}) free_list_block(t, *p, s);
+    for (void *p : {(void *)pool, (void *)next}) {
+        tmp.keep(p);
+        t->list_allocs.push_back(p);
+    }
+    t->nb_pool = pool;
+    t->nb_next = next;
+    t->nb_sub_cap = used;
+    return true;
 }
 
 rcb_status neighbours_fill(rcb_tree *t, const int64_t *offsets, int32_t *ids, int64_t cap,

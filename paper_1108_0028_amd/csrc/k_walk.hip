@@ -575,6 +575,16 @@ __global__ __launch_bounds__(kBlock) void k_expand(int64_t nleaf, int gk,
     }
 }
 
+// lists from their slabs into one array, one wave per group
+__global__ __launch_bounds__(kBlock) void k_pack_lists(int64_t ngroup, const int64_t *__restrict__ beg,
+                                                       const uint64_t *__restrict__ list,
+                                                       const int64_t *__restrict__ off, uint64_t *__restrict__ out) {
+    const int64_t g = wave_index();
+    if (g >= ngroup) return;
+    const int64_t o = off[g], n = off[g + 1] - o;
+    for (int64_t i = lane_id(); i < n; i += kWave) out[o + i] = list[beg[g] + i];
+}
+
 }  // namespace
 
 // Slab capacities: 1024 near entries per group, with `wide` up to 16384 (and no
@@ -726,6 +736,7 @@ rcb_status ensure_walk(rcb_tree *t, hipStream_t s) {
         t->gfar_end = ends + 3 * NG;
         t->gnear = nslab;
         t->gfar = fslab;
+        t->near_slab = cn > 1024 ? sizeof(uint64_t) * NG * cn : 0;
         for (void *p : slabs) {
             tmp.keep(p);
             t->list_allocs.push_back(p);
@@ -776,6 +787,34 @@ rcb_status ensure_walk(rcb_tree *t, hipStream_t s) {
     return RCB_OK;
 }
 
+// The counts of the last walk are still in walk_ws (the slabs were not outgrown).
+bool shrink_near_lists(rcb_tree *t, hipStream_t s) {
+    if (!t->walked || !t->near_slab) return false;
+    const int64_t NG = t->ngroup;
+    Scratch tmp(t, s);
+    int64_t *off = (int64_t *)dalloc(t, sizeof(int64_t) * (NG + 1), s, tmp);
+    int64_t total = 0;
+    if (!off || scan_i64(t, (const int64_t *)t->walk_ws, off, NG, s) != RCB_OK) return false;
+    const HostRead r{off + NG, &total, (int)sizeof(total)};
+    if (read_small(s, &r, 1, "near lists") != RCB_OK) return false;
+    const size_t bytes = sizeof(uint64_t) * std::max<int64_t>(1, total);
+    if (bytes >= t->near_slab) return false;
+    uint64_t *exact = (uint64_t *)dalloc(t, bytes, s, tmp);
+    if (!exact) return false;
+    k_pack_lists<<<(unsigned)((NG + kWaves - 1) / kWaves), kBlock, 0, s>>>(NG, t->gnear_beg, t->gnear, off, exact);
+    if (hipGetLastError() != hipSuccess) return false;
+    for (void *p : {(void *)off, (void *)exact}) {
+        tmp.keep(p);
+        t->list_allocs.push_back(p);
+    }
+    free_list_block(t, t->gnear, s);
+    t->gnear = exact;
+    t->gnear_beg = off;
+    t->gnear_end = off + 1;
+    t->near_slab = 0;
+    return true;
+}
+
 rcb_status ensure_leaf_lists(rcb_tree *t, hipStream_t s) {
     rcb_status st = ensure_walk(t, s);
     if (st != RCB_OK) return st;
@@ -814,6 +853,17 @@ rcb_status ensure_leaf_lists(rcb_tree *t, hipStream_t s) {
     return RCB_OK;
 }
 
+void free_list_block(rcb_tree *t, void *p, hipStream_t s) {
+    auto &v = t->list_allocs;
+    v.erase(std::remove(v.begin(), v.end(), p), v.end());
+    dfree(t, p, s);
+}
+
+bool give_back(rcb_tree *t, hipStream_t s) {
+    const bool near = shrink_near_lists(t, s), pool = shrink_neigh_pool(t, s);
+    return near || pool;
+}
+
 void drop_lists(rcb_tree *t, hipStream_t s) {
     for (void *p : t->list_allocs) dfree(t, p, s);
     t->list_allocs.clear();
@@ -821,6 +871,7 @@ void drop_lists(rcb_tree *t, hipStream_t s) {
     t->lists_kept = false;
     t->gnear_beg = t->gnear_end = t->gfar_beg = t->gfar_end = nullptr;
     t->gnear = t->gfar = nullptr;
+    t->near_slab = 0;
     t->leaf_lists = false;
     t->near_total = t->far_total = -1;
     t->near_off = t->far_off = nullptr;

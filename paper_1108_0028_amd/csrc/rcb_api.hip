@@ -307,6 +307,18 @@ static void free_all(rcb_tree *t, hipStream_t s) {
 
 using namespace rcb;
 
+// A call on a tree that ran out of memory is made once more if the tree could
+// give some back (nothing of a failed call is kept but the lists it may have made).
+template <typename F>
+static rcb_status again_with_less(rcb_tree *t, F call) {
+    rcb_status st = call();
+    if (st == RCB_ENOMEM && give_back(t, t->stream)) {
+        g_last_error.clear();
+        st = call();
+    }
+    return st;
+}
+
 extern "C" {
 
 void rcb_params_default(rcb_params *p) {
@@ -454,7 +466,7 @@ rcb_status rcb_refresh(rcb_tree *t, const double *x, const double *y, const doub
         return RCB_EINVAL;
     }
     t->stream = (hipStream_t)stream;
-    rcb_status st = refresh_tree(t, x, y, z, m, h, t->stream);
+    rcb_status st = again_with_less(t, [&] { return refresh_tree(t, x, y, z, m, h, t->stream); });
     if (st != RCB_OK) return st;
     if (!keep_lists) drop_lists(t, t->stream);   // walked again by the next call that needs lists
     else if (t->walked) t->lists_kept = true;
@@ -502,7 +514,7 @@ rcb_status rcb_neighbours_count(rcb_tree *t, int64_t *offsets, int64_t *total, v
         return RCB_EINVAL;
     }
     t->stream = (hipStream_t)stream;
-    return neighbours_count(t, offsets, total, t->stream);
+    return again_with_less(t, [&] { return neighbours_count(t, offsets, total, t->stream); });
 }
 
 rcb_status rcb_neighbours_fill(rcb_tree *t, const int64_t *offsets, int32_t *ids, int64_t capacity,
@@ -517,7 +529,7 @@ rcb_status rcb_neighbours_fill(rcb_tree *t, const int64_t *offsets, int32_t *ids
         return RCB_EINVAL;
     }
     t->stream = (hipStream_t)stream;
-    return neighbours_fill(t, offsets, ids, capacity, t->stream);
+    return again_with_less(t, [&] { return neighbours_fill(t, offsets, ids, capacity, t->stream); });
 }
 
 rcb_status rcb_gravity(rcb_tree *t, void *ax, void *ay, void *az, void *stream) {
@@ -527,7 +539,7 @@ rcb_status rcb_gravity(rcb_tree *t, void *ax, void *ay, void *az, void *stream) 
         return RCB_EINVAL;
     }
     t->stream = (hipStream_t)stream;
-    return gravity(t, ax, ay, az, t->stream);
+    return again_with_less(t, [&] { return gravity(t, ax, ay, az, t->stream); });
 }
 
 rcb_status rcb_gravity_vjp(rcb_tree *t, const void *gx, const void *gy, const void *gz, void *dx,
@@ -542,7 +554,7 @@ rcb_status rcb_gravity_vjp(rcb_tree *t, const void *gx, const void *gy, const vo
         return RCB_EINVAL;
     }
     t->stream = (hipStream_t)stream;
-    return gravity_vjp(t, gx, gy, gz, dx, dy, dz, dm, t->stream);
+    return again_with_less(t, [&] { return gravity_vjp(t, gx, gy, gz, dx, dy, dz, dm, t->stream); });
 }
 
 rcb_status rcb_get_info(const rcb_tree *t, rcb_tree_info *info) {
@@ -572,7 +584,7 @@ rcb_status rcb_tree_export(rcb_tree *t, int32_t field, void *dst, size_t bytes, 
     hipStream_t s = (hipStream_t)stream;
     t->stream = s;
     if (field >= RCB_FIELD_NEAR_OFF) {
-        rcb_status st = ensure_leaf_lists(t, s);
+        rcb_status st = again_with_less(t, [&] { return ensure_leaf_lists(t, s); });
         if (st != RCB_OK) return st;
     }
     const void *src = nullptr;

@@ -85,6 +85,7 @@ struct rcb_tree {
     // group list of group g: gnear[gnear_beg[g] .. gnear_end[g]) (likewise far)
     int64_t *gnear_beg = nullptr, *gnear_end = nullptr, *gfar_beg = nullptr, *gfar_end = nullptr;
     uint64_t *gnear = nullptr, *gfar = nullptr;
+    size_t near_slab = 0;   // bytes of gnear where it is a slab of more than the least entries
     // per-leaf lists, expanded from the group lists on demand (inspection)
     bool leaf_lists = false;
     int64_t near_total = -1, far_total = -1;
@@ -169,6 +170,15 @@ struct Scratch : std::vector<void *> {
             if (p) dfree(t, p, s);
     }
 };
+
+// One of the blocks made with the lists, freed before they are dropped
+void free_list_block(rcb_tree *t, void *p, hipStream_t s);
+// What a tree holds beyond its need, given back when a call lacks memory: the
+// wide near slab for lists of their exact size, and the neighbour pool for one of the
+// chunks in use. True if anything was; the lists stay as they are.
+bool give_back(rcb_tree *t, hipStream_t s);
+bool shrink_near_lists(rcb_tree *t, hipStream_t s);   // k_walk.hip
+bool shrink_neigh_pool(rcb_tree *t, hipStream_t s);   // k_neigh.hip
 
 // Forget the interaction lists and everything made from them (neighbour
 // slab, kept far coefficients); the next call that needs lists walks again.

@@ -102,9 +102,9 @@ def test_count_after_a_refused_count(monkeypatch):
     from paper_1108_0028_amd import RcbError
     _say("count after a refused count")
     c = W.small_random(20000, 20011, "plummer")
-    off, ids = _oracle_lists(c, 12)
+    off, ids = _oracle_lists(c, 24)
     lim = LimitedAlloc()
-    t = lim.tree(monkeypatch, [_t(a) for a in c.arrays()], n_ll=12, theta=0.7)
+    t = lim.tree(monkeypatch, [_t(a) for a in c.arrays()], n_ll=24, theta=0.7)   # 1024 cells: no wide near slab to give back
     t.walk()
     live = lim.live
     for room in (0, 256 * c.n, 292 * c.n):   # (the smallest scratch takes 293 bytes a particle)
