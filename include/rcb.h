@@ -110,7 +110,9 @@ typedef struct {
                                  that hold each node or cell are made by a stable sort, and
                                  every sum runs in a fixed order, so repeated calls give the
                                  same bits (more time; device memory of 16 B per entry
-                                 of the per-group lists and 72 B per far entry) */
+                                 of the per-group lists, 72 B per far entry (left out
+                                 where it cannot be had), and 32 B per particle for every
+                                 64 groups that its cell is near to, at least once) */
     /* Optional workspace allocator, both or neither (NULL: the library
        allocates from the device's stream-ordered pool and keeps freed blocks
        for reuse on the stream that freed them). alloc(bytes, stream, ctx) returns device

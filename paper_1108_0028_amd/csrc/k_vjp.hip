@@ -95,6 +95,7 @@ struct VjpArgs {
     // the cell's chunks are srcc[cell] .. srcc[cell + 1]
     double *srcpart;
     const int64_t *srcc, *srcp;
+    int64_t srcchunk;   // sink groups of a chunk
     int64_t first;   // this launch's first leaf, where a workgroup takes one
 };
 
@@ -803,20 +804,21 @@ __global__ void k_det_adj_sum(const double *__restrict__ part, const int64_t *__
     adj[i] = v;
 }
 
-// chunks of kSrcChunk sink groups per lowest-level cell, and their rows of
-// source terms (one per particle of the cell)
-constexpr int kSrcChunk = 64;
+// chunks of `chunk` sink groups per lowest-level cell, and their rows of
+// source terms (one per particle of the cell): kSrcChunk, or all of a cell's in one
+// (32 bytes a particle in all) where the rows of more cannot be had
+constexpr int64_t kSrcChunk = 64, kSrcAll = (int64_t)1 << 40;
 __global__ void k_src_count(const int64_t *__restrict__ lb, const int64_t *__restrict__ le,
-                            const int32_t *__restrict__ ncount, int64_t nleaf, int64_t *__restrict__ nc,
+                            const int32_t *__restrict__ ncount, int64_t chunk, int64_t nleaf, int64_t *__restrict__ nc,
                             int64_t *__restrict__ nrow) {
     const int64_t l = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (l >= nleaf) return;
-    const int64_t c = ncount[nleaf + l] > 0 ? (le[nleaf + l] - lb[nleaf + l] + kSrcChunk - 1) / kSrcChunk : 0;
+    const int64_t c = ncount[nleaf + l] > 0 ? (le[nleaf + l] - lb[nleaf + l] + chunk - 1) / chunk : 0;
     nc[l] = c;
     nrow[l] = c * ncount[nleaf + l];
 }
 
-// source-side near terms, one wave per chunk of kSrcChunk sink groups of a
+// source-side near terms, one wave per chunk of a.srcchunk sink groups of a
 // lowest-level cell B: lanes (source
 // slot, slice) over B's particles as in leaf_lanes. The sink cells A whose
 // near list holds B (the groups ascending, then the cells of each group's
@@ -857,8 +859,8 @@ __global__ __launch_bounds__(kWave) void k_vjp_near_src(VjpArgs a, const uint64_
     const int32_t sB = a.nfirst[B], c = a.ncount[B];
     const int64_t part = ci - a.srcc[bl];
     double *const rows = a.srcpart + 4 * (a.srcp[bl] + part * c);
-    const int64_t e_beg = lb[B] + part * kSrcChunk;
-    const int64_t e_end = e_beg + kSrcChunk < le[B] ? e_beg + kSrcChunk : le[B];
+    const int64_t e_beg = lb[B] + part * a.srcchunk;
+    const int64_t e_end = e_beg + a.srcchunk < le[B] ? e_beg + a.srcchunk : le[B];
     const double cB[3] = {a.ncom[3 * B], a.ncom[3 * B + 1], a.ncom[3 * B + 2]};
     sh.mark[lane] = 0;
     uint32_t gen = 0;
@@ -1086,19 +1088,30 @@ rcb_status vjp_det(rcb_tree *t, VjpArgs &a, double *adj, bool mixed, Scratch &tm
     int64_t *sc = (int64_t *)dalloc(t, sizeof(int64_t) * 2 * (NL + 1), s, tmp), *sp = sc + NL + 1;
     if (!sc) return RCB_ENOMEM;
     const unsigned gs = (unsigned)((NL + 255) / 256);
-    k_src_count<<<gs, 256, 0, s>>>(near.lb, near.le, t->ncount, NL, sc, sp);
-    RCB_LAUNCH_CHECK("k_src_count");
-    st = scan_i64(t, sc, sc, NL, s);
-    if (st != RCB_OK) return st;
-    st = scan_i64(t, sp, sp, NL, s);
-    if (st != RCB_OK) return st;
     int64_t tot[2] = {0, 0};   // chunks, rows
-    const HostRead rs[2] = {{sc + NL, &tot[0], (int)sizeof(int64_t)}, {sp + NL, &tot[1], (int)sizeof(int64_t)}};
-    st = read_small(s, rs, 2, "deterministic VJP: source chunks");
-    if (st != RCB_OK) return st;
-    int32_t *sown = (int32_t *)dalloc(t, sizeof(int32_t) * (tot[0] + 1), s, tmp);
-    a.srcpart = (double *)dalloc(t, sizeof(double) * 4 * (tot[1] + 1), s, tmp);
-    if (!sown || !a.srcpart) return RCB_ENOMEM;
+    int32_t *sown = nullptr;
+    for (int64_t chunk : {kSrcChunk, kSrcAll}) {
+        a.srcchunk = chunk;
+        k_src_count<<<gs, 256, 0, s>>>(near.lb, near.le, t->ncount, chunk, NL, sc, sp);
+        RCB_LAUNCH_CHECK("k_src_count");
+        st = scan_i64(t, sc, sc, NL, s);
+        if (st != RCB_OK) return st;
+        st = scan_i64(t, sp, sp, NL, s);
+        if (st != RCB_OK) return st;
+        const HostRead rs[2] = {{sc + NL, &tot[0], (int)sizeof(int64_t)}, {sp + NL, &tot[1], (int)sizeof(int64_t)}};
+        st = read_small(s, rs, 2, "deterministic VJP: source chunks");
+        if (st != RCB_OK) return st;
+        Scratch rows(t, s);
+        a.srcpart = (double *)dalloc(t, sizeof(double) * 4 * (tot[1] + 1), s, rows);
+        sown = (int32_t *)dalloc(t, sizeof(int32_t) * (tot[0] + 1), s, rows);
+        if (sown && a.srcpart) {
+            tmp.insert(tmp.end(), rows.begin(), rows.end());
+            rows.clear();
+            break;
+        }
+        a.srcpart = nullptr;
+    }
+    if (!a.srcpart) return RCB_ENOMEM;
     a.srcc = sc;
     a.srcp = sp;
     k_det_owner<<<gs, 256, 0, s>>>(sc, NL, sown);
@@ -1152,7 +1165,7 @@ rcb_status gravity_vjp(rcb_tree *t, const void *gx, const void *gy, const void *
               t->gnear_beg, t->gnear_end, t->gfar_beg, t->gfar_end, t->gnear, t->gfar, t->px, t->py, t->pz, t->pm, t->ph,
               t->fd, t->fh, t->pid, gx, gy, gz, mom, leafc, sink, mixed ? nullptr : (double *)srcv,
               mixed ? (float *)srcv : nullptr, adj, nullptr, nmid, n, t->nlab, nullptr, nullptr, nullptr, nullptr, nullptr,
-              nullptr, 0};
+              nullptr, kSrcChunk, 0};
     const unsigned gridg = (unsigned)((t->ngroup + kWaves - 1) / kWaves);
     if (det && mixed) k_vjp_moments_det<true><<<gridg, kBlock, 0, s>>>(a);
     else if (det) k_vjp_moments_det<false><<<gridg, kBlock, 0, s>>>(a);
