@@ -1029,15 +1029,15 @@ rcb_status det_sort(rcb_tree *t, const int64_t *beg, const int64_t *end, const u
 // sink-centre sums and node adjoints (FP64, B * kAdj + q) of the far field,
 // and the source-side near terms. Each far entry's node adjoint is stored by
 // k_vjp_far and summed per node (72 B per entry); if that array cannot be had
-// (or RCB_VJP_DET_RECOMPUTE is set) k_vjp_far_node recomputes it per node.
-rcb_status vjp_det(rcb_tree *t, VjpArgs &a, double *adj, bool mixed, Scratch &tmp, hipStream_t s) {
+// (or store is false) k_vjp_far_node recomputes it per node.
+rcb_status vjp_det(rcb_tree *t, VjpArgs &a, double *adj, bool mixed, bool store, Scratch &tmp, hipStream_t s) {
     const int64_t nlab = t->nlab;
     const unsigned gridg = (unsigned)((t->ngroup + kWaves - 1) / kWaves);
     DetLists far, near;
     rcb_status st = det_count(t, t->gfar_beg, t->gfar_end, tmp, s, far);
     if (st != RCB_OK) return st;
     double *contrib = nullptr;
-    if (far.total > 0 && far.total < (int64_t(1) << 32) && getenv("RCB_VJP_DET_RECOMPUTE") == nullptr)
+    if (far.total > 0 && far.total < (int64_t(1) << 32) && store)
         contrib = (double *)dalloc(t, sizeof(double) * kAdj * far.total, s, tmp);
     a.contrib = contrib;
     a.cbase = far.base;
@@ -1131,7 +1131,7 @@ rcb_status gravity_vjp(rcb_tree *t, const void *gx, const void *gy, const void *
                        void *dy, void *dz, void *dm, hipStream_t s) {
     rcb_status st = ensure_walk(t, s);
     if (st != RCB_OK) return st;
-    Scratch tmp(t, s);
+    Scratch tmp(t, s), lists(t, s);   // lists: of the deterministic form
     const int64_t n = t->n;
     double *sink = (double *)dalloc(t, sizeof(double) * 4 * n, s, tmp);
     const bool mixed = t->p.precision == RCB_MIXED;
@@ -1202,7 +1202,12 @@ rcb_status gravity_vjp(rcb_tree *t, const void *gx, const void *gy, const void *
     if (det) {
         // far field, then node adjoints and source-side terms from the
         // per-node lists
-        st = vjp_det(t, a, adj, mixed, tmp, s);
+        st = vjp_det(t, a, adj, mixed, getenv("RCB_VJP_DET_RECOMPUTE") == nullptr, lists, s);
+        if (st == RCB_ENOMEM && a.contrib) {   // the stored adjoints left too little for the rest
+            for (void *p : lists) dfree(t, p, s);
+            lists.clear();
+            st = vjp_det(t, a, adj, mixed, false, lists, s);
+        }
         if (st != RCB_OK) return st;
         near(std::false_type{});
         RCB_LAUNCH_CHECK("k_vjp_near");

@@ -48,3 +48,31 @@ def test_one_row_a_particle(prec, monkeypatch):
         assert torch.equal(a, b)
         assert np.abs(_np(a) - _np(r)).max() <= TOL[prec] * np.abs(_np(r)).max()
     t.destroy()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+def test_any_budget_above_the_least(prec, monkeypatch):
+    """more memory than the form that recomputes node adjoints takes is never too
+    little, however much of it the stored adjoints would leave"""
+    import torch
+    _say("deterministic vjp: budgets", prec)
+    n = 12000
+    c = W.small_random(n, 62, "plummer")
+    arrs = [_t(a) for a in c.arrays()]
+    g = [_t(v, torch.float32 if prec == "mixed" else torch.float64) for v in W.cotangents(n, seed=6)]
+    opt = dict(n_ll=12, theta=0.6, precision=prec)
+    ref, most = _measured(monkeypatch, arrs, g, **opt)
+    with monkeypatch.context() as mp:
+        mp.setenv("RCB_VJP_DET_RECOMPUTE", "1")
+        _, least = _measured(mp, arrs, g, **opt)
+    assert least < most
+    lim = LimitedAlloc()
+    t = lim.tree(monkeypatch, arrs, deterministic=True, **opt)
+    t.walk()
+    t.gravity()
+    held = lim.live
+    for i in range(33):
+        lim.budget = held + least + (most - least) * i // 32
+        for a, r in zip(t.vjp(*g), ref):
+            assert np.abs(_np(a) - _np(r)).max() <= TOL[prec] * np.abs(_np(r)).max()
+    t.destroy()
