@@ -271,7 +271,8 @@ rcb_status rcb_neighbours_fill(rcb_tree *t, const int64_t *offsets, int32_t *ids
  * The tree keeps f_A, J_A, H_A of every lowest-level cell (22 doubles per
  * cell, allocated on the first call) for a later rcb_gravity_vjp on the same
  * moments; rcb_refresh discards them. If they cannot be allocated, ranges of
- * cells are taken in turn with a smaller buffer, and nothing is kept.
+ * cells are taken in turn with a smaller buffer, and nothing is kept; nor is it
+ * with RCB_READING_B, which has no VJP.
  */
 rcb_status rcb_gravity(rcb_tree *t, void *ax, void *ay, void *az, void *stream);
 

@@ -425,11 +425,12 @@ rcb_status gravity(rcb_tree *t, void *ax, void *ay, void *az, hipStream_t s) {
     if (st != RCB_OK) return st;
     const bool rb = t->p.taylor_reading == RCB_READING_B;
     const int64_t per_group = (int64_t)kLeafC << t->gk;   // doubles
-    // the far coefficients of all leaves, kept for a VJP on the same moments; if
-    // they cannot be had, of ranges of groups in turn
-    if (!t->farc) t->farc = (double *)dalloc(t, sizeof(double) * per_group * t->ngroup, s, t->list_allocs);
+    // the far coefficients of all leaves, kept for a VJP on the same moments (there
+    // is none for reading B); if they cannot be had, of ranges of groups in turn
     Scratch tmp(t, s);
-    double *buf = t->farc;
+    double *buf = rb ? nullptr : t->farc;
+    if (!buf) buf = (double *)dalloc(t, sizeof(double) * per_group * t->ngroup, s, rb ? tmp : t->list_allocs);
+    if (!rb) t->farc = buf;
     int64_t range = t->ngroup;
     while (!buf && range > 1) {
         range = (range + 7) / 8;
