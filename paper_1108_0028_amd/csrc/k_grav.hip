@@ -192,9 +192,28 @@ struct NearStage {
     T h[2 * kWave];
     uint32_t mark[kWave];
 };
+constexpr int kFew = 2;
+__device__ __forceinline__ double lane_sum(double v) { return wave_sum(v); }
+__device__ __forceinline__ float lane_sum(float v) { return wave_sumf(v); }
+template <typename T>
+__device__ __forceinline__ T lane_value(T v, int lane) {
+    union {
+        T t;
+        int w[sizeof(T) / 4];
+    } u;
+    u.t = v;
+#pragma unroll
+    for (int i = 0; i < (int)sizeof(T) / 4; ++i) u.w[i] = __builtin_amdgcn_readlane(u.w[i], lane);
+    return u.t;
+}
 // Near field and L2P, a workgroup of H waves per leaf: the tiles go to the
 // waves in turn and the waves' sums are added in order.
-template <bool MIXED, int H>
+// FEW: for trees of small leaves. Those of one or two sinks take lanes as sources,
+// straight from their loads, and each sink's sums over all lanes: a row or two of a
+// tile cost less than the tile's order and the reach it needs (FP64, 500,000 particles
+// in cells of one 2.79 ms, now 2.68). (A branch in every instance made cells of 8
+// to 61 particles 1 to 2% slower.)
+template <bool MIXED, int H, bool FEW = false>
 __global__ __launch_bounds__(H * kWave, MIXED ? 6 : 5) void k_near(GravArgs g) {
     using T = typename std::conditional<MIXED, float, double>::type;
     __shared__ NearStage<MIXED> sh_all[H];
@@ -232,9 +251,23 @@ __global__ __launch_bounds__(H * kWave, MIXED ? 6 : 5) void k_near(GravArgs g) {
             za = g.pz[pa];
             ha = g.ph[pa];
         }
-        const T reach = MIXED ? sink_reach(xa, ya, za, ha)
-                              : sink_reach(T(xa - cA[0]), T(ya - cA[1]), T(za - cA[2]), ha);
+        const bool few = FEW && c <= kFew;
+        T sx[kFew], sy[kFew], sz[kFew], ss[kFew];
+        if constexpr (FEW) {
+#pragma unroll
+            for (int q = 0; q < kFew; ++q) {   // (of one sink every lane has it)
+                sx[q] = lane_value(xa, q * (kWave / kFew));
+                sy[q] = lane_value(ya, q * (kWave / kFew));
+                sz[q] = lane_value(za, q * (kWave / kFew));
+                ss[q] = lane_value(ha, q * (kWave / kFew));
+            }
+        }
+        T reach = 0;
+        if (!few)
+            reach = MIXED ? sink_reach(xa, ya, za, ha)
+                          : sink_reach(T(xa - cA[0]), T(ya - cA[1]), T(za - cA[2]), ha);
         T ax = 0, ay = 0, az = 0;
+        T ex = 0, ey = 0, ez = 0;   // few: the second sink's
         int turn = 0;   // H > 1: the wave that takes the next tile
         for (int64_t e0 = n0; e0 < n1; e0 += kWave) {
             const ChunkEntry ce = load_chunk(g.gnear, g.nfirst, g.ncount, e0, n1, 1u << li);
@@ -279,6 +312,26 @@ __global__ __launch_bounds__(H * kWave, MIXED ? 6 : 5) void k_near(GravArgs g) {
                     bz = s.z - cA[2];
                 }
                 s.m = lane < nt ? s.m : (T)0;
+                if constexpr (FEW) {
+                    if (few) {
+                        auto pair = [&](int q, T &px, T &py, T &pz) {
+                            const T vx = sx[q] - s.x, vy = sy[q] - s.y, vz = sz[q] - s.z;
+                            const T r2 = (vx * vx + vy * vy) + vz * vz;
+                            const T hsum = ss[q] + sh;
+                            const T ri = rsq_t(r2);
+                            const T r3 = ri * ri * ri;
+                            T F = r3;
+                            if (!soft_outside<T>(r2, hsum)) F = soft_F<T>(r2, ri, r3, hsum);
+                            F *= s.m;
+                            px -= F * vx;
+                            py -= F * vy;
+                            pz -= F * vz;
+                        };
+                        pair(0, ax, ay, az);
+                        if (c > 1) pair(1, ex, ey, ez);
+                        continue;
+                    }
+                }
                 // sources outside the support of every sink go behind the others
                 // (those past the end last)
                 const T lim = (reach + sh) * (T)1.001;
@@ -328,9 +381,23 @@ __global__ __launch_bounds__(H * kWave, MIXED ? 6 : 5) void k_near(GravArgs g) {
             }
             if constexpr (H > 1) tile_sync();   // (a wave may have taken none of the chunk's tiles)
         }
-        ax = seg_sum(ax, L.slice, L.J);
-        ay = seg_sum(ay, L.slice, L.J);
-        az = seg_sum(az, L.slice, L.J);
+        if (FEW && few) {
+            // (over all lanes, before a lane takes its sink's)
+            const T sum[3] = {lane_sum(ax), lane_sum(ay), lane_sum(az)};
+            T sum2[3] = {0, 0, 0};
+            if (c > 1) {
+                sum2[0] = lane_sum(ex);
+                sum2[1] = lane_sum(ey);
+                sum2[2] = lane_sum(ez);
+            }
+            ax = L.sslot > 0 ? sum2[0] : sum[0];
+            ay = L.sslot > 0 ? sum2[1] : sum[1];
+            az = L.sslot > 0 ? sum2[2] : sum[2];
+        } else {
+            ax = seg_sum(ax, L.slice, L.J);
+            ay = seg_sum(ay, L.slice, L.J);
+            az = seg_sum(az, L.slice, L.J);
+        }
         if constexpr (H > 1) {
             if (L.slice == 0) {
                 red[wv][0][L.sslot] = ax;
@@ -397,13 +464,17 @@ rcb_status launch_far(const rcb_tree *t, GravArgs g, int64_t g0, int64_t g1, hip
 // Waves per leaf: as many as fill the SIMDs (gravity in us with 1, 2, 4, 8 waves:
 // 256 leaves 120, 76, 51, 40; 4096 leaves 193, 120, 94, 90; 8192 leaves of 61
 // particles 1362, 1102, 988, 1000; 32,768 clumpy 629, 574, 570, 712; 131,072
-// 1887, 2000, 2072, 2607).
+// 1887, 2000, 2072, 2607). Each wave reads the whole list, and of leaves of fewer than
+// five particles on average that is most of the work: they take one wave where
+// there are enough of them (256 leaves of 2.5 particles 26, 24, 23, 22; 4096 of 5
+// particles 57, 57, 62, 80, of 1.5 40, 43, 49, 65; 32,768 of 5 262, 278, 344, 530).
 template <bool MIXED>
 rcb_status launch_near(const rcb_tree *t, GravArgs g, int64_t g0, int64_t g1, hipStream_t s) {   // of groups [g0, g1)
     const int64_t end = g1 << t->gk;
     for (g.first = g0 << t->gk; g.first < end; g.first += kMaxGrid) {
         const unsigned n = (unsigned)std::min(kMaxGrid, end - g.first);
-        if (t->nleaf <= 4096) k_near<MIXED, 8><<<n, 8 * kWave, 0, s>>>(g);
+        if (t->nleaf > 1024 && t->n < 5 * t->nleaf) k_near<MIXED, 1, true><<<n, kWave, 0, s>>>(g);
+        else if (t->nleaf <= 4096) k_near<MIXED, 8><<<n, 8 * kWave, 0, s>>>(g);
         else if (t->nleaf <= 16384) k_near<MIXED, 4><<<n, 4 * kWave, 0, s>>>(g);
         else if (t->nleaf <= 32768) k_near<MIXED, 2><<<n, 2 * kWave, 0, s>>>(g);
         else k_near<MIXED, 1><<<n, kWave, 0, s>>>(g);
