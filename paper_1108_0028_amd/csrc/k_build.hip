@@ -2773,7 +2773,6 @@ rcb_status build_tree(rcb_tree *t, const double *x, const double *y, const doubl
 static rcb_status finish_build(rcb_tree *t, BuildScratch &b, const NodeOut &o, Scratch &tmp, int cur,
                                hipStream_t s) {
     const int64_t n = t->n;
-    auto A = [&](size_t bytes, std::vector<void *> &owner) { return dalloc(t, bytes, s, owner); };
     k_records<<<(unsigned)((t->nlab + 255) / 256), 256, 0, s>>>(t->nlab, o, t->wrec);
     RCB_LAUNCH_CHECK("k_records");
 

@@ -49,7 +49,6 @@ using rcbfar::m2l_accumulate;
 struct GravArgs {
     int64_t nleaf;
     int gk;
-    int64_t ngroup;
     const int32_t *nfirst, *ncount;
     const double *ncom, *nM, *nQ;
     const int64_t *gnear_beg, *gnear_end, *gfar_beg, *gfar_end;
@@ -439,7 +438,7 @@ __global__ __launch_bounds__(H * kWave, MIXED ? 6 : 5) void k_near(GravArgs g) {
 }
 
 GravArgs grav_args(const rcb_tree *t, void *ax, void *ay, void *az, double *farc) {
-    return GravArgs{t->nleaf, t->gk, t->ngroup, t->nfirst, t->ncount, t->ncom, t->nM, t->nQ,
+    return GravArgs{t->nleaf, t->gk, t->nfirst, t->ncount, t->ncom, t->nM, t->nQ,
                     t->gnear_beg, t->gnear_end, t->gfar_beg, t->gfar_end, t->gnear, t->gfar, t->px, t->py, t->pz, t->pm, t->ph,
                     t->fd, t->fh, t->pid, ax, ay, az, farc, 0};
 }

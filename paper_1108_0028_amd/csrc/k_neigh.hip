@@ -54,7 +54,6 @@ constexpr int kSinks = 32;        // sinks of a pass over the candidates
 struct NeighArgs {
     int64_t nleaf;
     int gk;
-    int64_t ngroup;
     const double4 *rec;       // walk records: rec[2 label] = (box centre, h_node_int)
     const double *hnode;
     const int32_t *nfirst, *ncount;
@@ -699,7 +698,7 @@ rcb_status neighbours_count(rcb_tree *t, int64_t *offsets, int64_t *total, hipSt
             return RCB_ENOMEM;
     }
     RCB_ZERO(t->nb_ctl, ctl_bytes(t->nb_subs), s);
-    NeighArgs a{t->nleaf, t->gk, t->ngroup, t->wrec, t->nhnode, t->nfirst, t->ncount, t->gnear_beg,
+    NeighArgs a{t->nleaf, t->gk, t->wrec, t->nhnode, t->nfirst, t->ncount, t->gnear_beg,
                 t->gnear_end, t->gnear, t->px, t->py, t->pz, t->ph, t->pid, offsets, nullptr, t->nb_slab,
                 t->nb_pool, t->nb_next, t->nb_sub_cap, t->nb_subs - 1, t->nb_head, t->nb_ctl, t->nb_queue, nullptr,
                 0, tree_rows(t)};
@@ -796,7 +795,7 @@ rcb_status neighbours_fill(rcb_tree *t, const int64_t *offsets, int32_t *ids, in
                                           nlong, longq);
     RCB_LAUNCH_CHECK("k_nb_compact");
     if (t->nb_nq > 0) {
-        NeighArgs a{t->nleaf, t->gk, t->ngroup, t->wrec, t->nhnode, t->nfirst, t->ncount, t->gnear_beg,
+        NeighArgs a{t->nleaf, t->gk, t->wrec, t->nhnode, t->nfirst, t->ncount, t->gnear_beg,
                     t->gnear_end, t->gnear, t->px, t->py, t->pz, t->ph, t->pid, nullptr, offsets, ids,
                     nullptr, nullptr, 0, 0, t->nb_head, nlong, t->nb_queue, longq, 0, false};
         k_neigh<false, 1><<<(unsigned)t->nb_nq, kWave, 0, s>>>(a);

@@ -78,8 +78,6 @@ struct VjpArgs {
     double *sink;   // 4 n, tree order: dx dy dz dm
     double *src;    // 4 per particle, tree order, atomics (FP64 form)
     float *srcf;    // the same in the mixed form (FP32 atomics, its contract's accumulation)
-    double *adj;    // kAdj per label (summed copies); component q of label B at B * kAdj + q
-    double *adjm;   // unused
     int64_t nmid;   // labels below nmid have kAdjMidCopies adjoint copies, the others kAdjCopies
     int64_t n;
     int64_t nlab;
@@ -1032,7 +1030,6 @@ rcb_status det_sort(rcb_tree *t, const int64_t *beg, const int64_t *end, const u
 // (or store is false) k_vjp_far_node recomputes it per node.
 rcb_status vjp_det(rcb_tree *t, VjpArgs &a, double *adj, bool mixed, bool store, Scratch &tmp, hipStream_t s) {
     const int64_t nlab = t->nlab;
-    const unsigned gridg = (unsigned)((t->ngroup + kWaves - 1) / kWaves);
     DetLists far, near;
     rcb_status st = det_count(t, t->gfar_beg, t->gfar_end, tmp, s, far);
     if (st != RCB_OK) return st;
@@ -1164,7 +1161,7 @@ rcb_status gravity_vjp(rcb_tree *t, const void *gx, const void *gy, const void *
     VjpArgs a{t->nleaf, t->gk, t->ngroup, t->nfirst, t->ncount, t->ncom, t->nM, t->nQ,
               t->gnear_beg, t->gnear_end, t->gfar_beg, t->gfar_end, t->gnear, t->gfar, t->px, t->py, t->pz, t->pm, t->ph,
               t->fd, t->fh, t->pid, gx, gy, gz, mom, leafc, sink, mixed ? nullptr : (double *)srcv,
-              mixed ? (float *)srcv : nullptr, adj, nullptr, nmid, n, t->nlab, nullptr, nullptr, nullptr, nullptr, nullptr,
+              mixed ? (float *)srcv : nullptr, nmid, n, t->nlab, nullptr, nullptr, nullptr, nullptr, nullptr,
               nullptr, kSrcChunk, 0};
     const unsigned gridg = (unsigned)((t->ngroup + kWaves - 1) / kWaves);
     if (det && mixed) k_vjp_moments_det<true><<<gridg, kBlock, 0, s>>>(a);

@@ -139,9 +139,4 @@ __device__ __forceinline__ double sink_reach(double x, double y, double z, doubl
     return uniform_f64(wave_max(sqrt((x * x + y * y) + z * z) + h));
 }
 
-// ballot bits of the lanes of this lane's segment
-__device__ __forceinline__ uint64_t seg_mask(const LeafLanes &L) {
-    return L.J == kWave ? ~0ull : (((1ull << L.J) - 1ull) << (L.sslot * L.J));
-}
-
 }  // namespace rcb

@@ -106,10 +106,9 @@ struct rcb_tree {
     int32_t nb_long = 0;               // kept lists that one workgroup each sorts
     int32_t nb_nq = 0;                 // entries of nb_queue
     // device flags: [0] 8-wide walk stack overflow, [1] long near lists, [2] their
-    // queue, [3] groups outgrowing the list slabs, [4] particles outgrowing
-    // the neighbour slab, [5] median selection, [6] groups outgrowing the
-    // first wide-walk FIFO, [7] groups outgrowing the second FIFO (walk) and
-    // leaves queued for the neighbour re-search (neighbours)
+    // queue, [3] groups outgrowing the list slabs, [5] a capacity of the build
+    // outgrown, [6] groups outgrowing the first wide-walk FIFO, [7] and the second
+    // ([0] also: the input check's verdict, before any walk)
     int32_t *dflag = nullptr;
     int64_t walk_requeued = 0;         // groups of the last walk that outgrew the first ring
     int64_t walk_nodes = -1;           // node records the first walk tier tested (per group)
