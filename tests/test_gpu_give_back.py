@@ -34,6 +34,8 @@ def test_vjp_between_count_and_fill(n, nll, kind, hs, prec, monkeypatch):
     arrs = [_t(a) for a in c.arrays()]
     g = [_t(v, torch.float32 if prec == "mixed" else torch.float64) for v in W.cotangents(n, seed=9)]
     runs = []
+    # (the stored adjoints are not taken: they are what a VJP does without first)
+    monkeypatch.setenv("RCB_VJP_DET_RECOMPUTE", "1")
     for limited in (False, True):
         lim = LimitedAlloc()
         t = _tree(lim, monkeypatch, arrs, nll, prec)
@@ -42,9 +44,10 @@ def test_vjp_between_count_and_fill(n, nll, kind, hs, prec, monkeypatch):
         t.gravity()
         held = lim.peak = lim.live
         if limited:
-            lim.budget = held + need - (1 << 20)
+            lim.budget = held + need // 2
         grad = t.vjp(*g)
         need = lim.peak - held
+        print(f"   held {held}, needed {need}, held after {lim.live}", flush=True)
         if limited:
             assert lim.refused > 0 and lim.live < held - (1 << 20)
         lim.budget = lim.live + (64 << 10)
