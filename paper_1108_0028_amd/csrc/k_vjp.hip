@@ -43,17 +43,16 @@ constexpr int kWaves = kBlock / kWave;
 constexpr int kAdj = 9;
 // Nodes of the levels above kMidLevel sit in the far lists of many groups at
 // once: their adjoints are added to several copies, in their own array of
-// kAdj * 2^kMidLevel per copy. FP64: 8 copies, and one of the deeper nodes (with
-// 64 and 8 the VJP of 300,000 particles took 2.88 ms, so 2.74). FP32 (mixed
-// form): 64, and 8 of the deeper nodes, added in FP64 by k_adj_reduce: they keep
-// each FP32 sum short. A node that all 16,384 groups of a cloud accept has its
-// mass adjoint to 2.4e-7 from 8 copies, to 1.9e-6 from one (1M particles: the VJP takes
-// the same time, 8.54 ms with the forward).
+// kAdj * 2^kMidLevel per copy, which k_adj_reduce adds in FP64. FP64 form: 8 copies
+// (with 64, and 8 of the deeper nodes, the VJP of 300,000 particles took 2.88 ms, so
+// 2.74). Mixed form: 64 of FP32, which keep each FP32 sum short. The deeper nodes
+// are added to in FP64 in both forms: a node that all 16,384 groups of a cloud
+// accept has its mass adjoint to 2.7e-8 so, to 2.4e-7 from 8 FP32 copies and to
+// 1.9e-6 from one (mixed VJP of 1M particles 5.74, 5.81 and 5.70 ms, of 4M 21.83,
+// 22.18 and 21.91).
 constexpr int kMidLevel = 16;
 template <typename AT>
 constexpr int kAdjMidCopies = sizeof(AT) == 4 ? 64 : 8;
-template <typename AT>
-constexpr int kAdjCopies = sizeof(AT) == 4 ? 8 : 1;
 constexpr int kAcc = 30;    // G0(3), G1(9), G2(18) while accumulating
 constexpr int kMom = 19;    // S1(3), S2(6), S3(10): far_math.h SymMoments
 
@@ -78,7 +77,7 @@ struct VjpArgs {
     double *sink;   // 4 n, tree order: dx dy dz dm
     double *src;    // 4 per particle, tree order, atomics (FP64 form)
     float *srcf;    // the same in the mixed form (FP32 atomics, its contract's accumulation)
-    int64_t nmid;   // labels below nmid have kAdjMidCopies adjoint copies, the others kAdjCopies
+    int64_t nmid;   // labels below nmid have kAdjMidCopies adjoint copies
     int64_t n;
     int64_t nlab;
     // deterministic form: each far entry's node adjoint (kAdj FP64) at row
@@ -190,7 +189,8 @@ struct VjpFarShared {
 };
 
 // AT: the type of the node-adjoint copies (FP64; FP32 in the mixed form, whose
-// contract allows FP32 accumulation), summed in FP64 by k_adj_reduce
+// contract allows FP32 accumulation), summed in FP64 by k_adj_reduce; adj takes the
+// nodes that have none
 // MODE kFarAtomic: node adjoints added atomically to the copies. The
 // deterministic form: kFarStore writes each entry's node adjoint (its sum over
 // the group's leaves, in leaf order) to a.contrib, summed per node later;
@@ -198,7 +198,7 @@ struct VjpFarShared {
 // the node adjoints itself).
 constexpr int kFarAtomic = 0, kFarCot = 1, kFarStore = 2;
 template <typename AT, int MODE>
-__global__ __launch_bounds__(kFarWaves * kWave, sizeof(AT) == 4 ? 4 : 3) void k_vjp_far(VjpArgs a, AT *__restrict__ adjc,
+__global__ __launch_bounds__(kFarWaves * kWave, sizeof(AT) == 4 ? 4 : 3) void k_vjp_far(VjpArgs a, double *__restrict__ adj,
                                                                AT *__restrict__ adjmc) {
     __shared__ VjpFarShared<AT> sh_all[kFarWaves];
     __shared__ double mom[8][kMom];   // the group's leaves: symmetrised moments
@@ -279,7 +279,6 @@ __global__ __launch_bounds__(kFarWaves * kWave, sizeof(AT) == 4 ? 4 : 3) void k_
             // each copy takes the groups of one residue mod the number of
             // copies, i.e. of one XCD under round-robin dispatch (8 | copies)
             AT *const mid = adjmc + (int64_t)(blockIdx.x % kAdjMidCopies<AT>) * kAdj * a.nmid;
-            AT *const deep = adjc + (int64_t)(blockIdx.x % kAdjCopies<AT>) * kAdj * (a.nlab - a.nmid);
 #pragma unroll 1
             for (int f = lane; f < nw * kAdj; f += kWave) {
                 const int r = f / kAdj;
@@ -288,9 +287,14 @@ __global__ __launch_bounds__(kFarWaves * kWave, sizeof(AT) == 4 ? 4 : 3) void k_
                 } else {
                     const int32_t L = sh.lab[r];
                     if (L < 0) continue;
-                    AT *const node = L < a.nmid ? mid + (int64_t)L * kAdj : deep + (L - a.nmid) * kAdj;
-                    __hip_atomic_fetch_add(node + (f - r * kAdj), sh.rows[f], __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
+                    auto add = [&](auto *p, int64_t row) {
+                        using V = typename std::remove_pointer<decltype(p)>::type;
+                        __hip_atomic_fetch_add(p + row * kAdj + (f - r * kAdj), (V)sh.rows[f], __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+                    };
+                    if constexpr (std::is_same<AT, double>::value) add(L < a.nmid ? mid : adj, L);
+                    else if (L < a.nmid) add(mid, L);
+                    else add(adj, L);
                 }
             }
             tile_sync();
@@ -574,26 +578,14 @@ __global__ __launch_bounds__(kBlock) void k_vjp_push(VjpArgs a, const double *__
     }
 }
 
-// node adjoints into out, FP64: the sum of each label's copies in order, of the
-// labels below nmid in adjmc, of the others in adjc (from label nmid on; a single
-// copy may stand in out itself)
+// adjoints of the nodes below nmid into out: the sum of their copies in order
 template <typename A>
-__global__ void k_adj_reduce(double *out, const A *adjc, const A *__restrict__ adjmc, int64_t nlab,
-                             int64_t nmid) {
+__global__ void k_adj_reduce(double *__restrict__ out, const A *__restrict__ adjmc, int64_t nmid) {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= kAdj * nlab) return;
-    double v;
-    if (i >= kAdj * nmid) {
-        const int64_t j = i - kAdj * nmid;
-        if ((const void *)(adjc + j) == (const void *)(out + i)) return;
-        v = (double)adjc[j];
-#pragma unroll
-        for (int c = 1; c < kAdjCopies<A>; ++c) v += (double)adjc[(int64_t)c * kAdj * (nlab - nmid) + j];
-    } else {
-        v = (double)adjmc[i];
+    if (i >= kAdj * nmid) return;
+    double v = (double)adjmc[i];
 #pragma unroll 8
-        for (int c = 1; c < kAdjMidCopies<A>; ++c) v += (double)adjmc[(int64_t)c * kAdj * nmid + i];
-    }
+    for (int c = 1; c < kAdjMidCopies<A>; ++c) v += (double)adjmc[(int64_t)c * kAdj * nmid + i];
     out[i] = v;
 }
 
@@ -1139,24 +1131,24 @@ rcb_status gravity_vjp(rcb_tree *t, const void *gx, const void *gy, const void *
         return RCB_ECAPACITY;
     }
     const int64_t nmid = std::min<int64_t>(t->nlab, int64_t(1) << kMidLevel);
-    // node adjoints as the far kernel adds them: FP64 in adj itself, FP32
-    // (mixed form) apart; the deterministic form writes adj alone
-    const size_t adj_n = det ? 0 : (size_t)(mixed ? kAdjCopies<float> : kAdjCopies<double>) * kAdj * (t->nlab - nmid);
-    const size_t adjm_n = det ? 0 : (size_t)(mixed ? kAdjMidCopies<float> : kAdjMidCopies<double>) * kAdj * nmid;
+    // the copies of the upper nodes' adjoints; the others go into adj itself, as all
+    // do in the deterministic form
+    const size_t adjm_bytes = det ? 0
+                                  : (mixed ? sizeof(float) * kAdjMidCopies<float> : sizeof(double) * kAdjMidCopies<double>) *
+                                        kAdj * (size_t)nmid;
     double *adj = (double *)dalloc(t, sizeof(double) * kAdj * t->nlab, s, tmp);
-    void *adjc = det ? (void *)adj : mixed ? dalloc(t, sizeof(float) * adj_n, s, tmp) : (void *)(adj + kAdj * nmid);
-    void *adjmc = det ? (void *)adj : dalloc(t, (mixed ? sizeof(float) : sizeof(double)) * adjm_n, s, tmp);
+    void *adjmc = det ? (void *)adj : dalloc(t, adjm_bytes, s, tmp);
     double *mom = (double *)dalloc(t, sizeof(double) * kMom * t->nleaf, s, tmp);
     if (!t->farc) {
         t->farc = (double *)dalloc(t, sizeof(double) * kLeafC * t->nleaf, s, t->list_allocs);
         t->farc_valid = false;
     }
     double *leafc = t->farc;   // 19 far coefficients + the leaf's cotangent sum per leaf
-    if (!sink || !srcv || !adj || !adjc || !adjmc || !mom || !leafc) return RCB_ENOMEM;
+    if (!sink || !srcv || !adj || !adjmc || !mom || !leafc) return RCB_ENOMEM;
     if (!det) {
         RCB_ZERO(srcv, (mixed ? sizeof(float) : sizeof(double)) * 4 * n, s);
-        RCB_ZERO(adjc, (mixed ? sizeof(float) : sizeof(double)) * adj_n, s);
-        RCB_ZERO(adjmc, (mixed ? sizeof(float) : sizeof(double)) * adjm_n, s);
+        RCB_ZERO(adj + kAdj * nmid, sizeof(double) * kAdj * (t->nlab - nmid), s);
+        RCB_ZERO(adjmc, adjm_bytes, s);
     }
     VjpArgs a{t->nleaf, t->gk, t->ngroup, t->nfirst, t->ncount, t->ncom, t->nM, t->nQ,
               t->gnear_beg, t->gnear_end, t->gfar_beg, t->gfar_end, t->gnear, t->gfar, t->px, t->py, t->pz, t->pm, t->ph,
@@ -1194,8 +1186,7 @@ rcb_status gravity_vjp(rcb_tree *t, const void *gx, const void *gy, const void *
             else sized(std::false_type{});
         }
     };
-    const int64_t alen = kAdj * t->nlab;
-    const unsigned gridr = (unsigned)((alen + 255) / 256);
+    const unsigned gridr = (unsigned)((kAdj * nmid + 255) / 256);
     if (det) {
         // far field, then node adjoints and source-side terms from the
         // per-node lists
@@ -1211,14 +1202,12 @@ rcb_status gravity_vjp(rcb_tree *t, const void *gx, const void *gy, const void *
     } else {
         for (a.first = 0; a.first < t->ngroup; a.first += kMaxGrid) {
             const unsigned gf = (unsigned)std::min(kMaxGrid, t->ngroup - a.first);
-            if (mixed) k_vjp_far<float, kFarAtomic><<<gf, kFarWaves * kWave, 0, s>>>(a, (float *)adjc, (float *)adjmc);
-            else k_vjp_far<double, kFarAtomic><<<gf, kFarWaves * kWave, 0, s>>>(a, (double *)adjc, (double *)adjmc);
+            if (mixed) k_vjp_far<float, kFarAtomic><<<gf, kFarWaves * kWave, 0, s>>>(a, adj, (float *)adjmc);
+            else k_vjp_far<double, kFarAtomic><<<gf, kFarWaves * kWave, 0, s>>>(a, adj, (double *)adjmc);
             RCB_LAUNCH_CHECK("k_vjp_far");
         }
-        if (mixed)
-            k_adj_reduce<float><<<gridr, 256, 0, s>>>(adj, (const float *)adjc, (const float *)adjmc, t->nlab, nmid);
-        else
-            k_adj_reduce<double><<<gridr, 256, 0, s>>>(adj, (const double *)adjc, (const double *)adjmc, t->nlab, nmid);
+        if (mixed) k_adj_reduce<float><<<gridr, 256, 0, s>>>(adj, (const float *)adjmc, nmid);
+        else k_adj_reduce<double><<<gridr, 256, 0, s>>>(adj, (const double *)adjmc, nmid);
         RCB_LAUNCH_CHECK("k_adj_reduce");
         near(std::true_type{});
         RCB_LAUNCH_CHECK("k_vjp_near");

@@ -1,12 +1,12 @@
-"""Mixed form: the FP32 sums of a deep node's adjoint. One light particle far out
-on the diagonal of a cube of 2^17 - 1 others (N_ll = 1, k = 17) ends in a leaf
+"""Mixed form: the sum of a deep node's adjoint, added in FP64. One light particle
+far out on the diagonal of a cube of 2^17 - 1 others (N_ll = 1, k = 17) ends in a leaf
 whose box shrinks to a point, and no node above level 17 that holds it is small
 enough for the MAC: all 16,384 groups add to the adjoint of that leaf, and the
-particle's dm is their sum. With terms of one sign added in eight FP32 parts of
-2048 terms, each addition rounding by at most half an ulp of the part (uniformly:
-2^-23 / sqrt(12) of it, an ulp being 0.72 times that on average), a part is off by
-2^-23 0.72 / sqrt(12) sqrt(2048 / 3) = 6.5e-7 and their sum by 2.3e-7 (rms); in one
-part of 16,384 it would be 1.8e-6. The bar, 6e-7 rms over twelve cotangents, lies
+particle's dm is their sum. What is asked for is that of eight FP32 parts of 2048
+terms of one sign: each addition rounding by at most half an ulp of the part
+(uniformly: 2^-23 / sqrt(12) of it, an ulp being 0.72 times that on average), a part is
+off by 2^-23 0.72 / sqrt(12) sqrt(2048 / 3) = 6.5e-7 and their sum by 2.3e-7 (rms); in
+one part of 16,384 it would be 1.8e-6. The bar, 6e-7 rms over twelve cotangents, lies
 a factor of three from either."""
 import numpy as np
 import pytest
