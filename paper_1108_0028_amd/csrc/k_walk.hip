@@ -668,8 +668,9 @@ rcb_status ensure_walk(rcb_tree *t, hipStream_t s) {
     // the slab lists' ends per group (in the common case, that no list
     // outgrew its slab); launched before the flags are read, again if the
     // later tiers rewrote some counts
-    int64_t *ends = (int64_t *)dalloc(t, sizeof(int64_t) * 4 * NG, s, t->list_allocs);
+    int64_t *ends = (int64_t *)dalloc(t, sizeof(int64_t) * 4 * NG, s, tmp);
     if (!ends) return RCB_ENOMEM;
+    std::vector<void *> lists;   // of tmp: the tree's once the walk is done
     const NbEstimate ne{t->nleaf, t->gk, (double)t->n, t->ncount, t->nlo, t->nhi, t->nhnode, t->wrec};
     auto slab_ends = [&](unsigned long long *out) -> rcb_status {
         k_slab_ends<<<(unsigned)((NG + kBlock - 1) / kBlock), kBlock, 0, s>>>(NG, cn, cf, ncnt, fcnt, ends, ends + NG,
@@ -737,13 +738,10 @@ rcb_status ensure_walk(rcb_tree *t, hipStream_t s) {
         t->gnear = nslab;
         t->gfar = fslab;
         t->near_slab = cn > 1024 ? sizeof(uint64_t) * NG * cn : 0;
-        for (void *p : slabs) {
-            tmp.keep(p);
-            t->list_allocs.push_back(p);
-        }
+        lists = {ends, nslab, fslab};
     } else {
-        int64_t *noff = (int64_t *)dalloc(t, sizeof(int64_t) * (NG + 1), s, t->list_allocs);
-        int64_t *foff = (int64_t *)dalloc(t, sizeof(int64_t) * (NG + 1), s, t->list_allocs);
+        int64_t *noff = (int64_t *)dalloc(t, sizeof(int64_t) * (NG + 1), s, tmp);
+        int64_t *foff = (int64_t *)dalloc(t, sizeof(int64_t) * (NG + 1), s, tmp);
         if (!noff || !foff) return RCB_ENOMEM;
         rcb_status st = scan_i64(t, ncnt, noff, NG, s);
         if (st != RCB_OK) return st;
@@ -753,9 +751,10 @@ rcb_status ensure_walk(rcb_tree *t, hipStream_t s) {
         const HostRead r[2] = {{noff + NG, &tot[0], (int)sizeof(int64_t)}, {foff + NG, &tot[1], (int)sizeof(int64_t)}};
         st = read_small(s, r, 2, "rcb_walk");
         if (st != RCB_OK) return st;
-        t->gnear = (uint64_t *)dalloc(t, sizeof(uint64_t) * std::max<int64_t>(1, tot[0]), s, t->list_allocs);
-        t->gfar = (uint64_t *)dalloc(t, sizeof(uint64_t) * std::max<int64_t>(1, tot[1]), s, t->list_allocs);
+        t->gnear = (uint64_t *)dalloc(t, sizeof(uint64_t) * std::max<int64_t>(1, tot[0]), s, tmp);
+        t->gfar = (uint64_t *)dalloc(t, sizeof(uint64_t) * std::max<int64_t>(1, tot[1]), s, tmp);
         if (!t->gnear || !t->gfar) return RCB_ENOMEM;
+        lists = {noff, foff, t->gnear, t->gfar};
         t->gnear_beg = noff;
         t->gnear_end = noff + 1;
         t->gfar_beg = foff;
@@ -781,6 +780,10 @@ rcb_status ensure_walk(rcb_tree *t, hipStream_t s) {
     if (nlong > 0) {
         k_sort_long<<<nlong, 1024, 0, s>>>(long_q, t->gnear_beg, t->gnear_end, t->gnear);
         RCB_LAUNCH_CHECK("k_sort_long");
+    }
+    for (void *p : lists) {
+        tmp.keep(p);
+        t->list_allocs.push_back(p);
     }
     t->walked = true;
     t->lists_kept = false;
@@ -823,8 +826,8 @@ rcb_status ensure_leaf_lists(rcb_tree *t, hipStream_t s) {
     Scratch tmp(t, s);
     int64_t *ncnt = (int64_t *)dalloc(t, sizeof(int64_t) * L, s, tmp);
     int64_t *fcnt = (int64_t *)dalloc(t, sizeof(int64_t) * L, s, tmp);
-    t->near_off = (int64_t *)dalloc(t, sizeof(int64_t) * (L + 1), s, t->list_allocs);
-    t->far_off = (int64_t *)dalloc(t, sizeof(int64_t) * (L + 1), s, t->list_allocs);
+    t->near_off = (int64_t *)dalloc(t, sizeof(int64_t) * (L + 1), s, tmp);
+    t->far_off = (int64_t *)dalloc(t, sizeof(int64_t) * (L + 1), s, tmp);
     if (!ncnt || !fcnt || !t->near_off || !t->far_off) return RCB_ENOMEM;
     const unsigned grid = (unsigned)((L + kWaves - 1) / kWaves);
     k_expand<false><<<grid, kBlock, 0, s>>>(L, t->gk, t->gnear_beg, t->gnear_end, t->gnear,
@@ -839,14 +842,18 @@ rcb_status ensure_leaf_lists(rcb_tree *t, hipStream_t s) {
     RCB_HIP(hipMemcpyAsync(&tot[0], t->near_off + L, sizeof(int64_t), hipMemcpyDeviceToHost, s));
     RCB_HIP(hipMemcpyAsync(&tot[1], t->far_off + L, sizeof(int64_t), hipMemcpyDeviceToHost, s));
     RCB_HIP(hipStreamSynchronize(s));
-    t->near_list = (int32_t *)dalloc(t, sizeof(int32_t) * std::max<int64_t>(1, tot[0]), s, t->list_allocs);
-    t->far_list = (int32_t *)dalloc(t, sizeof(int32_t) * std::max<int64_t>(1, tot[1]), s, t->list_allocs);
+    t->near_list = (int32_t *)dalloc(t, sizeof(int32_t) * std::max<int64_t>(1, tot[0]), s, tmp);
+    t->far_list = (int32_t *)dalloc(t, sizeof(int32_t) * std::max<int64_t>(1, tot[1]), s, tmp);
     if (!t->near_list || !t->far_list) return RCB_ENOMEM;
     k_expand<true><<<grid, kBlock, 0, s>>>(L, t->gk, t->gnear_beg, t->gnear_end, t->gnear,
                                            t->gfar_beg, t->gfar_end, t->gfar,
                                            nullptr, nullptr, t->near_off, t->far_off, t->near_list,
                                            t->far_list);
     RCB_LAUNCH_CHECK("k_expand<fill>");
+    for (void *p : std::initializer_list<void *>{t->near_off, t->far_off, t->near_list, t->far_list}) {
+        tmp.keep(p);
+        t->list_allocs.push_back(p);
+    }
     t->near_total = tot[0];
     t->far_total = tot[1];
     t->leaf_lists = true;
