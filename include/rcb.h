@@ -39,9 +39,9 @@
  *  - Two environment variables select equivalent code paths, for tests:
  *    RCB_BUILD_LEVELS (any value) makes rcb_build() run every level as one
  *    device-wide pass instead of finishing small subtrees in one workgroup each
- *    (same tree, bit for bit); RCB_WALK_WIDE_STACK=n caps the walk's
- *    first-tier node queue at n entries, so that more groups go to the later
- *    tiers (same lists); RCB_VJP_DET_RECOMPUTE (any value) makes the
+ *    (same tree, bit for bit); RCB_WALK_WIDE_STACK=n (n >= 2) caps the
+ *    breadth-first walk's queues at n nodes, the children of n / 2 opened ones,
+ *    so that more groups go to the later tiers (same lists); RCB_VJP_DET_RECOMPUTE (any value) makes the
  *    deterministic rcb_gravity_vjp() recompute each node's adjoint per node
  *    instead of storing each far entry's (the path it takes when that array
  *    cannot be allocated; equal to rounding, each path repeats bit for bit).
@@ -194,7 +194,8 @@ rcb_status rcb_refresh(rcb_tree *t, const double *x, const double *y, const doub
  * simulation or serving loops, harnesses that forbid hipMalloc. It allocates
  * and frees nothing: its scratch (the gathered inputs of each level, 32 bytes
  * per particle, and the level passes' bookkeeping, about 33 bytes per
- * particle in all) lives in one static device array of 64 MiB that every GPU
+ * particle in all; up to about a million particles also the inputs as records, 32 more)
+ * lives in one static device array of 64 MiB that every GPU
  * the library runs on holds until the process ends. The interaction lists
  * are kept, as with keep_lists = 1 (rcb_walk() makes new ones, and
  * allocates). Calls on one device share the array: calls that overlap in
@@ -222,9 +223,9 @@ size_t rcb_refresh_noalloc_scratch(const rcb_tree *t);
  * flags are read back through pinned host memory).
  * Errors: RCB_ECAPACITY if the last-resort walk's stack overflows (a tree
  * deeper than 29 levels), RCB_ENOMEM.
- * Environment (testing): RCB_WALK_WIDE_STACK=n caps the breadth-first
- * walk's node queues at n entries, so that more groups of cells are walked
- * again by the later tiers; the lists do not change.
+ * The lists go into slabs of 1024 or, in clouds of up to some millions, up to
+ * 16384 near entries per 8 cells (the fewer where the more cannot be allocated), and
+ * into storage of their size after a second walk where one is longer.
  */
 rcb_status rcb_walk(rcb_tree *t, void *stream);
 
@@ -253,7 +254,7 @@ rcb_status rcb_neighbours_count(rcb_tree *t, int64_t *offsets, int64_t *total, v
  * it, a chain of chunks of 64 slots from a pool of N/8 chunks (36 bytes per
  * particle) and as many more as the walk's estimate of the neighbour counts
  * asks for (at most 4 per particle; clouds of a few thousand particles get up to
- * 16 MiB; the N/8 alone if the larger pool cannot be allocated). The cells
+ * 16 MiB; the N/8 alone if all of that cannot be allocated). The cells
  * holding a list for which the pool had no chunk left are searched again here.
  */
 rcb_status rcb_neighbours_fill(rcb_tree *t, const int64_t *offsets, int32_t *ids,

@@ -23,13 +23,13 @@
 // A near entry then may be a candidate without being in a leaf's gravity
 // near field (candidate bit set, near bit clear).
 //
-// Two kernels walk a group. k_walk_wide, the one normally run, gives each
-// lane one popped stack entry (up to 64 per round) and tests it against all
-// the group's leaves in turn, so a node costs one record load and one set
-// of list/stack bookkeeping for 8 leaf tests; its LDS ring holds kWQueue
-// entries, and a group that would outgrow it is queued and walked again by
-// k_walk_group, whose lanes are (pending entry, leaf) and whose stack bound
-// is proved below. Both make the same per-leaf decisions; their lists differ
+// Two kernels walk a group. k_walk_wide, the one normally run, takes up to 32
+// opened nodes a round from a FIFO ring in LDS, gives each lane one of their 64
+// children and tests it against all the group's leaves in turn, so a node costs
+// one record load and one set of list/queue bookkeeping for 8 leaf tests; the
+// ring holds kWQueue opened nodes, and a group that would outgrow it is queued and
+// walked again with a ring of kWQueue2, or, past that, by k_walk_group, whose lanes
+// are (pending entry, leaf) and whose stack bound is proved below. All make the same per-leaf decisions; their lists differ
 // only in order (the wide walk's near lists are sorted by label, the 8-wide
 // walk's are sorted afterwards).
 //

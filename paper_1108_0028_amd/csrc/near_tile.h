@@ -7,8 +7,8 @@
 // have sources stand in LDS by their rank among them. Sources are then staged
 // 64 at a time: lane j of a tile finds its entry by counting the entries that
 // start at or before it (a mark at each start inside the tile, read back as a
-// ballot), and every sink lane reads the tile back as broadcasts. Entries that
-// the caller does not need (for example cells with no candidate bit, for the
+// ballot), and the caller takes them from its lane or puts them into LDS in the
+// order it needs. Entries that the caller does not need (for example cells with no candidate bit, for the
 // neighbour search) are given zero sources.
 // The staging is a good part of a tile's instructions where cells are small
 // (cells of 8: 64 sources are 8 rows of a dozen instructions). A binary search
