@@ -314,7 +314,7 @@ def _rooflines(c, phases, prec, n, k):
     near_f = FLOP_P2P * c["pairs"] + FLOP_L2P * n
     far_f = FLOP_M2L * c["far_pairs"]
     g = alu(near_f if mixed else 0, far_f + (0 if mixed else near_f), phases["gravity"])
-    kname = ["k_far<false, 2>", "k_near<true, 1>" if mixed else "k_near<false, 1>"]
+    kname = ["k_far<false, 2>", "k_near<true, 1, false>" if mixed else "k_near<false, 1, false>"]
     traffic = [_profiled(k_) for k_ in kname]
     g.update({"kernel": " + ".join(kname), "kernel_ms": phases["gravity"],
               "traffic": None if None in traffic else sum(traffic),

@@ -465,14 +465,14 @@ rcb_status launch_far(const rcb_tree *t, GravArgs g, int64_t g0, int64_t g1, hip
 // particles 1362, 1102, 988, 1000; 32,768 clumpy 629, 574, 570, 712; 131,072
 // 1887, 2000, 2072, 2607). Each wave reads the whole list, and of leaves of fewer than
 // five particles on average that is most of the work: they take one wave where
-// there are enough of them (256 leaves of 2.5 particles 26, 24, 23, 22; 4096 of 5
+// there are enough of them and none is large (256 leaves of 2.5 particles 26, 24, 23, 22; 4096 of 5
 // particles 57, 57, 62, 80, of 1.5 40, 43, 49, 65; 32,768 of 5 262, 278, 344, 530).
 template <bool MIXED>
 rcb_status launch_near(const rcb_tree *t, GravArgs g, int64_t g0, int64_t g1, hipStream_t s) {   // of groups [g0, g1)
     const int64_t end = g1 << t->gk;
     for (g.first = g0 << t->gk; g.first < end; g.first += kMaxGrid) {
         const unsigned n = (unsigned)std::min(kMaxGrid, end - g.first);
-        if (t->nleaf > 1024 && t->n < 5 * t->nleaf) k_near<MIXED, 1, true><<<n, kWave, 0, s>>>(g);
+        if (t->nleaf > 1024 && t->n < 5 * t->nleaf && !t->large_leaf) k_near<MIXED, 1, true><<<n, kWave, 0, s>>>(g);
         else if (t->nleaf <= 4096) k_near<MIXED, 8><<<n, 8 * kWave, 0, s>>>(g);
         else if (t->nleaf <= 16384) k_near<MIXED, 4><<<n, 4 * kWave, 0, s>>>(g);
         else if (t->nleaf <= 32768) k_near<MIXED, 2><<<n, 2 * kWave, 0, s>>>(g);

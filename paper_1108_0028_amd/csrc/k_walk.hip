@@ -238,10 +238,10 @@ __global__ __launch_bounds__(kBlock) void k_walk_group(WalkArgs w, const int32_t
 constexpr int kWQueue = 1024;    // powers of two
 constexpr int kWQueue2 = 4096;
 
-// the walk's flags (not [4] and [5], the build's) and totals, in one launch
+// the walk's flags (not [5], the build's) and totals, in one launch
 __global__ void k_walk_clear(int32_t *__restrict__ flags, unsigned long long *__restrict__ tot) {
     const int i = threadIdx.x;
-    if (i < 4 || i == 6 || i == 7) flags[i] = 0;
+    if (i < 5 || i == 6 || i == 7) flags[i] = 0;
     if (i < 4) tot[i] = 0;
 }
 
@@ -397,17 +397,20 @@ __global__ __launch_bounds__(WAVES * kWave) void k_walk_wide(WalkArgs w, int32_t
 // particles in volume V expects c / V 4 pi / 3 r^3 neighbours each (r = 2h:
 // h_node - h_node_int), r on no axis past the root's side, beyond which there are
 // none (a flat cloud's cells have no volume: taken as full of particles, they asked
-// for 1 KB a particle, now 0.2), and lists past 64 ids take chunks of 64. [2] and
-// [3] only choose a launch and size a pool.
+// for 1 KB a particle, now 0.2), and lists past 64 ids take chunks of 64. large: set
+// if a cell holds more than 64 particles. It, [2] and [3] only choose launches and
+// size a pool.
 __global__ __launch_bounds__(kBlock) void k_slab_ends(int64_t ngroup, int64_t near_cap, int64_t far_cap,
                                                       const int64_t *__restrict__ ncnt,
                                                       const int64_t *__restrict__ fcnt,
                                                       int64_t *__restrict__ nbeg, int64_t *__restrict__ nend,
                                                       int64_t *__restrict__ fbeg, int64_t *__restrict__ fend,
                                                       const NbEstimate e, const uint2 *__restrict__ stats,
-                                                      unsigned long long *__restrict__ tot) {
+                                                      unsigned long long *__restrict__ tot,
+                                                      int32_t *__restrict__ large) {
     const int64_t g = blockIdx.x * (int64_t)kBlock + threadIdx.x;
     double sum[4] = {0.0, 0.0, 0.0, 0.0};   // (exact: below 2^53)
+    bool big = false;
     if (g < ngroup) {
         nbeg[g] = g * near_cap;
         nend[g] = g * near_cap + ncnt[g];
@@ -435,6 +438,7 @@ __global__ __launch_bounds__(kBlock) void k_slab_ends(int64_t ngroup, int64_t ne
                     nb *= side > 0.0 ? (r < all[q] ? r : all[q]) * __builtin_amdgcn_rcp(side) : 1.0;
                 }
                 if (!(nb < e.n)) nb = e.n;
+                big |= c > kWave;
                 if (c > 0.0 && nb > 64.0) sum[3] += c * ceil((nb - 64.0) / 64.0);
             }
         }
@@ -445,6 +449,7 @@ __global__ __launch_bounds__(kBlock) void k_slab_ends(int64_t ngroup, int64_t ne
         const double v = wave_sum(sum[q]);
         if (lane_id() == 0 && v > 0.0) atomicAdd(tot + q, (unsigned long long)v);
     }
+    if (ballot(big) != 0ull && lane_id() == 0) atomicOr(large, 1);
 }
 
 // Sort the near lists of the groups walked by k_walk_group by label (bitonic
@@ -674,7 +679,8 @@ rcb_status ensure_walk(rcb_tree *t, hipStream_t s) {
     const NbEstimate ne{t->nleaf, t->gk, (double)t->n, t->ncount, t->nlo, t->nhi, t->nhnode, t->wrec};
     auto slab_ends = [&](unsigned long long *out) -> rcb_status {
         k_slab_ends<<<(unsigned)((NG + kBlock - 1) / kBlock), kBlock, 0, s>>>(NG, cn, cf, ncnt, fcnt, ends, ends + NG,
-                                                                              ends + 2 * NG, ends + 3 * NG, ne, stats, out);
+                                                                              ends + 2 * NG, ends + 3 * NG, ne, stats, out,
+                                                                              t->dflag + 4);
         RCB_LAUNCH_CHECK("k_slab_ends");
         return RCB_OK;
     };
@@ -717,6 +723,7 @@ rcb_status ensure_walk(rcb_tree *t, hipStream_t s) {
     t->walk_tests = (int64_t)htot[1];
     t->far_entries = (int64_t)htot[2];
     t->nb_est = (int64_t)htot[3];
+    t->large_leaf = flags[4] != 0;
     if (flags[0]) {
         set_error("walk: stack overflow (tree deeper than the walk stack supports)");
         return RCB_ECAPACITY;

@@ -106,7 +106,8 @@ struct rcb_tree {
     int32_t nb_long = 0;               // kept lists that one workgroup each sorts
     int32_t nb_nq = 0;                 // entries of nb_queue
     // device flags: [0] 8-wide walk stack overflow, [1] long near lists, [2] their
-    // queue, [3] groups outgrowing the list slabs, [5] a capacity of the build
+    // queue, [3] groups outgrowing the list slabs, [4] a cell of more than 64
+    // particles, [5] a capacity of the build
     // outgrown, [6] groups outgrowing the first wide-walk FIFO, [7] and the second
     // ([0] also: the input check's verdict, before any walk)
     int32_t *dflag = nullptr;
@@ -114,6 +115,7 @@ struct rcb_tree {
     int64_t walk_nodes = -1;           // node records the first walk tier tested (per group)
     int64_t walk_tests = -1;           // (node, visiting leaf) tests of the first tier
     int64_t far_entries = 0;           // entries of all groups' far lists after the first tier
+    bool large_leaf = false;           // a lowest-level cell holds more than 64 particles
     // per leaf: the 19 far-field coefficients of the current moments (written
     // by rcb_gravity, or by the VJP if no gravity call has) and 3 VJP scratch values
     double *farc = nullptr;

@@ -31,3 +31,20 @@ def test_small_leaves(n, nll, theta, prec):
     gt = _gpu_tree(c, nll, theta, prec)
     assert gate(np.stack([_np(a) for a in gt.gravity()], 1), ref) <= TOL[prec]
     gt.destroy()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("same", [64, 65, 1500])
+def test_a_large_leaf_among_them(same, prec):
+    """(2048 cells: the rule for small leaves ends at 64 particles in one)"""
+    c = W.small_random(4000, 305, "uniform", h_scale=0.5)
+    for a in (c.x, c.y, c.z):
+        a[100:100 + same] = a[99]
+    _say("a large leaf among small ones", same, prec)
+    ot = O.OracleTree(*c.arrays(), n_ll=2)
+    ot.walk(0.6)
+    ref = np.stack(ot.gravity(), 1)
+    gt = _gpu_tree(c, 2, 0.6, prec)
+    assert int(gt.export("count")[1 << ot.k:].max()) > same
+    assert gate(np.stack([_np(a) for a in gt.gravity()], 1), ref) <= TOL[prec]
+    gt.destroy()
