@@ -211,7 +211,10 @@ __device__ __forceinline__ T lane_value(T v, int lane) {
 // straight from their loads, and each sink's sums over all lanes: a row or two of a
 // tile cost less than the tile's order and the reach it needs (FP64, 500,000 particles
 // in cells of one 2.79 ms, now 2.68). (A branch in every instance made cells of 8
-// to 61 particles 1 to 2% slower.)
+// to 61 particles 1 to 2% slower.) Gravity without and with it, 131,072 leaves of 0.95,
+// 1.9, 2.3, 2.8 and 3.9 particles: FP64 587 and 561, 668 and 651, 700 and 689, 738 and
+// 735, 839 and 858 us; mixed 517 and 492, 569 and 547, 587 and 570, 601 and 591, 642 and
+// 646; 524,288 leaves of 2.8 FP64 3446 and 3508: up to 2.5 on average.
 template <bool MIXED, int H, bool FEW = false>
 __global__ __launch_bounds__(H * kWave, MIXED ? 6 : 5) void k_near(GravArgs g) {
     using T = typename std::conditional<MIXED, float, double>::type;
@@ -472,7 +475,9 @@ rcb_status launch_near(const rcb_tree *t, GravArgs g, int64_t g0, int64_t g1, hi
     const int64_t end = g1 << t->gk;
     for (g.first = g0 << t->gk; g.first < end; g.first += kMaxGrid) {
         const unsigned n = (unsigned)std::min(kMaxGrid, end - g.first);
-        if (t->nleaf > 1024 && t->n < 5 * t->nleaf && !t->large_leaf) k_near<MIXED, 1, true><<<n, kWave, 0, s>>>(g);
+        const bool one = t->nleaf > 1024 && t->n < 5 * t->nleaf && !t->large_leaf;
+        if (one && 2 * t->n < 5 * t->nleaf) k_near<MIXED, 1, true><<<n, kWave, 0, s>>>(g);
+        else if (one) k_near<MIXED, 1><<<n, kWave, 0, s>>>(g);
         else if (t->nleaf <= 4096) k_near<MIXED, 8><<<n, 8 * kWave, 0, s>>>(g);
         else if (t->nleaf <= 16384) k_near<MIXED, 4><<<n, 4 * kWave, 0, s>>>(g);
         else if (t->nleaf <= 32768) k_near<MIXED, 2><<<n, 2 * kWave, 0, s>>>(g);
