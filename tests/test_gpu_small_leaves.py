@@ -12,14 +12,15 @@ from test_gpu_parity import TOL, _gpu_tree, _np, _say, gate
 pytestmark = pytest.mark.gpu
 
 
-# (cells: 1 to 32,768; the wave counts change at 1024 cells, and with five particles a cell)
+# cells: 1 to 32,768; the wave counts change at 1024 cells, and with five and two
+# and a half particles a cell (theta = 0, the sum over all pairs, for the smaller clouds)
+SMALL = [(1, 1), (2, 1), (2, 2), (3, 2), (65, 1), (700, 1), (1500, 2), (2600, 2)]
+CASES = [(n, nll, th) for n, nll in SMALL for th in (0.0, 0.6)] + [(9000, 5, 0.6), (11000, 5, 0.6), (20000, 1, 0.6)]
+
+
 @pytest.mark.parametrize("prec", ["fp64", "mixed"])
-@pytest.mark.parametrize("theta", [0.0, 0.6])
-@pytest.mark.parametrize("n,nll", [(1, 1), (2, 1), (2, 2), (3, 2), (65, 1), (700, 1), (1500, 2), (2600, 2),
-                                   (9000, 5), (11000, 5), (20000, 1)])
+@pytest.mark.parametrize("n,nll,theta", CASES)
 def test_small_leaves(n, nll, theta, prec):
-    if theta == 0.0 and n > 3000:
-        pytest.skip("the sum over all pairs is left to the smaller ones")
     c = W.small_random(n, 300 + n, "uniform" if n % 2 else "clustered", h_scale=0.5)
     if n > 60:
         for a in (c.x, c.y, c.z):
